@@ -289,7 +289,7 @@ __global__ void __launch_bounds__(256) k_refresh_list(Ctx cx, int fixed_count)
         }
         if (idx >= (unsigned)count) break;
         int C = cx.tlist[idx++];
-        long long s = cx.cr[C].s;
+        const int s = cx.cr[C].s;
         long long base = cx.cm_off[C];
         long long cap = cx.cm_off[C + 1] - base;
         long long len = cx.cm_len[C];

@@ -25,14 +25,27 @@ typedef long long i64;
 struct X192 { u64 w0, w1, w2; };
 struct X256 { u64 w0, w1, w2, w3; };
 
-__device__ __forceinline__ u64 addc64(u64 a, u64 b, u64 &carry)
+typedef unsigned __int128 u128;
+
+// Limb arithmetic on 32-bit words: __builtin_addc / __builtin_subc become one
+// v_addc_co_u32 / v_subb_co_u32 per word (a 64-bit compare per carry costs three times the
+// instructions).  The evaluation kernels are bound by each node's chain of gathers and of
+// arithmetic between them: with these limbs, the 128-bit terms and the DPP reductions of
+// method.h, k_eval went from 19.9 to 16.2 us per launch on a 4M-node social-shaped graph at
+// queue 4096 (all 12,701 launches: 252.7 -> 205.8 ms) and from 154 to 116 us at queue 65,536
+// on a 1M-node one.
+__device__ __forceinline__ u64 add_word(u64 a, u64 b, unsigned &c)
 {
-    u64 s = a + b;
-    u64 c1 = s < a;
-    u64 s2 = s + carry;
-    u64 c2 = s2 < s;
-    carry = c1 | c2;
-    return s2;
+    const unsigned lo = __builtin_addc((unsigned)a, (unsigned)b, c, &c);
+    const unsigned hi = __builtin_addc((unsigned)(a >> 32), (unsigned)(b >> 32), c, &c);
+    return (u64)lo | ((u64)hi << 32);
+}
+
+__device__ __forceinline__ u64 sub_word(u64 a, u64 b, unsigned &c)
+{
+    const unsigned lo = __builtin_subc((unsigned)a, (unsigned)b, c, &c);
+    const unsigned hi = __builtin_subc((unsigned)(a >> 32), (unsigned)(b >> 32), c, &c);
+    return (u64)lo | ((u64)hi << 32);
 }
 
 __device__ __forceinline__ X192 x192_zero() { X192 r = {0, 0, 0}; return r; }
@@ -40,35 +53,34 @@ __device__ __forceinline__ X256 x256_zero() { X256 r = {0, 0, 0, 0}; return r; }
 
 __device__ __forceinline__ void x192_add(X192 &a, const X192 &b)
 {
-    u64 c = 0;
-    a.w0 = addc64(a.w0, b.w0, c);
-    a.w1 = addc64(a.w1, b.w1, c);
-    a.w2 = addc64(a.w2, b.w2, c);
+    unsigned c = 0;
+    a.w0 = add_word(a.w0, b.w0, c);
+    a.w1 = add_word(a.w1, b.w1, c);
+    a.w2 = add_word(a.w2, b.w2, c);
 }
 
 __device__ __forceinline__ void x256_add(X256 &a, const X256 &b)
 {
-    u64 c = 0;
-    a.w0 = addc64(a.w0, b.w0, c);
-    a.w1 = addc64(a.w1, b.w1, c);
-    a.w2 = addc64(a.w2, b.w2, c);
-    a.w3 = addc64(a.w3, b.w3, c);
-}
-
-__device__ __forceinline__ X192 x192_neg(X192 a)
-{
-    X192 r;
-    u64 c = 1;
-    r.w0 = addc64(~a.w0, 0, c);
-    r.w1 = addc64(~a.w1, 0, c);
-    r.w2 = addc64(~a.w2, 0, c);
-    return r;
+    unsigned c = 0;
+    a.w0 = add_word(a.w0, b.w0, c);
+    a.w1 = add_word(a.w1, b.w1, c);
+    a.w2 = add_word(a.w2, b.w2, c);
+    a.w3 = add_word(a.w3, b.w3, c);
 }
 
 __device__ __forceinline__ void x192_sub(X192 &a, const X192 &b)
 {
-    X192 nb = x192_neg(b);
-    x192_add(a, nb);
+    unsigned c = 0;
+    a.w0 = sub_word(a.w0, b.w0, c);
+    a.w1 = sub_word(a.w1, b.w1, c);
+    a.w2 = sub_word(a.w2, b.w2, c);
+}
+
+__device__ __forceinline__ X192 x192_neg(const X192 &a)
+{
+    X192 r = {0, 0, 0};
+    x192_sub(r, a);
+    return r;
 }
 
 // Split a double into (53-bit integer mantissa, shift) relative to a fixed point whose
@@ -145,23 +157,22 @@ __device__ __forceinline__ double fx_round_top64(u64 H, bool sticky, int top, in
     return __longlong_as_double((i64)bits);
 }
 
+// The top 64 significant bits go through the u64 -> double conversion, which rounds to
+// nearest even; every lower bit is folded into the last of them (11 bits below the
+// rounding position), and scaling by a power of two is exact (no result is subnormal).
 __device__ __forceinline__ double x192_round(X192 a)
 {
-    bool neg = (i64)a.w2 < 0;
+    const bool neg = (i64)a.w2 < 0;
     if (neg) a = x192_neg(a);
-    int top;
-    if (a.w2) top = 128 + 63 - __clzll((i64)a.w2);
-    else if (a.w1) top = 64 + 63 - __clzll((i64)a.w1);
-    else if (a.w0) top = 63 - __clzll((i64)a.w0);
-    else return 0.0;
-    // left-normalise so that bit `top` lands on bit 191
-    int s = 191 - top;
-    int q = s >> 6, r = s & 63;
-    u64 a0 = a.w0, a1 = a.w1, a2 = a.w2;
-    if (q == 1) { a2 = a1; a1 = a0; a0 = 0; }
-    else if (q == 2) { a2 = a0; a1 = 0; a0 = 0; }
-    if (r) { a2 = (a2 << r) | (a1 >> (64 - r)); a1 = (a1 << r) | (a0 >> (64 - r)); a0 <<= r; }
-    double d = fx_round_top64(a2, (a1 | a0) != 0, top, 120);
+    const bool t2 = a.w2 != 0, t1 = t2 || a.w1 != 0;
+    const u64 hi = t2 ? a.w2 : t1 ? a.w1 : a.w0;
+    const u64 mid = t2 ? a.w1 : t1 ? a.w0 : 0;
+    const u64 low = t2 ? a.w0 : 0;
+    if (hi == 0) return 0.0;
+    const int z = __clzll((i64)hi);                  // 0 .. 63
+    const u64 H = (hi << z) | ((mid >> 1) >> (63 - z));
+    const u64 rest = (mid << z) | low;
+    const double d = ldexp((double)(H | (u64)(rest != 0)), (t2 ? 128 : t1 ? 64 : 0) - z - 120);
     return neg ? -d : d;
 }
 
@@ -186,6 +197,32 @@ __device__ __forceinline__ double x256_round(X256 a)   // a >= 0
     return fx_round_top64(a3, (a2 | a1 | a0) != 0, top, 192);
 }
 
+// ---- 128-bit terms ---------------------------------------------------------------------
+// A node term g in {0} or (2^-62, 1] as a 128-bit integer (lowest bit 2^-120); anything
+// outside [2^-67, 2^7) sets the flag.  A candidate's corrections sum to well within the
+// two's-complement range of +-2^7: a neighbour y of x in C changes by at most
+// 3 / (|C| - 2) (|C| >= 3; at most 1 below), and C has fewer than |C| of them.
+__device__ __forceinline__ u128 fx128(double v, int &bad)
+{
+    const u64 bits = (u64)__double_as_longlong(v);
+    const int sh = (int)(bits >> 52) - 955;         // weight of the mantissa's lowest bit above 2^-120
+    if (bits == 0) return 0;
+    if ((unsigned)sh > 73u) bad = 1;
+    const u64 m = (bits & 0xFFFFFFFFFFFFFull) | (1ull << 52);
+    const u64 l = m << (sh & 63), h = (m >> 1) >> (63 - (sh & 63));
+    const u64 lo = sh < 64 ? l : 0, hi = sh < 64 ? h : l;
+    return ((u128)hi << 64) | lo;
+}
+
+__device__ __forceinline__ X192 x192_sext128(u128 v)
+{
+    X192 r;
+    r.w0 = (u64)v;
+    r.w1 = (u64)(v >> 64);
+    r.w2 = (i64)r.w1 < 0 ? ~0ull : 0ull;
+    return r;
+}
+
 // ---- digit form (for atomics) ----------------------------------------------------------
 // A term t with |t| < 2^127 (in units of 2^-120) as four 32-bit digits: d0..d2 unsigned,
 // d3 signed, t = d0 + d1 2^32 + d2 2^64 + d3 2^96.
@@ -195,6 +232,21 @@ __device__ __forceinline__ void x192_digits(const X192 &t, i64 &d0, i64 &d1, i64
     d1 = (i64)(t.w0 >> 32);
     d2 = (i64)(t.w1 & 0xffffffffull);
     d3 = (i64)(int)(unsigned)(t.w1 >> 32);
+}
+
+// the same digits of a 128-bit term, and the 128-bit sum of digit counters
+__device__ __forceinline__ void x128_digits(u128 t, i64 &d0, i64 &d1, i64 &d2, i64 &d3)
+{
+    d0 = (i64)(unsigned)t;
+    d1 = (i64)(unsigned)(t >> 32);
+    d2 = (i64)(unsigned)(t >> 64);
+    d3 = (i64)(int)(unsigned)(t >> 96);
+}
+
+__device__ __forceinline__ u128 x128_from_digits(i64 D0, i64 D1, i64 D2, i64 D3)
+{
+    const u128 s0 = (u128)(__int128)D0, s1 = (u128)(__int128)D1, s2 = (u128)(u64)D2, s3 = (u128)(u64)D3;
+    return s0 + (s1 << 32) + (s2 << 64) + (s3 << 96);
 }
 
 __device__ __forceinline__ X192 x192_sext(i64 v)

@@ -144,23 +144,20 @@ __device__ __forceinline__ void node_sync()
     else __syncthreads();
 }
 
-// inclusive prefix sum of v over the NT threads (wave shuffles, then the waves' totals
+// inclusive prefix sum of v over the NT threads (within each wave, then the waves' totals
 // through LDS); *total receives the sum over all NT threads
 template <int NT, int VCAP>
 __device__ __forceinline__ int node_incl_scan(int v, int tid, NodeLds<VCAP> &L, int *total)
 {
     const int lane = tid & (WAVE - 1);
-    int incl = v;
-    for (int o = 1; o < WAVE; o <<= 1) {
-        int t = __shfl_up(incl, o, WAVE);
-        if (lane >= o) incl += t;
-    }
+    int wsum;
+    const int incl = wave_incl_scan(v, &wsum);
     if constexpr (NT == WAVE) {
-        *total = __shfl(incl, WAVE - 1, WAVE);
+        *total = wsum;
         return incl;
     } else {
         const int wv = tid / WAVE;
-        if (lane == WAVE - 1) L.wtot[wv] = incl;
+        if (lane == 0) L.wtot[wv] = wsum;
         __syncthreads();
         int off = 0, tot = 0;
         for (int w = 0; w < NT / WAVE; w++) {
@@ -371,8 +368,8 @@ __device__ __forceinline__ bool eval_node(const Ctx &cx, int j, const NodeRec nr
             c = L.ci[h];
             bool leave = false;
             for (int a = 0; a < mcnt; a++) leave |= (L.mx[a] == C);
-            X192 term = visit_term(leave, L.vin[v], L.vdeg[v], L.sz[c], bad);
-            x192_digits(term, t0, t1, t2, t3);
+            const u128 term = visit_term(leave, L.vin[v], L.vdeg[v], L.sz[c], bad);
+            x128_digits(term, t0, t1, t2, t3);
         }
         bool pend = act;
         for (int att = 0; att < 2; att++) {
@@ -417,7 +414,7 @@ __device__ __forceinline__ bool eval_node(const Ctx &cx, int j, const NodeRec nr
                 if (L.mx[q] == C) a = q;
             if (L.mxin[a] != k) atomicOr(&cx.ctr->error, LF_DEVERR_INCOUNT);
         }
-        X192 corr = x192_from_digits((i64)L.d[0][c], (i64)L.d[1][c], (i64)L.d[2][c], (i64)L.d[3][c]);
+        const u128 corr = x128_from_digits((i64)L.d[0][c], (i64)L.d[1][c], (i64)L.d[2][c], (i64)L.d[3][c]);
         double dl = cand_delta(rc[b], lv[b], k, d, corr, bad);
         if (lv[b]) better(dl, C, bld, bl);
         else better(dl, C, bjd, bj);
@@ -630,12 +627,8 @@ __device__ __forceinline__ void table_visits(const Ctx &cx, int cstart, int ls, 
                 xcnt = xc0;
             }
         }
-        int incl = vc;
-        for (int o = 1; o < WAVE; o <<= 1) {
-            int t = __shfl_up(incl, o, WAVE);
-            if (lane >= o) incl += t;
-        }
-        const int Vw = __shfl(incl, WAVE - 1, WAVE);
+        int Vw;
+        const int incl = wave_incl_scan(vc, &Vw);
         // this wave's occupied-list slots [obase, obase + Vw): one atomic for the block
         if (lane == 0) S.vw[wv] = Vw;
         __syncthreads();
@@ -689,10 +682,10 @@ __device__ __forceinline__ void table_visits(const Ctx &cx, int cstart, int ls, 
             const bool extra = vis && !claimed;
             i64 t0 = 0, t1 = 0, t2 = 0, t3 = 0;
             if (extra) {
-                long long s = cx.cr[C].s;
+                const int s = cx.cr[C].s;
                 bool leave = find_slot((const Slot *)xo, 0, xc, C) >= 0;
-                X192 term = visit_term(leave, iv, dyv, s, bad);
-                x192_digits(term, t0, t1, t2, t3);
+                const u128 term = visit_term(leave, iv, dyv, s, bad);
+                x128_digits(term, t0, t1, t2, t3);
             }
             bool pending = extra;
             for (int attempt = 0; attempt < 3; attempt++) {
@@ -829,18 +822,15 @@ __device__ __forceinline__ void body_big_final(const Ctx &cx, const QStep &qs, i
             const NodeLine hx = cx.big_ln[b];
             const CommRec rec = cx.cr[C];
             int k = ge.cnt + (ge.idy > 0 ? 1 : 0);
-            X192 corr = x192_from_digits(ge.d[0], ge.d[1], ge.d[2], ge.d[3]);
+            u128 corr = x128_from_digits(ge.d[0], ge.d[1], ge.d[2], ge.d[3]);
             int own_in = 0;
             int a = line_find(cx, hx, C, &own_in);
             leave = a >= 0;
-            if (ge.idy > 0) {
-                X192 t = visit_term(leave, ge.ii, ge.idy, rec.s, bad);
-                x192_add(corr, t);
-            }
+            if (ge.idy > 0) corr += visit_term(leave, ge.ii, ge.idy, rec.s, bad);
             if (leave && own_in != k) atomicOr(&cx.ctr->error, LF_DEVERR_INCOUNT);
             CandRec r;
             r.s = rec.s;
-            r.m = rec.m;
+            r.m = (int)rec.m;
             r.W = rec.W;
 #pragma unroll
             for (int q = 0; q < 5; q++) r.S[q] = leave ? rec.Sm[q] : rec.Sp[q];
@@ -1210,7 +1200,7 @@ __device__ __forceinline__ void body_refresh(const Ctx &cx, const QStep &qs, int
         const int k = pr.k;
         const long long base = pr.base, cap = pr.cap;
         // size, list length and overflow after the edits, read beside the part's entries
-        const long long s = cx.cr[C].s;
+        const int s = cx.cr[C].s;
         long long len = cx.cm_len[C];
         const int ovf = cx.ovf_flag[C];
         const long long lo = (long long)k * PART;

@@ -20,19 +20,22 @@
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");                             \
     } while (0)
 
-__device__ __forceinline__ double g_term(long long i, long long d, long long s)
+// Numerator and denominator are products of two integers below 2^33, each exact in FP64, so
+// one FP64 multiplication rounds the product exactly as a conversion of the 64-bit integer
+// product would (half the instructions of the integer product and its conversion).
+__device__ __forceinline__ double g_term(int i, int d, int s)
 {
     if (d < 2 || i < 2) return 0.0;
-    long long num = i * (i - 1);
-    long long den = (d - 1) * (s - 1 + d - i);
-    return (double)num / (double)den;
+    const double num = (double)i * (double)(i - 1);
+    const double den = (double)(d - 1) * ((double)(s - 1) + (double)(d - i));
+    return num / den;
 }
 
 // density of a community with s members and m internal edges
-__device__ __forceinline__ double density(long long s, long long m)
+__device__ __forceinline__ double density(int s, long long m)
 {
     if (s < 2) return 0.0;
-    return (double)(2 * m) / (double)(s * (s - 1));
+    return (double)(2 * m) / ((double)s * (double)(s - 1));
 }
 
 __device__ __forceinline__ X192 rec_load(const unsigned *p)
@@ -55,7 +58,7 @@ __device__ __forceinline__ void rec_store(unsigned *p, const X192 &v, int &bad)
 }
 
 // write a re-summed community (members' exact sums at sizes s, s+1, s-1 and in-count sum)
-__device__ __forceinline__ void store_comm(const Ctx &cx, int C, long long s, X192 a0, X192 ap, X192 am,
+__device__ __forceinline__ void store_comm(const Ctx &cx, int C, int s, X192 a0, X192 ap, X192 am,
                                            long long sumi, int &bad)
 {
     if (sumi & 1) atomicOr(&cx.ctr->error, LF_DEVERR_ODD);
@@ -103,22 +106,19 @@ __device__ __forceinline__ int find_slot(const Slot *slot, long long off, int cn
 
 // correction of one neighbour y (in C with in-count i, degree dy) when x joins C (its
 // in-count rises by one, the size to s+1) or leaves C (falls by one, size s-1)
-__device__ __forceinline__ X192 visit_term(bool leave, long long i, long long dy, long long s, int &bad)
+__device__ __forceinline__ u128 visit_term(bool leave, int i, int dy, int s, int &bad)
 {
-    double gn, go;
-    if (leave) { gn = g_term(i - 1, dy, s - 1); go = g_term(i, dy, s - 1); }
-    else { gn = g_term(i + 1, dy, s + 1); go = g_term(i, dy, s + 1); }
-    X192 t = x192_from_double(gn, bad);
-    X192 o = x192_from_double(go, bad);
-    x192_sub(t, o);
-    return t;
+    const int sn = leave ? s - 1 : s + 1;
+    const double gn = g_term(leave ? i - 1 : i + 1, dy, sn);
+    const double go = g_term(i, dy, sn);
+    return fx128(gn, bad) - fx128(go, bad);
 }
 
 // the fields of C's record a candidate evaluation needs (S = S- for a leave, S+ for a join)
 struct CandRec {
-    long long m;
     double W;
     unsigned S[5];
+    int m;                                   // below 2^30 (2|E| < 2^31)
     int s;
 };
 
@@ -126,7 +126,7 @@ __device__ __forceinline__ void load_cand(const Ctx &cx, int C, bool leave, Cand
 {
     const CommRec *p = &cx.cr[C];
     r.s = p->s;
-    r.m = p->m;
+    r.m = (int)p->m;
     r.W = p->W;
     const unsigned *S = leave ? p->Sm : p->Sp;
 #pragma unroll
@@ -135,33 +135,13 @@ __device__ __forceinline__ void load_cand(const Ctx &cx, int C, bool leave, Cand
 
 // change of C's cc-free score when x (degree dx, k neighbours in C) joins / leaves C;
 // corr = exact sum of the neighbours' corrections
-__device__ __forceinline__ double cand_delta(const CandRec &r, bool leave, long long k, long long dx, X192 corr,
-                                             int &bad)
+__device__ __forceinline__ double cand_delta(const CandRec &r, bool leave, int k, int dx, u128 corr, int &bad)
 {
-    long long s = r.s;
-    long long m = r.m;
+    const int sn = leave ? r.s - 1 : r.s + 1;
+    const u128 own = fx128(g_term(k, dx, sn), bad);
     X192 S = rec_load(r.S);
-    x192_add(S, corr);
-    double p;
-    if (leave) {
-        X192 own = x192_from_double(g_term(k, dx, s - 1), bad);
-        x192_sub(S, own);
-        p = density(s - 1, m - k);
-    } else {
-        X192 own = x192_from_double(g_term(k, dx, s + 1), bad);
-        x192_add(S, own);
-        p = density(s + 1, m + k);
-    }
-    double pS = p * x192_round(S);
-    return pS - r.W;
-}
-
-__device__ __forceinline__ double candidate_delta(const Ctx &cx, int C, bool leave, long long k, long long dx,
-                                                  X192 corr, int &bad)
-{
-    CandRec r;
-    load_cand(cx, C, leave, r);
-    return cand_delta(r, leave, k, dx, corr, bad);
+    x192_add(S, x192_sext128(leave ? corr - own : corr + own));
+    return density(sn, leave ? r.m - k : r.m + k) * x192_round(S) - r.W;
 }
 
 // strictly positive changes only; larger wins; equal -> lower community id
@@ -171,30 +151,66 @@ __device__ __forceinline__ void better(double d, int c, double &bd, int &bc)
     if (bc < 0 || d > bd || (d == bd && c < bc)) { bd = d; bc = c; }
 }
 
+// Cross-lane reductions over a whole wave with DPP moves (every lane active): within rows of
+// 16 lanes by shifts, then across the rows by broadcasts of each row's last lane.  A step
+// is one VALU instruction; a shuffle through LDS costs some 60 cycles of latency each.
+#define DPP_STEP(x, op, ctrl, rows) x = op(x, (unsigned)__builtin_amdgcn_update_dpp(0, (int)(x), ctrl, rows, 0xf, false))
+#define DPP_INCLUSIVE(x, op)                                                               \
+    do {                                                                                   \
+        DPP_STEP(x, op, 0x111, 0xf);                                                       \
+        DPP_STEP(x, op, 0x112, 0xf);                                                       \
+        DPP_STEP(x, op, 0x114, 0xf);                                                       \
+        DPP_STEP(x, op, 0x118, 0xf);                                                       \
+        DPP_STEP(x, op, 0x142, 0xa);                                                       \
+        DPP_STEP(x, op, 0x143, 0xc);                                                       \
+    } while (0)
+
+__device__ __forceinline__ unsigned op_add(unsigned a, unsigned b) { return a + b; }
+__device__ __forceinline__ unsigned op_max(unsigned a, unsigned b) { return a > b ? a : b; }
+
+// inclusive prefix sum over the wave's lanes; *total = the sum of all 64
+__device__ __forceinline__ int wave_incl_scan(int v, int *total)
+{
+    unsigned x = (unsigned)v;
+    DPP_INCLUSIVE(x, op_add);
+    *total = __builtin_amdgcn_readlane((int)x, WAVE - 1);
+    return (int)x;
+}
+
+// the largest of the lanes' values (unsigned), the same on every lane
+__device__ __forceinline__ unsigned wave_max_u32(unsigned x)
+{
+    DPP_INCLUSIVE(x, op_max);
+    return (unsigned)__builtin_amdgcn_readlane((int)x, WAVE - 1);
+}
+
+// best (change, community) of the wave's lanes, on every lane: the largest positive change
+// (positive doubles order like their bits), the lowest id among equals.  Most nodes have no
+// improving move, so the common case is one ballot.
 __device__ __forceinline__ void wave_best(double &bd, int &bc)
 {
-    for (int m = 32; m >= 1; m >>= 1) {
-        double od = __shfl_xor(bd, m, WAVE);
-        int oc = __shfl_xor(bc, m, WAVE);
-        if (oc >= 0 && (bc < 0 || od > bd || (od == bd && oc < bc))) { bd = od; bc = oc; }
-    }
+    if (!__ballot(bc >= 0)) return;
+    const unsigned long long bits = bc >= 0 ? (unsigned long long)__double_as_longlong(bd) : 0ull;
+    const unsigned hi = wave_max_u32((unsigned)(bits >> 32));
+    const unsigned lo = wave_max_u32((unsigned)(bits >> 32) == hi ? (unsigned)bits : 0u);
+    const unsigned long long top = ((unsigned long long)hi << 32) | lo;
+    // ids are >= 0: the lowest id is the largest complement
+    bc = (int)(0x7fffffffu - wave_max_u32(bits == top ? 0x7fffffffu - (unsigned)bc : 0u));
+    bd = __longlong_as_double((long long)top);
 }
 
 // the g-terms of one member of C with in-count i and degree d at sizes s, s+1, s-1
-__device__ __forceinline__ void member_add(long long i, long long d, long long s, X192 &a0, X192 &ap, X192 &am,
+__device__ __forceinline__ void member_add(int i, int d, int s, X192 &a0, X192 &ap, X192 &am,
                                            long long &sumi, int &bad)
 {
     sumi += i;
-    X192 v = x192_from_double(g_term(i, d, s), bad);
-    x192_add(a0, v);
-    v = x192_from_double(g_term(i, d, s + 1), bad);
-    x192_add(ap, v);
-    v = x192_from_double(g_term(i, d, s - 1), bad);
-    x192_add(am, v);
+    x192_add(a0, x192_sext128(fx128(g_term(i, d, s), bad)));
+    x192_add(ap, x192_sext128(fx128(g_term(i, d, s + 1), bad)));
+    x192_add(am, x192_sext128(fx128(g_term(i, d, s - 1), bad)));
 }
 
 // exact g-sums of one member y of C (at sizes s, s+1, s-1) if y is still in C
-__device__ __forceinline__ void member_terms(const Ctx &cx, int y, int C, long long s, X192 &a0, X192 &ap,
+__device__ __forceinline__ void member_terms(const Ctx &cx, int y, int C, int s, X192 &a0, X192 &ap,
                                              X192 &am, long long &sumi, int &bad)
 {
     NodeHdr hy = cx.nh[y];
@@ -230,7 +246,7 @@ __device__ __forceinline__ int line_find(const Ctx &cx, const NodeLine &l, int c
 }
 
 // member_terms on the membership lines
-__device__ __forceinline__ void member_terms_line(const Ctx &cx, int y, int C, long long s, X192 &a0, X192 &ap,
+__device__ __forceinline__ void member_terms_line(const Ctx &cx, int y, int C, int s, X192 &a0, X192 &ap,
                                                   X192 &am, long long &sumi, int &bad)
 {
     const NodeLine ly = cx.ln[y];
