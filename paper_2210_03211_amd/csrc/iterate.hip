@@ -6,16 +6,15 @@
 // its visits that holds for the whole iteration (k_node_bounds), and each path gets the
 // list of its nodes in order.  Per queue (all launches on the handle's stream, no host
 // synchronisation):
-//   k_eval           the small path (queues with >= 1024 such nodes): one wave per node
-//                    with <= 64 visits; then the medium path: one 256-thread block per
-//                    node with <= 256 visits, one visit per thread; each node decided
-//                    entirely in an LDS hash table
-//   k_eval_big       by block role: the table path's visits (largest nodes): every
-//                    neighbour membership (y in C) adds its exact correction to the entry
-//                    (node, C) of a global open-addressing table, own memberships add the
-//                    leave candidates; the workgroup path (one workgroup per node with
-//                    <= 1024 visits, LDS tables); the small path of smaller queues; in
-//                    multi-graph steps also the medium path (one wave per node); block 0
+//   k_eval           the small path: one wave per node with <= 64 visits; then the medium
+//                    path: one 256-thread block per node with <= 256 visits, one visit per
+//                    thread; each node decided entirely in an LDS hash table
+//   k_eval_big       (queues with larger nodes) by block role: the table path's visits
+//                    (largest nodes): every neighbour membership (y in C) adds its exact
+//                    correction to the entry (node, C) of a global open-addressing table,
+//                    own memberships add the leave candidates; the workgroup path (one
+//                    workgroup per node with <= 1024 visits, LDS tables); in short queues
+//                    and in multi-graph steps also the small and medium paths; block 0
 //                    of either launch resets the queue's counters
 //   k_big_final      every occupied table entry -> change of C's score; per node the
 //                    largest positive change (atomicMax on the bits of a positive double)
@@ -56,39 +55,39 @@ __global__ void k_queue_reset(Ctx cx)
 // ------------------------------------------------------------------------------------
 // evaluation, wave path
 // ------------------------------------------------------------------------------------
-__device__ __forceinline__ int lds_insert(int *key, int T, int lg, int C)
+// entry of C in the open-addressing table of T = 2^lg keys (-1: empty), claimed if absent
+__device__ __forceinline__ int lds_insert(int *key, int T, int lg, int C, bool &claimed)
 {
     unsigned hsh = hash_tab(C) >> (32 - lg);
     while (true) {
         int old = atomicCAS(&key[hsh], -1, C);
-        if (old == -1 || old == C) return (int)hsh;
+        if (old == -1 || old == C) {
+            claimed = old == -1;
+            return (int)hsh;
+        }
         hsh = (hsh + 1) & (T - 1);
     }
 }
 
-// LDS of one node evaluation: a candidate hash table of 2*VCAP entries, per candidate
-// (compact index, at most VCAP) its size and four correction digits, and per visit its
-// degree, table entry and in-count.  The visit-slot list is only needed before the digits
-// are cleared and shares their storage.  The last fields exchange values between the
-// waves of a workgroup evaluation.
+// LDS of one node evaluation, 36 bytes per visit: the visit list (own memberships first,
+// then the neighbours'), a hash table of 2*VCAP entries (community, count, the list entry
+// that claimed it) and, in the list's storage once it is read, 128-bit sums for the few
+// visits whose community another entry claimed first.  The last fields exchange values
+// between the waves of a workgroup evaluation.
+#define OWN_BIT 0x10000u    // kk: the community is one of the node's own (neighbours count below)
 template <int VCAP>
 struct NodeLds {
     int key[2 * VCAP];
-    int kk[2 * VCAP];
-    int ci[2 * VCAP];
-    int sz[VCAP];
-    int cl[VCAP];
+    unsigned kk[2 * VCAP];
+    unsigned short ow[2 * VCAP];
     union {
-        unsigned long long d[4][VCAP];
-        long long vslot[VCAP];
+        struct {
+            long long vslot[VCAP];
+            int vdeg[VCAP];
+        };
+        unsigned long long acc[2][VCAP];
     };
-    int vdeg[VCAP];
-    int vhash[VCAP];
-    int vin[VCAP];
-    int mx[MXCAP];
-    int mxin[MXCAP];
     int wtot[4];
-    int nc;
     double bjd[4], bld[4];
     int bj[4], bl[4];
 };
@@ -100,7 +99,7 @@ struct NodeLds {
 #define VMED 256        // visits of the medium wave path
 #define VGRP 1024       // visits of the workgroup path
 #define GT 256          // threads of the workgroup path
-#define SMALL_OWN_LAUNCH 1024   // small-path nodes from which a queue launches k_eval
+#define FUSE_BLOCKS 1024   // small and medium blocks that ride along in k_eval_big
 
 // member owning block b of a multi-graph launch (boff: first block of each member, nm + 1
 // entries); -1 past the last member's blocks
@@ -173,11 +172,20 @@ __device__ __forceinline__ int node_incl_scan(int v, int tid, NodeLds<VCAP> &L, 
 
 // Evaluate queued node j with NT threads (one wave, or a workgroup of GT threads) if its
 // neighbours (<= VCAP), visits and own memberships fit (2 * (visits + own) <= table,
-// <= VCAP visits, <= MXCAP own).  Returns false (decision not written) otherwise; the
+// <= VCAP of them, <= MXCAP own).  Returns false (decision not written) otherwise; the
 // decision to return is the same for all NT threads.  Every phase issues all of a
 // thread's global gathers (at most VCAP / NT of them) before it uses any, so a node costs
 // a handful of memory round trips whatever its size: own slots + column indices,
 // neighbour headers, neighbour slots, and one record per candidate.
+//
+// Some 95 % of the visits are their community's only one, so the list entry that claims a
+// community's table entry also scores it: it gathers the record and keeps its own
+// correction in registers.  Only the other visits of a claimed community add theirs
+// through LDS (two 64-bit atomics, the first one's carry taken into the second).  This
+// needs no list of candidates, no record exchange and half the LDS of a table with digit
+// counters, so eight 256-thread blocks share a CU instead of seven and the chain between
+// the gathers is shorter: k_eval 16.2 -> 13.1 us per launch (4M-node social-shaped graph,
+// queue 4096), 116 -> 86 us (1M nodes, queue 65,536).
 template <int NT, int VCAP>
 __device__ __forceinline__ bool eval_node(const Ctx &cx, int j, const NodeRec nr, int tid, NodeLds<VCAP> &L,
                                           int wcap, int path)
@@ -201,8 +209,7 @@ __device__ __forceinline__ bool eval_node(const Ctx &cx, int j, const NodeRec nr
     Slot own = {-1, 0};
     if (tid < LINE_SLOTS) own = lxp->s[tid];
     if (mcnt > MXCAP) return false;
-    if (xoff >= 0) own = tid < mcnt ? cx.slot[xoff + tid] : Slot{-1, 0};
-    else if (tid >= mcnt) own = Slot{-1, 0};
+    if (xoff >= 0 && tid < mcnt) own = cx.slot[xoff + tid];
     // one line per neighbour: its count, degree and memberships in one gather
     NodeLine ly[NB];
 #pragma unroll
@@ -215,18 +222,18 @@ __device__ __forceinline__ bool eval_node(const Ctx &cx, int j, const NodeRec nr
             ly[b].off = -1;
         }
     }
-    // neighbour memberships flattened into the visit list: an inline membership is kept
-    // as its (community, in-count) pair, one in the slot array as the complement of its
-    // slot index (read in phase 1)
-    int V = 0;
+    // neighbour memberships flattened into the list behind the own ones: an inline
+    // membership is kept as its (community, in-count) pair, one in the slot array as the
+    // complement of its slot index
+    int N = mcnt;
 #pragma unroll
     for (int b = 0; b < NB; b++) {
         if (b * NT < d) {                   // uniform over the NT threads
             int yc = ly[b].cnt, tot;
             int incl = node_incl_scan<NT>(yc, tid, L, &tot);
-            int p0 = V + incl - yc;
-            V += tot;
-            if (V + mcnt > VCAP || 2 * (V + mcnt) > wcap) return false;   // uniform
+            int p0 = N + incl - yc;
+            N += tot;
+            if (N > VCAP || 2 * N > wcap) return false;   // uniform
             if (ly[b].off < 0) {
 #pragma unroll
                 for (int t = 0; t < LINE_SLOTS; t++)
@@ -242,31 +249,32 @@ __device__ __forceinline__ bool eval_node(const Ctx &cx, int j, const NodeRec nr
             }
         }
     }
-    int T = 8;
-    while (T < 2 * (V + mcnt)) T <<= 1;
-    const int lg = 31 - __clz(T);
+    const int lg = N <= 4 ? 3 : 32 - __clz(2 * N - 1);    // T = 2^lg >= 2 N
+    const int T = 1 << lg;
     for (int t = tid; t < T; t += NT) {
         L.key[t] = -1;
         L.kk[t] = 0;
     }
     if (tid < mcnt) {
-        L.mx[tid] = own.comm;
-        L.mxin[tid] = own.in;
+        L.vslot[tid] = ((long long)own.in << 32) | (unsigned)own.comm;
+        L.vdeg[tid] = -1;                   // an own membership, not a visit
     }
-    if (tid == 0) L.nc = 0;
     node_sync<NT>();
-    // 1. candidates and neighbour counts: own communities are leave candidates even without
-    //    a neighbour in them; every neighbour membership counts towards its community
-    if (tid < mcnt) lds_insert(L.key, T, lg, own.comm);
+    // 1. every entry counts towards its community; own communities are leave candidates
+    //    even without a neighbour in them, and a membership its neighbour left earlier in
+    //    this iteration (a hole) is no visit
     Slot sv[NB];
+    int dg[NB];
 #pragma unroll
     for (int b = 0; b < NB; b++) {
-        int v = b * NT + tid;
+        const int v = b * NT + tid;
         sv[b].comm = -1;
         sv[b].in = 0;
-        if (v < V) {
+        dg[b] = 0;
+        if (v < N) {
             const long long e = L.vslot[v];
-            if (e >= 0) {
+            dg[b] = L.vdeg[v];
+            if (e >= 0 || dg[b] < 0) {
                 sv[b].comm = (int)(unsigned)e;
                 sv[b].in = (int)(e >> 32);
             } else {
@@ -274,150 +282,76 @@ __device__ __forceinline__ bool eval_node(const Ctx &cx, int j, const NodeRec nr
             }
         }
     }
+    int hs[NB];                             // table entry, or -1
+    bool mine[NB];                          // this entry claimed it
 #pragma unroll
     for (int b = 0; b < NB; b++) {
-        // lanes of a wave that share the first pending community (a node's own
-        // communities often hold most of its neighbours) insert and count it once; a
-        // membership its neighbour left earlier in this iteration is no visit
-        const int v = b * NT + tid;
-        const int C = sv[b].comm;
-        bool pend = v < V && C >= 0;
-        int h = -1;
-        for (int att = 0; att < 2; att++) {
-            const unsigned long long pm = __ballot(pend);
-            if (!pm) break;
-            const int first = __ffsll((long long)pm) - 1;
-            const int c0 = __shfl(C, first, WAVE);
-            const bool in = pend && C == c0;
-            const unsigned long long gm = __ballot(in);
-            if (__popcll(gm) < 4) break;    // uniform over the wave
-            int h0 = 0;
-            if (lane == first) {
-                h0 = lds_insert(L.key, T, lg, c0);
-                atomicAdd(&L.kk[h0], __popcll(gm));
-            }
-            h0 = __shfl(h0, first, WAVE);
-            if (in) {
-                h = h0;
-                pend = false;
-            }
-        }
-        if (pend) {
-            h = lds_insert(L.key, T, lg, C);
-            atomicAdd(&L.kk[h], 1);
-        }
-        if (v < V) {
-            L.vhash[v] = h;                 // -1 for a left membership
-            L.vin[v] = sv[b].in;
+        hs[b] = -1;
+        mine[b] = false;
+        if (sv[b].comm >= 0) {
+            hs[b] = lds_insert(L.key, T, lg, sv[b].comm, mine[b]);
+            if (mine[b]) L.ow[hs[b]] = (unsigned short)(b * NT + tid);
+            atomicAdd(&L.kk[hs[b]], dg[b] < 0 ? OWN_BIT : 1u);
         }
     }
     node_sync<NT>();
-    // compact list of the occupied entries (at most V + mcnt <= VCAP; the order within the
-    // list does not matter); the visit slots are consumed, so their storage becomes the
-    // candidates' digits
-    for (int t0 = 0; t0 < T; t0 += NT) {
-        int t = t0 + tid;
-        bool occ = t < T && L.key[t] >= 0;
-        unsigned long long m = __ballot(occ);
-        int base = 0;
-        if (lane == 0 && m) base = atomicAdd(&L.nc, __popcll(m));
-        base = __shfl(base, 0, WAVE);
-        int c = base + __popcll(m & ((1ull << lane) - 1));
-        if (occ) {
-            L.cl[c] = t;
-            L.ci[t] = c;
-        }
-    }
-    node_sync<NT>();
-    const int NC = L.nc;
-    for (int c = tid; c < NC; c += NT) {
-        L.d[0][c] = 0; L.d[1][c] = 0; L.d[2][c] = 0; L.d[3][c] = 0;
-    }
-    // 2. one community-record gather per candidate; its size feeds the visit terms
-    int ct[NB];
-    bool lv[NB];
+    // 2. one record gather per candidate (the other visits need its size only); the list is
+    //    read, its storage becomes the sums
     CandRec rc[NB];
+    unsigned kk[NB];
 #pragma unroll
     for (int b = 0; b < NB; b++) {
-        int c = b * NT + tid;
-        ct[b] = c < NC ? L.cl[c] : -1;
-        lv[b] = false;
-        if (ct[b] >= 0) {
-            int C = L.key[ct[b]];
-            for (int q = 0; q < mcnt; q++) lv[b] |= (L.mx[q] == C);
-            load_cand(cx, C, lv[b], rc[b]);
+        kk[b] = 0;
+        if (hs[b] >= 0) {
+            kk[b] = L.kk[hs[b]];
+            if (mine[b]) load_cand(cx, sv[b].comm, kk[b] >= OWN_BIT, rc[b]);
+            else rc[b].s = cx.cr[sv[b].comm].s;
+            L.acc[0][b * NT + tid] = 0;
+            L.acc[1][b * NT + tid] = 0;
         }
     }
+    // 3. exact correction of every visit; those of a community another entry claimed are
+    //    summed at that entry
+    int bad = 0;
+    u128 term[NB];
 #pragma unroll
     for (int b = 0; b < NB; b++) {
-        int c = b * NT + tid;
-        if (ct[b] >= 0) L.sz[c] = rc[b].s;
+        term[b] = 0;
+        if (hs[b] >= 0 && dg[b] >= 0) term[b] = visit_term(kk[b] >= OWN_BIT, sv[b].in, dg[b], rc[b].s, bad);
     }
     node_sync<NT>();
-    // 3. exact correction of every visit, summed per candidate; as in phase 1, lanes of a
-    //    wave that share the first pending candidate add one wave-summed set of digits
-    int bad = 0;
-    for (int v0 = 0; v0 < V; v0 += NT) {    // same trip count on every lane of a wave
-        const int v = v0 + tid;
-        const bool act = v < V && L.vhash[v] >= 0;
-        int c = 0;
-        i64 t0 = 0, t1 = 0, t2 = 0, t3 = 0;
-        if (act) {
-            int h = L.vhash[v];
-            int C = L.key[h];
-            c = L.ci[h];
-            bool leave = false;
-            for (int a = 0; a < mcnt; a++) leave |= (L.mx[a] == C);
-            const u128 term = visit_term(leave, L.vin[v], L.vdeg[v], L.sz[c], bad);
-            x128_digits(term, t0, t1, t2, t3);
-        }
-        bool pend = act;
-        for (int att = 0; att < 2; att++) {
-            const unsigned long long pm = __ballot(pend);
-            if (!pm) break;
-            const int first = __ffsll((long long)pm) - 1;
-            const int c0 = __shfl(c, first, WAVE);
-            const bool in = pend && c == c0;
-            const unsigned long long gm = __ballot(in);
-            if (__popcll(gm) < 4) break;    // uniform over the wave
-            const i64 a0 = wave_sum_i64(in ? t0 : 0), a1 = wave_sum_i64(in ? t1 : 0);
-            const i64 a2 = wave_sum_i64(in ? t2 : 0), a3 = wave_sum_i64(in ? t3 : 0);
-            if (lane == first) {
-                atomicAdd(&L.d[0][c0], (unsigned long long)a0);
-                atomicAdd(&L.d[1][c0], (unsigned long long)a1);
-                atomicAdd(&L.d[2][c0], (unsigned long long)a2);
-                atomicAdd(&L.d[3][c0], (unsigned long long)a3);
+#pragma unroll
+    for (int b = 0; b < NB; b++) {
+        if (hs[b] >= 0) {
+            if (dg[b] < 0) {
+                if ((unsigned)sv[b].in != (kk[b] & (OWN_BIT - 1))) atomicOr(&cx.ctr->error, LF_DEVERR_INCOUNT);
+            } else if (!mine[b]) {
+                const int o = L.ow[hs[b]];
+                const unsigned long long lo = (unsigned long long)term[b];
+                const unsigned long long was = atomicAdd(&L.acc[0][o], lo);
+                atomicAdd(&L.acc[1][o], (unsigned long long)(term[b] >> 64) + (was + lo < lo ? 1ull : 0ull));
             }
-            if (in) pend = false;
-        }
-        if (pend) {
-            atomicAdd(&L.d[0][c], (unsigned long long)t0);
-            atomicAdd(&L.d[1][c], (unsigned long long)t1);
-            atomicAdd(&L.d[2][c], (unsigned long long)t2);
-            atomicAdd(&L.d[3][c], (unsigned long long)t3);
         }
     }
     node_sync<NT>();
     // 4. change of every candidate's score, best join and best leave
     double bjd = 0.0, bld = 0.0;
     int bj = -1, bl = -1;
+    int ncand = 0;
 #pragma unroll
     for (int b = 0; b < NB; b++) {
-        int t = ct[b];
-        if (t < 0) continue;
-        int c = b * NT + tid;
-        int C = L.key[t];
-        int k = L.kk[t];
-        if (lv[b]) {
-            int a = -1;
-            for (int q = 0; q < mcnt; q++)
-                if (L.mx[q] == C) a = q;
-            if (L.mxin[a] != k) atomicOr(&cx.ctr->error, LF_DEVERR_INCOUNT);
+        if (!mine[b]) continue;
+        ncand++;
+        const bool leave = kk[b] >= OWN_BIT;
+        const int k = (int)(kk[b] & (OWN_BIT - 1));
+        u128 corr = term[b];
+        if (k > (dg[b] >= 0 ? 1 : 0)) {
+            const int v = b * NT + tid;
+            corr += ((u128)L.acc[1][v] << 64) | L.acc[0][v];
         }
-        const u128 corr = x128_from_digits((i64)L.d[0][c], (i64)L.d[1][c], (i64)L.d[2][c], (i64)L.d[3][c]);
-        double dl = cand_delta(rc[b], lv[b], k, d, corr, bad);
-        if (lv[b]) better(dl, C, bld, bl);
-        else better(dl, C, bjd, bj);
+        const double dl = cand_delta(rc[b], leave, k, d, corr, bad);
+        if (leave) better(dl, sv[b].comm, bld, bl);
+        else better(dl, sv[b].comm, bjd, bj);
     }
     wave_best(bjd, bj);
     wave_best(bld, bl);
@@ -447,12 +381,14 @@ __device__ __forceinline__ bool eval_node(const Ctx &cx, int j, const NodeRec nr
         cx.dld[j] = bl >= 0 ? bld : 0.0;
         cx.dpos[j] = mcnt;
         cx.big_idx[j] = Q_DONE;
-        if (cx.stats) {
-            unsigned long long *w = cx.ctr->work[path];
+    }
+    if (cx.stats) {
+        unsigned long long *w = cx.ctr->work[path];
+        if (ncand) atomicAdd(&w[3], (unsigned long long)ncand);
+        if (tid == 0) {
             atomicAdd(&w[0], 1ull);
             atomicAdd(&w[1], (unsigned long long)d);
-            atomicAdd(&w[2], (unsigned long long)V);
-            atomicAdd(&w[3], (unsigned long long)NC);
+            atomicAdd(&w[2], (unsigned long long)(N - mcnt));
             atomicAdd(&w[4], (unsigned long long)mcnt);
         }
     }
@@ -479,25 +415,18 @@ __device__ __forceinline__ void mark_table(const Ctx &cx, int j, int deg, int ow
 // The in-LDS evaluation paths take their queue's nodes from their path lists; the path
 // was chosen so that the node fits, and a node that does not is an internal error.
 
-// The small and medium paths of a single graph's queue in one launch of 256-thread
-// blocks with 21 KB of LDS (seven blocks per CU): the first es blocks evaluate small-path
-// nodes, one wave each (queues with many of them; otherwise they are a block role of
-// k_eval_big), the next em blocks one medium-path node each, one visit per thread.
-// Block 0 also resets the queue's apply counters.
+// The small and medium paths, in 256-thread blocks: the first es blocks evaluate four
+// small-path nodes each, one per wave; the next em blocks one medium-path node each, one
+// visit per thread.  These are all of k_eval (10 KB of LDS, eight blocks per CU), and
+// block roles of k_eval_big where a launch of their own does not pay.
 union EvalLds {
     NodeLds<VSMALL> w[EW];
     NodeLds<VMED> m;
 };
 
-__device__ __forceinline__ void body_eval(const Ctx &cx, const QStep &qs, int blk, int nblk, EvalLds &L)
+__device__ __forceinline__ void eval_small_med(const Ctx &cx, const QStep &qs, int blk, EvalLds &L)
 {
-    (void)nblk;
     const int wv = threadIdx.x / WAVE, lane = threadIdx.x & (WAVE - 1);
-    if (blk == 0 && threadIdx.x == 0) {
-        DevCounters *c = cx.ctr;
-        c->parts_total = 0;
-        c->mslots = 0;
-    }
     if (blk < qs.es) {
         const int p = blk * EW + wv;
         if (p >= qs.ln) return;             // small blocks have no block barriers
@@ -509,16 +438,27 @@ __device__ __forceinline__ void body_eval(const Ctx &cx, const QStep &qs, int bl
     }
     const int m = blk - qs.es;              // a medium block: every thread takes part
     if (m >= qs.em) return;
-    const int j = cx.plist[LF_PATH_MED][qs.br.lm + m] - qs.cstart;
-    const NodeRec nr = cx.prec[LF_PATH_MED][qs.br.lm + m];
+    const int j = cx.plist[LF_PATH_MED][qs.lm + m] - qs.cstart;
+    const NodeRec nr = cx.prec[LF_PATH_MED][qs.lm + m];
     if (!eval_node<EW * WAVE, VMED>(cx, j, nr, threadIdx.x, L.m, qs.mcap, LF_PATH_MED) && threadIdx.x == 0)
         atomicOr(&cx.ctr->error, LF_DEVERR_CAP);
+}
+
+// block 0 of a queue's first launch resets its apply counters (no evaluation role uses them)
+__device__ __forceinline__ void reset_apply_counters(const Ctx &cx, int blk)
+{
+    if (blk == 0 && threadIdx.x == 0) {
+        DevCounters *c = cx.ctr;
+        c->parts_total = 0;
+        c->mslots = 0;
+    }
 }
 
 __global__ void __launch_bounds__(EW * WAVE) k_eval(Ctx cx, QStep qs)
 {
     __shared__ EvalLds lds;
-    body_eval(cx, qs, (int)blockIdx.x, (int)gridDim.x, lds);
+    reset_apply_counters(cx, (int)blockIdx.x);
+    eval_small_med(cx, qs, (int)blockIdx.x, lds);
 }
 
 // ------------------------------------------------------------------------------------
@@ -743,8 +683,7 @@ __device__ __forceinline__ void table_visits(const Ctx &cx, int cstart, int ls, 
 union BigLds {
     TabLds t;
     NodeLds<VGRP> g;
-    NodeLds<VMED> m[GT / WAVE];
-    NodeLds<VSMALL> s[GT / WAVE];
+    EvalLds e;
 };
 
 __device__ __forceinline__ void body_eval_big(const Ctx &cx, const QStep &qs, int blk, int nblk, BigLds &L)
@@ -752,11 +691,7 @@ __device__ __forceinline__ void body_eval_big(const Ctx &cx, const QStep &qs, in
     (void)nblk;
     const BigRoles &r = qs.br;
     const int cstart = qs.cstart;
-    if (blk == 0 && threadIdx.x == 0) {     // the queue's apply counters (no role uses them)
-        DevCounters *c = cx.ctr;
-        c->parts_total = 0;
-        c->mslots = 0;
-    }
+    reset_apply_counters(cx, blk);
     int b = blk;
     if (b < r.bt) {
         table_visits(cx, cstart, r.lt, r.nt, b, r.bt, L.t);
@@ -773,24 +708,7 @@ __device__ __forceinline__ void body_eval_big(const Ctx &cx, const QStep &qs, in
         }
         return;
     }
-    b -= r.bg;
-    const int wv = threadIdx.x / WAVE, lane = threadIdx.x & (WAVE - 1);
-    if (b < r.bm) {
-        for (int p = b * (GT / WAVE) + wv; p < r.nm; p += r.bm * (GT / WAVE)) {   // no block barriers
-            const int j = cx.plist[LF_PATH_MED][r.lm + p] - cstart;
-            const NodeRec nr = cx.prec[LF_PATH_MED][r.lm + p];
-            if (!eval_node<WAVE, VMED>(cx, j, nr, lane, L.m[wv], qs.mcap, LF_PATH_MED) && lane == 0)
-                atomicOr(&cx.ctr->error, LF_DEVERR_CAP);
-        }
-        return;
-    }
-    b -= r.bm;
-    for (int p = b * (GT / WAVE) + wv; p < r.ns; p += r.bs * (GT / WAVE)) {    // small path, one wave per node
-        const int j = cx.plist[LF_PATH_SMALL][qs.ls + p] - cstart;
-        const NodeRec nr = cx.prec[LF_PATH_SMALL][qs.ls + p];
-        if (!eval_node<WAVE, VSMALL>(cx, j, nr, lane, L.s[wv], qs.wcap, LF_PATH_SMALL) && lane == 0)
-            atomicOr(&cx.ctr->error, LF_DEVERR_CAP);
-    }
+    if (r.fuse) eval_small_med(cx, qs, b - r.bg, L.e);
 }
 QUEUE_KERNELS(k_eval_big, GT, BigLds, body_eval_big)
 
@@ -1970,28 +1888,19 @@ void lf_queue_params(lf_handle *h, long long k, long long nq, long long qq, bool
     br.bt = ln[LF_PATH_TABLE] > 0 ? (int)grid_for(titems, 2 * EWB * WAVE) : 0;
     if (br.bt > gb) br.bt = gb;
     br.bg = ln[LF_PATH_GROUP] < gb ? ln[LF_PATH_GROUP] : gb;
-    // a single graph's medium-path nodes take one k_eval block each (one visit per thread,
-    // seven blocks per CU); in a multi-graph step they are a role of k_eval_big (one wave
-    // per node), as is everything there
-    const bool own_med = !compact_grids;
-    br.bm = own_med ? 0 : (int)grid_for(ln[LF_PATH_MED], GT / WAVE);
-    // a queue with many small-path nodes gives them blocks of k_eval too (more blocks per
-    // CU than the fused kernel's LDS allows); otherwise they are a role of k_eval_big
-    const bool own_small = !compact_grids && ln[LF_PATH_SMALL] >= SMALL_OWN_LAUNCH;
-    br.ns = own_small ? 0 : ln[LF_PATH_SMALL];
-    br.bs = (int)grid_for(br.ns, GT / WAVE);
+    qs->es = (int)grid_for(ln[LF_PATH_SMALL], EW);
+    qs->em = ln[LF_PATH_MED];
+    qs->lm = ls[LF_PATH_MED];
     br.lt = ls[LF_PATH_TABLE];
     br.nt = ln[LF_PATH_TABLE];
     br.lg = ls[LF_PATH_GROUP];
     br.ng = ln[LF_PATH_GROUP];
-    br.lm = ls[LF_PATH_MED];
-    br.nm = own_med ? 0 : ln[LF_PATH_MED];
     qs->ub = hu[k];
     qs->un = (int)(hu[k + 1] - hu[k]);
-    qs->es = own_small ? (int)grid_for(ln[LF_PATH_SMALL], EW) : 0;
-    qs->em = own_med ? ln[LF_PATH_MED] : 0;
-    g->eval = qs->es + qs->em;
-    g->big = br.bt + br.bg + br.bm + br.bs;
+    const bool heavy = br.bt + br.bg > 0;
+    br.fuse = compact_grids || (heavy && qs->es + qs->em <= FUSE_BLOCKS);
+    g->eval = br.fuse ? 0 : qs->es + qs->em;
+    g->big = br.bt + br.bg + (br.fuse ? qs->es + qs->em : 0);
     if (g->big < 1 && g->eval == 0) g->big = 1;   // block 0 resets the queue's counters
     g->fin = ln[LF_PATH_TABLE] > 0 ? (compact_grids ? (br.bt > 0 ? br.bt : 1) : gb) : 0;
     g->apply = (int)grid_for(clen, 256) + (int)grid_for(qs->un, 256 / WAVE);

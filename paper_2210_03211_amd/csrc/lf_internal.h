@@ -180,14 +180,13 @@ struct Ctx {
 };
 
 // Block roles of k_eval_big: [0, bt) walk the table-path work items, the next bg blocks
-// evaluate workgroup-path nodes (one node per block at a time), the last bm blocks
-// medium-path nodes (one node per wave).
+// evaluate workgroup-path nodes (one node per block at a time), and with fuse the rest are
+// the small and medium blocks of QStep.
 struct BigRoles {
-    int bt, bg, bm, bs;      // blocks per role (table, workgroup, medium, small)
-    int ns;                  // small-path nodes in this launch (the rest: k_eval)
+    int bt, bg;              // blocks per role (table, workgroup)
+    int fuse;                // the small and medium paths are in this launch, not in k_eval
     int lt, nt;              // table-path list positions of the queue
     int lg, ng;              // workgroup-path list positions
-    int lm, nm;              // medium-path list positions
 };
 
 // Everything the kernels of one queue need besides the graph's Ctx.
@@ -195,8 +194,9 @@ struct QStep {
     int cstart, clen;        // the queue: order positions [cstart, cstart + clen)
     int wcap, mcap, gcap;    // LDS table sizes of the small, medium and workgroup paths
     int ls, ln;              // small-path list positions
-    int es, em;              // k_eval: blocks of small-path nodes (four per block), then one
-                             // block per medium-path node (the first em of list br.lm)
+    int lm;                  // first medium-path list position
+    int es, em;              // blocks of small-path nodes (four per block), then one block per
+                             // medium-path node
     BigRoles br;
     long long ub;            // the queue's in-count units: [ub, ub + un)
     int un;
