@@ -68,13 +68,13 @@ typedef struct {
 #define LF_K_TRIANGLES 1    /* triangle counting (all launches) */
 #define LF_K_ORDER 2        /* CC, cc reduction, node order */
 #define LF_K_INITCLUST 3    /* initial clustering and state set-up */
-#define LF_K_EVAL 4         /* k_eval: small wave path (<= 64 visits) of queues with many
-                               such nodes */
-#define LF_K_EVAL_BIG 5     /* k_eval_big: the other evaluation paths of a queue, by block
-                               role: table-path visits, workgroup path (<= 1024 visits),
-                               medium wave path (<= 256), small path of smaller queues */
-#define LF_K_TAB_FINAL 6    /* k_big_final: table path, candidate changes and maxima */
-#define LF_K_TAB_TIE 7      /* k_big_tie: table path, lowest id among equal maxima */
+#define LF_K_EVAL 4         /* k_eval: small wave path (<= 64 visits) and medium path (<= 256)
+                               of queues without larger nodes, or with very many of these */
+#define LF_K_EVAL_BIG 5     /* k_eval_big: queues with larger nodes, by block role: table-path
+                               visits, workgroup path (<= 1024 visits), and the small and
+                               medium paths */
+#define LF_K_TAB_FINAL 6    /* k_big_final: table path, candidate changes per hash bucket */
+#define LF_K_TAB_TIE 7      /* k_big_tie: table path, the best of each node's buckets */
 #define LF_K_APPLY_EDIT 8   /* k_apply: the bulk apply of a queue: membership edits, sizes,
                                member lists and re-sum planning beside the in-count changes
                                around the moved nodes */
@@ -302,8 +302,9 @@ int lf_reset_profile(lf_handle *h);
 #define LF_OPT_TRI_LDS_CAP 1       /* max out-list length staged in LDS by the workgroup
                                       triangle kernel (0 = as much as LDS holds); longer
                                       out-lists use global scratch */
-#define LF_OPT_HUB_BLOCKS 3        /* most workgroups of the table path and of the workgroup
-                                      path per launch */
+#define LF_OPT_HUB_BLOCKS 3        /* a quarter of the most workgroups that place the table
+                                      path's visits, and that evaluate the workgroup path,
+                                      per launch */
 #define LF_OPT_REFRESH_BLOCKS 4    /* workgroups of the in-count and re-sum kernels */
 #define LF_OPT_WAVE_TABLE 5        /* candidate-table entries per wave in the wave path
                                       (power of two, 16 .. 128); nodes needing more go to

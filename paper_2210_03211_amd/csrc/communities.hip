@@ -485,31 +485,21 @@ Ctx lf_ctx(lf_handle *h)
     c.ovf_node = h->ovf_node;
     c.ovf_comm = h->ovf_comm;
     c.ovf_flag = h->ovf_flag;
-    c.dj = h->dj;
-    c.dl = h->dl;
-    c.djd = h->djd;
-    c.dld = h->dld;
-    c.dpos = h->dpos;
+    c.dec = h->dec;
     c.ctr = h->ctr;
-    c.big_idx = h->big_idx;
     for (int k = 0; k < LF_PATH_COUNT; k++) {
         c.plist[k] = h->plist[k];
         c.prec[k] = h->prec[k];
     }
     c.rank = h->rank;
     c.col_rank = h->col_rank;
-    c.titem_base = h->titem_base;
-    c.titem_node = h->titem_node;
-    c.big_bj = h->big_bj;
-    c.big_bl = h->big_bl;
-    c.big_cj = h->big_cj;
-    c.big_cl = h->big_cl;
-    c.big_ln = h->big_ln;
-    c.gt = h->gt;
-    c.occ = h->occ;
-    c.occ_key = h->occ_key;
-    c.occ_d = h->occ_d;
-    c.gmask = h->gT > 0 ? h->gT - 1 : 0;
+    c.tpos = h->tpos;
+    c.tchunk = h->tchunk;
+    c.tbuck = h->tbuck;
+    c.tcur = h->tcur;
+    c.tvis = h->tvis;
+    c.trow = h->trow;
+    c.tres = h->tres;
     c.unit = h->unit;
     c.part_rec = h->part_rec;
     c.part_done = h->part_done;

@@ -10,15 +10,13 @@
 //                    path: one 256-thread block per node with <= 256 visits, one visit per
 //                    thread; each node decided entirely in an LDS hash table
 //   k_eval_big       (queues with larger nodes) by block role: the table path's visits
-//                    (largest nodes): every neighbour membership (y in C) adds its exact
-//                    correction to the entry (node, C) of a global open-addressing table,
-//                    own memberships add the leave candidates; the workgroup path (one
-//                    workgroup per node with <= 1024 visits, LDS tables); in short queues
-//                    and in multi-graph steps also the small and medium paths; block 0
-//                    of either launch resets the queue's counters
-//   k_big_final      every occupied table entry -> change of C's score; per node the
-//                    largest positive change (atomicMax on the bits of a positive double)
-//   k_big_tie        among the entries equal to that maximum the lowest community id
+//                    (largest nodes), grouped by hash bucket of their communities; the
+//                    workgroup path (one workgroup per node with <= 1024 visits, LDS
+//                    tables); in all but very long queues and in multi-graph steps also the
+//                    small and medium paths; block 0 of either launch resets the queue's
+//                    counters
+//   k_big_final      table path: one block per bucket, evaluated in LDS
+//   k_big_tie        table path: the best of each node's buckets
 //   k_apply          the bulk apply: membership edits, sizes, member-list appends and
 //                    re-sum planning (a thread per queued node) beside the in-count
 //                    changes around the moved nodes (a wave per in-count unit)
@@ -37,7 +35,6 @@
 #define HOLE (-2)       // a membership left in the current iteration (removed at its end)
 #define PART 128        // members per re-sum part
 #define MACC 19         // carry-save counters per multi-part community (3 x 6 digits + in-sum)
-#define GEMPTY (~0ull)
 
 static inline unsigned grid_for(long long n, int block) { return (unsigned)((n + block - 1) / block); }
 
@@ -46,7 +43,6 @@ __global__ void k_queue_reset(Ctx cx)
 {
     if (threadIdx.x == 0) {
         DevCounters *c = cx.ctr;
-        c->occ_cnt = 0;
         c->parts_total = 0;
         c->mslots = 0;
     }
@@ -92,14 +88,15 @@ struct NodeLds {
     int bj[4], bl[4];
 };
 
-// big_idx states of a queue index
-#define Q_DONE 0        // decided by a wave or workgroup path
-#define Q_TABLE 1       // decided by the table path
 #define VSMALL 64       // visits of the small wave path
 #define VMED 256        // visits of the medium wave path
 #define VGRP 1024       // visits of the workgroup path
 #define GT 256          // threads of the workgroup path
-#define FUSE_BLOCKS 1024   // small and medium blocks that ride along in k_eval_big
+// Small and medium blocks ride along in k_eval_big, beside the larger nodes, unless there are
+// more of them than it keeps resident some five times over (it holds three blocks per CU, k_eval
+// eight).  Measured on the social-shaped graphs: 4M nodes, queue 4096 (about 1,500 blocks) 556
+// ms fused against 560 apart; 1M nodes, queue 65,536 (over 10,000 blocks) 88 ms apart.
+#define FUSE_BLOCKS 4096
 
 // member owning block b of a multi-graph launch (boff: first block of each member, nm + 1
 // entries); -1 past the last member's blocks
@@ -170,13 +167,9 @@ __device__ __forceinline__ int node_incl_scan(int v, int tid, NodeLds<VCAP> &L, 
     }
 }
 
-// Evaluate queued node j with NT threads (one wave, or a workgroup of GT threads) if its
-// neighbours (<= VCAP), visits and own memberships fit (2 * (visits + own) <= table,
-// <= VCAP of them, <= MXCAP own).  Returns false (decision not written) otherwise; the
-// decision to return is the same for all NT threads.  Every phase issues all of a
-// thread's global gathers (at most VCAP / NT of them) before it uses any, so a node costs
-// a handful of memory round trips whatever its size: own slots + column indices,
-// neighbour headers, neighbour slots, and one record per candidate.
+// A node of degree d, evaluated from its list entries (entry b * NT + tid in sv[b]; a
+// community below 0 is no entry; dg < 0: an own membership, else the neighbour's degree) in
+// the cleared table of T = 2^lg entries.  Best join and leave on thread 0.
 //
 // Some 95 % of the visits are their community's only one, so the list entry that claims a
 // community's table entry also scores it: it gathers the record and keeps its own
@@ -186,102 +179,17 @@ __device__ __forceinline__ int node_incl_scan(int v, int tid, NodeLds<VCAP> &L, 
 // counters, so eight 256-thread blocks share a CU instead of seven and the chain between
 // the gathers is shorter: k_eval 16.2 -> 13.1 us per launch (4M-node social-shaped graph,
 // queue 4096), 116 -> 86 us (1M nodes, queue 65,536).
-template <int NT, int VCAP>
-__device__ __forceinline__ bool eval_node(const Ctx &cx, int j, const NodeRec nr, int tid, NodeLds<VCAP> &L,
-                                          int wcap, int path)
+struct Best {
+    double jd, ld;
+    int j, l;
+    int ncand;                              // candidates this thread scored
+};
+
+template <int NT, int NB, int VCAP>
+__device__ __forceinline__ Best score_list(const Ctx &cx, int d, const Slot (&sv)[NB], const int (&dg)[NB], int tid,
+                                           NodeLds<VCAP> &L, int T, int lg)
 {
-    constexpr int NB = VCAP / NT;
     const int lane = tid & (WAVE - 1);
-    const int x = nr.x, d = nr.d;
-    const long long rb = nr.rb;
-    if (d > VCAP) return false;
-    // the adjacency gathers need only the node record; the header is fetched beside them
-    int yv[NB];
-#pragma unroll
-    for (int b = 0; b < NB; b++) {
-        int e = b * NT + tid;
-        yv[b] = e < d ? cx.col[rb + e] : -1;
-    }
-    // own line: count, placement and (inline) memberships, read beside the adjacency
-    const NodeLine *lxp = cx.ln + x;
-    const int mcnt = lxp->cnt;
-    const long long xoff = lxp->off;
-    Slot own = {-1, 0};
-    if (tid < LINE_SLOTS) own = lxp->s[tid];
-    if (mcnt > MXCAP) return false;
-    if (xoff >= 0 && tid < mcnt) own = cx.slot[xoff + tid];
-    // one line per neighbour: its count, degree and memberships in one gather
-    NodeLine ly[NB];
-#pragma unroll
-    for (int b = 0; b < NB; b++) {
-        if (yv[b] >= 0) {
-            ly[b] = cx.ln[yv[b]];
-        } else {
-            ly[b].cnt = 0;
-            ly[b].deg = 0;
-            ly[b].off = -1;
-        }
-    }
-    // neighbour memberships flattened into the list behind the own ones: an inline
-    // membership is kept as its (community, in-count) pair, one in the slot array as the
-    // complement of its slot index
-    int N = mcnt;
-#pragma unroll
-    for (int b = 0; b < NB; b++) {
-        if (b * NT < d) {                   // uniform over the NT threads
-            int yc = ly[b].cnt, tot;
-            int incl = node_incl_scan<NT>(yc, tid, L, &tot);
-            int p0 = N + incl - yc;
-            N += tot;
-            if (N > VCAP || 2 * N > wcap) return false;   // uniform
-            if (ly[b].off < 0) {
-#pragma unroll
-                for (int t = 0; t < LINE_SLOTS; t++)
-                    if (t < yc) {
-                        L.vslot[p0 + t] = ((long long)ly[b].s[t].in << 32) | (unsigned)ly[b].s[t].comm;
-                        L.vdeg[p0 + t] = ly[b].deg;
-                    }
-            } else {
-                for (int t = 0; t < yc; t++) {
-                    L.vslot[p0 + t] = ~(ly[b].off + t);
-                    L.vdeg[p0 + t] = ly[b].deg;
-                }
-            }
-        }
-    }
-    const int lg = N <= 4 ? 3 : 32 - __clz(2 * N - 1);    // T = 2^lg >= 2 N
-    const int T = 1 << lg;
-    for (int t = tid; t < T; t += NT) {
-        L.key[t] = -1;
-        L.kk[t] = 0;
-    }
-    if (tid < mcnt) {
-        L.vslot[tid] = ((long long)own.in << 32) | (unsigned)own.comm;
-        L.vdeg[tid] = -1;                   // an own membership, not a visit
-    }
-    node_sync<NT>();
-    // 1. every entry counts towards its community; own communities are leave candidates
-    //    even without a neighbour in them, and a membership its neighbour left earlier in
-    //    this iteration (a hole) is no visit
-    Slot sv[NB];
-    int dg[NB];
-#pragma unroll
-    for (int b = 0; b < NB; b++) {
-        const int v = b * NT + tid;
-        sv[b].comm = -1;
-        sv[b].in = 0;
-        dg[b] = 0;
-        if (v < N) {
-            const long long e = L.vslot[v];
-            dg[b] = L.vdeg[v];
-            if (e >= 0 || dg[b] < 0) {
-                sv[b].comm = (int)(unsigned)e;
-                sv[b].in = (int)(e >> 32);
-            } else {
-                sv[b] = cx.slot[~e];
-            }
-        }
-    }
     int hs[NB];                             // table entry, or -1
     bool mine[NB];                          // this entry claimed it
 #pragma unroll
@@ -374,17 +282,129 @@ __device__ __forceinline__ bool eval_node(const Ctx &cx, int j, const NodeRec nr
         }
     }
     if (bad) atomicOr(&cx.ctr->error, LF_DEVERR_INEXACT);
+    Best r;
+    r.jd = bjd;
+    r.ld = bld;
+    r.j = bj;
+    r.l = bl;
+    r.ncand = ncand;
+    return r;
+}
+
+// Evaluate queued node j with NT threads (one wave, or a workgroup of GT threads) if its
+// neighbours (<= VCAP), visits and own memberships fit (2 * (visits + own) <= table,
+// <= VCAP of them, <= MXCAP own).  Returns false (decision not written) otherwise; the
+// decision to return is the same for all NT threads.  Every phase issues all of a
+// thread's global gathers (at most VCAP / NT of them) before it uses any, so a node costs
+// a handful of memory round trips whatever its size: own slots + column indices,
+// neighbour headers, neighbour slots, and one record per candidate.
+template <int NT, int VCAP>
+__device__ __forceinline__ bool eval_node(const Ctx &cx, int j, const NodeRec nr, int tid, NodeLds<VCAP> &L,
+                                          int wcap, int path)
+{
+    constexpr int NB = VCAP / NT;
+    const int x = nr.x, d = nr.d;
+    const long long rb = nr.rb;
+    if (d > VCAP) return false;
+    // the adjacency gathers need only the node record; the header is fetched beside them
+    int yv[NB];
+#pragma unroll
+    for (int b = 0; b < NB; b++) {
+        int e = b * NT + tid;
+        yv[b] = e < d ? cx.col[rb + e] : -1;
+    }
+    // own line: count, placement and (inline) memberships, read beside the adjacency
+    const NodeLine *lxp = cx.ln + x;
+    const int mcnt = lxp->cnt;
+    const long long xoff = lxp->off;
+    Slot own = {-1, 0};
+    if (tid < LINE_SLOTS) own = lxp->s[tid];
+    if (mcnt > MXCAP) return false;
+    if (xoff >= 0 && tid < mcnt) own = cx.slot[xoff + tid];
+    // one line per neighbour: its count, degree and memberships in one gather
+    NodeLine ly[NB];
+#pragma unroll
+    for (int b = 0; b < NB; b++) {
+        if (yv[b] >= 0) {
+            ly[b] = cx.ln[yv[b]];
+        } else {
+            ly[b].cnt = 0;
+            ly[b].deg = 0;
+            ly[b].off = -1;
+        }
+    }
+    // neighbour memberships flattened into the list behind the own ones: an inline
+    // membership is kept as its (community, in-count) pair, one in the slot array as the
+    // complement of its slot index
+    int N = mcnt;
+#pragma unroll
+    for (int b = 0; b < NB; b++) {
+        if (b * NT < d) {                   // uniform over the NT threads
+            int yc = ly[b].cnt, tot;
+            int incl = node_incl_scan<NT>(yc, tid, L, &tot);
+            int p0 = N + incl - yc;
+            N += tot;
+            if (N > VCAP || 2 * N > wcap) return false;   // uniform
+            if (ly[b].off < 0) {
+#pragma unroll
+                for (int t = 0; t < LINE_SLOTS; t++)
+                    if (t < yc) {
+                        L.vslot[p0 + t] = ((long long)ly[b].s[t].in << 32) | (unsigned)ly[b].s[t].comm;
+                        L.vdeg[p0 + t] = ly[b].deg;
+                    }
+            } else {
+                for (int t = 0; t < yc; t++) {
+                    L.vslot[p0 + t] = ~(ly[b].off + t);
+                    L.vdeg[p0 + t] = ly[b].deg;
+                }
+            }
+        }
+    }
+    const int lg = N <= 4 ? 3 : 32 - __clz(2 * N - 1);    // T = 2^lg >= 2 N
+    const int T = 1 << lg;
+    for (int t = tid; t < T; t += NT) {
+        L.key[t] = -1;
+        L.kk[t] = 0;
+    }
+    if (tid < mcnt) {
+        L.vslot[tid] = ((long long)own.in << 32) | (unsigned)own.comm;
+        L.vdeg[tid] = -1;                   // an own membership, not a visit
+    }
+    node_sync<NT>();
+    // 1. every entry counts towards its community; own communities are leave candidates
+    //    even without a neighbour in them, and a membership its neighbour left earlier in
+    //    this iteration (a hole) is no visit
+    Slot sv[NB];
+    int dg[NB];
+#pragma unroll
+    for (int b = 0; b < NB; b++) {
+        const int v = b * NT + tid;
+        sv[b].comm = -1;
+        sv[b].in = 0;
+        dg[b] = 0;
+        if (v < N) {
+            const long long e = L.vslot[v];
+            dg[b] = L.vdeg[v];
+            if (e >= 0 || dg[b] < 0) {
+                sv[b].comm = (int)(unsigned)e;
+                sv[b].in = (int)(e >> 32);
+            } else {
+                sv[b] = cx.slot[~e];
+            }
+        }
+    }
+    const Best r = score_list<NT, NB, VCAP>(cx, d, sv, dg, tid, L, T, lg);
     if (tid == 0) {
-        cx.dj[j] = bj;
-        cx.djd[j] = bj >= 0 ? bjd : 0.0;
-        cx.dl[j] = bl;
-        cx.dld[j] = bl >= 0 ? bld : 0.0;
-        cx.dpos[j] = mcnt;
-        cx.big_idx[j] = Q_DONE;
+        Decision dc;
+        dc.J = r.j;
+        dc.L = r.l;
+        dc.pos = mcnt;
+        dc.pad = 0;
+        cx.dec[j] = dc;
     }
     if (cx.stats) {
         unsigned long long *w = cx.ctr->work[path];
-        if (ncand) atomicAdd(&w[3], (unsigned long long)ncand);
+        if (r.ncand) atomicAdd(&w[3], (unsigned long long)r.ncand);
         if (tid == 0) {
             atomicAdd(&w[0], 1ull);
             atomicAdd(&w[1], (unsigned long long)d);
@@ -394,23 +414,6 @@ __device__ __forceinline__ bool eval_node(const Ctx &cx, int j, const NodeRec nr
     }
     return true;
 }
-
-__device__ __forceinline__ void mark_table(const Ctx &cx, int j, int deg, int own, const NodeLine &line)
-{
-    cx.big_ln[j] = line;                    // k_big_final reads it beside each entry's record
-    if (cx.stats) {
-        atomicAdd(&cx.ctr->work[LF_PATH_TABLE][0], 1ull);
-        atomicAdd(&cx.ctr->work[LF_PATH_TABLE][1], (unsigned long long)deg);
-        atomicAdd(&cx.ctr->work[LF_PATH_TABLE][4], (unsigned long long)own);
-    }
-    cx.big_idx[j] = Q_TABLE;
-    cx.dpos[j] = own;
-    cx.big_bj[j] = 0;
-    cx.big_bl[j] = 0;
-    cx.big_cj[j] = 0x7fffffff;
-    cx.big_cl[j] = 0x7fffffff;
-}
-
 
 // The in-LDS evaluation paths take their queue's nodes from their path lists; the path
 // was chosen so that the node fits, and a node that does not is an internal error.
@@ -464,224 +467,136 @@ __global__ void __launch_bounds__(EW * WAVE) k_eval(Ctx cx, QStep qs)
 // ------------------------------------------------------------------------------------
 // evaluation, table path
 // ------------------------------------------------------------------------------------
-// slot of key (b, C) in the global table, claimed if absent (claimed = true then)
-__device__ __forceinline__ long long gfind(const Ctx &cx, int b, int C, bool &claimed)
+// The largest nodes take two launches, without global atomics per visit.  First (a role of
+// k_eval_big) one block per chunk of TAB_CHUNK neighbours gathers their lines, counts their
+// memberships per hash bucket of the communities, and writes them to the node's visit
+// region grouped by bucket, with a row of the buckets' positions.  Then (k_big_final) one
+// block per bucket collects its piece of every chunk and evaluates it like a medium-path
+// node: all visits of a community meet in one bucket.  k_big_tie folds a node's buckets.
+// A node has one bucket per BUCK_AVG visits of its bound, so a bucket's entries nearly
+// always fit one per thread.
+// The path is bound by its gathers (64-byte lines of the neighbours, 64-byte records of the
+// candidates).  The former global hash table moved a 64-byte entry four to five times per
+// visit besides: on a dense-shaped graph (1M nodes, 39M pairs, queue 16,384) its three launches took
+// 201 + 146 + 19 us per queue, these take 56 + 74 + 6; on the social-shaped one (4M nodes,
+// queue 4096) 54 + 61 + 10 against 25 + 35 + 6.
+#define TAB_CHUNK 256
+#define TAB_MAXP 4096
+#define VBUCK 256           // entries of a bucket evaluated one per thread
+#define BUCK_AVG 192        // bound on visits per bucket aimed at
+
+// hash of a community: the top of h * P is its bucket of P, the rest orders it within
+__device__ __forceinline__ unsigned long long bucket_hash(int C, int P)
 {
-    unsigned long long key = ((unsigned long long)(unsigned)b << 32) | (unsigned)C;
-    long long h = (long long)(hash64(key) & (unsigned long long)cx.gmask);
-    claimed = false;
-    for (long long probe = 0; probe <= cx.gmask; probe++) {
-        unsigned long long cur = __atomic_load_n(&cx.gt[h].key, __ATOMIC_RELAXED);
-        if (cur == key) return h;
-        if (cur == GEMPTY) {
-            unsigned long long old = atomicCAS(&cx.gt[h].key, GEMPTY, key);
-            if (old == GEMPTY) {
-                claimed = true;
-                return h;
-            }
-            if (old == key) return h;
-        }
-        h = (h + 1) & cx.gmask;
-    }
-    return -1;
+    return (unsigned long long)((unsigned)C * 0x85EBCA6Bu) * (unsigned)P;
 }
 
-// The occupied list: a wave reserves one slot per visit of its 64 work items with a single
-// atomic (a returning atomic on one shared counter costs ~10-20 ns, serialised, so one per
-// 64-visit step would be the table path's bottleneck); each visit then writes the entry it
-// claimed, or -1, into its own slot.
+__device__ __forceinline__ int bucket_of(int C, int P) { return (int)(bucket_hash(C, P) >> 32); }
 
-#define EWB 4           // waves per block in the table-path kernels
-
-// Table path, one wave per 64 consecutive work items (neighbours, then own memberships,
-// of the table-path nodes of this queue).  The wave flattens its items' neighbour
-// memberships and walks them 64 at a time with every lane converged.  The lane that
-// claims a key records its visit inline (no community gather, one atomic in total); every
-// other visit adds its exact correction, with lanes of one wave that hit the same entry
-// summed first so that a hot entry gets one set of atomics per wave.
-struct TabLds {
-    int vw[EWB];             // visits of each wave's chunk (block-wide slot reservation)
-    long long obase;         // first occupied-list slot of the block's chunk
-    long long sbase[EWB][WAVE];
-    long long xoff[EWB][WAVE];
-    int start[EWB][WAVE];
-    int dy[EWB][WAVE];
-    int j[EWB][WAVE];
-    int xcnt[EWB][WAVE];
-    int own[EWB][WAVE];
+struct PartLds {
+    int hist[TAB_MAXP];      // per bucket: visits, then the next position
+    int wtot[GT / WAVE];
+    int base;
 };
 
-// blocks blk of nblk (EWB waves each) walk the work items of the queue's table-path
-// nodes (list positions [ls, ls + ln))
-__device__ __forceinline__ void table_visits(const Ctx &cx, int cstart, int ls, int ln, int blk, int nblk,
-                                             TabLds &S)
+// the TAB_CHUNK-neighbour chunk k (thread per neighbour)
+__device__ __forceinline__ void table_chunk(const Ctx &cx, const QStep &qs, int k, PartLds &S)
 {
-    auto &s_sbase = S.sbase;
-    auto &s_xoff = S.xoff;
-    auto &s_start = S.start;
-    auto &s_dy = S.dy;
-    auto &s_j = S.j;
-    auto &s_xcnt = S.xcnt;
-    auto &s_own = S.own;
-    const int wv = threadIdx.x / WAVE, lane = threadIdx.x & (WAVE - 1);
-    const long long ib0 = cx.titem_base[ls];
-    const long long count = cx.titem_base[ls + ln] - ib0;
-    const long long bstride = (long long)nblk * EWB * WAVE;
-    int bad = 0, capfail = 0;
-    unsigned long long nvis = 0;
-    // the block walks its chunks of EWB * 64 items in lockstep (same trip count for every
-    // wave), so its waves can reserve their occupied-list slots with one atomic
-    for (long long bbase = (long long)blk * EWB * WAVE; bbase < count; bbase += bstride) {
-        const long long base = bbase + (long long)wv * WAVE;
-        long long f = base + lane;
-        int vc = 0, dy = 0, jj = -1, own = 0, xcnt = 0;
-        long long sb = 0, xoff = 0;
-        if (f < count) {
-            int p = cx.titem_node[ib0 + f];
-            int r = cx.plist[LF_PATH_TABLE][p];
-            int j = r - cstart;
-            {
-                const NodeRec nr = cx.prec[LF_PATH_TABLE][p];
-                const int x = nr.x;
-                long long e = ib0 + f - cx.titem_base[p];
-                int y = -1;
-                if (e < nr.d) y = cx.col[nr.rb + e];  // issued beside the node's header
-                const NodeLine *lxp = cx.ln + x;
-                const int xdeg = lxp->deg, xc0 = lxp->cnt;
-                const long long xo0 = lxp->off;
-                Slot *xs = xo0 < 0 ? (Slot *)lxp->s : cx.slot + xo0;
-                if (e == 0) mark_table(cx, j, xdeg, xc0, *lxp);   // k_big_final reads it after this launch
-                if (e < xdeg) {
-                    const NodeLine *lyp = cx.ln + y;
-                    vc = lyp->cnt;
-                    dy = lyp->deg;
-                    const long long yo = lyp->off;
-                    sb = (long long)(yo < 0 ? (Slot *)lyp->s : cx.slot + yo);
-                } else if (e < (long long)xdeg + xc0) {
-                    vc = 1;
-                    sb = (long long)(xs + (e - xdeg));
-                    own = 1;
-                }
-                jj = j;
-                xoff = (long long)xs;
-                xcnt = xc0;
+    const int tid = threadIdx.x;
+    const ChunkRec cr = cx.tchunk[k];
+    const int P = cr.P;
+    const int y = tid < cr.cnt ? cx.col[cr.rb + tid] : -1;
+    for (int t = tid; t < P; t += GT) S.hist[t] = 0;
+    NodeLine ly;
+    ly.cnt = 0;
+    ly.deg = 0;
+    ly.off = -1;
+    if (y >= 0) ly = cx.ln[y];
+    __syncthreads();
+    int mine = 0;                            // memberships (holes left out)
+    if (ly.off < 0) {
+#pragma unroll
+        for (int t = 0; t < LINE_SLOTS; t++)
+            if (t < ly.cnt && ly.s[t].comm >= 0) {
+                atomicAdd(&S.hist[bucket_of(ly.s[t].comm, P)], 1);
+                mine++;
             }
+    } else {
+        for (int t0 = 0; t0 < ly.cnt; t0 += 4) {   // four slot loads per round trip
+            int c[4];
+#pragma unroll
+            for (int q = 0; q < 4; q++) c[q] = t0 + q < ly.cnt ? cx.slot[ly.off + t0 + q].comm : -1;
+#pragma unroll
+            for (int q = 0; q < 4; q++)
+                if (c[q] >= 0) {
+                    atomicAdd(&S.hist[bucket_of(c[q], P)], 1);
+                    mine++;
+                }
         }
-        int Vw;
-        const int incl = wave_incl_scan(vc, &Vw);
-        // this wave's occupied-list slots [obase, obase + Vw): one atomic for the block
-        if (lane == 0) S.vw[wv] = Vw;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            int tot = 0;
-            for (int w = 0; w < EWB; w++) tot += S.vw[w];
-            S.obase = tot > 0 ? (long long)atomicAdd(&cx.ctr->occ_cnt, tot) : 0;
-        }
-        __syncthreads();
-        long long obase = S.obase;
-        for (int w = 0; w < wv; w++) obase += S.vw[w];
-        s_start[wv][lane] = incl - vc;
-        s_sbase[wv][lane] = sb;
-        s_dy[wv][lane] = dy;
-        s_j[wv][lane] = jj;
-        s_xoff[wv][lane] = xoff;
-        s_xcnt[wv][lane] = xcnt;
-        s_own[wv][lane] = own;
-        WAVE_SYNC();
-        for (int v0 = 0; v0 < Vw; v0 += WAVE) {
-            const int v = v0 + lane;
-            const bool act = v < Vw;
-            int C = 0, iv = 0, dyv = 0, xc = 0;
-            long long hh = -1, xo = 0;
-            bool claimed = false, ownv = false;
-            if (act) {
-                int lo = 0, hi = WAVE - 1;          // owner: last lane whose range starts <= v
-                while (lo < hi) {
-                    int mid = (lo + hi + 1) >> 1;
-                    if (s_start[wv][mid] <= v) lo = mid; else hi = mid - 1;
-                }
-                int j = s_j[wv][lo];
-                ownv = s_own[wv][lo] != 0;
-                dyv = s_dy[wv][lo];
-                xo = s_xoff[wv][lo];
-                xc = s_xcnt[wv][lo];
-                Slot sl = ((const Slot *)s_sbase[wv][lo])[v - s_start[wv][lo]];
-                C = sl.comm;
-                iv = sl.in;
-                if (C >= 0) {                   // not a membership left in this iteration
-                    hh = gfind(cx, j, C, claimed);
-                    if (hh < 0) capfail = 1;
-                }
-            }
-            if (act) cx.occ[obase + v] = claimed ? (int)hh : -1;
-            const bool vis = act && hh >= 0 && !ownv;
-            if (vis && claimed) {
-                cx.gt[hh].ii = iv;
-                cx.gt[hh].idy = dyv;
-            }
-            const bool extra = vis && !claimed;
-            i64 t0 = 0, t1 = 0, t2 = 0, t3 = 0;
-            if (extra) {
-                const int s = cx.cr[C].s;
-                bool leave = find_slot((const Slot *)xo, 0, xc, C) >= 0;
-                const u128 term = visit_term(leave, iv, dyv, s, bad);
-                x128_digits(term, t0, t1, t2, t3);
-            }
-            bool pending = extra;
-            for (int attempt = 0; attempt < 3; attempt++) {
-                unsigned long long pm = __ballot(pending);
-                if (!pm) break;
-                int first = __ffsll((long long)pm) - 1;
-                long long h0 = __shfl(hh, first, WAVE);
-                bool in = pending && hh == h0;
-                unsigned long long gm = __ballot(in);
-                if (__popcll(gm) >= 4) {
-                    i64 a0 = wave_sum_i64(in ? t0 : 0), a1 = wave_sum_i64(in ? t1 : 0);
-                    i64 a2 = wave_sum_i64(in ? t2 : 0), a3 = wave_sum_i64(in ? t3 : 0);
-                    if (lane == first) {
-                        GEntry *g = &cx.gt[h0];
-                        atomicAdd(&g->cnt, __popcll(gm));
-                        atomicAdd((unsigned long long *)&g->d[0], (unsigned long long)a0);
-                        atomicAdd((unsigned long long *)&g->d[1], (unsigned long long)a1);
-                        atomicAdd((unsigned long long *)&g->d[2], (unsigned long long)a2);
-                        atomicAdd((unsigned long long *)&g->d[3], (unsigned long long)a3);
-                    }
-                    if (in) pending = false;
-                } else if (in) {
-                    GEntry *g = &cx.gt[hh];
-                    atomicAdd(&g->cnt, 1);
-                    atomicAdd((unsigned long long *)&g->d[0], (unsigned long long)t0);
-                    atomicAdd((unsigned long long *)&g->d[1], (unsigned long long)t1);
-                    atomicAdd((unsigned long long *)&g->d[2], (unsigned long long)t2);
-                    atomicAdd((unsigned long long *)&g->d[3], (unsigned long long)t3);
-                    pending = false;
-                }
-            }
-            if (pending) {
-                GEntry *g = &cx.gt[hh];
-                atomicAdd(&g->cnt, 1);
-                atomicAdd((unsigned long long *)&g->d[0], (unsigned long long)t0);
-                atomicAdd((unsigned long long *)&g->d[1], (unsigned long long)t1);
-                atomicAdd((unsigned long long *)&g->d[2], (unsigned long long)t2);
-                atomicAdd((unsigned long long *)&g->d[3], (unsigned long long)t3);
-            }
-            nvis += vis ? 1 : 0;
-        }
-        __syncthreads();                      // the chunk's LDS (and the reservation) is reused
     }
-    if (cx.stats) {
-        nvis = (unsigned long long)wave_sum_i64((long long)nvis);
-        if (lane == 0 && nvis) atomicAdd(&cx.ctr->work[LF_PATH_TABLE][2], nvis);
+    int total;
+    (void)wave_incl_scan(mine, &total);
+    if ((tid & (WAVE - 1)) == 0) S.wtot[tid / WAVE] = total;
+    __syncthreads();
+    if (tid == 0) {
+        int all = 0;
+        for (int w = 0; w < GT / WAVE; w++) all += S.wtot[w];
+        S.base = atomicAdd(&cx.tcur[cr.p], all);   // this chunk's place in the node's region
+        if (cx.stats) {
+            atomicAdd(&cx.ctr->work[LF_PATH_TABLE][1], (unsigned long long)cr.cnt);
+            atomicAdd(&cx.ctr->work[LF_PATH_TABLE][2], (unsigned long long)all);
+        }
     }
-    if (bad) atomicOr(&cx.ctr->error, LF_DEVERR_INEXACT);
-    if (capfail) atomicOr(&cx.ctr->error, LF_DEVERR_CAP);
+    __syncthreads();
+    // positions of the buckets: exclusive sums of the counts, GT buckets at a time
+    int *row = cx.trow + (cr.row - qs.br.row0);
+    int run = S.base;
+    for (int t0 = 0; t0 < P; t0 += GT) {
+        const int t = t0 + tid;
+        const int v = t < P ? S.hist[t] : 0;
+        int wsum;
+        const int incl = wave_incl_scan(v, &wsum);
+        __syncthreads();                     // the previous round's totals are read
+        if ((tid & (WAVE - 1)) == 0) S.wtot[tid / WAVE] = wsum;
+        __syncthreads();
+        int off = run, all = 0;
+        for (int w = 0; w < GT / WAVE; w++) {
+            if (w < tid / WAVE) off += S.wtot[w];
+            all += S.wtot[w];
+        }
+        if (t < P) {
+            S.hist[t] = off + incl - v;
+            row[t] = off + incl - v;
+        }
+        run += all;
+    }
+    if (tid == 0) row[P] = run;
+    __syncthreads();
+    TabVisit *out = cx.tvis + (cr.vis - qs.br.vis0);
+    if (ly.off < 0) {
+#pragma unroll
+        for (int t = 0; t < LINE_SLOTS; t++)
+            if (t < ly.cnt && ly.s[t].comm >= 0)
+                out[atomicAdd(&S.hist[bucket_of(ly.s[t].comm, P)], 1)] = TabVisit{ly.s[t].comm, ly.s[t].in, ly.deg, 0};
+    } else {
+        for (int t0 = 0; t0 < ly.cnt; t0 += 4) {
+            Slot sl[4];
+#pragma unroll
+            for (int q = 0; q < 4; q++)
+                sl[q] = t0 + q < ly.cnt ? cx.slot[ly.off + t0 + q] : Slot{-1, 0};
+#pragma unroll
+            for (int q = 0; q < 4; q++)
+                if (sl[q].comm >= 0)
+                    out[atomicAdd(&S.hist[bucket_of(sl[q].comm, P)], 1)] = TabVisit{sl[q].comm, sl[q].in, ly.deg, 0};
+        }
+    }
 }
 
 // The larger nodes of a queue in one launch, by block role (BigRoles).  All read the state
 // at the queue's start, so the roles are independent.
 
 union BigLds {
-    TabLds t;
+    PartLds t;
     NodeLds<VGRP> g;
     EvalLds e;
 };
@@ -694,7 +609,10 @@ __device__ __forceinline__ void body_eval_big(const Ctx &cx, const QStep &qs, in
     reset_apply_counters(cx, blk);
     int b = blk;
     if (b < r.bt) {
-        table_visits(cx, cstart, r.lt, r.nt, b, r.bt, L.t);
+        for (int k = b; k < r.nc; k += r.bt) {
+            table_chunk(cx, qs, r.c0 + k, L.t);
+            __syncthreads();                // the next chunk reuses the LDS
+        }
         return;
     }
     b -= r.bt;
@@ -712,111 +630,284 @@ __device__ __forceinline__ void body_eval_big(const Ctx &cx, const QStep &qs, in
 }
 QUEUE_KERNELS(k_eval_big, GT, BigLds, body_eval_big)
 
-__device__ __forceinline__ void body_big_final(const Ctx &cx, const QStep &qs, int blk, int nblk, NoLds &)
+// A bucket whose entries do not fit one per thread (a community that many of the node's
+// neighbours share, a node with very many chunks): the visits are streamed from memory,
+// twice, and the distinct communities kept in the table.  If they are more than VBUCK the
+// bucket is cut into R slices of its hash range, R doubling until every slice fits;
+// communities scored before a cut are scored again, which changes nothing.
+struct GenLds {
+    int key[2 * VBUCK];
+    unsigned kk[2 * VBUCK];
+    unsigned short ow[2 * VBUCK];   // candidate index
+    int cl[VBUCK];                  // table entry of each candidate
+    int sz[VBUCK];
+    unsigned long long acc[2][VBUCK];
+    int n, over;
+};
+
+__device__ __forceinline__ int gen_find(const GenLds &G, int C)
 {
-    const int cstart = qs.cstart, clen = qs.clen;
-    int count = __atomic_load_n(&cx.ctr->occ_cnt, __ATOMIC_RELAXED);
-    int bad = 0;
-    unsigned long long ncand = 0;
-    long long stride = (long long)nblk * blockDim.x;
-    // every lane of a wave runs the same number of trips (invalid lanes idle), so the
-    // per-wave reduction below sees all 64 lanes
-    for (long long base = blk * (long long)blockDim.x; base < count; base += stride) {
-        long long e = base + threadIdx.x;
-        const bool inrange = e < count;
-        long long h = inrange ? cx.occ[e] : -1;   // -1: a visit that claimed no entry
-        bool valid = h >= 0;
-        GEntry ge;
-        ge.key = GEMPTY;
-        if (valid) ge = cx.gt[h];
-        unsigned long long key = ge.key;
-        int b = valid ? (int)(key >> 32) : -1, C = (int)(unsigned)key;
-        if (b >= clen) b = -1;
-        double dlt = 0.0;
-        bool leave = false;
-        if (b >= 0) {
-            // the node's line (copied at its marking) and the whole community record are
-            // gathered side by side; the leave test then picks the record's half
-            const NodeLine hx = cx.big_ln[b];
-            const CommRec rec = cx.cr[C];
-            int k = ge.cnt + (ge.idy > 0 ? 1 : 0);
-            u128 corr = x128_from_digits(ge.d[0], ge.d[1], ge.d[2], ge.d[3]);
-            int own_in = 0;
-            int a = line_find(cx, hx, C, &own_in);
-            leave = a >= 0;
-            if (ge.idy > 0) corr += visit_term(leave, ge.ii, ge.idy, rec.s, bad);
-            if (leave && own_in != k) atomicOr(&cx.ctr->error, LF_DEVERR_INCOUNT);
-            CandRec r;
-            r.s = rec.s;
-            r.m = (int)rec.m;
-            r.W = rec.W;
-#pragma unroll
-            for (int q = 0; q < 5; q++) r.S[q] = leave ? rec.Sm[q] : rec.Sp[q];
-            dlt = cand_delta(r, leave, k, hx.deg, corr, bad);
-            ncand++;
-        }
-        // per-node maximum of the positive changes; one atomic per wave when every active
-        // lane works on the same node (the common case: a node's entries are contiguous)
-        {
-            unsigned long long bits = dlt > 0.0 ? (unsigned long long)__double_as_longlong(dlt) : 0ull;
-            unsigned long long jb = leave ? 0ull : bits, lb = leave ? bits : 0ull;
-            int lane = threadIdx.x & (WAVE - 1);
-            int b0 = __shfl(b, 0, WAVE);
-            bool uni = __ballot(b != b0) == 0 && b0 >= 0;
-            if (uni) {
-                for (int o = 32; o >= 1; o >>= 1) {
-                    unsigned long long oj = (unsigned long long)__shfl_xor((long long)jb, o, WAVE);
-                    unsigned long long ol = (unsigned long long)__shfl_xor((long long)lb, o, WAVE);
-                    if (oj > jb) jb = oj;
-                    if (ol > lb) lb = ol;
-                }
-                if (lane == 0) {
-                    if (jb) atomicMax(&cx.big_bj[b0], jb);
-                    if (lb) atomicMax(&cx.big_bl[b0], lb);
-                }
-            } else if (b >= 0) {
-                if (jb) atomicMax(&cx.big_bj[b], jb);
-                if (lb) atomicMax(&cx.big_bl[b], lb);
+    unsigned h = hash_tab(C) >> (32 - 9);
+    while (G.key[h] != C) h = (h + 1) & (2 * VBUCK - 1);
+    return (int)h;
+}
+
+__device__ __forceinline__ void gen_insert(GenLds &G, int C, unsigned add)
+{
+    static_assert(2 * VBUCK == 1 << 9, "table size of gen_find and gen_insert");
+    if (*(volatile int *)&G.over) return;
+    unsigned h = hash_tab(C) >> (32 - 9);
+    for (int probe = 0; probe < 2 * VBUCK; probe++) {
+        const int old = atomicCAS(&G.key[h], -1, C);
+        if (old == -1) {
+            const int i = atomicAdd(&G.n, 1);
+            if (i >= VBUCK) {
+                G.over = 1;
+                return;
             }
+            G.ow[h] = (unsigned short)i;
+            G.cl[i] = (int)h;
         }
-        if (inrange && !valid) cx.occ_d[e] = 0.0;   // k_big_tie skips it
-        if (valid) {
-            cx.occ_key[e] = key | (leave ? (1ull << 63) : 0ull);
-            cx.occ_d[e] = dlt;
-            // leave the entry empty for the next queue
-            GEntry *gp = &cx.gt[h];
-            gp->key = GEMPTY;
-            gp->cnt = 0;
-            gp->ii = 0;
-            gp->idy = 0;
-            gp->d[0] = 0; gp->d[1] = 0; gp->d[2] = 0; gp->d[3] = 0;
+        if (old == -1 || old == C) {
+            atomicAdd(&G.kk[h], add);
+            return;
         }
+        h = (h + 1) & (2 * VBUCK - 1);
     }
-    if (cx.stats) {
-        ncand = (unsigned long long)wave_sum_i64((long long)ncand);
-        if ((threadIdx.x & (WAVE - 1)) == 0 && ncand) atomicAdd(&cx.ctr->work[LF_PATH_TABLE][3], ncand);
+    G.over = 1;                              // the table is full
+}
+
+// whether C belongs to slice r of R of bucket b
+__device__ __forceinline__ bool in_slice(int C, int P, int b, unsigned r, unsigned R)
+{
+    const unsigned long long h = bucket_hash(C, P);
+    return (int)(h >> 32) == b && (unsigned)(((h & 0xffffffffull) * R) >> 32) == r;
+}
+
+__device__ __forceinline__ Best bucket_general(const Ctx &cx, const BuckRec &br, const int *rows, const TabVisit *vis,
+                                               const Slot *xs, int mcnt, GenLds &G)
+{
+    const int tid = threadIdx.x;
+    Best r = {0.0, 0.0, -1, -1, 0};
+    int bad = 0;
+    for (unsigned R = 1;; R *= 2) {
+        bool fits = true;
+        for (unsigned sl = 0; sl < R && fits; sl++) {
+            for (int t = tid; t < 2 * VBUCK; t += GT) {
+                G.key[t] = -1;
+                G.kk[t] = 0;
+            }
+            if (tid == 0) {
+                G.n = 0;
+                G.over = 0;
+            }
+            __syncthreads();
+            for (int t = tid; t < mcnt; t += GT) {
+                const int C = xs[t].comm;
+                if (C >= 0 && in_slice(C, br.P, br.b, sl, R)) gen_insert(G, C, 0x80000000u);
+            }
+            for (int c = 0; c < br.nch; c++) {
+                const int lo = rows[(long long)c * (br.P + 1) + br.b], hi = rows[(long long)c * (br.P + 1) + br.b + 1];
+                for (int i = lo + tid; i < hi; i += GT) {
+                    const int C = vis[i].comm;
+                    if (in_slice(C, br.P, br.b, sl, R)) gen_insert(G, C, 1u);
+                }
+            }
+            __syncthreads();
+            if (G.over) {                    // uniform
+                fits = false;
+                __syncthreads();
+                break;
+            }
+            const int nc = G.n;
+            if (tid < nc) {
+                G.sz[tid] = cx.cr[G.key[G.cl[tid]]].s;
+                G.acc[0][tid] = 0;
+                G.acc[1][tid] = 0;
+            }
+            __syncthreads();
+            for (int t = tid; t < mcnt; t += GT) {
+                const Slot o = xs[t];
+                if (o.comm >= 0 && in_slice(o.comm, br.P, br.b, sl, R) &&
+                    (unsigned)o.in != (G.kk[gen_find(G, o.comm)] & 0x7fffffffu))
+                    atomicOr(&cx.ctr->error, LF_DEVERR_INCOUNT);
+            }
+            for (int c = 0; c < br.nch; c++) {
+                const int lo = rows[(long long)c * (br.P + 1) + br.b], hi = rows[(long long)c * (br.P + 1) + br.b + 1];
+                for (int i = lo + tid; i < hi; i += GT) {
+                    const TabVisit v = vis[i];
+                    if (!in_slice(v.comm, br.P, br.b, sl, R)) continue;
+                    const int h = gen_find(G, v.comm);
+                    const int o = G.ow[h];
+                    const u128 term = visit_term(G.kk[h] >> 31, v.in, v.deg, G.sz[o], bad);
+                    const unsigned long long lw = (unsigned long long)term;
+                    const unsigned long long was = atomicAdd(&G.acc[0][o], lw);
+                    atomicAdd(&G.acc[1][o], (unsigned long long)(term >> 64) + (was + lw < lw ? 1ull : 0ull));
+                }
+            }
+            __syncthreads();
+            if (tid < nc) {
+                const int C = G.key[G.cl[tid]];
+                const unsigned kk = G.kk[G.cl[tid]];
+                CandRec rc;
+                load_cand(cx, C, kk >> 31, rc);
+                const u128 corr = ((u128)G.acc[1][tid] << 64) | G.acc[0][tid];
+                const double dl = cand_delta(rc, kk >> 31, (int)(kk & 0x7fffffffu), br.d, corr, bad);
+                if (kk >> 31) better(dl, C, r.ld, r.l);
+                else better(dl, C, r.jd, r.j);
+                r.ncand++;
+            }
+            __syncthreads();
+        }
+        if (fits) break;
+        r.ncand = 0;
     }
     if (bad) atomicOr(&cx.ctr->error, LF_DEVERR_INEXACT);
+    return r;
 }
 
-QUEUE_KERNELS(k_big_final, 256, NoLds, body_big_final)
+struct BuckLds {
+    union {
+        NodeLds<VBUCK> n;
+        GenLds g;
+    };
+    double jd[GT / WAVE], ld[GT / WAVE];
+    int j[GT / WAVE], l[GT / WAVE];
+};
 
-__device__ __forceinline__ void body_big_tie(const Ctx &cx, const QStep &qs, int blk, int nblk, NoLds &)
+__device__ __forceinline__ void eval_bucket(const Ctx &cx, const QStep &qs, int k, BuckLds &S)
 {
-    (void)qs;
-    int count = __atomic_load_n(&cx.ctr->occ_cnt, __ATOMIC_RELAXED);
-    long long stride = (long long)nblk * blockDim.x;
-    for (long long e = blk * (long long)blockDim.x + threadIdx.x; e < count; e += stride) {
-        double dlt = cx.occ_d[e];
-        if (!(dlt > 0.0)) continue;
-        unsigned long long key = cx.occ_key[e];
-        bool leave = (key >> 63) != 0;
-        int b = (int)((key >> 32) & 0x7fffffffull), C = (int)(unsigned)key;
-        unsigned long long best = leave ? cx.big_bl[b] : cx.big_bj[b];
-        if ((unsigned long long)__double_as_longlong(dlt) == best) atomicMin(leave ? &cx.big_cl[b] : &cx.big_cj[b], C);
+    const int tid = threadIdx.x;
+    const BuckRec br = cx.tbuck[qs.br.b0 + k];
+    const int *rows = cx.trow + (br.row - qs.br.row0);
+    const TabVisit *vis = cx.tvis + (br.vis - qs.br.vis0);
+    int lo = 0, len = 0;
+    if (tid < br.nch) {
+        const int *rp = rows + (long long)tid * (br.P + 1) + br.b;
+        lo = rp[0];
+        len = rp[1] - lo;
+    }
+    const NodeLine *lxp = cx.ln + br.x;
+    const int mcnt = lxp->cnt;
+    const long long xoff = lxp->off;
+    const Slot *xs = xoff < 0 ? lxp->s : cx.slot + xoff;
+    Slot own = {-1, 0};
+    if (tid < mcnt) own = xs[tid];
+    const bool ownb = own.comm >= 0 && bucket_of(own.comm, br.P) == br.b;
+    NodeLds<VBUCK> &L = S.n;
+    // own memberships of this bucket, then its piece of every chunk
+    int m, N;
+    const int pm = node_incl_scan<GT>(ownb ? 1 : 0, tid, L, &m);
+    const int pl = node_incl_scan<GT>(len, tid, L, &N);
+    N += m;
+    Best r;
+    if (N <= VBUCK && br.nch <= GT && mcnt <= GT) {      // uniform
+        if (ownb) {
+            L.vslot[pm - 1] = ((long long)own.in << 32) | (unsigned)own.comm;
+            L.vdeg[pm - 1] = -1;
+        }
+        for (int i = 0; i < len; i++) {
+            L.vslot[m + pl - len + i] = lo + i;
+            L.vdeg[m + pl - len + i] = 0;
+        }
+        const int lg = N <= 4 ? 3 : 32 - __clz(2 * N - 1);    // T = 2^lg >= 2 N
+        const int T = 1 << lg;
+        for (int t = tid; t < T; t += GT) {
+            L.key[t] = -1;
+            L.kk[t] = 0;
+        }
+        __syncthreads();
+        Slot sv[1] = {{-1, 0}};
+        int dg[1] = {0};
+        if (tid < N) {
+            const long long e = L.vslot[tid];
+            dg[0] = L.vdeg[tid];
+            if (dg[0] < 0) {
+                sv[0].comm = (int)(unsigned)e;
+                sv[0].in = (int)(e >> 32);
+            } else {
+                const TabVisit v = vis[e];
+                sv[0].comm = v.comm;
+                sv[0].in = v.in;
+                dg[0] = v.deg;
+            }
+        }
+        r = score_list<GT, 1, VBUCK>(cx, br.d, sv, dg, tid, L, T, lg);
+    } else {
+        __syncthreads();                     // the scans' LDS is read
+        r = bucket_general(cx, br, rows, vis, xs, mcnt, S.g);
+        wave_best(r.jd, r.j);
+        wave_best(r.ld, r.l);
+        const int wv = tid / WAVE;
+        if ((tid & (WAVE - 1)) == 0) {
+            S.jd[wv] = r.jd;
+            S.ld[wv] = r.ld;
+            S.j[wv] = r.j;
+            S.l[wv] = r.l;
+        }
+        __syncthreads();
+        if (tid == 0)
+            for (int w = 1; w < GT / WAVE; w++) {
+                better(S.jd[w], S.j[w], r.jd, r.j);
+                better(S.ld[w], S.l[w], r.ld, r.l);
+            }
+    }
+    if (tid == 0) {
+        BuckRes q;
+        q.jd = r.jd;
+        q.ld = r.ld;
+        q.j = r.j;
+        q.l = r.l;
+        cx.tres[k] = q;
+    }
+    if (cx.stats && r.ncand) atomicAdd(&cx.ctr->work[LF_PATH_TABLE][3], (unsigned long long)r.ncand);
+}
+
+__device__ __forceinline__ void body_big_final(const Ctx &cx, const QStep &qs, int blk, int nblk, BuckLds &S)
+{
+    for (int k = blk; k < qs.br.nb; k += nblk) {
+        eval_bucket(cx, qs, k, S);
+        __syncthreads();                     // the next bucket reuses the LDS
     }
 }
-QUEUE_KERNELS(k_big_tie, 256, NoLds, body_big_tie)
+#define FINAL_BOUNDS GT, 5
+QUEUE_KERNELS(k_big_final, FINAL_BOUNDS, BuckLds, body_big_final)
+
+// the decision of every table-path node of the queue: the best of its buckets (one wave per
+// node); communities in different buckets differ, so equal changes go to the lower id
+__device__ __forceinline__ void body_big_tie(const Ctx &cx, const QStep &qs, int blk, int nblk, NoLds &)
+{
+    const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x / WAVE;
+    for (int i = blk * (GT / WAVE) + wv; i < qs.br.nt; i += nblk * (GT / WAVE)) {
+        const int p = qs.br.lt + i;
+        const int b0 = cx.tpos[p].bucket - qs.br.b0, b1 = cx.tpos[p + 1].bucket - qs.br.b0;
+        const int x = cx.prec[LF_PATH_TABLE][p].x, j = cx.plist[LF_PATH_TABLE][p] - qs.cstart;
+        const int mcnt = cx.ln[x].cnt;
+        double bjd = 0.0, bld = 0.0;
+        int bj = -1, bl = -1;
+        for (int b = b0 + lane; b < b1; b += WAVE) {
+            const BuckRes q = cx.tres[b];
+            better(q.jd, q.j, bjd, bj);
+            better(q.ld, q.l, bld, bl);
+        }
+        WAVE_SYNC();
+        wave_best(bjd, bj);
+        wave_best(bld, bl);
+        if (lane == 0) {
+            Decision dc;
+            dc.J = bj;
+            dc.L = bl;
+            dc.pos = mcnt;
+            dc.pad = 0;
+            cx.dec[j] = dc;
+            if (cx.stats) {
+                atomicAdd(&cx.ctr->work[LF_PATH_TABLE][0], 1ull);
+                atomicAdd(&cx.ctr->work[LF_PATH_TABLE][4], (unsigned long long)mcnt);
+            }
+        }
+    }
+}
+QUEUE_KERNELS(k_big_tie, GT, NoLds, body_big_tie)
 
 // ------------------------------------------------------------------------------------
 // bulk apply
@@ -830,25 +921,6 @@ QUEUE_KERNELS(k_big_tie, 256, NoLds, body_big_tie)
 // updates can target slots while the edits run, and they take each neighbour's
 // membership after the queue from the neighbour's own decision rather than from its
 // slots: the result is a from-scratch recount of every in-count on the new partition.
-
-// decision of the node at queue position j: community joined J and left L (-1: none)
-__device__ __forceinline__ void queue_decision(const Ctx &cx, int j, int &J, int &L, unsigned long long *bjp,
-                                               unsigned long long *blp)
-{
-    const int bi = cx.big_idx[j];
-    const int dj = cx.dj[j], dl = cx.dl[j];
-    const unsigned long long bj = cx.big_bj[j], bl = cx.big_bl[j];
-    const int cj = cx.big_cj[j], cl = cx.big_cl[j];
-    if (bi == Q_TABLE) {
-        J = bj ? cj : -1;
-        L = bl ? cl : -1;
-    } else {
-        J = dj;
-        L = dl;
-    }
-    if (bjp) *bjp = bi == Q_TABLE ? bj : 0;
-    if (blp) *blp = bi == Q_TABLE ? bl : 0;
-}
 
 // Re-sum parts of community C at its first touch in the queue, planned from its
 // member-list capacity (fixed within an iteration).  Every lane of the wave calls this
@@ -892,19 +964,13 @@ __device__ __forceinline__ void apply_edit(const Ctx &cx, const QStep &qs, int j
 {
     const int cstart = qs.cstart, clen = qs.clen;
     const int lane = threadIdx.x & (WAVE - 1);
-    if (j == 0) cx.ctr->occ_cnt = 0;        // the table path of this queue is done
     const bool inq = j < clen;
     int J = -1, L = -1, x = -1;
     if (inq) {
-        unsigned long long bj = 0, bl = 0;
-        queue_decision(cx, j, J, L, &bj, &bl);
+        const Decision dc = cx.dec[j];
+        J = dc.J;
+        L = dc.L;
         x = cx.order[cstart + j];
-        if (bj || bl || cx.big_idx[j] == Q_TABLE) {
-            cx.dj[j] = J;
-            cx.dl[j] = L;
-            cx.djd[j] = __longlong_as_double((long long)bj);
-            cx.dld[j] = __longlong_as_double((long long)bl);
-        }
     }
     unsigned long long ml = __ballot(L >= 0);
     if (lane == 0 && ml) atomicAdd(&cx.ctr->leaves, (unsigned long long)__popcll(ml));
@@ -987,9 +1053,8 @@ __device__ __forceinline__ void apply_unit(const Ctx &cx, const QStep &qs, long 
     // the unit's neighbours, the node's decision, join position and line placement
     const int y = lane < ur.cnt ? cx.col[ur.rb + lane] : -1;
     const int ry = lane < ur.cnt ? cx.col_rank[ur.rb + lane] : -1;
-    int J, L;
-    queue_decision(cx, j, J, L, nullptr, nullptr);
-    const int pos = cx.dpos[j];
+    const Decision dc = cx.dec[j];
+    const int J = dc.J, L = dc.L, pos = dc.pos;
     const long long xoff = cx.ln[ur.x].off;
     if (J < 0 && L < 0) return;             // uniform over the wave
     NodeLine ly;
@@ -999,7 +1064,11 @@ __device__ __forceinline__ void apply_unit(const Ctx &cx, const QStep &qs, long 
     if (y >= 0) {
         ly = cx.ln[y];
         const int jy = ry - qs.cstart;
-        if (jy >= 0 && jy < qs.clen) queue_decision(cx, jy, Jy, Ly, nullptr, nullptr);
+        if (jy >= 0 && jy < qs.clen) {
+            const Decision dy = cx.dec[jy];
+            Jy = dy.J;
+            Ly = dy.L;
+        }
     }
     bool inJ = false;
     if (y >= 0) {
@@ -1264,39 +1333,6 @@ __global__ void __launch_bounds__(256) k_node_bounds(Ctx cx, long long *vbound, 
     }
 }
 
-// per queue: work items and table keys of its table-path nodes, and in-count items of
-// all its nodes; the maxima over queues go to out[0..2]
-__global__ void __launch_bounds__(256) k_chunk_bounds(Ctx cx, const long long *vbound, const int *cls, int q,
-                                                      unsigned long long *out)
-{
-    __shared__ long long s_a[256 / WAVE], s_b[256 / WAVE], s_c[256 / WAVE];
-    long long start = (long long)blockIdx.x * q;
-    long long end = start + q < cx.n ? start + q : cx.n;
-    long long a = 0, b = 0, c = 0;
-    for (long long r = start + threadIdx.x; r < end; r += blockDim.x) {
-        int x = cx.order[r];
-        NodeHdr hx = cx.nh[x];
-        if (cls[r] == LF_PATH_TABLE) {
-            a += hx.deg + hx.cnt + 1;
-            b += vbound[x];
-        }
-        c += (hx.deg + INB - 1) / INB;
-    }
-    a = wave_sum_i64(a);
-    b = wave_sum_i64(b);
-    c = wave_sum_i64(c);
-    int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x / WAVE;
-    if (lane == 0) { s_a[wv] = a; s_b[wv] = b; s_c[wv] = c; }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        long long ta = 0, tb = 0, tc = 0;
-        for (int k = 0; k < 256 / WAVE; k++) { ta += s_a[k]; tb += s_b[k]; tc += s_c[k]; }
-        atomicMax(&out[0], (unsigned long long)ta);
-        atomicMax(&out[1], (unsigned long long)tb);
-        atomicMax(&out[2], (unsigned long long)tc);
-    }
-}
-
 // flags[r] = (cls[r] == c) for the scan that places path c's nodes; flags[n] = 0
 __global__ void k_class_flags(const int *cls, int c, long long *flags, long long n)
 {
@@ -1334,36 +1370,115 @@ __global__ void k_path_base(const long long *scan, long long n, int c, long long
     if (threadIdx.x == 0 && blockIdx.x == 0) pbase[c + 1] = pbase[c] + scan[n];
 }
 
-// work items of every table-path node: its neighbours, its own memberships and one spare;
-// the number of table-path nodes nt is read on the device (the path list's length), and
-// the counts are written for all n + 1 positions (0 from nt on)
-__global__ void k_titem_counts(Ctx cx, const long long *nt_dev, long long n, long long *cnt)
+// layout of the table path: for each of its nodes the exclusive sums of chunks, buckets, row
+// entries and visit bounds (one block; the number of nodes is read on the device), and the
+// visits placed so far cleared
+__device__ __forceinline__ long long scan1024(long long v, long long *s_w, long long *total)
 {
-    long long p = blockIdx.x * (long long)blockDim.x + threadIdx.x;
-    if (p > n) return;
-    if (p >= *nt_dev) { cnt[p] = 0; return; }
-    NodeHdr hx = cx.nh[cx.order[cx.plist[LF_PATH_TABLE][p]]];
-    cnt[p] = (long long)hx.deg + hx.cnt + 1;
+    const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x / WAVE;
+    long long incl = v;
+    for (int o = 1; o < WAVE; o <<= 1) {
+        const long long t = __shfl_up(incl, o, WAVE);
+        if (lane >= o) incl += t;
+    }
+    __syncthreads();
+    if (lane == WAVE - 1) s_w[wv] = incl;
+    __syncthreads();
+    long long off = 0, tot = 0;
+#pragma unroll 1
+    for (int w = 0; w < 1024 / WAVE; w++) {
+        const long long t = s_w[w];
+        if (w < wv) off += t;
+        tot += t;
+    }
+    *total = tot;
+    return off + incl - v;
 }
 
-__global__ void k_queue_items(const long long *titem_base, const long long *qoff_t, long long nq, long long *out)
+__global__ void __launch_bounds__(1024) k_table_layout(const int *plist, const int *order, const int *deg,
+                                                       const long long *vbound, const long long *nt_dev, TabPos *tpos,
+                                                       int *tcur)
 {
-    long long k = blockIdx.x * (long long)blockDim.x + threadIdx.x;
-    if (k <= nq) out[k] = titem_base[qoff_t[k]];
+    __shared__ long long s_w[1024 / WAVE];
+    const long long nt = *nt_dev;
+    long long vis0 = 0, row0 = 0, ch0 = 0, bu0 = 0;
+    for (long long p0 = 0; p0 < nt; p0 += 1024) {
+        const long long p = p0 + threadIdx.x;
+        long long vb = 0, nch = 0, P = 0;
+        if (p < nt) {
+            const int x = order[plist[p]];
+            vb = vbound[x];                          // visits + own memberships + 1
+            nch = (deg[x] + TAB_CHUNK - 1) / TAB_CHUNK;
+            P = (vb + BUCK_AVG - 1) / BUCK_AVG;
+            if (P > TAB_MAXP) P = TAB_MAXP;
+            tcur[p] = 0;
+        }
+        long long tv, tr, tc, tb;
+        const long long v = scan1024(vb, s_w, &tv);
+        const long long r = scan1024(nch * (P + 1), s_w, &tr);
+        const long long c = scan1024(nch, s_w, &tc);
+        const long long b = scan1024(P, s_w, &tb);
+        if (p < nt) tpos[p] = TabPos{vis0 + v, row0 + r, (int)(ch0 + c), (int)(bu0 + b)};
+        vis0 += tv;
+        row0 += tr;
+        ch0 += tc;
+        bu0 += tb;
+    }
+    if (threadIdx.x == 0) tpos[nt] = TabPos{vis0, row0, (int)ch0, (int)bu0};
 }
 
-// owner of every work item; waves stride over the nt table-path nodes.  Nothing is written
-// if the items exceed the buffer's capacity (the host then grows it and runs this again).
-__global__ void __launch_bounds__(256) k_titem_fill(Ctx cx, const long long *nt_dev, long long cap)
+// the chunks and buckets of every table-path node (waves stride over the nodes).  Nothing is
+// written if they exceed the buffers (the host then grows them and runs this again).
+__global__ void __launch_bounds__(256) k_table_fill(const int *plist, const int *order, const long long *rowptr,
+                                                    const int *deg, const TabPos *tpos, const long long *nt_dev,
+                                                    ChunkRec *chunk, long long chunk_cap, BuckRec *buck,
+                                                    long long buck_cap)
 {
     const long long nt = *nt_dev;
-    if (cx.titem_base[nt] > cap) return;
+    if (tpos[nt].chunk > chunk_cap || tpos[nt].bucket > buck_cap) return;
     const int lane = threadIdx.x & (WAVE - 1);
     const long long nw = (long long)gridDim.x * (blockDim.x / WAVE);
     for (long long p = (blockIdx.x * (long long)blockDim.x + threadIdx.x) / WAVE; p < nt; p += nw) {
-        long long a = cx.titem_base[p], b = cx.titem_base[p + 1];
-        for (long long f = a + lane; f < b; f += WAVE) cx.titem_node[f] = (int)p;
+        const TabPos t0 = tpos[p], t1 = tpos[p + 1];
+        const int r = plist[p], x = order[r], d = deg[x];
+        const int nch = t1.chunk - t0.chunk, P = t1.bucket - t0.bucket;
+        const long long rb = rowptr[x];
+        for (int c = lane; c < nch; c += WAVE) {
+            ChunkRec cr;
+            cr.rb = rb + (long long)c * TAB_CHUNK;
+            cr.vis = t0.vis;
+            cr.row = t0.row + (long long)c * (P + 1);
+            cr.cnt = d - c * TAB_CHUNK < TAB_CHUNK ? d - c * TAB_CHUNK : TAB_CHUNK;
+            cr.p = (int)p;
+            cr.P = P;
+            cr.pad = 0;
+            chunk[t0.chunk + c] = cr;
+        }
+        for (int b = lane; b < P; b += WAVE) {
+            BuckRec br;
+            br.vis = t0.vis;
+            br.row = t0.row;
+            br.x = x;
+            br.d = d;
+            br.nch = nch;
+            br.P = P;
+            br.b = b;
+            br.pad = 0;
+            buck[t0.bucket + b] = br;
+        }
     }
+}
+
+// first chunk, bucket, visit and row entry of every queue (out: four arrays of nq + 1)
+__global__ void k_queue_table(const TabPos *tpos, const long long *qoff_t, long long nq, long long *out)
+{
+    const long long k = blockIdx.x * (long long)blockDim.x + threadIdx.x;
+    if (k > nq) return;
+    const TabPos t = tpos[qoff_t[k]];
+    out[k] = t.chunk;
+    out[nq + 1 + k] = t.bucket;
+    out[2 * (nq + 1) + k] = t.vis;
+    out[3 * (nq + 1) + k] = t.row;
 }
 
 // the membership lines of an iteration, from the slot layout (nodes whose capacity fits a
@@ -1443,44 +1558,44 @@ __global__ void k_queue_units(const long long *ubase, long long n, int q, long l
     if (k <= nq) out[k] = ubase[k * q < n ? k * q : n];
 }
 
-__global__ void k_empty_table(GEntry *t, long long n)
-{
-    long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x;
-    if (i < n) t[i].key = GEMPTY;
-}
-
 // ------------------------------------------------------------------------------------
 // host side
 // ------------------------------------------------------------------------------------
 void lf_free_iteration_buffers(lf_handle *h)
 {
-    void **ptrs[] = {(void **)&h->dj, (void **)&h->dl, (void **)&h->djd, (void **)&h->dld,
-                     (void **)&h->big_idx,
-                     (void **)&h->big_bj, (void **)&h->big_bl, (void **)&h->big_cj, (void **)&h->big_cl,
-                     (void **)&h->big_ln,
-                     (void **)&h->gt, (void **)&h->occ, (void **)&h->occ_key, (void **)&h->occ_d,
-                     (void **)&h->unit, (void **)&h->dpos, (void **)&h->part_rec, (void **)&h->macc,
-                     (void **)&h->titem_base, (void **)&h->titem_node};
+    void **ptrs[] = {(void **)&h->dec, (void **)&h->unit, (void **)&h->part_rec, (void **)&h->macc,
+                     (void **)&h->cflag, (void **)&h->tpos, (void **)&h->tcur, (void **)&h->tchunk,
+                     (void **)&h->tbuck, (void **)&h->tvis, (void **)&h->trow, (void **)&h->tres};
     for (void **p : ptrs) {
         lf_dev_free(h, *p);
         *p = nullptr;
     }
     h->q_cap = 0;
-    h->gT = 0;
     h->unit_cap = 0;
     h->part_cap = 0;
     h->mslot_cap = 0;
-    h->titem_cap = 0;
+    h->tchunk_cap = 0;
+    h->tbuck_cap = 0;
+    h->tvis_cap = 0;
+    h->trow_cap = 0;
+    h->tres_cap = 0;
 }
 
 // The iteration start's report (device dq, copied to the pinned host hqoff), for nq
-// queues: per path the first list position of every queue ([LF_PATH_COUNT][nq + 1]),
-// the first table-path work item of every queue, the first in-count unit of every queue,
-// then 4 bounds of k_chunk_bounds.
-#define REP_ITEMS(nq) ((long long)LF_PATH_COUNT * ((nq) + 1))
-#define REP_UNITS(nq) ((long long)(LF_PATH_COUNT + 1) * ((nq) + 1))
-#define REP_BOUNDS(nq) ((long long)(LF_PATH_COUNT + 2) * ((nq) + 1))
-#define REP_LEN(nq) (REP_BOUNDS(nq) + 4)
+// queues: per path the first list position of every queue ([LF_PATH_COUNT][nq + 1]), the
+// first table-path chunk, bucket, visit and row entry of every queue, and the first
+// in-count unit of every queue.
+#define REP_TABLE(nq) ((long long)LF_PATH_COUNT * ((nq) + 1))
+#define REP_UNITS(nq) ((long long)(LF_PATH_COUNT + 4) * ((nq) + 1))
+#define REP_LEN(nq) ((long long)(LF_PATH_COUNT + 5) * ((nq) + 1))
+
+static void table_fill(lf_handle *h, const long long *nt_dev)
+{
+    hipLaunchKernelGGL(k_table_fill, dim3(h->fill_grid), dim3(256), 0, h->stream,
+                       (const int *)h->plist[LF_PATH_TABLE], (const int *)h->order, (const long long *)h->rowptr,
+                       (const int *)h->deg, (const TabPos *)h->tpos, nt_dev, h->tchunk, h->tchunk_cap, h->tbuck,
+                       h->tbuck_cap);
+}
 
 // Start of an iteration, first half: everything the host does not need to see, queued on
 // the stream, ending with one copy of the queue offsets and bounds to pinned host memory.
@@ -1493,25 +1608,9 @@ static int size_queue_enqueue(lf_handle *h, long long q)
     long long n = h->n;
     bool moved = false;
     if (q > h->q_cap) {
-        void **ptrs[] = {(void **)&h->dj, (void **)&h->dl, (void **)&h->djd, (void **)&h->dld, (void **)&h->dpos,
-                         (void **)&h->big_idx,
-                         (void **)&h->big_bj, (void **)&h->big_bl, (void **)&h->big_cj, (void **)&h->big_cl,
-                         (void **)&h->big_ln};
-        for (void **p : ptrs) {
-            lf_dev_free(h, *p);
-            *p = nullptr;
-        }
-        LF_TRY(lf_dev_alloc(h, (void **)&h->dpos, sizeof(int) * q));
-        LF_TRY(lf_dev_alloc(h, (void **)&h->dj, sizeof(int) * q));
-        LF_TRY(lf_dev_alloc(h, (void **)&h->dl, sizeof(int) * q));
-        LF_TRY(lf_dev_alloc(h, (void **)&h->djd, sizeof(double) * q));
-        LF_TRY(lf_dev_alloc(h, (void **)&h->dld, sizeof(double) * q));
-        LF_TRY(lf_dev_alloc(h, (void **)&h->big_idx, sizeof(int) * q));
-        LF_TRY(lf_dev_alloc(h, (void **)&h->big_bj, sizeof(unsigned long long) * q));
-        LF_TRY(lf_dev_alloc(h, (void **)&h->big_bl, sizeof(unsigned long long) * q));
-        LF_TRY(lf_dev_alloc(h, (void **)&h->big_cj, sizeof(int) * q));
-        LF_TRY(lf_dev_alloc(h, (void **)&h->big_cl, sizeof(int) * q));
-        LF_TRY(lf_dev_alloc(h, (void **)&h->big_ln, sizeof(NodeLine) * q));
+        lf_dev_free(h, h->dec);
+        h->dec = nullptr;
+        LF_TRY(lf_dev_alloc(h, (void **)&h->dec, sizeof(Decision) * q));
         h->q_cap = q;
         moved = true;
     }
@@ -1532,7 +1631,7 @@ static int size_queue_enqueue(lf_handle *h, long long q)
         h->hqoff_cap = nq + 1;
         h->hqoff_len = REP_LEN(nq);
     }
-    const long long nrep = REP_LEN(nq);    // list offsets, queue items, queue units, bounds
+    const long long nrep = REP_LEN(nq);    // list offsets, table path, queue units
     if (nrep > h->dq_cap) {                 // kept across the two halves (and iterations)
         lf_dev_free(h, h->dq);
         h->dq = nullptr;
@@ -1540,16 +1639,21 @@ static int size_queue_enqueue(lf_handle *h, long long q)
         h->dq_cap = nrep + nrep / 4 + 64;
     }
     long long *dq = h->dq;
-    if (!h->titem_base) {
-        LF_TRY(lf_dev_alloc(h, (void **)&h->titem_base, sizeof(long long) * (n + 1)));
+    if (!h->tpos) {
+        h->tchunk_cap = 1024 + n / 16;
+        h->tbuck_cap = 1024 + n / 8;
+        LF_TRY(lf_dev_alloc(h, (void **)&h->cflag, sizeof(long long) * (n + 1)));
+        LF_TRY(lf_dev_alloc(h, (void **)&h->tpos, sizeof(TabPos) * (n + 1)));
+        LF_TRY(lf_dev_alloc(h, (void **)&h->tcur, sizeof(int) * (n + 1)));
+        LF_TRY(lf_dev_alloc(h, (void **)&h->tchunk, sizeof(ChunkRec) * h->tchunk_cap));
+        LF_TRY(lf_dev_alloc(h, (void **)&h->tbuck, sizeof(BuckRec) * h->tbuck_cap));
         moved = true;
     }
     LF_TRY(lf_zero(h, h->pbase, sizeof(long long)));
     for (int c = 0; c < LF_PATH_COUNT; c++) {
-        // titem_base serves as the flag array until the table-path items are laid out
         hipLaunchKernelGGL(k_class_flags, dim3(grid_for(n + 1, BS)), dim3(BS), 0, st, (const int *)h->cls, c,
-                           h->titem_base, n);
-        LF_TRY(lf_exclusive_scan_i64(h, h->titem_base, h->cscan, n + 1));
+                           h->cflag, n);
+        LF_TRY(lf_exclusive_scan_i64(h, h->cflag, h->cscan, n + 1));
         long long m = (n > nq ? n : nq) + 1;
         hipLaunchKernelGGL(k_class_scatter, dim3(grid_for(m, BS)), dim3(BS), 0, st, (const int *)h->cls, c,
                            (const long long *)h->cscan, h->plist[c], n, (int)q, nq, dq + c * (nq + 1),
@@ -1557,28 +1661,19 @@ static int size_queue_enqueue(lf_handle *h, long long q)
                            (const long long *)h->pbase, h->prec_all);
         hipLaunchKernelGGL(k_path_base, dim3(1), dim3(1), 0, st, (const long long *)h->cscan, n, c, h->pbase);
     }
-    unsigned long long *dout = (unsigned long long *)(dq + REP_BOUNDS(nq));
-    LF_TRY(lf_zero(h, dout, sizeof(unsigned long long) * 4));
-    hipLaunchKernelGGL(k_chunk_bounds, dim3((unsigned)nq), dim3(BS), 0, st, cx, (const long long *)h->vbound,
-                       (const int *)h->cls, (int)q, dout);
-    // static work-item layout of the table-path nodes (list position p owns deg + cnt + 1),
-    // all on the device: the table path's length is the last queue offset of its list
+    // chunks and buckets of the table-path nodes, all on the device: the table path's length
+    // is the last queue offset of its list
     const long long *nt_dev = dq + LF_PATH_TABLE * (nq + 1) + nq;
-    hipLaunchKernelGGL(k_titem_counts, dim3(grid_for(n + 1, BS)), dim3(BS), 0, st, lf_ctx(h), nt_dev, n, h->cscan);
-    LF_TRY(lf_exclusive_scan_i64(h, h->cscan, h->titem_base, n + 1));
-    if (!h->titem_node) {
-        long long want = 4096 + n / 4;
-        LF_TRY(lf_dev_alloc(h, (void **)&h->titem_node, sizeof(int) * want));
-        h->titem_cap = want;
-        moved = true;
-    }
+    hipLaunchKernelGGL(k_table_layout, dim3(1), dim3(1024), 0, st, (const int *)h->plist[LF_PATH_TABLE],
+                       (const int *)h->order, (const int *)h->deg, (const long long *)h->vbound, nt_dev, h->tpos,
+                       h->tcur);
     unsigned fill_grid = grid_for(n * WAVE, BS);
     if (fill_grid > 2048) fill_grid = 2048;
     if (fill_grid < 1) fill_grid = 1;
-    hipLaunchKernelGGL(k_titem_fill, dim3(fill_grid), dim3(BS), 0, st, lf_ctx(h), nt_dev, h->titem_cap);
-    // first table-path work item of every queue (sizes the table-visit role)
-    hipLaunchKernelGGL(k_queue_items, dim3(grid_for(nq + 1, BS)), dim3(BS), 0, st, (const long long *)h->titem_base,
-                       (const long long *)(dq + LF_PATH_TABLE * (nq + 1)), nq, dq + REP_ITEMS(nq));
+    h->fill_grid = fill_grid;
+    table_fill(h, nt_dev);
+    hipLaunchKernelGGL(k_queue_table, dim3(grid_for(nq + 1, BS)), dim3(BS), 0, st, (const TabPos *)h->tpos,
+                       (const long long *)(dq + LF_PATH_TABLE * (nq + 1)), nq, dq + REP_TABLE(nq));
     // in-count units of every node in node order, and the first unit of every queue
     {
         const long long ucap = n + 2 * h->ne / INB + 1;   // >= sum of ceil(degree / INB)
@@ -1603,11 +1698,10 @@ static int size_queue_enqueue(lf_handle *h, long long q)
                            (int)q, nq, dq + REP_UNITS(nq));
     }
     // the host's one wait of the iteration start: list offsets per queue and path, the
-    // queues' first table items, the bounds
+    // queues' table-path and unit positions
     LF_HIP(h, hipMemcpyAsync(h->hqoff, dq, sizeof(long long) * nrep, hipMemcpyDeviceToHost, st));
     LF_HIP(h, hipGetLastError());
     h->pending_moved = moved;
-    h->fill_grid = fill_grid;
     return LF_OK;
 }
 
@@ -1621,9 +1715,7 @@ static int size_queue_complete(lf_handle *h, long long q)
     const long long nq = (n + q - 1) / q;
     bool moved = h->pending_moved;
     h->second_half_work = false;
-    const unsigned fill_grid = h->fill_grid;
     const long long *nt_dev = h->dq + LF_PATH_TABLE * (nq + 1) + nq;
-    const unsigned long long *hb = (const unsigned long long *)(h->hqoff + REP_BOUNDS(nq));
     {   // the records of path c start after those of the paths before it
         long long base = 0;
         for (int c = 0; c < LF_PATH_COUNT; c++) {
@@ -1631,40 +1723,48 @@ static int size_queue_complete(lf_handle *h, long long q)
             base += h->hqoff[c * (nq + 1) + nq];
         }
     }
-    long long keys = (long long)hb[1] + 64;
-    if (keys >= (1ll << 30))
+    // the queue with the largest table path sizes its buffers
+    const long long *tb = h->hqoff + REP_TABLE(nq);
+    long long most[4] = {0, 0, 0, 0};        // chunks, buckets, visits, row entries
+    for (int a = 0; a < 4; a++)
+        for (long long k = 0; k < nq; k++) {
+            const long long v = tb[a * (nq + 1) + k + 1] - tb[a * (nq + 1) + k];
+            if (v > most[a]) most[a] = v;
+        }
+    if (most[2] + 64 >= (1ll << 30))
         return lf_set_error(h, LF_EOVERFLOW, "queue of %lld nodes too large for the table path", q);
-    const long long nt = h->hqoff[LF_PATH_TABLE * (nq + 1) + nq];
-    const long long items = h->hqoff[REP_ITEMS(nq) + nq];
-    if (items > h->titem_cap) {             // rare: grow and lay the items out again
-        lf_dev_free(h, h->titem_node);
-        h->titem_node = nullptr;
-        long long want = (h->phase_graphs ? 4 : 2) * items + 1024;
-        LF_TRY(lf_dev_alloc(h, (void **)&h->titem_node, sizeof(int) * want));
-        h->titem_cap = want;
+    const long long chunks = tb[nq], bucks = tb[2 * nq + 1];
+    if (chunks > h->tchunk_cap || bucks > h->tbuck_cap) {   // rare: grow and lay them out again
+        const long long f = h->phase_graphs ? 4 : 2;        // a batch member's graphs survive more growth
+        if (chunks > h->tchunk_cap) {
+            lf_dev_free(h, h->tchunk);
+            h->tchunk = nullptr;
+            LF_TRY(lf_dev_alloc(h, (void **)&h->tchunk, sizeof(ChunkRec) * (f * chunks + 1024)));
+            h->tchunk_cap = f * chunks + 1024;
+        }
+        if (bucks > h->tbuck_cap) {
+            lf_dev_free(h, h->tbuck);
+            h->tbuck = nullptr;
+            LF_TRY(lf_dev_alloc(h, (void **)&h->tbuck, sizeof(BuckRec) * (f * bucks + 1024)));
+            h->tbuck_cap = f * bucks + 1024;
+        }
         moved = true;
-        if (nt > 0) {
-            hipLaunchKernelGGL(k_titem_fill, dim3(fill_grid), dim3(BS), 0, st, lf_ctx(h), nt_dev, h->titem_cap);
-            h->second_half_work = true;
-        }
-    }
-    long long T = 1024;
-    while (T < 2 * keys) T <<= 1;
-    if (T > h->gT) {
-        if (h->phase_graphs) T *= 4;        // a batch member's graphs survive more growth
-        void **ptrs[] = {(void **)&h->gt, (void **)&h->occ, (void **)&h->occ_key, (void **)&h->occ_d};
-        for (void **p : ptrs) {
-            lf_dev_free(h, *p);
-            *p = nullptr;
-        }
-        LF_TRY(lf_dev_alloc(h, (void **)&h->gt, sizeof(GEntry) * T));
-        LF_TRY(lf_dev_alloc(h, (void **)&h->occ, sizeof(int) * T));
-        LF_TRY(lf_dev_alloc(h, (void **)&h->occ_key, sizeof(unsigned long long) * T));
-        LF_TRY(lf_dev_alloc(h, (void **)&h->occ_d, sizeof(double) * T));
-        LF_HIP(h, hipMemsetAsync(h->gt, 0, sizeof(GEntry) * T, st));
+        table_fill(h, nt_dev);
+        LF_HIP(h, hipGetLastError());
         h->second_half_work = true;
-        hipLaunchKernelGGL(k_empty_table, dim3(grid_for(T, BS)), dim3(BS), 0, st, h->gt, T);
-        h->gT = T;
+    }
+    const long long grown = h->phase_graphs ? 3 : 0;        // spare room, in quarters beyond one
+    struct { void **p; long long *cap; long long need; size_t each; } bufs[3] = {
+        {(void **)&h->tres, &h->tres_cap, most[1], sizeof(BuckRes)},
+        {(void **)&h->tvis, &h->tvis_cap, most[2], sizeof(TabVisit)},
+        {(void **)&h->trow, &h->trow_cap, most[3], sizeof(int)}};
+    for (auto &bf : bufs) {
+        if (bf.need <= *bf.cap) continue;
+        const long long want = bf.need + (1 + 4 * grown) * (bf.need / 4) + 256;
+        lf_dev_free(h, *bf.p);
+        *bf.p = nullptr;
+        LF_TRY(lf_dev_alloc(h, bf.p, bf.each * want));
+        *bf.cap = want;
         moved = true;
     }
     long long pcap = 2 * q + (h->cm_cap + n) / PART + 64;
@@ -1798,8 +1898,7 @@ static bool phase_allocates(lf_handle *h, int which, long long qq)
     const long long nq = (n + qq - 1) / qq;
     const long long nrep = REP_LEN(nq);
     const long long ucap = n + 2 * h->ne / INB + 1;
-    return qq > h->q_cap || h->hqoff_cap < nq + 1 || nrep > h->dq_cap || !h->titem_base || !h->titem_node ||
-           ucap > h->unit_cap || (n > 0 && !h->lines);
+    return qq > h->q_cap || h->hqoff_cap < nq + 1 || nrep > h->dq_cap || !h->tpos || ucap > h->unit_cap || (n > 0 && !h->lines);
 }
 
 // one iteration start (0) or end (1), from a graph where the state allows
@@ -1861,7 +1960,7 @@ void lf_queue_params(lf_handle *h, long long k, long long nq, long long qq, bool
                      QGrids *g)
 {
     const long long *qo = h->hqoff;                                // [path][nq + 1]
-    const long long *hit = h->hqoff + REP_ITEMS(nq);   // first table-path work item per queue
+    const long long *tb = h->hqoff + REP_TABLE(nq);    // [4][nq + 1]
     const long long *hu = h->hqoff + REP_UNITS(nq);    // first in-count unit per queue
     const long long start = k * qq;
     const int clen = (int)((h->n - start) < qq ? (h->n - start) : qq);
@@ -1884,10 +1983,14 @@ void lf_queue_params(lf_handle *h, long long k, long long nq, long long qq, bool
     qs->ls = ls[LF_PATH_SMALL];
     qs->ln = ln[LF_PATH_SMALL];
     BigRoles &br = qs->br;
-    const long long titems = hit[k + 1] - hit[k];
-    br.bt = ln[LF_PATH_TABLE] > 0 ? (int)grid_for(titems, 2 * EWB * WAVE) : 0;
-    if (br.bt > gb) br.bt = gb;
-    br.bg = ln[LF_PATH_GROUP] < gb ? ln[LF_PATH_GROUP] : gb;
+    br.c0 = (int)tb[k];
+    br.nc = (int)(tb[k + 1] - tb[k]);
+    br.b0 = (int)tb[nq + 1 + k];
+    br.nb = (int)(tb[nq + 2 + k] - tb[nq + 1 + k]);
+    br.vis0 = tb[2 * (nq + 1) + k];
+    br.row0 = tb[3 * (nq + 1) + k];
+    br.bt = br.nc < 4 * gb ? br.nc : 4 * gb;
+    br.bg = ln[LF_PATH_GROUP] < 4 * gb ? ln[LF_PATH_GROUP] : 4 * gb;
     qs->es = (int)grid_for(ln[LF_PATH_SMALL], EW);
     qs->em = ln[LF_PATH_MED];
     qs->lm = ls[LF_PATH_MED];
@@ -1902,7 +2005,8 @@ void lf_queue_params(lf_handle *h, long long k, long long nq, long long qq, bool
     g->eval = br.fuse ? 0 : qs->es + qs->em;
     g->big = br.bt + br.bg + (br.fuse ? qs->es + qs->em : 0);
     if (g->big < 1 && g->eval == 0) g->big = 1;   // block 0 resets the queue's counters
-    g->fin = ln[LF_PATH_TABLE] > 0 ? (compact_grids ? (br.bt > 0 ? br.bt : 1) : gb) : 0;
+    g->fin = br.nb;
+    g->tie = (int)grid_for(br.nt, GT / WAVE);
     g->apply = (int)grid_for(clen, 256) + (int)grid_for(qs->un, 256 / WAVE);
     g->refresh = rbk;
 }
@@ -1927,7 +2031,7 @@ int lf_launch_queue(lf_handle *h, Ctx &cx, const QStep &qs, const QGrids &g)
         hipLaunchKernelGGL(k_big_final, dim3(g.fin), dim3(256), 0, st, cx, qs);
         LF_TRY(lf_prof_end(h, LF_K_TAB_FINAL, 1));
         LF_TRY(lf_prof_begin(h, LF_K_TAB_TIE));
-        hipLaunchKernelGGL(k_big_tie, dim3(g.fin), dim3(256), 0, st, cx, qs);
+        hipLaunchKernelGGL(k_big_tie, dim3(g.tie), dim3(GT), 0, st, cx, qs);
         LF_TRY(lf_prof_end(h, LF_K_TAB_TIE, 1));
     }
     LF_TRY(lf_prof_begin(h, LF_K_APPLY_EDIT));

@@ -80,18 +80,44 @@ struct __align__(64) CommRec {
     unsigned Sm[5];
 };
 
-// One entry of the table path's global hash table, one 64-byte line: key (node, community),
-// neighbour count, the first visiting neighbour's (in-count, degree) kept inline (its
-// correction is computed when the entry is finalised), and four correction digits for
-// every later visit.
-struct __align__(64) GEntry {
-    unsigned long long key;
-    int cnt;
-    int ii;                // inline visit: in-count of the neighbour
-    int idy;               // inline visit: degree of the neighbour (0 = none)
+// Table path (the largest nodes), laid out at the start of an iteration: a node's
+// neighbours in chunks of TAB_CHUNK, its communities in hash buckets.  A chunk's visits are
+// grouped by bucket in the node's region of the visit buffer, with one row of bucket
+// positions per chunk; a bucket is then evaluated by one block.
+struct TabPos {                // per table-path node, exclusive sums over the nodes before it
+    long long vis;             // visit region
+    long long row;             // row entries
+    int chunk, bucket;
+};
+
+struct ChunkRec {
+    long long rb;              // adjacency position of the chunk's first neighbour
+    long long vis, row;        // the node's visit region, this chunk's row (iteration-wide)
+    int cnt;                   // neighbours (1 .. TAB_CHUNK)
+    int p, P;                  // table-path list position, buckets of the node
     int pad;
-    long long d[4];
-    long long pad2;
+};
+
+struct BuckRec {
+    long long vis, row;        // the node's visit region and its first row
+    int x, d;                  // the node, its degree
+    int nch, P, b;             // its chunks and buckets, this bucket
+    int pad;
+};
+
+struct TabVisit {              // one neighbour membership of a table-path node
+    int comm, in, deg, pad;
+};
+
+struct BuckRes {               // best join and leave of one bucket
+    double jd, ld;
+    int j, l;
+};
+
+// decision on a queued node: community joined and left (-1: none), and its slot count when
+// it was evaluated (where a join is appended)
+struct __align__(16) Decision {
+    int J, L, pos, pad;
 };
 
 // Device-side counters and flags (one struct in device memory).  The per-queue counters
@@ -105,7 +131,7 @@ struct DevCounters {
     int tcount;                    // communities re-summed at initialisation
     int unused0;
     int unused1;
-    int occ_cnt;                   // occupied entries of the global table (queue)
+    int unused3;
     int unused2;
     int parts_total;               // re-sum parts (queue)
     int mslots;                    // multi-part re-sum accumulators in use (queue)
@@ -146,29 +172,22 @@ struct Ctx {
     int *ovf_node;           // overflow joiners (node, community)
     int *ovf_comm;
     int *ovf_flag;
-    int *dj, *dl;            // decisions of the current queue
-    double *djd, *dld;
-    int *dpos;               // [q] slot count of each queued node when it was evaluated
-                             // (where a join is appended)
+    Decision *dec;           // [q] decisions of the current queue
     DevCounters *ctr;
-    // table path (nodes whose candidates do not fit one wave), indexed by queue position j
-    int *big_idx;            // [q] evaluation state of queue index j (Q_* in iterate.hip)
     // evaluation path of every node for the current iteration: per path the order
     // positions of its nodes, ascending (a queue's nodes of a path are contiguous)
     int *plist[LF_PATH_COUNT];
     const NodeRec *prec[LF_PATH_COUNT];   // parallel to plist: the node's record
     const int *rank;         // [n] order position of each node
     const int *col_rank;     // [2 ne] order position of col[e], beside col
-    long long *titem_base;   // [table-path nodes + 1] first work item of each
-    int *titem_node;         // [items] table-path list position owning each item
-    unsigned long long *big_bj, *big_bl;   // [q] best join / leave change (bits; 0 = none)
-    int *big_cj, *big_cl;    // [q] lowest community id among the best
-    NodeLine *big_ln;        // [q] a table-path node's line at the queue start
-    GEntry *gt;                // [gT] key (j << 32 | C), empty = ~0
-    int *occ;                  // [gT] occupied entries
-    unsigned long long *occ_key;  // [gT] key | leave << 63
-    double *occ_d;             // [gT] change of each occupied entry
-    long long gmask;           // gT - 1
+    // table path
+    const TabPos *tpos;      // [table-path nodes + 1]
+    const ChunkRec *tchunk;
+    const BuckRec *tbuck;
+    int *tcur;               // per table-path node: visits placed in its region
+    TabVisit *tvis;          // the queue's visit regions
+    int *trow;               // the queue's rows
+    BuckRes *tres;           // the queue's bucket results
     // in-count units of the current iteration (every node's, in node order)
     const UnitRec *unit;
     // re-sum parts
@@ -179,14 +198,17 @@ struct Ctx {
     int stats;               // collect the per-path work counters
 };
 
-// Block roles of k_eval_big: [0, bt) walk the table-path work items, the next bg blocks
-// evaluate workgroup-path nodes (one node per block at a time), and with fuse the rest are
-// the small and medium blocks of QStep.
+// Block roles of k_eval_big: [0, bt) place the table path's visits (a chunk at a time), the
+// next bg blocks evaluate workgroup-path nodes (one node per block at a time), and with fuse
+// the rest are the small and medium blocks of QStep.
 struct BigRoles {
     int bt, bg;              // blocks per role (table, workgroup)
     int fuse;                // the small and medium paths are in this launch, not in k_eval
     int lt, nt;              // table-path list positions of the queue
     int lg, ng;              // workgroup-path list positions
+    int c0, nc;              // the queue's chunks [c0, c0 + nc)
+    int b0, nb;              // and buckets
+    long long vis0, row0;    // its first visit and row entry
 };
 
 // Everything the kernels of one queue need besides the graph's Ctx.
@@ -210,7 +232,7 @@ struct Member {
 
 // launch grids of one queue's kernels (0 = not launched)
 struct QGrids {
-    int eval, big, fin, apply, refresh;
+    int eval, big, fin, tie, apply, refresh;
 };
 
 struct TmpChunk {
@@ -267,24 +289,28 @@ struct lf_handle {
     int *tflag, *tlist;
     unsigned qtag;           // next queue tag
     int *ovf_node, *ovf_comm, *ovf_flag;
-    int *dj, *dl;
-    double *djd, *dld;
-    int *dpos;
+    Decision *dec;
     long long q_cap;         // capacity of the per-queue arrays
     // table path and work lists (sized per iteration)
-    int *big_idx;
     int *cls;                // [n] evaluation path per order position (this iteration)
     long long *cscan;        // [n + 1] scan scratch of the path lists
     int *plist[LF_PATH_COUNT];
     NodeRec *prec_all;       // [n] node records of all path lists, path after path
     long long *pbase;        // [LF_PATH_COUNT + 1] device: first record of each path
     NodeRec *prec[LF_PATH_COUNT];   // host-set views into prec_all
-    long long *titem_base;
-    int *titem_node;
-    long long titem_cap;
+    long long *cflag;        // [n + 1] scan scratch of the path lists
+    TabPos *tpos;            // [n + 1]
+    int *tcur;               // [n]
+    ChunkRec *tchunk;
+    BuckRec *tbuck;
+    long long tchunk_cap, tbuck_cap;
+    TabVisit *tvis;
+    int *trow;
+    BuckRes *tres;
+    long long tvis_cap, trow_cap, tres_cap;
     long long *hqoff;        // pinned host: [LF_PATH_COUNT][nq + 1] first list position per
-                             // queue, then [nq + 1] first table-path work item per queue,
-                             // then the 4 bounds of k_chunk_bounds
+                             // queue, then [4][nq + 1] first table-path chunk, bucket, visit
+                             // and row entry per queue, then [nq + 1] first in-count unit
     long long hqoff_cap;     // queues (nq + 1) it has room for
     long long hqoff_len;     // its length in long longs (as allocated)
     long long *hrep;         // pinned host report of an iteration end (REP_* entries)
@@ -295,14 +321,6 @@ struct lf_handle {
     bool pending_moved;      // buffers moved in the first half of an iteration start
     bool second_half_work;   // the second half of the last start queued device work
     unsigned fill_grid;      // grid of the table work-item fill of that start
-    unsigned long long *big_bj, *big_bl;
-    int *big_cj, *big_cl;
-    NodeLine *big_ln;
-    GEntry *gt;
-    int *occ;
-    unsigned long long *occ_key;
-    double *occ_d;
-    long long gT;
     UnitRec *unit;           // [unit_cap] in-count units of the iteration
     long long unit_cap;
     PartRec *part_rec;
