@@ -68,19 +68,22 @@ typedef struct {
 #define LF_K_TRIANGLES 1    /* triangle counting (all launches) */
 #define LF_K_ORDER 2        /* CC, cc reduction, node order */
 #define LF_K_INITCLUST 3    /* initial clustering and state set-up */
-#define LF_K_EVAL 4         /* k_eval: small wave path (<= 64 visits) and medium path (<= 256)
-                               of queues without larger nodes, or with very many of these */
-#define LF_K_EVAL_BIG 5     /* k_eval_big: queues with larger nodes, by block role: table-path
-                               visits, workgroup path (<= 1024 visits), and the small and
-                               medium paths */
-#define LF_K_TAB_FINAL 6    /* k_big_final: table path, candidate changes per hash bucket */
+#define LF_K_EVAL 4         /* k_eval: scoring of the small (<= 64 list entries) and medium (<=
+                               256) paths of queues without larger nodes, or with very many
+                               of these (then k_eval_whole, which also gathers them) */
+#define LF_K_EVAL_BIG 5     /* k_eval_big: scoring of queues with larger nodes: workgroup path
+                               (<= 1024), the table path's buckets, and the small and medium
+                               paths */
+#define LF_K_TAB_FINAL 6    /* no longer launched (its work is part of k_eval_big); kept so
+                               that the class indices stay the same */
 #define LF_K_TAB_TIE 7      /* k_big_tie: table path, the best of each node's buckets */
 #define LF_K_APPLY_EDIT 8   /* k_apply: the bulk apply of a queue: membership edits, sizes,
                                member lists and re-sum planning beside the in-count changes
                                around the moved nodes */
 #define LF_K_APPLY_IN 9     /* no longer launched (its work is part of k_apply); kept so
                                that the class indices stay the same */
-#define LF_K_REFRESH 10     /* k_refresh: exact re-sums of the touched communities */
+#define LF_K_REFRESH 10     /* k_refresh: exact re-sums of the communities that the queue
+                               before touched, beside the gather of this queue's nodes */
 #define LF_K_ITEREND 11     /* iteration end: degenerate removal, compaction, score */
 #define LF_K_COUNT 12
 #define LF_PROF_COUNTERS_BIT 16 /* profiling mask bit: also count the evaluation work per

@@ -454,7 +454,7 @@ int lf_batch_step(lf_batch *b, int32_t *running)
             lf_queue_params(m->h, m->k, m->nq, m->qq, true, &hm[i].qs, &g);
             m->cx.qtag = m->h->qtag++;
             hm[i].cx = m->cx;
-            const int blocks[LF_MULTI_GRIDS] = {g.big, g.fin, g.apply, g.refresh};
+            const int blocks[LF_MULTI_GRIDS] = {g.refresh, g.big, g.tie, g.apply};
             for (int t = 0; t < LF_MULTI_GRIDS; t++) {
                 hb[t * (b->cap + 1) + i] = total[t];
                 total[t] += blocks[t];

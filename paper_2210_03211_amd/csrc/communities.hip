@@ -500,6 +500,9 @@ Ctx lf_ctx(lf_handle *h)
     c.tvis = h->tvis;
     c.trow = h->trow;
     c.tres = h->tres;
+    c.lhdr = h->lhdr;
+    c.lpair = h->lpair;
+    c.ldeg = h->ldeg;
     c.unit = h->unit;
     c.part_rec = h->part_rec;
     c.part_done = h->part_done;

@@ -6,22 +6,23 @@
 // its visits that holds for the whole iteration (k_node_bounds), and each path gets the
 // list of its nodes in order.  Per queue (all launches on the handle's stream, no host
 // synchronisation):
-//   k_eval           the small path: one wave per node with <= 64 visits; then the medium
-//                    path: one 256-thread block per node with <= 256 visits, one visit per
-//                    thread; each node decided entirely in an LDS hash table
-//   k_eval_big       (queues with larger nodes) by block role: the table path's visits
-//                    (largest nodes), grouped by hash bucket of their communities; the
-//                    workgroup path (one workgroup per node with <= 1024 visits, LDS
-//                    tables); in all but very long queues and in multi-graph steps also the
-//                    small and medium paths; block 0 of either launch resets the queue's
-//                    counters
-//   k_big_final      table path: one block per bucket, evaluated in LDS
+//   k_refresh        the exact re-sums of the communities that the queue before touched, a
+//                    wave per part (multi-part communities meet in digit counters and the
+//                    last part stores them); beside them, by block role, the gather of this
+//                    queue's nodes: own and neighbours' memberships flattened into a list per
+//                    node, and the table path's visits (largest nodes) grouped by hash bucket
+//                    of their communities
+//   k_eval           scores the lists in an LDS hash table: the small path, one wave per node
+//                    with <= 64 entries, and the medium path, one 256-thread block per node
+//                    with <= 256 (k_eval_whole gathers and scores, in very long queues)
+//   k_eval_big       in queues with larger nodes: the workgroup path (one workgroup per node
+//                    with <= 1024 entries), the table path's buckets (one block each), and the
+//                    small and medium paths; block 0 of the scoring resets the queue's counters
 //   k_big_tie        table path: the best of each node's buckets
 //   k_apply          the bulk apply: membership edits, sizes, member-list appends and
 //                    re-sum planning (a thread per queued node) beside the in-count
 //                    changes around the moved nodes (a wave per in-count unit)
-//   k_refresh        exact re-sum per part; multi-part communities combine their parts
-//                    through carry-save counters and the last part finalises
+// After the last queue k_refresh runs once more, for the re-sums alone.
 // k_queue_reset clears the queue counters at the start and the end of an iteration.
 //
 // Every sum is exact (fixed point), so none of the launch shapes above can change a bit
@@ -33,8 +34,8 @@
 #define MXCAP 32        // own memberships kept in LDS (wave path)
 #define INB 64          // neighbours per in-count unit (one per lane)
 #define HOLE (-2)       // a membership left in the current iteration (removed at its end)
-#define PART 128        // members per re-sum part
-#define MACC 19         // carry-save counters per multi-part community (3 x 6 digits + in-sum)
+#define PART 512        // members per re-sum part
+#define MACC 19         // digit counters per multi-part community (3 x 6 digits, in-sum)
 
 static inline unsigned grid_for(long long n, int block) { return (unsigned)((n + block - 1) / block); }
 
@@ -92,11 +93,13 @@ struct NodeLds {
 #define VMED 256        // visits of the medium wave path
 #define VGRP 1024       // visits of the workgroup path
 #define GT 256          // threads of the workgroup path
-// Small and medium blocks ride along in k_eval_big, beside the larger nodes, unless there are
-// more of them than it keeps resident some five times over (it holds three blocks per CU, k_eval
-// eight).  Measured on the social-shaped graphs: 4M nodes, queue 4096 (about 1,500 blocks) 556
-// ms fused against 560 apart; 1M nodes, queue 65,536 (over 10,000 blocks) 88 ms apart.
-#define FUSE_BLOCKS 4096
+// Small and medium blocks of a queue up to which its nodes go through lists in memory: their
+// gather rides along in k_refresh and their scoring in k_eval_big (where there are larger
+// nodes).  Beyond, both launches are bound by throughput, the lists are only traffic, and one
+// light kernel does both.  Whole paths of social-shaped graphs: 1M nodes, queue 65,536 (over
+// 10,000 blocks) 93 ms through lists, 85 without; 4M nodes, queue 4096 (about 1,500 blocks) 500
+// through lists, 520 without; co-purchase shape, queue 256 (some 70 blocks) 103 against 115.
+#define LIST_BLOCKS 4096
 
 // member owning block b of a multi-graph launch (boff: first block of each member, nm + 1
 // entries); -1 past the last member's blocks
@@ -142,8 +145,8 @@ __device__ __forceinline__ void node_sync()
 
 // inclusive prefix sum of v over the NT threads (within each wave, then the waves' totals
 // through LDS); *total receives the sum over all NT threads
-template <int NT, int VCAP>
-__device__ __forceinline__ int node_incl_scan(int v, int tid, NodeLds<VCAP> &L, int *total)
+template <int NT>
+__device__ __forceinline__ int node_incl_scan(int v, int tid, int *wtot, int *total)
 {
     const int lane = tid & (WAVE - 1);
     int wsum;
@@ -153,11 +156,11 @@ __device__ __forceinline__ int node_incl_scan(int v, int tid, NodeLds<VCAP> &L, 
         return incl;
     } else {
         const int wv = tid / WAVE;
-        if (lane == 0) L.wtot[wv] = wsum;
+        if (lane == 0) wtot[wv] = wsum;
         __syncthreads();
         int off = 0, tot = 0;
         for (int w = 0; w < NT / WAVE; w++) {
-            int t = L.wtot[w];
+            int t = wtot[w];
             if (w < wv) off += t;
             tot += t;
         }
@@ -291,16 +294,57 @@ __device__ __forceinline__ Best score_list(const Ctx &cx, int d, const Slot (&sv
     return r;
 }
 
-// Evaluate queued node j with NT threads (one wave, or a workgroup of GT threads) if its
+// The LDS evaluation takes two launches.  The gather (a role of k_refresh) flattens a node's
+// own memberships and its neighbours' into a list in memory; the scoring (k_eval, k_eval_big)
+// reads that list and needs the communities' records.  The gather reads nothing that the
+// re-sums of the queue before write, so the two share a launch, and of a node's chain of
+// dependent reads (column indices, neighbour lines, slots, records) only the last is left
+// beside the scoring's own.  Each path's lists lie at a fixed stride per node.  Per queue of
+// the 4M-node social-shaped graph: scoring 9.0 us instead of 13.1 for both, k_refresh 13.0
+// instead of 10.7, and the larger nodes' launch is one instead of two.
+struct NodeList {
+    ListHdr *hdr;
+    long long *pair;         // community | in-count << 32
+    int *deg;                // neighbour's degree; -1: an own membership
+};
+
+// lists of the queue's small, medium and workgroup paths (path-list position i of each)
+__device__ __forceinline__ NodeList list_at(const Ctx &cx, long long node, long long entry)
+{
+    return NodeList{cx.lhdr + node, cx.lpair + entry, cx.ldeg + entry};
+}
+__device__ __forceinline__ NodeList small_list(const Ctx &cx, const QStep &, int i)
+{
+    return list_at(cx, i, (long long)i * VSMALL);
+}
+__device__ __forceinline__ NodeList med_list(const Ctx &cx, const QStep &qs, int i)
+{
+    return list_at(cx, qs.ln + i, (long long)qs.ln * VSMALL + (long long)i * VMED);
+}
+__device__ __forceinline__ NodeList group_list(const Ctx &cx, const QStep &qs, int i)
+{
+    return list_at(cx, qs.ln + qs.em + i,
+                   (long long)qs.ln * VSMALL + (long long)qs.em * VMED + (long long)i * VGRP);
+}
+
+template <int VCAP>
+struct GathLds {
+    long long vslot[VCAP];
+    int vdeg[VCAP];
+    int wtot[4];
+};
+
+// Flatten queued node j with NT threads (one wave, or a workgroup of GT threads) if its
 // neighbours (<= VCAP), visits and own memberships fit (2 * (visits + own) <= table,
-// <= VCAP of them, <= MXCAP own).  Returns false (decision not written) otherwise; the
-// decision to return is the same for all NT threads.  Every phase issues all of a
-// thread's global gathers (at most VCAP / NT of them) before it uses any, so a node costs
-// a handful of memory round trips whatever its size: own slots + column indices,
-// neighbour headers, neighbour slots, and one record per candidate.
+// <= VCAP of them, <= MXCAP own).  Returns false otherwise, the same for all NT threads.
+// Every phase issues all of a thread's global gathers before it uses any: own slots +
+// column indices, neighbour lines, neighbour slots.  With several neighbours per thread the
+// lines' memberships are read a second time (from the cache) instead of held in registers.
+// Thread tid receives list entries b * NT + tid (those below N) in e[b] and dg[b].
 template <int NT, int VCAP>
-__device__ __forceinline__ bool eval_node(const Ctx &cx, int j, const NodeRec nr, int tid, NodeLds<VCAP> &L,
-                                          int wcap, int path)
+__device__ __forceinline__ bool gather_node(const Ctx &cx, const NodeRec nr, int tid, GathLds<VCAP> &L, int wcap,
+                                            int path, long long (&e)[VCAP / NT], int (&dg)[VCAP / NT], int &N,
+                                            int &mcnt)
 {
     constexpr int NB = VCAP / NT;
     const int x = nr.x, d = nr.d;
@@ -310,117 +354,205 @@ __device__ __forceinline__ bool eval_node(const Ctx &cx, int j, const NodeRec nr
     int yv[NB];
 #pragma unroll
     for (int b = 0; b < NB; b++) {
-        int e = b * NT + tid;
-        yv[b] = e < d ? cx.col[rb + e] : -1;
+        int q = b * NT + tid;
+        yv[b] = q < d ? cx.col[rb + q] : -1;
     }
     // own line: count, placement and (inline) memberships, read beside the adjacency
     const NodeLine *lxp = cx.ln + x;
-    const int mcnt = lxp->cnt;
+    mcnt = lxp->cnt;
     const long long xoff = lxp->off;
     Slot own = {-1, 0};
     if (tid < LINE_SLOTS) own = lxp->s[tid];
     if (mcnt > MXCAP) return false;
     if (xoff >= 0 && tid < mcnt) own = cx.slot[xoff + tid];
     // one line per neighbour: its count, degree and memberships in one gather
-    NodeLine ly[NB];
+    constexpr int NL = NB == 1 ? 1 : 0;     // lines held
+    NodeLine held;
+    int yc[NB], yd[NB];
+    long long yo[NB];
 #pragma unroll
     for (int b = 0; b < NB; b++) {
+        yc[b] = 0;
+        yd[b] = 0;
+        yo[b] = -1;
         if (yv[b] >= 0) {
-            ly[b] = cx.ln[yv[b]];
-        } else {
-            ly[b].cnt = 0;
-            ly[b].deg = 0;
-            ly[b].off = -1;
+            const NodeLine *lp = cx.ln + yv[b];
+            if constexpr (NL == 1) {
+                held = *lp;
+                yc[b] = held.cnt;
+                yd[b] = held.deg;
+                yo[b] = held.off;
+            } else {
+                yc[b] = lp->cnt;
+                yd[b] = lp->deg;
+                yo[b] = lp->off;
+            }
         }
     }
     // neighbour memberships flattened into the list behind the own ones: an inline
     // membership is kept as its (community, in-count) pair, one in the slot array as the
     // complement of its slot index
-    int N = mcnt;
+    N = mcnt;
+    int p0[NB];
 #pragma unroll
     for (int b = 0; b < NB; b++) {
+        p0[b] = 0;
         if (b * NT < d) {                   // uniform over the NT threads
-            int yc = ly[b].cnt, tot;
-            int incl = node_incl_scan<NT>(yc, tid, L, &tot);
-            int p0 = N + incl - yc;
+            int tot;
+            const int incl = node_incl_scan<NT>(yc[b], tid, L.wtot, &tot);
+            p0[b] = N + incl - yc[b];
             N += tot;
             if (N > VCAP || 2 * N > wcap) return false;   // uniform
-            if (ly[b].off < 0) {
-#pragma unroll
-                for (int t = 0; t < LINE_SLOTS; t++)
-                    if (t < yc) {
-                        L.vslot[p0 + t] = ((long long)ly[b].s[t].in << 32) | (unsigned)ly[b].s[t].comm;
-                        L.vdeg[p0 + t] = ly[b].deg;
-                    }
-            } else {
-                for (int t = 0; t < yc; t++) {
-                    L.vslot[p0 + t] = ~(ly[b].off + t);
-                    L.vdeg[p0 + t] = ly[b].deg;
-                }
-            }
         }
     }
-    const int lg = N <= 4 ? 3 : 32 - __clz(2 * N - 1);    // T = 2^lg >= 2 N
-    const int T = 1 << lg;
-    for (int t = tid; t < T; t += NT) {
-        L.key[t] = -1;
-        L.kk[t] = 0;
+#pragma unroll
+    for (int b = 0; b < NB; b++) {
+        if (yo[b] < 0) {
+            if constexpr (NL == 0)
+                if (yc[b] > 0) held = cx.ln[yv[b]];
+#pragma unroll
+            for (int t = 0; t < LINE_SLOTS; t++)
+                if (t < yc[b]) {
+                    L.vslot[p0[b] + t] = ((long long)held.s[t].in << 32) | (unsigned)held.s[t].comm;
+                    L.vdeg[p0[b] + t] = yd[b];
+                }
+        } else {
+            for (int t = 0; t < yc[b]; t++) {
+                L.vslot[p0[b] + t] = ~(yo[b] + t);
+                L.vdeg[p0[b] + t] = yd[b];
+            }
+        }
     }
     if (tid < mcnt) {
         L.vslot[tid] = ((long long)own.in << 32) | (unsigned)own.comm;
         L.vdeg[tid] = -1;                   // an own membership, not a visit
     }
     node_sync<NT>();
-    // 1. every entry counts towards its community; own communities are leave candidates
-    //    even without a neighbour in them, and a membership its neighbour left earlier in
-    //    this iteration (a hole) is no visit
-    Slot sv[NB];
-    int dg[NB];
 #pragma unroll
     for (int b = 0; b < NB; b++) {
         const int v = b * NT + tid;
-        sv[b].comm = -1;
-        sv[b].in = 0;
+        e[b] = -1;
         dg[b] = 0;
         if (v < N) {
-            const long long e = L.vslot[v];
+            e[b] = L.vslot[v];
             dg[b] = L.vdeg[v];
-            if (e >= 0 || dg[b] < 0) {
-                sv[b].comm = (int)(unsigned)e;
-                sv[b].in = (int)(e >> 32);
-            } else {
-                sv[b] = cx.slot[~e];
+            if (e[b] < 0 && dg[b] >= 0) {
+                const Slot sl = cx.slot[~e[b]];
+                e[b] = ((long long)sl.in << 32) | (unsigned)sl.comm;
             }
         }
     }
-    const Best r = score_list<NT, NB, VCAP>(cx, d, sv, dg, tid, L, T, lg);
-    if (tid == 0) {
-        Decision dc;
-        dc.J = r.j;
-        dc.L = r.l;
-        dc.pos = mcnt;
-        dc.pad = 0;
-        cx.dec[j] = dc;
-    }
-    if (cx.stats) {
+    if (cx.stats && tid == 0) {
         unsigned long long *w = cx.ctr->work[path];
-        if (r.ncand) atomicAdd(&w[3], (unsigned long long)r.ncand);
-        if (tid == 0) {
-            atomicAdd(&w[0], 1ull);
-            atomicAdd(&w[1], (unsigned long long)d);
-            atomicAdd(&w[2], (unsigned long long)(N - mcnt));
-            atomicAdd(&w[4], (unsigned long long)mcnt);
-        }
+        atomicAdd(&w[0], 1ull);
+        atomicAdd(&w[1], (unsigned long long)d);
+        atomicAdd(&w[2], (unsigned long long)(N - mcnt));
+        atomicAdd(&w[4], (unsigned long long)mcnt);
     }
     return true;
 }
 
-// The in-LDS evaluation paths take their queue's nodes from their path lists; the path
-// was chosen so that the node fits, and a node that does not is an internal error.
+// Score a flattened node (entry b * NT + tid in e[b], dg[b]; those past its length are
+// ignored); a membership its neighbour left earlier in this iteration (a hole) is no entry.
+template <int NT, int VCAP>
+__device__ __forceinline__ void score_entries(const Ctx &cx, const ListHdr h, const long long (&e)[VCAP / NT],
+                                              const int (&dg)[VCAP / NT], int tid, NodeLds<VCAP> &L, int path)
+{
+    constexpr int NB = VCAP / NT;
+    const int N = h.N;
+    const int lg = N <= 4 ? 3 : 32 - __clz(2 * N - 1);    // T = 2^lg >= 2 N
+    const int T = 1 << lg;
+    for (int t = tid; t < T; t += NT) {
+        L.key[t] = -1;
+        L.kk[t] = 0;
+    }
+    Slot sv[NB];
+#pragma unroll
+    for (int b = 0; b < NB; b++) {
+        sv[b].comm = b * NT + tid < N ? (int)(unsigned)e[b] : -1;
+        sv[b].in = (int)(e[b] >> 32);
+    }
+    node_sync<NT>();
+    const Best r = score_list<NT, NB, VCAP>(cx, h.d, sv, dg, tid, L, T, lg);
+    if (tid == 0) cx.dec[h.j] = Decision{r.j, r.l, h.m, 0};
+    if (cx.stats && r.ncand) atomicAdd(&cx.ctr->work[path][3], (unsigned long long)r.ncand);
+}
 
-// The small and medium paths, in 256-thread blocks: the first es blocks evaluate four
+// the list is read beside its length
+template <int NT, int VCAP>
+__device__ __forceinline__ void score_node(const Ctx &cx, const NodeList in, int tid, NodeLds<VCAP> &L, int path)
+{
+    constexpr int NB = VCAP / NT;
+    const ListHdr h = *in.hdr;
+    long long e[NB];
+    int dg[NB];
+#pragma unroll
+    for (int b = 0; b < NB; b++) {
+        e[b] = in.pair[b * NT + tid];
+        dg[b] = in.deg[b * NT + tid];
+    }
+    score_entries<NT, VCAP>(cx, h, e, dg, tid, L, path);
+}
+
+// The gather roles take their queue's nodes from their path lists; the path was chosen so
+// that the node fits, and a node that does not is an internal error (it is left without a
+// move).
+template <int NT, int VCAP>
+__device__ __forceinline__ void gather_path(const Ctx &cx, const QStep &qs, int path, int p, int tid,
+                                            GathLds<VCAP> &L, int wcap, const NodeList out)
+{
+    constexpr int NB = VCAP / NT;
+    const int j = cx.plist[path][p] - qs.cstart;
+    const NodeRec nr = cx.prec[path][p];
+    long long e[NB];
+    int dg[NB], N, mcnt;
+    if (!gather_node<NT, VCAP>(cx, nr, tid, L, wcap, path, e, dg, N, mcnt)) {
+        if (tid == 0) {
+            *out.hdr = ListHdr{0, 0, nr.d, j};
+            atomicOr(&cx.ctr->error, LF_DEVERR_CAP);
+        }
+        return;
+    }
+#pragma unroll
+    for (int b = 0; b < NB; b++) {
+        const int v = b * NT + tid;
+        if (v < N) {
+            out.pair[v] = e[b];
+            out.deg[v] = dg[b];
+        }
+    }
+    if (tid == 0) *out.hdr = ListHdr{N, mcnt, nr.d, j};
+}
+
+// both in one: gathered and scored by the same threads, no list in memory
+template <int VCAP>
+struct WholeLds {
+    GathLds<VCAP> g;
+    NodeLds<VCAP> n;
+};
+
+template <int NT, int VCAP>
+__device__ __forceinline__ void whole_path(const Ctx &cx, const QStep &qs, int path, int p, int tid,
+                                           WholeLds<VCAP> &L, int wcap)
+{
+    constexpr int NB = VCAP / NT;
+    const int j = cx.plist[path][p] - qs.cstart;
+    const NodeRec nr = cx.prec[path][p];
+    long long e[NB];
+    int dg[NB], N, mcnt;
+    if (!gather_node<NT, VCAP>(cx, nr, tid, L.g, wcap, path, e, dg, N, mcnt)) {
+        if (tid == 0) {
+            cx.dec[j] = Decision{-1, -1, 0, 0};
+            atomicOr(&cx.ctr->error, LF_DEVERR_CAP);
+        }
+        return;
+    }
+    score_entries<NT, VCAP>(cx, ListHdr{N, mcnt, nr.d, j}, e, dg, tid, L.n, path);
+}
+
+// The small and medium paths, in 256-thread blocks: the first es blocks score four
 // small-path nodes each, one per wave; the next em blocks one medium-path node each, one
-// visit per thread.  These are all of k_eval (10 KB of LDS, eight blocks per CU), and
+// list entry per thread.  These are all of k_eval (10 KB of LDS, eight blocks per CU), and
 // block roles of k_eval_big where a launch of their own does not pay.
 union EvalLds {
     NodeLds<VSMALL> w[EW];
@@ -431,23 +563,16 @@ __device__ __forceinline__ void eval_small_med(const Ctx &cx, const QStep &qs, i
 {
     const int wv = threadIdx.x / WAVE, lane = threadIdx.x & (WAVE - 1);
     if (blk < qs.es) {
-        const int p = blk * EW + wv;
-        if (p >= qs.ln) return;             // small blocks have no block barriers
-        const int j = cx.plist[LF_PATH_SMALL][qs.ls + p] - qs.cstart;
-        const NodeRec nr = cx.prec[LF_PATH_SMALL][qs.ls + p];
-        if (!eval_node<WAVE, VSMALL>(cx, j, nr, lane, L.w[wv], qs.wcap, LF_PATH_SMALL) && lane == 0)
-            atomicOr(&cx.ctr->error, LF_DEVERR_CAP);
+        const int i = blk * EW + wv;        // small blocks have no block barriers
+        if (i < qs.ln) score_node<WAVE, VSMALL>(cx, small_list(cx, qs, i), lane, L.w[wv], LF_PATH_SMALL);
         return;
     }
-    const int m = blk - qs.es;              // a medium block: every thread takes part
-    if (m >= qs.em) return;
-    const int j = cx.plist[LF_PATH_MED][qs.lm + m] - qs.cstart;
-    const NodeRec nr = cx.prec[LF_PATH_MED][qs.lm + m];
-    if (!eval_node<EW * WAVE, VMED>(cx, j, nr, threadIdx.x, L.m, qs.mcap, LF_PATH_MED) && threadIdx.x == 0)
-        atomicOr(&cx.ctr->error, LF_DEVERR_CAP);
+    const int i = blk - qs.es;              // a medium block: every thread takes part
+    if (i < qs.em) score_node<EW * WAVE, VMED>(cx, med_list(cx, qs, i), threadIdx.x, L.m, LF_PATH_MED);
 }
 
-// block 0 of a queue's first launch resets its apply counters (no evaluation role uses them)
+// block 0 of a queue's scoring resets its apply counters (the launch before, which re-sums
+// the communities of the queue before, is the last to use them)
 __device__ __forceinline__ void reset_apply_counters(const Ctx &cx, int blk)
 {
     if (blk == 0 && threadIdx.x == 0) {
@@ -464,22 +589,40 @@ __global__ void __launch_bounds__(EW * WAVE) k_eval(Ctx cx, QStep qs)
     eval_small_med(cx, qs, (int)blockIdx.x, lds);
 }
 
+// the same nodes gathered and scored in one launch (very long queues)
+__global__ void __launch_bounds__(EW * WAVE) k_eval_whole(Ctx cx, QStep qs)
+{
+    __shared__ union {
+        WholeLds<VSMALL> w[EW];
+        WholeLds<VMED> m;
+    } lds;
+    const int blk = (int)blockIdx.x, wv = threadIdx.x / WAVE, lane = threadIdx.x & (WAVE - 1);
+    reset_apply_counters(cx, blk);
+    if (blk < qs.es) {
+        const int i = blk * EW + wv;        // small blocks have no block barriers
+        if (i < qs.ln) whole_path<WAVE, VSMALL>(cx, qs, LF_PATH_SMALL, qs.ls + i, lane, lds.w[wv], qs.wcap);
+        return;
+    }
+    const int i = blk - qs.es;
+    if (i < qs.em) whole_path<EW * WAVE, VMED>(cx, qs, LF_PATH_MED, qs.lm + i, threadIdx.x, lds.m, qs.mcap);
+}
+
 // ------------------------------------------------------------------------------------
 // evaluation, table path
 // ------------------------------------------------------------------------------------
-// The largest nodes take two launches, without global atomics per visit.  First (a role of
-// k_eval_big) one block per chunk of TAB_CHUNK neighbours gathers their lines, counts their
+// The largest nodes are gathered and scored without global atomics per visit.  First (a role
+// of k_refresh) one block per chunk of TAB_CHUNK neighbours gathers their lines, counts their
 // memberships per hash bucket of the communities, and writes them to the node's visit
-// region grouped by bucket, with a row of the buckets' positions.  Then (k_big_final) one
+// region grouped by bucket, with a row of the buckets' positions.  Then (in k_eval_big) one
 // block per bucket collects its piece of every chunk and evaluates it like a medium-path
 // node: all visits of a community meet in one bucket.  k_big_tie folds a node's buckets.
 // A node has one bucket per BUCK_AVG visits of its bound, so a bucket's entries nearly
 // always fit one per thread.
 // The path is bound by its gathers (64-byte lines of the neighbours, 64-byte records of the
 // candidates).  The former global hash table moved a 64-byte entry four to five times per
-// visit besides: on a dense-shaped graph (1M nodes, 39M pairs, queue 16,384) its three launches took
-// 201 + 146 + 19 us per queue, these take 56 + 74 + 6; on the social-shaped one (4M nodes,
-// queue 4096) 54 + 61 + 10 against 25 + 35 + 6.
+// visit besides: on a dense-shaped graph (1M nodes, 39M pairs, queue 16,384) its three launches
+// took 201 + 146 + 19 us per queue, these roles as launches of their own 56 + 74 + 6; on the
+// social-shaped one (4M nodes, queue 4096) 54 + 61 + 10 against 25 + 35 + 6.
 #define TAB_CHUNK 256
 #define TAB_MAXP 4096
 #define VBUCK 256           // entries of a bucket evaluated one per thread
@@ -591,44 +734,6 @@ __device__ __forceinline__ void table_chunk(const Ctx &cx, const QStep &qs, int 
         }
     }
 }
-
-// The larger nodes of a queue in one launch, by block role (BigRoles).  All read the state
-// at the queue's start, so the roles are independent.
-
-union BigLds {
-    PartLds t;
-    NodeLds<VGRP> g;
-    EvalLds e;
-};
-
-__device__ __forceinline__ void body_eval_big(const Ctx &cx, const QStep &qs, int blk, int nblk, BigLds &L)
-{
-    (void)nblk;
-    const BigRoles &r = qs.br;
-    const int cstart = qs.cstart;
-    reset_apply_counters(cx, blk);
-    int b = blk;
-    if (b < r.bt) {
-        for (int k = b; k < r.nc; k += r.bt) {
-            table_chunk(cx, qs, r.c0 + k, L.t);
-            __syncthreads();                // the next chunk reuses the LDS
-        }
-        return;
-    }
-    b -= r.bt;
-    if (b < r.bg) {
-        for (int p = b; p < r.ng; p += r.bg) {
-            const int j = cx.plist[LF_PATH_GROUP][r.lg + p] - cstart;
-            const NodeRec nr = cx.prec[LF_PATH_GROUP][r.lg + p];
-            if (!eval_node<GT, VGRP>(cx, j, nr, threadIdx.x, L.g, qs.gcap, LF_PATH_GROUP) && threadIdx.x == 0)
-                atomicOr(&cx.ctr->error, LF_DEVERR_CAP);
-            __syncthreads();                // the next node reuses the LDS
-        }
-        return;
-    }
-    if (r.fuse) eval_small_med(cx, qs, b - r.bg, L.e);
-}
-QUEUE_KERNELS(k_eval_big, GT, BigLds, body_eval_big)
 
 // A bucket whose entries do not fit one per thread (a community that many of the node's
 // neighbours share, a node with very many chunks): the visits are streamed from memory,
@@ -797,8 +902,8 @@ __device__ __forceinline__ void eval_bucket(const Ctx &cx, const QStep &qs, int 
     NodeLds<VBUCK> &L = S.n;
     // own memberships of this bucket, then its piece of every chunk
     int m, N;
-    const int pm = node_incl_scan<GT>(ownb ? 1 : 0, tid, L, &m);
-    const int pl = node_incl_scan<GT>(len, tid, L, &N);
+    const int pm = node_incl_scan<GT>(ownb ? 1 : 0, tid, L.wtot, &m);
+    const int pl = node_incl_scan<GT>(len, tid, L.wtot, &N);
     N += m;
     Best r;
     if (N <= VBUCK && br.nch <= GT && mcnt <= GT) {      // uniform
@@ -863,15 +968,36 @@ __device__ __forceinline__ void eval_bucket(const Ctx &cx, const QStep &qs, int 
     if (cx.stats && r.ncand) atomicAdd(&cx.ctr->work[LF_PATH_TABLE][3], (unsigned long long)r.ncand);
 }
 
-__device__ __forceinline__ void body_big_final(const Ctx &cx, const QStep &qs, int blk, int nblk, BuckLds &S)
+// Queues with larger nodes, by block role: the workgroup path (one node per block at a time),
+// the table path's buckets, and with fuse the small and medium paths.
+union BigLds {
+    BuckLds b;
+    NodeLds<VGRP> g;
+    EvalLds e;
+};
+
+__device__ __forceinline__ void body_eval_big(const Ctx &cx, const QStep &qs, int blk, int nblk, BigLds &L)
 {
-    for (int k = blk; k < qs.br.nb; k += nblk) {
-        eval_bucket(cx, qs, k, S);
-        __syncthreads();                     // the next bucket reuses the LDS
+    (void)nblk;
+    const BigRoles &r = qs.br;
+    reset_apply_counters(cx, blk);
+    int b = blk;
+    if (b < r.bg) {
+        for (int i = b; i < r.ng; i += r.bg) {
+            score_node<GT, VGRP>(cx, group_list(cx, qs, i), threadIdx.x, L.g, LF_PATH_GROUP);
+            __syncthreads();                // the next node reuses the LDS
+        }
+        return;
     }
+    b -= r.bg;
+    if (b < r.nb) {
+        eval_bucket(cx, qs, b, L.b);
+        return;
+    }
+    if (qs.lists) eval_small_med(cx, qs, b - r.nb, L.e);
 }
-#define FINAL_BOUNDS GT, 5
-QUEUE_KERNELS(k_big_final, FINAL_BOUNDS, BuckLds, body_big_final)
+#define BIG_BOUNDS GT, 4
+QUEUE_KERNELS(k_eval_big, BIG_BOUNDS, BigLds, body_eval_big)
 
 // the decision of every table-path node of the queue: the best of its buckets (one wave per
 // node); communities in different buckets differ, so equal changes go to the lower id
@@ -922,12 +1048,14 @@ QUEUE_KERNELS(k_big_tie, GT, NoLds, body_big_tie)
 // membership after the queue from the neighbour's own decision rather than from its
 // slots: the result is a from-scratch recount of every in-count on the new partition.
 
-// Re-sum parts of community C at its first touch in the queue, planned from its
-// member-list capacity (fixed within an iteration).  Every lane of the wave calls this
-// (want = false: it only takes part in the wave's reservation).
-__device__ __forceinline__ void plan_parts(const Ctx &cx, bool want, int C, long long base, long long cap)
+// Re-sum parts of community C at its first touch in the queue, planned from its member
+// list's length then (joiners of the same queue that come later are the last part's).
+// Every lane of the wave calls this (want = false: it only takes part in the wave's
+// reservation).
+__device__ __forceinline__ void plan_parts(const Ctx &cx, bool want, int C, long long base, long long cap,
+                                           long long len)
 {
-    int parts = (int)((cap + PART - 1) / PART);
+    int parts = (int)(((len < cap ? len : cap) + PART - 1) / PART);
     if (parts < 1) parts = 1;
     int p0 = wave_reserve(&cx.ctr->parts_total, want && parts == 1);
     if (!want) return;
@@ -977,6 +1105,7 @@ __device__ __forceinline__ void apply_edit(const Ctx &cx, const QStep &qs, int j
     const bool act = inq && (J >= 0 || L >= 0);
     bool firstL = false, firstJ = false, joined = false;
     long long cmoL = 0, cmeL = 0, cmoJ = 0, cmeJ = 0;
+    int lenL = 0, lenJ = 0;
     int own_scanned = 0;
     if (act) {
         // the node's line and slot capacity and both member-list ranges in one round trip
@@ -985,6 +1114,7 @@ __device__ __forceinline__ void apply_edit(const Ctx &cx, const QStep &qs, int j
         if (L >= 0) {
             cmoL = cx.cm_off[L];
             cmeL = cx.cm_off[L + 1];
+            lenL = cx.cm_len[L];
         }
         if (J >= 0) {
             cmoJ = cx.cm_off[J];
@@ -1006,6 +1136,7 @@ __device__ __forceinline__ void apply_edit(const Ctx &cx, const QStep &qs, int j
         if (jfits) {
             atomicAdd(&cx.cr[J].s, 1);
             p = atomicAdd(&cx.cm_len[J], 1);
+            lenJ = p + 1;
             oldJ = atomicExch(&cx.tflag[J], 1);
         }
         if (L >= 0) {
@@ -1038,8 +1169,8 @@ __device__ __forceinline__ void apply_edit(const Ctx &cx, const QStep &qs, int j
             atomicAdd(&cx.ctr->apply[LF_APPLY_OWN_SLOTS], (unsigned long long)os);
         }
     }
-    plan_parts(cx, firstL, L, cmoL, cmeL - cmoL);
-    plan_parts(cx, firstJ, J, cmoJ, cmeJ - cmoJ);
+    plan_parts(cx, firstL, L, cmoL, cmeL - cmoL, lenL);
+    plan_parts(cx, firstJ, J, cmoJ, cmeJ - cmoJ, lenJ);
 }
 
 // in-count changes of the neighbours in unit u (one wave): a neighbour y that holds J
@@ -1135,128 +1266,202 @@ QUEUE_KERNELS(k_apply, 256, NoLds, body_apply)
 // ------------------------------------------------------------------------------------
 // exact re-sum of the touched communities
 // ------------------------------------------------------------------------------------
-__device__ __forceinline__ void x192_to_digits6(const X192 &v, long long *dg)
+// The wave's exact sum of its lanes' 128-bit values: each is cut into six 24-bit limbs, whose
+// sums over 64 lanes fit 32-bit words, so a limb is one DPP reduction (no carries, no LDS).
+__device__ __forceinline__ X192 wave_sum_u128(u128 v)
 {
-    dg[0] = (long long)(v.w0 & 0xffffffffull);
-    dg[1] = (long long)(v.w0 >> 32);
-    dg[2] = (long long)(v.w1 & 0xffffffffull);
-    dg[3] = (long long)(v.w1 >> 32);
-    dg[4] = (long long)(v.w2 & 0xffffffffull);
-    dg[5] = (long long)(int)(unsigned)(v.w2 >> 32);
+    const unsigned w0 = (unsigned)v, w1 = (unsigned)(v >> 32), w2 = (unsigned)(v >> 64), w3 = (unsigned)(v >> 96);
+    const u64 t0 = wave_sum_u32(w0 & 0xffffffu);
+    const u64 t1 = wave_sum_u32((w0 >> 24) | ((w1 & 0xffffu) << 8));
+    const u64 t2 = wave_sum_u32((w1 >> 16) | ((w2 & 0xffu) << 16));
+    const u64 t3 = wave_sum_u32(w2 >> 8);
+    const u64 t4 = wave_sum_u32(w3 & 0xffffffu);
+    const u64 t5 = wave_sum_u32(w3 >> 24);
+    const u64 lo = t0 + (t1 << 24), mid = t2 + (t3 << 24), hi = t4 + (t5 << 24);   // at 2^0, 2^48, 2^96
+    X192 r = {lo, 0, 0};
+    x192_add(r, X192{mid << 48, mid >> 16, 0});
+    x192_add(r, X192{0, hi << 32, hi >> 32});
+    return r;
 }
 
-// sum_k D_k 2^(32k) for six signed 64-bit counters
-__device__ __forceinline__ X192 x192_from_digits6(const long long *D)
+// 24-bit digits of a non-negative sum below 2^160 (the last one takes the rest), and back
+// from digit counters
+__device__ __forceinline__ u64 x192_digit24(const X192 &v, int k)
+{
+    const int li = (24 * k) >> 6, bi = (24 * k) & 63;
+    const u64 a = li == 0 ? v.w0 : v.w1, b = li == 0 ? v.w1 : v.w2;
+    const u64 d = bi ? (a >> bi) | (b << (64 - bi)) : a;
+    return k < 5 ? d & 0xffffffull : d;
+}
+
+__device__ __forceinline__ X192 x192_from_digits24(const unsigned long long *D)
 {
     X192 r = x192_zero();
-#pragma unroll
-    for (int k = 0; k < 6; k++) {
-        long long v = D[k];
-        u64 sgn = v < 0 ? ~0ull : 0ull;
-        // v * 2^(32k) as a 192-bit two's complement value
-        u64 w[3] = {0, 0, 0};
-        int sh = 32 * k;
-        int li = sh >> 6, bi = sh & 63;
-        u64 lo = (u64)v << bi;
-        u64 hi = bi ? (((u64)v >> (64 - bi)) | (sgn << bi)) : sgn;
-        w[li] = lo;
-        if (li + 1 < 3) w[li + 1] = hi;
-        for (int q = li + 2; q < 3; q++) w[q] = sgn;
-        X192 t = {w[0], w[1], w[2]};
-        x192_add(r, t);
+#pragma unroll 1
+    for (int k = 0; k < 6; k++) {            // (rolled up: registers matter more here)
+        const u64 d = __atomic_load_n(D + k, __ATOMIC_RELAXED);
+        const int li = (24 * k) >> 6, bi = (24 * k) & 63;
+        const u64 lo = d << bi, hi = bi ? d >> (64 - bi) : 0;
+        x192_add(r, X192{li == 0 ? lo : 0, li == 0 ? hi : li == 1 ? lo : 0, li == 1 ? hi : 0});
     }
     return r;
 }
 
-__device__ __forceinline__ void body_refresh(const Ctx &cx, const QStep &qs, int blk, int nblk, NoLds &)
+// Exact re-sum of one part (one wave): the members' terms at sizes s, s+1 and s-1, and the
+// sum of their in-counts.
+__device__ __forceinline__ void refresh_part(const Ctx &cx, const PartRec &pr, int lane, int &bad)
 {
-    (void)qs;
-    int lane = threadIdx.x & (WAVE - 1);
-    long long nw = (long long)nblk * (blockDim.x / WAVE);
-    int bad = 0;
-    long long p = (blk * (long long)blockDim.x + threadIdx.x) / WAVE;
-    // the wave's first part is read beside the count (the buffer holds part_cap records)
-    PartRec first;
-    if (p < cx.part_cap) first = cx.part_rec[p];
-    int count = __atomic_load_n(&cx.ctr->parts_total, __ATOMIC_RELAXED);
-    if (count > cx.part_cap) count = cx.part_cap;
-    for (bool at_first = true; p < count; p += nw, at_first = false) {
-        const PartRec pr = at_first ? first : cx.part_rec[p];
-        const int C = pr.C;
-        if (C < 0 || C >= cx.K) continue;          // only after a flagged overflow
-        const int k = pr.k;
-        const long long base = pr.base, cap = pr.cap;
-        // size, list length and overflow after the edits, read beside the part's entries
-        const int s = cx.cr[C].s;
-        long long len = cx.cm_len[C];
-        const int ovf = cx.ovf_flag[C];
-        const long long lo = (long long)k * PART;
-        int mem[PART / WAVE];
-#pragma unroll
-        for (int i = 0; i < PART / WAVE; i++) {
-            const long long q = lo + i * WAVE + lane;
-            mem[i] = q < cap ? cx.cm_node[base + q] : -1;
-        }
-        if (len > cap) len = cap;
-        // the plan covers the list's capacity; the parts that hold members after the edits
-        // (the same count for every part of C: the length is final here) do the re-sum
-        int parts = (int)((len + PART - 1) / PART);
-        if (parts < 1) parts = 1;
-        if (k >= parts) continue;
-        const long long hi = lo + PART < len ? lo + PART : len;
-        X192 a0 = x192_zero(), ap = x192_zero(), am = x192_zero();
+    const int C = pr.C;
+    const int k = pr.k;
+    const long long base = pr.base, cap = pr.cap;
+    // size, list length and overflow after the edits, read beside the part's entries
+    const int s = cx.cr[C].s;
+    long long len = cx.cm_len[C];
+    const int ovf = cx.ovf_flag[C];
+    const long long lo = (long long)k * PART;
+    int mem = lo + lane < cap ? cx.cm_node[base + lo + lane] : -1;
+    if (len > cap) len = cap;
+    // the plan is from the list's length at the community's first touch; the parts that hold
+    // members after the edits (the same count for every part of C: the length is final here)
+    // do the re-sum, the last one with whatever joined beyond the plan
+    int parts = (int)((len + PART - 1) / PART);
+    if (parts < 1) parts = 1;
+    if (parts > pr.parts) parts = pr.parts;
+    if (k >= parts) return;
+    const long long hi = k == parts - 1 ? len : lo + PART;
+    X192 S0 = x192_zero(), Sp = x192_zero(), Sm = x192_zero();
+    long long ins = 0, mslots = 0;
+    long long q = lo;
+    do {                                     // a lane's 128-bit sums are folded every 64 members
+        const long long end = hi - q < 64 * WAVE ? hi : q + 64 * WAVE;
+        u128 a0 = 0, ap = 0, am = 0;
         long long sumi = 0;
-#pragma unroll
-        for (int i = 0; i < PART / WAVE; i++)
-            if (lo + i * WAVE + lane < hi) member_terms_line(cx, mem[i], C, s, a0, ap, am, sumi, bad);
-        if (cx.stats) {
-            long long mslots = 0;
-            for (int i = 0; i < PART / WAVE; i++)
-                if (lo + i * WAVE + lane < hi) mslots += cx.ln[mem[i]].cnt;
-            mslots = wave_sum_i64(mslots);
-            if (lane == 0) {
-                atomicAdd(&cx.ctr->apply[LF_APPLY_PARTS], 1ull);
-                if (k == 0) atomicAdd(&cx.ctr->apply[LF_APPLY_TOUCHED], 1ull);
-                atomicAdd(&cx.ctr->apply[LF_APPLY_MEMBERS], (unsigned long long)(hi > lo ? hi - lo : 0));
-                atomicAdd(&cx.ctr->apply[LF_APPLY_MEMBER_SLOTS], (unsigned long long)mslots);
+#pragma unroll 1
+        for (; q < end; q += WAVE) {
+            const int y = mem;
+            mem = q + WAVE + lane < hi ? cx.cm_node[base + q + WAVE + lane] : -1;
+            if (q + lane < hi) {
+                member_terms_line(cx, y, C, s, a0, ap, am, sumi, bad);
+                if (cx.stats) mslots += cx.ln[y].cnt;
             }
         }
-        if (k == 0 && ovf) {
-            int no = __atomic_load_n(&cx.ctr->ovf_cnt, __ATOMIC_RELAXED);
-            for (int e = lane; e < no; e += WAVE)
-                if (cx.ovf_comm[e] == C) member_terms_line(cx, cx.ovf_node[e], C, s, a0, ap, am, sumi, bad);
-        }
-        a0 = wave_sum_x192(a0);
-        ap = wave_sum_x192(ap);
-        am = wave_sum_x192(am);
-        sumi = wave_sum_i64(sumi);
-        if (lane != 0) continue;
-        if (parts == 1) {
-            store_comm(cx, C, s, a0, ap, am, sumi, bad);
-            continue;
-        }
-        unsigned long long *acc = (unsigned long long *)&cx.macc[(long long)pr.ms * MACC];
-        long long dg[6];
-        x192_to_digits6(a0, dg);
-        for (int q = 0; q < 6; q++) atomicAdd(acc + q, (unsigned long long)dg[q]);
-        x192_to_digits6(ap, dg);
-        for (int q = 0; q < 6; q++) atomicAdd(acc + 6 + q, (unsigned long long)dg[q]);
-        x192_to_digits6(am, dg);
-        for (int q = 0; q < 6; q++) atomicAdd(acc + 12 + q, (unsigned long long)dg[q]);
-        atomicAdd(acc + 18, (unsigned long long)sumi);
-        __threadfence();
-        if (atomicAdd(&cx.part_done[C], 1) == parts - 1) {
-            // last part: every other part's counters are in (they fenced before counting)
-            __threadfence();
-            long long D[MACC];
-            for (int q = 0; q < MACC; q++) D[q] = (long long)__atomic_load_n(acc + q, __ATOMIC_RELAXED);
-            store_comm(cx, C, s, x192_from_digits6(D), x192_from_digits6(D + 6), x192_from_digits6(D + 12), D[18],
-                       bad);
+        WAVE_SYNC();
+        x192_add(S0, wave_sum_u128(a0));
+        x192_add(Sp, wave_sum_u128(ap));
+        x192_add(Sm, wave_sum_u128(am));
+        ins += (long long)wave_sum_u32((unsigned)sumi & 0xffffffu) +
+               ((long long)wave_sum_u32((unsigned)(sumi >> 24)) << 24);
+    } while (q < hi);
+    if (cx.stats) {
+        mslots = wave_sum_i64(mslots);
+        if (lane == 0) {
+            atomicAdd(&cx.ctr->apply[LF_APPLY_PARTS], 1ull);
+            if (k == 0) atomicAdd(&cx.ctr->apply[LF_APPLY_TOUCHED], 1ull);
+            atomicAdd(&cx.ctr->apply[LF_APPLY_MEMBERS], (unsigned long long)(hi > lo ? hi - lo : 0));
+            atomicAdd(&cx.ctr->apply[LF_APPLY_MEMBER_SLOTS], (unsigned long long)mslots);
         }
     }
-    if (bad) atomicOr(&cx.ctr->error, LF_DEVERR_INEXACT);
+    if (k == 0 && ovf) {                     // rare: joiners that did not fit the list
+        const int no = __atomic_load_n(&cx.ctr->ovf_cnt, __ATOMIC_RELAXED);
+        for (int e0 = 0; e0 < no; e0 += WAVE) {
+            const int e = e0 + lane;
+            u128 a0 = 0, ap = 0, am = 0;
+            long long sumi = 0;
+            if (e < no && cx.ovf_comm[e] == C) member_terms_line(cx, cx.ovf_node[e], C, s, a0, ap, am, sumi, bad);
+            WAVE_SYNC();
+            x192_add(S0, wave_sum_u128(a0));
+            x192_add(Sp, wave_sum_u128(ap));
+            x192_add(Sm, wave_sum_u128(am));
+            ins += wave_sum_i64(sumi);
+        }
+    }
+    if (lane != 0) return;
+    if (parts == 1) {
+        store_comm(cx, C, s, S0, Sp, Sm, ins, bad);
+        return;
+    }
+    // the parts of a community meet in its digit counters, and the last one stores the sums
+    unsigned long long *acc = (unsigned long long *)&cx.macc[(long long)pr.ms * MACC];
+#pragma unroll 1
+    for (int q = 0; q < 6; q++) {
+        atomicAdd(acc + q, x192_digit24(S0, q));
+        atomicAdd(acc + 6 + q, x192_digit24(Sp, q));
+        atomicAdd(acc + 12 + q, x192_digit24(Sm, q));
+    }
+    atomicAdd(acc + 18, (unsigned long long)ins);
+    // This wave's additions must have been performed before it counts its part.  They are
+    // device-scope atomics, which complete at the memory side, so waiting for them is
+    // enough; a device-scope fence would also write the whole L2 back (measured: 212 us per
+    // queue with fences, 82 with the wait, where planted communities of up to 3,000 members
+    // are re-summed on a 700,000-node graph at queue 4096).
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (atomicAdd(&cx.part_done[C], 1) == parts - 1)
+        store_comm(cx, C, s, x192_from_digits24(acc), x192_from_digits24(acc + 6), x192_from_digits24(acc + 12),
+                   (long long)__atomic_load_n(acc + 18, __ATOMIC_RELAXED), bad);
 }
-QUEUE_KERNELS(k_refresh, 256, NoLds, body_refresh)
+
+// Between two queues: the re-sums of the communities that the queue before touched (rb blocks,
+// a wave per part), beside the gather of the next queue's nodes.  The two are independent:
+// the re-sums write community records, the gather reads membership lines and slots, which
+// nothing here writes.  The last queue of an iteration is followed by the re-sums alone.
+union StepLds {
+    PartLds t;
+    GathLds<VGRP> g;
+    GathLds<VMED> m;
+    GathLds<VSMALL> w[EW];
+};
+
+__device__ __forceinline__ void body_refresh(const Ctx &cx, const QStep &qs, int blk, int nblk, StepLds &L)
+{
+    (void)nblk;
+    const int wv = threadIdx.x / WAVE, lane = threadIdx.x & (WAVE - 1);
+    int b = blk;
+    if (b < qs.rb) {
+        const long long nw = (long long)qs.rb * (GT / WAVE);
+        int bad = 0;
+        long long p = (long long)b * (GT / WAVE) + wv;
+        // the wave's first part is read beside the count (the buffer holds part_cap records)
+        PartRec pr;
+        if (p < cx.part_cap) pr = cx.part_rec[p];
+        int count = __atomic_load_n(&cx.ctr->parts_total, __ATOMIC_RELAXED);
+        if (count > cx.part_cap) count = cx.part_cap;
+        while (p < count) {
+            if (pr.C >= 0 && pr.C < cx.K) refresh_part(cx, pr, lane, bad);   // else: after a flagged overflow
+            WAVE_SYNC();
+            p += nw;
+            if (p < count) pr = cx.part_rec[p];
+        }
+        if (bad) atomicOr(&cx.ctr->error, LF_DEVERR_INEXACT);
+        return;
+    }
+    b -= qs.rb;
+    const BigRoles &r = qs.br;
+    if (b < r.bt) {
+        for (int k = b; k < r.nc; k += r.bt) {
+            table_chunk(cx, qs, r.c0 + k, L.t);
+            __syncthreads();                // the next chunk reuses the LDS
+        }
+        return;
+    }
+    b -= r.bt;
+    if (b < r.bg) {
+        for (int i = b; i < r.ng; i += r.bg) {
+            gather_path<GT, VGRP>(cx, qs, LF_PATH_GROUP, r.lg + i, threadIdx.x, L.g, qs.gcap, group_list(cx, qs, i));
+            __syncthreads();                // the next node reuses the LDS
+        }
+        return;
+    }
+    b -= r.bg;
+    if (!qs.lists) return;
+    if (b < qs.em) {
+        gather_path<GT, VMED>(cx, qs, LF_PATH_MED, qs.lm + b, threadIdx.x, L.m, qs.mcap, med_list(cx, qs, b));
+        return;
+    }
+    const int i = (b - qs.em) * EW + wv;    // small blocks have no block barriers
+    if (i < qs.ln)
+        gather_path<WAVE, VSMALL>(cx, qs, LF_PATH_SMALL, qs.ls + i, lane, L.w[wv], qs.wcap, small_list(cx, qs, i));
+}
+QUEUE_KERNELS(k_refresh, GT, StepLds, body_refresh)
 
 // ------------------------------------------------------------------------------------
 // per-iteration sizing of the queue buffers
@@ -1565,7 +1770,8 @@ void lf_free_iteration_buffers(lf_handle *h)
 {
     void **ptrs[] = {(void **)&h->dec, (void **)&h->unit, (void **)&h->part_rec, (void **)&h->macc,
                      (void **)&h->cflag, (void **)&h->tpos, (void **)&h->tcur, (void **)&h->tchunk,
-                     (void **)&h->tbuck, (void **)&h->tvis, (void **)&h->trow, (void **)&h->tres};
+                     (void **)&h->tbuck, (void **)&h->tvis, (void **)&h->trow, (void **)&h->tres,
+                     (void **)&h->lhdr, (void **)&h->lpair, (void **)&h->ldeg};
     for (void **p : ptrs) {
         lf_dev_free(h, *p);
         *p = nullptr;
@@ -1579,6 +1785,9 @@ void lf_free_iteration_buffers(lf_handle *h)
     h->tvis_cap = 0;
     h->trow_cap = 0;
     h->tres_cap = 0;
+    h->lhdr_cap = 0;
+    h->lpair_cap = 0;
+    h->ldeg_cap = 0;
 }
 
 // The iteration start's report (device dq, copied to the pinned host hqoff), for nq
@@ -1754,7 +1963,20 @@ static int size_queue_complete(lf_handle *h, long long q)
         h->second_half_work = true;
     }
     const long long grown = h->phase_graphs ? 3 : 0;        // spare room, in quarters beyond one
-    struct { void **p; long long *cap; long long need; size_t each; } bufs[3] = {
+    // flattened lists of the queue with the most entries
+    long long lnodes = 0, lentries = 0;
+    for (long long k = 0; k < nq; k++) {
+        long long m[LF_PATH_COUNT];
+        for (int c = 0; c < LF_PATH_COUNT; c++) m[c] = h->hqoff[c * (nq + 1) + k + 1] - h->hqoff[c * (nq + 1) + k];
+        const long long nodes = m[LF_PATH_SMALL] + m[LF_PATH_MED] + m[LF_PATH_GROUP];
+        const long long entries = m[LF_PATH_SMALL] * VSMALL + m[LF_PATH_MED] * VMED + m[LF_PATH_GROUP] * VGRP;
+        if (nodes > lnodes) lnodes = nodes;
+        if (entries > lentries) lentries = entries;
+    }
+    struct { void **p; long long *cap; long long need; size_t each; } bufs[6] = {
+        {(void **)&h->lhdr, &h->lhdr_cap, lnodes, sizeof(ListHdr)},
+        {(void **)&h->lpair, &h->lpair_cap, lentries, sizeof(long long)},
+        {(void **)&h->ldeg, &h->ldeg_cap, lentries, sizeof(int)},
         {(void **)&h->tres, &h->tres_cap, most[1], sizeof(BuckRes)},
         {(void **)&h->tvis, &h->tvis_cap, most[2], sizeof(TabVisit)},
         {(void **)&h->trow, &h->trow_cap, most[3], sizeof(int)}};
@@ -2000,15 +2222,16 @@ void lf_queue_params(lf_handle *h, long long k, long long nq, long long qq, bool
     br.ng = ln[LF_PATH_GROUP];
     qs->ub = hu[k];
     qs->un = (int)(hu[k + 1] - hu[k]);
-    const bool heavy = br.bt + br.bg > 0;
-    br.fuse = compact_grids || (heavy && qs->es + qs->em <= FUSE_BLOCKS);
-    g->eval = br.fuse ? 0 : qs->es + qs->em;
-    g->big = br.bt + br.bg + (br.fuse ? qs->es + qs->em : 0);
+    qs->rb = rbk;
+    const int light = qs->es + qs->em, heavy = br.bg + br.nb;
+    qs->lists = compact_grids || light <= LIST_BLOCKS;
+    const bool fuse = compact_grids || (heavy > 0 && qs->lists);
+    g->refresh = rbk + br.bt + br.bg + (qs->lists ? light : 0);
+    g->eval = fuse ? 0 : light;
+    g->big = heavy + (fuse ? light : 0);
     if (g->big < 1 && g->eval == 0) g->big = 1;   // block 0 resets the queue's counters
-    g->fin = br.nb;
     g->tie = (int)grid_for(br.nt, GT / WAVE);
     g->apply = (int)grid_for(clen, 256) + (int)grid_for(qs->un, 256 / WAVE);
-    g->refresh = rbk;
 }
 
 // the kernels of one queue of one graph, in order, on the handle's stream
@@ -2016,9 +2239,13 @@ int lf_launch_queue(lf_handle *h, Ctx &cx, const QStep &qs, const QGrids &g)
 {
     hipStream_t st = h->stream;
     cx.qtag = h->qtag++;
+    LF_TRY(lf_prof_begin(h, LF_K_REFRESH));
+    hipLaunchKernelGGL(k_refresh, dim3(g.refresh), dim3(GT), 0, st, cx, qs);
+    LF_TRY(lf_prof_end(h, LF_K_REFRESH, 1));
     if (g.eval > 0) {
         LF_TRY(lf_prof_begin(h, LF_K_EVAL));
-        hipLaunchKernelGGL(k_eval, dim3(g.eval), dim3(EW * WAVE), 0, st, cx, qs);
+        if (qs.lists) hipLaunchKernelGGL(k_eval, dim3(g.eval), dim3(EW * WAVE), 0, st, cx, qs);
+        else hipLaunchKernelGGL(k_eval_whole, dim3(g.eval), dim3(EW * WAVE), 0, st, cx, qs);
         LF_TRY(lf_prof_end(h, LF_K_EVAL, 1));
     }
     if (g.big > 0) {
@@ -2026,10 +2253,7 @@ int lf_launch_queue(lf_handle *h, Ctx &cx, const QStep &qs, const QGrids &g)
         hipLaunchKernelGGL(k_eval_big, dim3(g.big), dim3(GT), 0, st, cx, qs);
         LF_TRY(lf_prof_end(h, LF_K_EVAL_BIG, 1));
     }
-    if (g.fin > 0) {
-        LF_TRY(lf_prof_begin(h, LF_K_TAB_FINAL));
-        hipLaunchKernelGGL(k_big_final, dim3(g.fin), dim3(256), 0, st, cx, qs);
-        LF_TRY(lf_prof_end(h, LF_K_TAB_FINAL, 1));
+    if (g.tie > 0) {
         LF_TRY(lf_prof_begin(h, LF_K_TAB_TIE));
         hipLaunchKernelGGL(k_big_tie, dim3(g.tie), dim3(GT), 0, st, cx, qs);
         LF_TRY(lf_prof_end(h, LF_K_TAB_TIE, 1));
@@ -2037,30 +2261,24 @@ int lf_launch_queue(lf_handle *h, Ctx &cx, const QStep &qs, const QGrids &g)
     LF_TRY(lf_prof_begin(h, LF_K_APPLY_EDIT));
     hipLaunchKernelGGL(k_apply, dim3(g.apply), dim3(256), 0, st, cx, qs);
     LF_TRY(lf_prof_end(h, LF_K_APPLY_EDIT, 1));
-    LF_TRY(lf_prof_begin(h, LF_K_REFRESH));
-    hipLaunchKernelGGL(k_refresh, dim3(g.refresh), dim3(256), 0, st, cx, qs);
-    LF_TRY(lf_prof_end(h, LF_K_REFRESH, 1));
     h->prof.chunks++;
     h->prof.node_evals += qs.clen;
     return LF_OK;
 }
 
-// One queue of each of nm graphs: four grids (k_big_final and k_big_tie share one), each
-// block finding its graph from dboff (LF_MULTI_GRIDS arrays of first-block offsets, at
-// stride cap + 1, each with nm + 1 entries); total[i] = blocks of grid i.
+// One queue of each of nm graphs: four grids, each block finding its graph from dboff
+// (LF_MULTI_GRIDS arrays of first-block offsets, at stride cap + 1, each with nm + 1
+// entries); total[i] = blocks of grid i.
 int lf_launch_multi(hipStream_t st, const Member *dmem, const int *dboff, int cap, int nm, const int *total)
 {
     const int *o = dboff;
-    if (total[0] > 0) hipLaunchKernelGGL(k_eval_big_multi, dim3(total[0]), dim3(GT), 0, st, dmem, o, nm);
+    if (total[0] > 0) hipLaunchKernelGGL(k_refresh_multi, dim3(total[0]), dim3(GT), 0, st, dmem, o, nm);
     o += cap + 1;
-    if (total[1] > 0) {
-        hipLaunchKernelGGL(k_big_final_multi, dim3(total[1]), dim3(256), 0, st, dmem, o, nm);
-        hipLaunchKernelGGL(k_big_tie_multi, dim3(total[1]), dim3(256), 0, st, dmem, o, nm);
-    }
+    if (total[1] > 0) hipLaunchKernelGGL(k_eval_big_multi, dim3(total[1]), dim3(GT), 0, st, dmem, o, nm);
     o += cap + 1;
-    if (total[2] > 0) hipLaunchKernelGGL(k_apply_multi, dim3(total[2]), dim3(256), 0, st, dmem, o, nm);
+    if (total[2] > 0) hipLaunchKernelGGL(k_big_tie_multi, dim3(total[2]), dim3(GT), 0, st, dmem, o, nm);
     o += cap + 1;
-    if (total[3] > 0) hipLaunchKernelGGL(k_refresh_multi, dim3(total[3]), dim3(256), 0, st, dmem, o, nm);
+    if (total[3] > 0) hipLaunchKernelGGL(k_apply_multi, dim3(total[3]), dim3(256), 0, st, dmem, o, nm);
     return hipGetLastError() == hipSuccess ? LF_OK : LF_EDEVICE;
 }
 
@@ -2068,16 +2286,23 @@ int lf_launch_multi(hipStream_t st, const Member *dmem, const int *dboff, int ca
 // building a graph of one batch step.
 void lf_multi_kernels(const void **fn, int *grid, int *block)
 {
-    const void *f[LF_MULTI_KERNELS] = {(const void *)k_eval_big_multi, (const void *)k_big_final_multi,
-                                       (const void *)k_big_tie_multi, (const void *)k_apply_multi,
-                                       (const void *)k_refresh_multi};
-    const int gr[LF_MULTI_KERNELS] = {0, 1, 1, 2, 3};
-    const int b[LF_MULTI_KERNELS] = {GT, 256, 256, 256, 256};
+    const void *f[LF_MULTI_KERNELS] = {(const void *)k_refresh_multi, (const void *)k_eval_big_multi,
+                                       (const void *)k_big_tie_multi, (const void *)k_apply_multi};
+    const int b[LF_MULTI_KERNELS] = {GT, GT, GT, 256};
     for (int i = 0; i < LF_MULTI_KERNELS; i++) {
         fn[i] = f[i];
-        grid[i] = gr[i];
+        grid[i] = i;
         block[i] = b[i];
     }
+}
+
+// the re-sums of the last queue applied (no next queue to gather)
+static void refresh_alone(lf_handle *h)
+{
+    QStep qs;
+    memset(&qs, 0, sizeof qs);
+    qs.rb = h->refresh_blocks;
+    hipLaunchKernelGGL(k_refresh, dim3(qs.rb), dim3(GT), 0, h->stream, lf_ctx(h), qs);
 }
 
 // End of an iteration: counters reset, degenerate communities removed, exact score.
@@ -2085,13 +2310,16 @@ void lf_multi_kernels(const void **fn, int *grid, int *block)
 // the membership lines back into the slot layout (a batch member leaving mid-iteration)
 int lf_lines_back(lf_handle *h)
 {
-    if (h->n > 0 && h->lines)
+    if (h->n > 0 && h->lines) {
+        refresh_alone(h);
         hipLaunchKernelGGL(k_line_back, dim3(grid_for(h->n, 256)), dim3(256), 0, h->stream, lf_ctx(h));
+    }
     return hipGetLastError() == hipSuccess ? LF_OK : LF_EDEVICE;
 }
 
 static int finish_enqueue_plain(lf_handle *h)
 {
+    refresh_alone(h);
     hipLaunchKernelGGL(k_queue_reset, dim3(1), dim3(WAVE), 0, h->stream, lf_ctx(h));
     if (h->n > 0) hipLaunchKernelGGL(k_line_back, dim3(grid_for(h->n, 256)), dim3(256), 0, h->stream, lf_ctx(h));
     LF_HIP(h, hipGetLastError());

@@ -114,6 +114,10 @@ struct BuckRes {               // best join and leave of one bucket
     int j, l;
 };
 
+struct ListHdr {               // a flattened node: list entries (own memberships included), own
+    int N, m, d, j;            // memberships, degree, queue position
+};
+
 // decision on a queued node: community joined and left (-1: none), and its slot count when
 // it was evaluated (where a join is appended)
 struct __align__(16) Decision {
@@ -188,6 +192,10 @@ struct Ctx {
     TabVisit *tvis;          // the queue's visit regions
     int *trow;               // the queue's rows
     BuckRes *tres;           // the queue's bucket results
+    // flattened lists of the queue's other nodes (small, medium, then workgroup path)
+    ListHdr *lhdr;
+    long long *lpair;        // community | in-count << 32
+    int *ldeg;               // neighbour's degree, -1: an own membership
     // in-count units of the current iteration (every node's, in node order)
     const UnitRec *unit;
     // re-sum parts
@@ -198,12 +206,11 @@ struct Ctx {
     int stats;               // collect the per-path work counters
 };
 
-// Block roles of k_eval_big: [0, bt) place the table path's visits (a chunk at a time), the
-// next bg blocks evaluate workgroup-path nodes (one node per block at a time), and with fuse
-// the rest are the small and medium blocks of QStep.
+// Larger nodes: bt blocks of k_refresh place the table path's visits (a chunk at a time) and
+// bg flatten workgroup-path nodes (one at a time); k_eval_big has bg blocks that score
+// those and one per bucket of the table path.
 struct BigRoles {
-    int bt, bg;              // blocks per role (table, workgroup)
-    int fuse;                // the small and medium paths are in this launch, not in k_eval
+    int bt, bg;
     int lt, nt;              // table-path list positions of the queue
     int lg, ng;              // workgroup-path list positions
     int c0, nc;              // the queue's chunks [c0, c0 + nc)
@@ -222,6 +229,10 @@ struct QStep {
     BigRoles br;
     long long ub;            // the queue's in-count units: [ub, ub + un)
     int un;
+    int rb;                  // k_refresh: blocks that re-sum the queue before
+    int lists;               // small and medium nodes go through lists (k_refresh gathers them,
+                             // k_eval or, beside larger nodes, k_eval_big scores them);
+                             // else k_eval_whole does both
 };
 
 // One graph's queue in a multi-graph launch.
@@ -232,7 +243,7 @@ struct Member {
 
 // launch grids of one queue's kernels (0 = not launched)
 struct QGrids {
-    int eval, big, fin, tie, apply, refresh;
+    int refresh, eval, big, tie, apply;
 };
 
 struct TmpChunk {
@@ -308,6 +319,10 @@ struct lf_handle {
     int *trow;
     BuckRes *tres;
     long long tvis_cap, trow_cap, tres_cap;
+    ListHdr *lhdr;
+    long long *lpair;
+    int *ldeg;
+    long long lhdr_cap, lpair_cap, ldeg_cap;
     long long *hqoff;        // pinned host: [LF_PATH_COUNT][nq + 1] first list position per
                              // queue, then [4][nq + 1] first table-path chunk, bucket, visit
                              // and row entry per queue, then [nq + 1] first in-count unit
@@ -462,7 +477,7 @@ void lf_queue_params(lf_handle *h, long long k, long long nq, long long qq, bool
 int lf_launch_queue(lf_handle *h, Ctx &cx, const QStep &qs, const QGrids &g);
 int lf_launch_multi(hipStream_t st, const Member *dmem, const int *dboff, int cap, int nm, const int *total);
 #define LF_MULTI_GRIDS 4         // per-step launches of a batch with grids of their own
-#define LF_MULTI_KERNELS 5       // kernels of a batch step (k_big_final and k_big_tie share a grid)
+#define LF_MULTI_KERNELS 4       // kernels of a batch step
 void lf_multi_kernels(const void **fn, int *grid, int *block);
 int lf_iter_finish(lf_handle *h, long long *joins, long long *leaves, long long *live);
 int lf_lines_back(lf_handle *h);          // lines -> slot layout (mid-iteration stop)

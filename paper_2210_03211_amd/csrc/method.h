@@ -177,6 +177,13 @@ __device__ __forceinline__ int wave_incl_scan(int v, int *total)
     return (int)x;
 }
 
+// the sum of the lanes' values, the same on every lane
+__device__ __forceinline__ unsigned wave_sum_u32(unsigned x)
+{
+    DPP_INCLUSIVE(x, op_add);
+    return (unsigned)__builtin_amdgcn_readlane((int)x, WAVE - 1);
+}
+
 // the largest of the lanes' values (unsigned), the same on every lane
 __device__ __forceinline__ unsigned wave_max_u32(unsigned x)
 {
@@ -200,13 +207,19 @@ __device__ __forceinline__ void wave_best(double &bd, int &bc)
 }
 
 // the g-terms of one member of C with in-count i and degree d at sizes s, s+1, s-1
-__device__ __forceinline__ void member_add(int i, int d, int s, X192 &a0, X192 &ap, X192 &am,
-                                           long long &sumi, int &bad)
+// (a 128-bit accumulator holds 255 of them, each at most 1)
+__device__ __forceinline__ void acc_add(X192 &a, u128 t) { x192_add(a, x192_sext128(t)); }
+__device__ __forceinline__ void acc_add(u128 &a, u128 t) { a += t; }
+
+template <class Acc>
+__device__ __forceinline__ void member_add(int i, int d, int s, Acc &a0, Acc &ap, Acc &am, long long &sumi, int &bad)
 {
     sumi += i;
-    x192_add(a0, x192_sext128(fx128(g_term(i, d, s), bad)));
-    x192_add(ap, x192_sext128(fx128(g_term(i, d, s + 1), bad)));
-    x192_add(am, x192_sext128(fx128(g_term(i, d, s - 1), bad)));
+    acc_add(a0, fx128(g_term(i, d, s), bad));
+    __builtin_amdgcn_sched_barrier(0);       // one division at a time: fewer registers, more waves
+    acc_add(ap, fx128(g_term(i, d, s + 1), bad));
+    __builtin_amdgcn_sched_barrier(0);
+    acc_add(am, fx128(g_term(i, d, s - 1), bad));
 }
 
 // exact g-sums of one member y of C (at sizes s, s+1, s-1) if y is still in C
@@ -246,8 +259,8 @@ __device__ __forceinline__ int line_find(const Ctx &cx, const NodeLine &l, int c
 }
 
 // member_terms on the membership lines
-__device__ __forceinline__ void member_terms_line(const Ctx &cx, int y, int C, int s, X192 &a0, X192 &ap,
-                                                  X192 &am, long long &sumi, int &bad)
+__device__ __forceinline__ void member_terms_line(const Ctx &cx, int y, int C, int s, u128 &a0, u128 &ap,
+                                                  u128 &am, long long &sumi, int &bad)
 {
     const NodeLine ly = cx.ln[y];
     int in = 0;
