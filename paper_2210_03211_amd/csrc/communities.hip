@@ -37,7 +37,6 @@
 #include "method.h"
 
 static inline unsigned grid_for(long long n, int block) { return (unsigned)((n + block - 1) / block); }
-static inline unsigned min_u(unsigned a, unsigned b) { return a < b ? a : b; }
 
 // ------------------------------------------------------------------------------------
 // A3: initial clustering
@@ -315,34 +314,52 @@ __global__ void __launch_bounds__(256) k_refresh_list(Ctx cx, int fixed_count)
 // ------------------------------------------------------------------------------------
 // A6: iteration end
 // ------------------------------------------------------------------------------------
-// The iteration-end kernels fold their shared counters per block (a grid of at most
-// END_BLOCKS blocks striding over the range): one atomic per wave on a single address
-// would serialise the launch (about 15 ns each).
-#define END_BLOCKS 2048
+// Per iteration some ten launches, each a single pass: the removal of communities with fewer
+// than two members and the score's partial sums; the memberships that stay, counted per tile of
+// nodes, then copied to the other slot buffer and into the nodes' lines at once; the member
+// lists' capacities, summed per tile and placed; the lists filled; the report.  Shared counters
+// are folded per block: one atomic per wave on a single address would serialise a launch
+// (about 15 ns each).
+// Latency bounds the small graphs (each launch of a 2,000-node graph takes 2 to 12 us), so the
+// count of launches matters there: an iteration's start and end take some 20 launches
+// instead of 63 (300-node job, 17 iterations: 10.2 -> 8.1 ms a run; 120 served jobs 555 -> 420
+// ms).  Gathers and atomics bound the large ones: 4M nodes, 7.3M memberships: 1.1 ms an end, of
+// which 0.41 the copy with its capacity atomics and 0.31 the list fill.
+#define END_TILE 256            // nodes per block: one per thread, so that small graphs spread too
+#define CAP_TILE 1024           // communities per block of the list capacities
+#define END_PARTS 1024          // most blocks of the pass over the communities
 
-__device__ __forceinline__ int block_fold_int(int v, bool take_max)
+// sum of v over the block's 256 threads before this one, and of all
+__device__ __forceinline__ int block_excl_int(int v, int *s_w, int *total)
 {
-    __shared__ int s_part[256 / WAVE];
-    for (int o = WAVE / 2; o > 0; o >>= 1) {
-        const int t = __shfl_xor(v, o, WAVE);
-        v = take_max ? (t > v ? t : v) : v + t;
-    }
-    if ((threadIdx.x & (WAVE - 1)) == 0) s_part[threadIdx.x / WAVE] = v;
+    int wsum;
+    const int incl = wave_incl_scan(v, &wsum);
+    const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x / WAVE;
+    __syncthreads();                        // an earlier round's totals are read
+    if (lane == 0) s_w[wv] = wsum;
     __syncthreads();
-    v = s_part[0];
-    for (int w = 1; w < (int)blockDim.x / WAVE; w++) v = take_max ? (s_part[w] > v ? s_part[w] : v) : v + s_part[w];
-    return v;
+    int off = 0, tot = 0;
+    for (int w = 0; w < 256 / WAVE; w++) {
+        if (w < wv) off += s_w[w];
+        tot += s_w[w];
+    }
+    *total = tot;
+    return off + incl - v;
 }
 
 // communities with fewer than two members are removed: mark them (tflag = 2), zero their
-// statistics, count the live ones
-__global__ void __launch_bounds__(256) k_mark_dead(Ctx cx)
+// statistics; the live ones are counted and their scores summed exactly per block; every
+// community's member list is emptied
+__global__ void __launch_bounds__(256) k_end_mark(Ctx cx, long long *capx, X256 *part)
 {
-    int live = 0;
+    __shared__ X256 s_x[256 / WAVE];
+    __shared__ int s_live[256 / WAVE];
+    X256 acc = x256_zero();
+    int live = 0, bad = 0;
     for (long long c = blockIdx.x * (long long)blockDim.x + threadIdx.x; c < cx.K;
          c += (long long)gridDim.x * blockDim.x) {
         CommRec *r = &cx.cr[c];
-        int s = r->s;
+        const int s = r->s;
         if (s < 2) {
             if (s == 1) cx.tflag[c] = 2;
             r->s = 0;
@@ -351,65 +368,172 @@ __global__ void __launch_bounds__(256) k_mark_dead(Ctx cx)
             for (int k = 0; k < 5; k++) { r->Sp[k] = 0; r->Sm[k] = 0; }
         } else {
             live++;
+            x256_add(acc, x256_from_double(r->W, bad));
         }
         cx.cm_len[c] = 0;
         cx.ovf_flag[c] = 0;
+        capx[c] = 0;
     }
-    live = block_fold_int(live, false);
-    if (threadIdx.x == 0 && live) atomicAdd(&cx.ctr->live, live);
-}
-
-// drop removed communities from every node's slots (four slots and their flags per round
-// trip; a kept slot moves only to a position already read); next capacity = count + 1
-__global__ void __launch_bounds__(256) k_drop_dead(Ctx cx, long long *newcap)
-{
-    int mx = 0;
-    for (long long x = blockIdx.x * (long long)blockDim.x + threadIdx.x; x < cx.n;
-         x += (long long)gridDim.x * blockDim.x) {
-        NodeHdr hx = cx.nh[x];
-        Slot *xs = cx.slot + hx.off;
-        int w = 0;
-        for (int t0 = 0; t0 < hx.cnt; t0 += 4) {
-            Slot sl[4];
-            bool keep[4];
-#pragma unroll
-            for (int q = 0; q < 4; q++)
-                if (t0 + q < hx.cnt) sl[q] = xs[t0 + q];
-#pragma unroll
-            for (int q = 0; q < 4; q++) keep[q] = t0 + q < hx.cnt && cx.tflag[sl[q].comm] != 2;
-#pragma unroll
-            for (int q = 0; q < 4; q++)
-                if (keep[q]) xs[w++] = sl[q];
+    if (bad) atomicOr(&cx.ctr->error, LF_DEVERR_INEXACT);
+    acc = wave_sum_x256(acc);
+    live = wave_sum_int(live);
+    const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x / WAVE;
+    if (lane == 0) {
+        s_x[wv] = acc;
+        s_live[wv] = live;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < 256 / WAVE; w++) {
+            x256_add(acc, s_x[w]);
+            live += s_live[w];
         }
-        cx.nh[x].cnt = w;
-        newcap[x] = w + 1;
-        mx = w > mx ? w : mx;
+        part[blockIdx.x] = acc;
+        if (live) atomicAdd(&cx.ctr->live, live);
     }
-    mx = block_fold_int(mx, true);
-    if (threadIdx.x == 0) atomicMax(&cx.ctr->max_mem, mx);
 }
 
-__global__ void k_clear_dead(Ctx cx)
+// a membership that stays: not left in this iteration, its community not removed
+__device__ __forceinline__ bool stays(const Ctx &cx, int c) { return c >= 0 && cx.tflag[c] != 2; }
+
+__device__ __forceinline__ int count_staying(const Ctx &cx, const NodeLine &l)
 {
-    long long c = blockIdx.x * (long long)blockDim.x + threadIdx.x;
-    if (c >= cx.K) return;
-    cx.tflag[c] = 0;
+    int w = 0;
+    if (l.off < 0) {
+#pragma unroll
+        for (int t = 0; t < LINE_SLOTS; t++)
+            if (t < l.cnt && stays(cx, l.s[t].comm)) w++;
+    } else {
+        for (int t0 = 0; t0 < l.cnt; t0 += 4) {        // four slots and their flags per round trip
+            int c[4];
+#pragma unroll
+            for (int q = 0; q < 4; q++) c[q] = t0 + q < l.cnt ? cx.slot[l.off + t0 + q].comm : -1;
+#pragma unroll
+            for (int q = 0; q < 4; q++) w += stays(cx, c[q]);
+        }
+    }
+    return w;
 }
 
-__global__ void k_copy_slots(Ctx cx, const long long *noff, Slot *dst)
+// slots of the next layout per tile of END_TILE nodes: staying memberships + one free slot each
+__global__ void __launch_bounds__(256) k_end_count(Ctx cx, long long *tsum)
 {
-    long long x = blockIdx.x * (long long)blockDim.x + threadIdx.x;
-    if (x > cx.n) return;
-    if (x == cx.n) { cx.nh[x].off = noff[x]; return; }
-    NodeHdr hx = cx.nh[x];
-    long long o = noff[x];
-    for (int t = 0; t < hx.cnt; t++) dst[o + t] = cx.slot[hx.off + t];
-    Slot e = {-1, 0};
-    dst[o + hx.cnt] = e;
-    cx.nh[x].off = o;
+    __shared__ int s_w[256 / WAVE];
+    const long long x = (long long)blockIdx.x * END_TILE + threadIdx.x;
+    const int v = x < cx.n ? count_staying(cx, cx.ln[x]) + 1 : 0;
+    int tot;
+    (void)block_excl_int(v, s_w, &tot);
+    if (threadIdx.x == 0) tsum[blockIdx.x] = tot;
 }
 
-// exact partition score: per-block X256 partials, folded by one wave
+// the staying memberships at their new place (dst), the nodes' headers and lines, and every
+// community's room for joiners (sum of member degrees)
+__global__ void __launch_bounds__(256) k_end_copy(Ctx cx, const long long *toff, Slot *dst, long long *capx,
+                                                  unsigned char *mc8)
+{
+    __shared__ int s_w[256 / WAVE];
+    const long long base = toff[blockIdx.x];
+    const long long x = (long long)blockIdx.x * END_TILE + threadIdx.x;
+    NodeLine l;
+    l.cnt = 0;
+    l.off = -1;
+    if (x < cx.n) l = cx.ln[x];
+    const int w = count_staying(cx, l);
+    int tot;
+    const long long o = base + block_excl_int(x < cx.n ? w + 1 : 0, s_w, &tot);
+    if (x == cx.n) cx.nh[x].off = o;
+    if (x >= cx.n) return;
+    NodeLine ln;
+    ln.cnt = w;
+    ln.deg = l.deg;
+    ln.off = w + 1 <= LINE_SLOTS ? -1 : o;
+#pragma unroll
+    for (int t = 0; t < LINE_SLOTS; t++) ln.s[t] = Slot{-1, 0};
+    int k = 0;
+    for (int t0 = 0; t0 < l.cnt; t0 += LINE_SLOTS) {     // LINE_SLOTS slots and flags per round trip
+        Slot sl[LINE_SLOTS];
+        bool st[LINE_SLOTS];
+#pragma unroll
+        for (int q = 0; q < LINE_SLOTS; q++)
+            sl[q] = l.off < 0 ? l.s[q] : t0 + q < l.cnt ? cx.slot[l.off + t0 + q] : Slot{-1, 0};
+#pragma unroll
+        for (int q = 0; q < LINE_SLOTS; q++) st[q] = t0 + q < l.cnt && stays(cx, sl[q].comm);
+#pragma unroll
+        for (int q = 0; q < LINE_SLOTS; q++)
+            if (st[q]) {
+                dst[o + k] = sl[q];
+                atomicAdd((unsigned long long *)&capx[sl[q].comm], (unsigned long long)l.deg);
+#pragma unroll
+                for (int u = 0; u < LINE_SLOTS; u++)     // (register indices known at compile time)
+                    if (u == k && ln.off < 0) ln.s[u] = sl[q];
+                k++;
+            }
+    }
+    dst[o + w] = Slot{-1, 0};
+    NodeHdr hd;
+    hd.off = o;
+    hd.cnt = w;
+    hd.deg = l.deg;
+    cx.nh[x] = hd;
+    cx.ln[x] = ln;
+    mc8[x] = w < 255 ? (unsigned char)w : 255;
+}
+
+// member-list capacity of a community: its members plus room for joiners
+__device__ __forceinline__ long long list_cap(const Ctx &cx, const long long *capx, long long c)
+{
+    const long long ex = capx[c];
+    return cx.cr[c].s + (ex < cx.n ? ex : cx.n);
+}
+
+__global__ void __launch_bounds__(256) k_cap_sum(Ctx cx, const long long *capx, long long *tsum)
+{
+    __shared__ long long s_w[256 / WAVE];
+    long long v = 0;
+#pragma unroll
+    for (int i = 0; i < CAP_TILE / 256; i++) {
+        const long long c = (long long)blockIdx.x * CAP_TILE + i * 256 + threadIdx.x;
+        if (c < cx.K) v += list_cap(cx, capx, c);
+    }
+    v = wave_sum_i64(v);
+    if ((threadIdx.x & (WAVE - 1)) == 0) s_w[threadIdx.x / WAVE] = v;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < 256 / WAVE; w++) v += s_w[w];
+        tsum[blockIdx.x] = v;
+    }
+}
+
+// list offsets (K + 1); the removed marks are cleared on the way
+__global__ void __launch_bounds__(256) k_cap_place(Ctx cx, const long long *capx, const long long *toff,
+                                                   long long *cm_off)
+{
+    __shared__ long long s_w[256 / WAVE];
+    const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x / WAVE;
+    long long run = toff[blockIdx.x];
+    for (int i = 0; i < CAP_TILE / 256; i++) {
+        const long long c = (long long)blockIdx.x * CAP_TILE + i * 256 + threadIdx.x;
+        const long long v = c < cx.K ? list_cap(cx, capx, c) : 0;
+        long long incl = v;
+        for (int o = 1; o < WAVE; o <<= 1) {
+            const long long t = __shfl_up(incl, o, WAVE);
+            if (lane >= o) incl += t;
+        }
+        __syncthreads();
+        if (lane == WAVE - 1) s_w[wv] = incl;
+        __syncthreads();
+        long long off = run, tot = 0;
+        for (int w = 0; w < 256 / WAVE; w++) {
+            if (w < wv) off += s_w[w];
+            tot += s_w[w];
+        }
+        run += tot;
+        if (c <= cx.K) cm_off[c] = off + incl - v;
+        if (c < cx.K) cx.tflag[c] = 0;
+    }
+}
+
+// exact partition score: per-block X256 partials (the fold is k_score_fold's or the report's)
 __global__ void __launch_bounds__(256) k_score_partials(const CommRec *cr, int K, X256 *part, int *err)
 {
     __shared__ X256 s_w[256 / WAVE];
@@ -431,7 +555,7 @@ __global__ void __launch_bounds__(256) k_score_partials(const CommRec *cr, int K
     }
 }
 
-// everything an iteration end reports to the host, gathered into one record
+// everything an iteration end reports to the host, written to its pinned record
 #define REP_SLOTS 0
 #define REP_MEMBERS 1
 #define REP_SCORE 2
@@ -439,13 +563,17 @@ __global__ void __launch_bounds__(256) k_score_partials(const CommRec *cr, int K
 #define REP_LEAVES 4
 #define REP_LIVE 5
 #define REP_ERROR 6
-__global__ void k_end_report(const DevCounters *c, const long long *slots, const long long *members,
-                             const double *score, long long *rep)
+__global__ void __launch_bounds__(WAVE) k_end_report(const DevCounters *c, const long long *slots,
+                                                     const long long *members, const X256 *part, int np,
+                                                     long long *rep)
 {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
+    X256 acc = x256_zero();
+    for (int k = threadIdx.x; k < np; k += WAVE) x256_add(acc, part[k]);
+    acc = wave_sum_x256(acc);
+    if (threadIdx.x != 0) return;
     rep[REP_SLOTS] = *slots;
     rep[REP_MEMBERS] = *members;
-    rep[REP_SCORE] = __double_as_longlong(*score);
+    rep[REP_SCORE] = __double_as_longlong(x256_round(acc));
     rep[REP_JOINS] = (long long)c->joins;
     rep[REP_LEAVES] = (long long)c->leaves;
     rep[REP_LIVE] = c->live;
@@ -520,8 +648,8 @@ void lf_free_partition(lf_handle *h)
                      (void **)&h->tlist, (void **)&h->ovf_node,
                      (void **)&h->ovf_comm, (void **)&h->ovf_flag, (void **)&h->ctr,
                      (void **)&h->part_done, (void **)&h->vbound,
-                     (void **)&h->cls, (void **)&h->cscan, (void **)&h->plist[0], (void **)&h->plist[1],
-                     (void **)&h->plist[2], (void **)&h->plist[3], (void **)&h->prec_all, (void **)&h->pbase};
+                     (void **)&h->cls, (void **)&h->clscnt, (void **)&h->clsbase, (void **)&h->plist_all,
+                     (void **)&h->prec_all, (void **)&h->mc8, (void **)&h->pre};
     for (void **p : ptrs) {
         lf_dev_free(h, *p);
         *p = nullptr;
@@ -531,6 +659,15 @@ void lf_free_partition(lf_handle *h)
     h->cm_cap = 0;
     lf_free_iteration_buffers(h);
     h->graph_version++;
+}
+
+static int alloc_member_lists(lf_handle *h)
+{
+    if (h->cm_node) return LF_OK;
+    const long long want = 2 * h->n + 1024;
+    LF_TRY(lf_dev_alloc(h, (void **)&h->cm_node, sizeof(int) * want));
+    h->cm_cap = want;
+    return LF_OK;
 }
 
 // member lists with capacity for joiners; requires sizes and slots to be current.  Queued
@@ -550,11 +687,7 @@ static int rebuild_member_lists_async(lf_handle *h)
     if (n > 0) hipLaunchKernelGGL(k_member_extra, dim3(grid_for(n, BS)), dim3(BS), 0, st, h->nh, cx.slot, n, capx);
     if (K > 0) hipLaunchKernelGGL(k_member_cap, dim3(grid_for(K, BS)), dim3(BS), 0, st, capx, h->cr, K, n);
     LF_TRY(lf_exclusive_scan_i64(h, capx, h->cm_off, K + 1));
-    if (!h->cm_node) {
-        long long want = 2 * n + 1024;
-        LF_TRY(lf_dev_alloc(h, (void **)&h->cm_node, sizeof(int) * want));
-        h->cm_cap = want;
-    }
+    LF_TRY(alloc_member_lists(h));
     LF_TRY(lf_zero(h, h->cm_len, sizeof(int) * (K > 0 ? K : 1)));
     if (n > 0)
         hipLaunchKernelGGL(k_member_fill, dim3(grid_for(n, BS)), dim3(BS), 0, st, h->nh, cx.slot, n, K, h->cm_off,
@@ -727,11 +860,17 @@ static int alloc_partition_state(lf_handle *h, long long K, long long slots)
     LF_TRY(lf_dev_alloc(h, (void **)&h->part_done, sizeof(int) * KK));
     LF_TRY(lf_dev_alloc(h, (void **)&h->vbound, sizeof(long long) * (nn + 1)));
     LF_TRY(lf_dev_alloc(h, (void **)&h->cls, sizeof(int) * nn));
-    LF_TRY(lf_dev_alloc(h, (void **)&h->cscan, sizeof(long long) * (nn + 1)));
-    for (int k = 0; k < LF_PATH_COUNT; k++) LF_TRY(lf_dev_alloc(h, (void **)&h->plist[k], sizeof(int) * nn));
+    const size_t ct = LF_PATH_COUNT * (nn / 1024 + 2) + 1;   // counts per path and tile of the path lists
+    LF_TRY(lf_dev_alloc(h, (void **)&h->clscnt, sizeof(int) * ct));
+    LF_TRY(lf_dev_alloc(h, (void **)&h->clsbase, sizeof(long long) * ct));
+    LF_TRY(lf_dev_alloc(h, (void **)&h->plist_all, sizeof(int) * nn));
     LF_TRY(lf_dev_alloc(h, (void **)&h->prec_all, sizeof(NodeRec) * nn));
-    LF_TRY(lf_dev_alloc(h, (void **)&h->pbase, sizeof(long long) * (LF_PATH_COUNT + 1)));
-    for (int k = 0; k < LF_PATH_COUNT; k++) h->prec[k] = h->prec_all;
+    for (int k = 0; k < LF_PATH_COUNT; k++) {
+        h->prec[k] = h->prec_all;
+        h->plist[k] = h->plist_all;
+    }
+    LF_TRY(lf_dev_alloc(h, (void **)&h->mc8, nn));
+    LF_TRY(lf_dev_alloc(h, (void **)&h->pre, sizeof(int) * nn));
     LF_TRY(lf_dev_alloc(h, (void **)&h->ovf_node, sizeof(int) * nn));
     LF_TRY(lf_dev_alloc(h, (void **)&h->ovf_comm, sizeof(int) * nn));
     LF_HIP(h, hipMemsetAsync(h->cr, 0, sizeof(CommRec) * KK, st));
@@ -831,18 +970,22 @@ int lf_iteration_end_enqueue(lf_handle *h)
     const int BS = 256;
     long long n = h->n;
     int K = h->K;
-    Ctx cx = lf_ctx(h);
-    LF_TRY(lf_zero(h, &h->ctr->live, sizeof(int) * 2));   // live, max_mem
-    LF_TRY(lf_zero(h, &h->ctr->ovf_cnt, sizeof(int)));
-    if (K > 0) hipLaunchKernelGGL(k_mark_dead, dim3(min_u(grid_for(K, BS), END_BLOCKS)), dim3(BS), 0, st, cx);
-    long long *newcap = nullptr, *noff = nullptr;
-    LF_TRY(lf_tmp_alloc(h, (void **)&newcap, sizeof(long long) * (n + 1)));
-    LF_TRY(lf_tmp_alloc(h, (void **)&noff, sizeof(long long) * (n + 1)));
-    if (n > 0)
-        hipLaunchKernelGGL(k_drop_dead, dim3(min_u(grid_for(n, BS), END_BLOCKS)), dim3(BS), 0, st, cx, newcap);
-    if (K > 0) hipLaunchKernelGGL(k_clear_dead, dim3(grid_for(K, BS)), dim3(BS), 0, st, cx);
-    LF_TRY(lf_zero(h, newcap + n, sizeof(long long)));
-    LF_TRY(lf_exclusive_scan_i64(h, newcap, noff, n + 1));
+    const Ctx cx = lf_ctx(h);
+    const long long nt = n / END_TILE + 1, kt = K / CAP_TILE + 1;       // tiles (position n and id K included)
+    int np = (int)grid_for(K, BS);
+    if (np > END_PARTS) np = END_PARTS;
+    if (np < 1) np = 1;
+    long long *capx = nullptr, *nsum = nullptr, *noff = nullptr, *ksum = nullptr, *koff = nullptr;
+    X256 *part = nullptr;
+    LF_TRY(lf_tmp_alloc(h, (void **)&capx, sizeof(long long) * (K + 1)));
+    LF_TRY(lf_tmp_alloc(h, (void **)&nsum, sizeof(long long) * nt));
+    LF_TRY(lf_tmp_alloc(h, (void **)&noff, sizeof(long long) * nt));
+    LF_TRY(lf_tmp_alloc(h, (void **)&ksum, sizeof(long long) * kt));
+    LF_TRY(lf_tmp_alloc(h, (void **)&koff, sizeof(long long) * kt));
+    LF_TRY(lf_tmp_alloc(h, (void **)&part, sizeof(X256) * np));
+    hipLaunchKernelGGL(k_end_mark, dim3(np), dim3(BS), 0, st, cx, capx, part);
+    hipLaunchKernelGGL(k_end_count, dim3((unsigned)nt), dim3(BS), 0, st, cx, nsum);
+    LF_TRY(lf_exclusive_scan_i64(h, nsum, noff, nt));
     // the new layout holds at most the current one's entries plus one per node (a node's
     // count grows only into its free slot), so the copy needs no wait for its size
     int other = 1 - h->cur;
@@ -854,18 +997,20 @@ int lf_iteration_end_enqueue(lf_handle *h)
         LF_TRY(lf_dev_alloc(h, (void **)&h->slot[other], sizeof(Slot) * want));
         h->slot_capb[other] = want;
     }
-    hipLaunchKernelGGL(k_copy_slots, dim3(grid_for(n + 1, BS)), dim3(BS), 0, st, cx, noff, h->slot[other]);
+    hipLaunchKernelGGL(k_end_copy, dim3((unsigned)nt), dim3(BS), 0, st, cx, (const long long *)noff, h->slot[other],
+                       capx, h->mc8);
     h->cur = other;
-    LF_TRY(rebuild_member_lists_async(h));
-    double *dw = nullptr;
-    LF_TRY(lf_tmp_alloc(h, (void **)&dw, sizeof(double)));
-    LF_TRY(partition_score_async(h, dw));
+    hipLaunchKernelGGL(k_cap_sum, dim3((unsigned)kt), dim3(BS), 0, st, cx, (const long long *)capx, ksum);
+    LF_TRY(lf_exclusive_scan_i64(h, ksum, koff, kt));
+    hipLaunchKernelGGL(k_cap_place, dim3((unsigned)kt), dim3(BS), 0, st, cx, (const long long *)capx,
+                       (const long long *)koff, h->cm_off);
+    LF_TRY(alloc_member_lists(h));
+    hipLaunchKernelGGL(k_member_fill, dim3(grid_for(n, BS)), dim3(BS), 0, st, h->nh, h->slot[other], n, K, h->cm_off,
+                       h->cm_len, h->cm_node, h->cm_cap);
     // the host's one wait of the iteration end: every value it needs in one pinned record
-    long long *drep = nullptr;
-    LF_TRY(lf_tmp_alloc(h, (void **)&drep, sizeof(long long) * 16));
-    hipLaunchKernelGGL(k_end_report, dim3(1), dim3(1), 0, st, (const DevCounters *)h->ctr, noff + n,
-                       (const long long *)h->cm_off + K, (const double *)dw, drep);
-    LF_HIP(h, hipMemcpyAsync(h->hrep, drep, sizeof(long long) * 16, hipMemcpyDeviceToHost, st));
+    hipLaunchKernelGGL(k_end_report, dim3(1), dim3(WAVE), 0, st, (const DevCounters *)h->ctr,
+                       (const long long *)&h->nh[n].off, (const long long *)h->cm_off + K, (const X256 *)part, np,
+                       h->hrep);
     LF_HIP(h, hipGetLastError());
     return LF_OK;
 }

@@ -23,7 +23,6 @@
 //                    re-sum planning (a thread per queued node) beside the in-count
 //                    changes around the moved nodes (a wave per in-count unit)
 // After the last queue k_refresh runs once more, for the re-sums alone.
-// k_queue_reset clears the queue counters at the start and the end of an iteration.
 //
 // Every sum is exact (fixed point), so none of the launch shapes above can change a bit
 // of the result.
@@ -38,16 +37,6 @@
 #define MACC 19         // digit counters per multi-part community (3 x 6 digits, in-sum)
 
 static inline unsigned grid_for(long long n, int block) { return (unsigned)((n + block - 1) / block); }
-
-// reset the counters of a queue (at the start and the end of an iteration)
-__global__ void k_queue_reset(Ctx cx)
-{
-    if (threadIdx.x == 0) {
-        DevCounters *c = cx.ctr;
-        c->parts_total = 0;
-        c->mslots = 0;
-    }
-}
 
 // ------------------------------------------------------------------------------------
 // evaluation, wave path
@@ -1474,16 +1463,30 @@ QUEUE_KERNELS(k_refresh, GT, StepLds, body_refresh)
 // chosen from B always fits.  vbound[x] = B + own + 1 bounds x's distinct table keys.
 // NB_NODES consecutive nodes per wave: their neighbour ranges are walked as one flattened
 // range (most nodes have far fewer than 64 neighbours), each lane finding its node in the
-// wave's range starts, and the per-node sums collect in LDS.
+// wave's range starts, and the per-node sums collect in LDS.  A neighbour's membership count
+// comes from one byte per node (mc8, 255: look in the node's header), an array that the
+// caches hold where the headers do not (70M gathers on the 4M-node social-shaped graph: 643
+// us a pass against 1,360 from the headers), and the neighbours earlier in the order are
+// counted once per clustering (FIRST) and kept.
 #define NB_NODES 16
-__global__ void __launch_bounds__(256) k_node_bounds(Ctx cx, long long *vbound, int *cls, int wcap, int mcap,
-                                                     int gcap)
+template <bool FIRST>
+__global__ void __launch_bounds__(256) k_node_bounds(Ctx cx, const unsigned char *mc8, int *pre, long long *vbound,
+                                                     int *cls, int wcap, int mcap, int gcap)
 {
     __shared__ long long s_start[256 / WAVE][NB_NODES + 1];
     __shared__ long long s_rb[256 / WAVE][NB_NODES];
     __shared__ unsigned long long s_v[256 / WAVE][NB_NODES];
     __shared__ unsigned s_pre[256 / WAVE][NB_NODES];
     __shared__ int s_rx[256 / WAVE][NB_NODES];
+    if (blockIdx.x == 0 && threadIdx.x == 0) {          // the iteration's counters
+        DevCounters *c = cx.ctr;
+        c->joins = 0;
+        c->leaves = 0;
+        c->parts_total = 0;
+        c->mslots = 0;
+        c->ovf_cnt = 0;
+        c->live = 0;
+    }
     const int wv = threadIdx.x / WAVE, lane = threadIdx.x & (WAVE - 1);
     const long long x0 = (blockIdx.x * (long long)(blockDim.x / WAVE) + wv) * NB_NODES;
     if (x0 >= cx.n) return;                 // uniform over the wave; only wave-level syncs below
@@ -1518,15 +1521,19 @@ __global__ void __launch_bounds__(256) k_node_bounds(Ctx cx, long long *vbound, 
         }
         const long long e = s_rb[wv][lo] + (f - s_start[wv][lo]);
         const int y = cx.col[e];
-        const int ry = cx.col_rank[e];
-        atomicAdd(&s_v[wv][lo], (unsigned long long)cx.nh[y].cnt);
-        if (ry < s_rx[wv][lo]) atomicAdd(&s_pre[wv][lo], 1u);
+        unsigned c = mc8[y];
+        if (c == 255) c = (unsigned)cx.nh[y].cnt;
+        atomicAdd(&s_v[wv][lo], (unsigned long long)c);
+        if (FIRST && cx.col_rank[e] < s_rx[wv][lo]) atomicAdd(&s_pre[wv][lo], 1u);
     }
     WAVE_SYNC();
     if (lane < nn) {
         const long long x = x0 + lane;
         NodeHdr hx = cx.nh[x];
-        const long long B = (long long)s_v[wv][lane] + s_pre[wv][lane], M = hx.cnt, dd = hx.deg;
+        int before;
+        if (FIRST) pre[x] = before = (int)s_pre[wv][lane];
+        else before = pre[x];
+        const long long B = (long long)s_v[wv][lane] + before, M = hx.cnt, dd = hx.deg;
         vbound[x] = B + M + 1;
         int c = LF_PATH_TABLE;
         if (M <= MXCAP) {
@@ -1538,46 +1545,85 @@ __global__ void __launch_bounds__(256) k_node_bounds(Ctx cx, long long *vbound, 
     }
 }
 
-// flags[r] = (cls[r] == c) for the scan that places path c's nodes; flags[n] = 0
-__global__ void k_class_flags(const int *cls, int c, long long *flags, long long n)
+// The path lists (ascending order positions, path after path): every tile of CLS_TILE positions
+// counts its nodes per path (cnt[path][tile], a last entry of 0), one scan of those counts
+// gives each tile's first list position per path, and the tiles place their nodes with their
+// records and write the queues' first list positions.
+#define CLS_ITEMS 4         // small tiles, so that small graphs spread over several blocks too
+#define CLS_TILE (256 * CLS_ITEMS)
+
+// a tile's counts per path, packed 16 bits each, before this thread's CLS_ITEMS positions
+__device__ __forceinline__ unsigned long long class_prefix(unsigned long long v, unsigned long long *s_w,
+                                                           unsigned long long *total)
 {
-    long long r = blockIdx.x * (long long)blockDim.x + threadIdx.x;
-    if (r < n) flags[r] = cls[r] == c ? 1 : 0;
-    else if (r == n) flags[r] = 0;
+    const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x / WAVE;
+    unsigned long long incl = v;
+    for (int o = 1; o < WAVE; o <<= 1) {
+        const unsigned long long t = (unsigned long long)__shfl_up((long long)incl, o, WAVE);
+        if (lane >= o) incl += t;
+    }
+    if (lane == WAVE - 1) s_w[wv] = incl;
+    __syncthreads();
+    unsigned long long off = 0, tot = 0;
+    for (int w = 0; w < 256 / WAVE; w++) {
+        const unsigned long long t = s_w[w];
+        if (w < wv) off += t;
+        tot += t;
+    }
+    *total = tot;
+    return off + incl - v;
 }
 
-// path c's list (ascending order positions) with its node records (at pbase[c] of the
-// shared record array), and its first list position per queue
-__global__ void k_class_scatter(const int *cls, int c, const long long *scan, int *list, long long n, int q,
-                                long long nq, long long *qoff, const int *order, const long long *rowptr,
-                                const int *deg, const long long *pbase, NodeRec *prec)
+__global__ void __launch_bounds__(256) k_class_count(const int *cls, long long n, long long ntiles, int *cnt)
 {
-    long long r = blockIdx.x * (long long)blockDim.x + threadIdx.x;
-    if (r < n && cls[r] == c) {
-        const long long i = scan[r];
+    __shared__ unsigned long long s_w[256 / WAVE];
+    const long long r0 = (long long)blockIdx.x * CLS_TILE + threadIdx.x * CLS_ITEMS;
+    unsigned long long v = 0;
+#pragma unroll
+    for (int i = 0; i < CLS_ITEMS; i++)
+        if (r0 + i < n) v += 1ull << (16 * cls[r0 + i]);
+    unsigned long long tot;
+    (void)class_prefix(v, s_w, &tot);
+    if (threadIdx.x < LF_PATH_COUNT)
+        cnt[threadIdx.x * ntiles + blockIdx.x] = (int)((tot >> (16 * threadIdx.x)) & 0xffff);
+    if (blockIdx.x == 0 && threadIdx.x == 0) cnt[LF_PATH_COUNT * ntiles] = 0;
+}
+
+__global__ void __launch_bounds__(256) k_class_place(const int *cls, long long n, long long ntiles,
+                                                     const long long *base, int *list, NodeRec *prec, int q,
+                                                     long long nq, long long *qoff, const int *order,
+                                                     const long long *rowptr, const int *deg)
+{
+    __shared__ unsigned long long s_w[256 / WAVE];
+    const long long r0 = (long long)blockIdx.x * CLS_TILE + threadIdx.x * CLS_ITEMS;
+    int cl[CLS_ITEMS];
+    unsigned long long v = 0;
+#pragma unroll
+    for (int i = 0; i < CLS_ITEMS; i++) {
+        cl[i] = r0 + i < n ? cls[r0 + i] : -1;
+        if (cl[i] >= 0) v += 1ull << (16 * cl[i]);
+    }
+    unsigned long long tot;
+    unsigned long long at = class_prefix(v, s_w, &tot);
+#pragma unroll
+    for (int i = 0; i < CLS_ITEMS; i++) {
+        const long long r = r0 + i;
+        if (r <= n && (r % q == 0 || r == n))          // a queue starts here (the end: after the last)
+            for (int c = 0; c < LF_PATH_COUNT; c++)
+                qoff[c * (nq + 1) + (r == n ? nq : r / q)] =
+                    base[c * ntiles + blockIdx.x] + (long long)((at >> (16 * c)) & 0xffff) - base[c * ntiles];
+        if (cl[i] < 0) continue;
+        const long long p = base[cl[i] * ntiles + blockIdx.x] + (long long)((at >> (16 * cl[i])) & 0xffff);
+        at += 1ull << (16 * cl[i]);
         const int x = order[r];
-        list[i] = (int)r;
-        NodeRec nr;
-        nr.rb = rowptr[x];
-        nr.x = x;
-        nr.d = deg[x];
-        prec[pbase[c] + i] = nr;
+        list[p] = (int)r;
+        prec[p] = NodeRec{rowptr[x], x, deg[x]};
     }
-    if (r <= nq) {
-        long long p = r * q < n ? r * q : n;
-        qoff[r] = scan[p];
-    }
-}
-
-// pbase[c + 1] = pbase[c] + the number of path-c nodes (scan[n])
-__global__ void k_path_base(const long long *scan, long long n, int c, long long *pbase)
-{
-    if (threadIdx.x == 0 && blockIdx.x == 0) pbase[c + 1] = pbase[c] + scan[n];
 }
 
 // layout of the table path: for each of its nodes the exclusive sums of chunks, buckets, row
-// entries and visit bounds (one block; the number of nodes is read on the device), and the
-// visits placed so far cleared
+// entries and visit bounds (one block; its list starts at lbase[0] and ends at lbase[ntiles]),
+// and the visits placed so far cleared
 __device__ __forceinline__ long long scan1024(long long v, long long *s_w, long long *total)
 {
     const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x / WAVE;
@@ -1600,12 +1646,13 @@ __device__ __forceinline__ long long scan1024(long long v, long long *s_w, long 
     return off + incl - v;
 }
 
-__global__ void __launch_bounds__(1024) k_table_layout(const int *plist, const int *order, const int *deg,
-                                                       const long long *vbound, const long long *nt_dev, TabPos *tpos,
-                                                       int *tcur)
+__global__ void __launch_bounds__(1024) k_table_layout(const int *list, const long long *lbase, long long ntiles,
+                                                       const int *order, const int *deg, const long long *vbound,
+                                                       TabPos *tpos, int *tcur)
 {
     __shared__ long long s_w[1024 / WAVE];
-    const long long nt = *nt_dev;
+    const int *plist = list + lbase[0];
+    const long long nt = lbase[ntiles] - lbase[0];
     long long vis0 = 0, row0 = 0, ch0 = 0, bu0 = 0;
     for (long long p0 = 0; p0 < nt; p0 += 1024) {
         const long long p = p0 + threadIdx.x;
@@ -1632,14 +1679,27 @@ __global__ void __launch_bounds__(1024) k_table_layout(const int *plist, const i
     if (threadIdx.x == 0) tpos[nt] = TabPos{vis0, row0, (int)ch0, (int)bu0};
 }
 
-// the chunks and buckets of every table-path node (waves stride over the nodes).  Nothing is
-// written if they exceed the buffers (the host then grows them and runs this again).
-__global__ void __launch_bounds__(256) k_table_fill(const int *plist, const int *order, const long long *rowptr,
-                                                    const int *deg, const TabPos *tpos, const long long *nt_dev,
-                                                    ChunkRec *chunk, long long chunk_cap, BuckRec *buck,
-                                                    long long buck_cap)
+// the chunks and buckets of every table-path node (waves stride over the nodes; not written
+// if they exceed the buffers: the host then grows them and runs this again), and the queues'
+// first chunk, bucket, visit, row entry (out: four arrays of nq + 1) and in-count unit
+__global__ void __launch_bounds__(256) k_table_fill(const int *list, const long long *lbase, long long ntiles,
+                                                    const int *order, const long long *rowptr, const int *deg,
+                                                    const TabPos *tpos, ChunkRec *chunk, long long chunk_cap,
+                                                    BuckRec *buck, long long buck_cap, const long long *qoff_t,
+                                                    long long nq, long long *out, const long long *ubase,
+                                                    long long n, int q, long long *out_units)
 {
-    const long long nt = *nt_dev;
+    for (long long k = blockIdx.x * (long long)blockDim.x + threadIdx.x; k <= nq;
+         k += (long long)gridDim.x * blockDim.x) {
+        const TabPos t = tpos[qoff_t[k]];
+        out[k] = t.chunk;
+        out[nq + 1 + k] = t.bucket;
+        out[2 * (nq + 1) + k] = t.vis;
+        out[3 * (nq + 1) + k] = t.row;
+        out_units[k] = ubase[k * q < n ? k * q : n];
+    }
+    const int *plist = list + lbase[0];
+    const long long nt = lbase[ntiles] - lbase[0];
     if (tpos[nt].chunk > chunk_cap || tpos[nt].bucket > buck_cap) return;
     const int lane = threadIdx.x & (WAVE - 1);
     const long long nw = (long long)gridDim.x * (blockDim.x / WAVE);
@@ -1674,21 +1734,9 @@ __global__ void __launch_bounds__(256) k_table_fill(const int *plist, const int 
     }
 }
 
-// first chunk, bucket, visit and row entry of every queue (out: four arrays of nq + 1)
-__global__ void k_queue_table(const TabPos *tpos, const long long *qoff_t, long long nq, long long *out)
-{
-    const long long k = blockIdx.x * (long long)blockDim.x + threadIdx.x;
-    if (k > nq) return;
-    const TabPos t = tpos[qoff_t[k]];
-    out[k] = t.chunk;
-    out[nq + 1 + k] = t.bucket;
-    out[2 * (nq + 1) + k] = t.vis;
-    out[3 * (nq + 1) + k] = t.row;
-}
-
 // the membership lines of an iteration, from the slot layout (nodes whose capacity fits a
 // line keep their memberships inline, the others point into the slot array)
-__global__ void __launch_bounds__(256) k_line_build(Ctx cx)
+__global__ void __launch_bounds__(256) k_line_build(Ctx cx, unsigned char *mc8)
 {
     const long long x = blockIdx.x * (long long)blockDim.x + threadIdx.x;
     if (x >= cx.n) return;
@@ -1705,10 +1753,11 @@ __global__ void __launch_bounds__(256) k_line_build(Ctx cx)
         l.s[t] = sl;
     }
     cx.ln[x] = l;
+    mc8[x] = hx.cnt < 255 ? (unsigned char)hx.cnt : 255;
 }
 
-// back to the slot layout at the end of an iteration (or of a stop within one): the
-// memberships in order without the ones left (holes), and their count
+// back to the slot layout where a batch member leaves within an iteration: the memberships in
+// order without the ones left (holes), and their count
 __global__ void __launch_bounds__(256) k_line_back(Ctx cx)
 {
     const long long x = blockIdx.x * (long long)blockDim.x + threadIdx.x;
@@ -1757,19 +1806,13 @@ __global__ void k_unit_fill(const int *order, const long long *rowptr, const int
     }
 }
 
-__global__ void k_queue_units(const long long *ubase, long long n, int q, long long nq, long long *out)
-{
-    const long long k = blockIdx.x * (long long)blockDim.x + threadIdx.x;
-    if (k <= nq) out[k] = ubase[k * q < n ? k * q : n];
-}
-
 // ------------------------------------------------------------------------------------
 // host side
 // ------------------------------------------------------------------------------------
 void lf_free_iteration_buffers(lf_handle *h)
 {
     void **ptrs[] = {(void **)&h->dec, (void **)&h->unit, (void **)&h->part_rec, (void **)&h->macc,
-                     (void **)&h->cflag, (void **)&h->tpos, (void **)&h->tcur, (void **)&h->tchunk,
+                     (void **)&h->ubase, (void **)&h->tpos, (void **)&h->tcur, (void **)&h->tchunk,
                      (void **)&h->tbuck, (void **)&h->tvis, (void **)&h->trow, (void **)&h->tres,
                      (void **)&h->lhdr, (void **)&h->lpair, (void **)&h->ldeg};
     for (void **p : ptrs) {
@@ -1778,6 +1821,8 @@ void lf_free_iteration_buffers(lf_handle *h)
     }
     h->q_cap = 0;
     h->unit_cap = 0;
+    h->static_ready = false;
+    h->lines_ready = false;
     h->part_cap = 0;
     h->mslot_cap = 0;
     h->tchunk_cap = 0;
@@ -1798,12 +1843,17 @@ void lf_free_iteration_buffers(lf_handle *h)
 #define REP_UNITS(nq) ((long long)(LF_PATH_COUNT + 4) * ((nq) + 1))
 #define REP_LEN(nq) ((long long)(LF_PATH_COUNT + 5) * ((nq) + 1))
 
-static void table_fill(lf_handle *h, const long long *nt_dev)
+static long long class_tiles(long long n) { return (n + CLS_TILE) / CLS_TILE; }   // covers position n
+
+static void table_fill(lf_handle *h, long long q, long long nq)
 {
-    hipLaunchKernelGGL(k_table_fill, dim3(h->fill_grid), dim3(256), 0, h->stream,
-                       (const int *)h->plist[LF_PATH_TABLE], (const int *)h->order, (const long long *)h->rowptr,
-                       (const int *)h->deg, (const TabPos *)h->tpos, nt_dev, h->tchunk, h->tchunk_cap, h->tbuck,
-                       h->tbuck_cap);
+    const long long nt = class_tiles(h->n);
+    const long long *lbase = h->clsbase + LF_PATH_TABLE * nt;
+    hipLaunchKernelGGL(k_table_fill, dim3(h->fill_grid), dim3(256), 0, h->stream, (const int *)h->plist_all, lbase, nt,
+                       (const int *)h->order, (const long long *)h->rowptr, (const int *)h->deg,
+                       (const TabPos *)h->tpos, h->tchunk, h->tchunk_cap, h->tbuck, h->tbuck_cap,
+                       (const long long *)(h->dq + LF_PATH_TABLE * (nq + 1)), nq, h->dq + REP_TABLE(nq),
+                       (const long long *)h->ubase, h->n, (int)q, h->dq + REP_UNITS(nq));
 }
 
 // Start of an iteration, first half: everything the host does not need to see, queued on
@@ -1823,13 +1873,7 @@ static int size_queue_enqueue(lf_handle *h, long long q)
         h->q_cap = q;
         moved = true;
     }
-    // paths of this iteration, then bounds of the table path and in-count items
     const long long nq = (n + q - 1) / q;
-    Ctx cx = lf_ctx(h);
-    hipLaunchKernelGGL(k_node_bounds, dim3(grid_for((n + NB_NODES - 1) / NB_NODES * WAVE, BS)), dim3(BS), 0, st,
-                       cx, h->vbound, h->cls,
-                       h->eval_wave_cap < 2 * VSMALL ? h->eval_wave_cap : 2 * VSMALL, h->eval_med_cap,
-                       h->eval_grp_cap);
     if (h->hqoff_cap < nq + 1) {            // pinned, so the one copy below is truly asynchronous
         // (the last copy into the old buffer was read by the previous iteration start)
         if (h->hqoff) lf_host_release(h->hqoff, sizeof(long long) * h->hqoff_len);
@@ -1851,61 +1895,66 @@ static int size_queue_enqueue(lf_handle *h, long long q)
     if (!h->tpos) {
         h->tchunk_cap = 1024 + n / 16;
         h->tbuck_cap = 1024 + n / 8;
-        LF_TRY(lf_dev_alloc(h, (void **)&h->cflag, sizeof(long long) * (n + 1)));
+        LF_TRY(lf_dev_alloc(h, (void **)&h->ubase, sizeof(long long) * (n + 1)));
         LF_TRY(lf_dev_alloc(h, (void **)&h->tpos, sizeof(TabPos) * (n + 1)));
         LF_TRY(lf_dev_alloc(h, (void **)&h->tcur, sizeof(int) * (n + 1)));
         LF_TRY(lf_dev_alloc(h, (void **)&h->tchunk, sizeof(ChunkRec) * h->tchunk_cap));
         LF_TRY(lf_dev_alloc(h, (void **)&h->tbuck, sizeof(BuckRec) * h->tbuck_cap));
         moved = true;
     }
-    LF_TRY(lf_zero(h, h->pbase, sizeof(long long)));
-    for (int c = 0; c < LF_PATH_COUNT; c++) {
-        hipLaunchKernelGGL(k_class_flags, dim3(grid_for(n + 1, BS)), dim3(BS), 0, st, (const int *)h->cls, c,
-                           h->cflag, n);
-        LF_TRY(lf_exclusive_scan_i64(h, h->cflag, h->cscan, n + 1));
-        long long m = (n > nq ? n : nq) + 1;
-        hipLaunchKernelGGL(k_class_scatter, dim3(grid_for(m, BS)), dim3(BS), 0, st, (const int *)h->cls, c,
-                           (const long long *)h->cscan, h->plist[c], n, (int)q, nq, dq + c * (nq + 1),
-                           (const int *)h->order, (const long long *)h->rowptr, (const int *)h->deg,
-                           (const long long *)h->pbase, h->prec_all);
-        hipLaunchKernelGGL(k_path_base, dim3(1), dim3(1), 0, st, (const long long *)h->cscan, n, c, h->pbase);
+    const long long ucap = n + 2 * h->ne / INB + 1;   // >= sum of ceil(degree / INB)
+    if (ucap > h->unit_cap) {
+        lf_dev_free(h, h->unit);
+        h->unit = nullptr;
+        LF_TRY(lf_dev_alloc(h, (void **)&h->unit, sizeof(UnitRec) * ucap));
+        h->unit_cap = ucap;
+        h->static_ready = false;
+        moved = true;
     }
-    // chunks and buckets of the table-path nodes, all on the device: the table path's length
-    // is the last queue offset of its list
-    const long long *nt_dev = dq + LF_PATH_TABLE * (nq + 1) + nq;
-    hipLaunchKernelGGL(k_table_layout, dim3(1), dim3(1024), 0, st, (const int *)h->plist[LF_PATH_TABLE],
-                       (const int *)h->order, (const int *)h->deg, (const long long *)h->vbound, nt_dev, h->tpos,
-                       h->tcur);
-    unsigned fill_grid = grid_for(n * WAVE, BS);
-    if (fill_grid > 2048) fill_grid = 2048;
-    if (fill_grid < 1) fill_grid = 1;
-    h->fill_grid = fill_grid;
-    table_fill(h, nt_dev);
-    hipLaunchKernelGGL(k_queue_table, dim3(grid_for(nq + 1, BS)), dim3(BS), 0, st, (const TabPos *)h->tpos,
-                       (const long long *)(dq + LF_PATH_TABLE * (nq + 1)), nq, dq + REP_TABLE(nq));
-    // in-count units of every node in node order, and the first unit of every queue
-    {
-        const long long ucap = n + 2 * h->ne / INB + 1;   // >= sum of ceil(degree / INB)
-        if (ucap > h->unit_cap) {
-            lf_dev_free(h, h->unit);
-            h->unit = nullptr;
-            LF_TRY(lf_dev_alloc(h, (void **)&h->unit, sizeof(UnitRec) * ucap));
-            h->unit_cap = ucap;
-            moved = true;
-        }
-        long long *ucnt = nullptr, *ubase = nullptr;
+    if (!h->lines) {
+        LF_TRY(lf_dev_alloc(h, (void **)&h->lines, sizeof(NodeLine) * n));
+        h->lines_ready = false;
+        moved = true;
+    }
+    // the lines follow from the iteration end before; only a fresh partition builds them here
+    if (!h->lines_ready)
+        hipLaunchKernelGGL(k_line_build, dim3(grid_for(n, BS)), dim3(BS), 0, st, lf_ctx(h), h->mc8);
+    h->lines_ready = true;
+    // paths of this iteration
+    const bool first = !h->static_ready;
+    const dim3 bg(grid_for((n + NB_NODES - 1) / NB_NODES * WAVE, BS));
+    const int wcap = h->eval_wave_cap < 2 * VSMALL ? h->eval_wave_cap : 2 * VSMALL;
+    if (first)
+        hipLaunchKernelGGL(k_node_bounds<true>, bg, dim3(BS), 0, st, lf_ctx(h), (const unsigned char *)h->mc8, h->pre,
+                           h->vbound, h->cls, wcap, h->eval_med_cap, h->eval_grp_cap);
+    else
+        hipLaunchKernelGGL(k_node_bounds<false>, bg, dim3(BS), 0, st, lf_ctx(h), (const unsigned char *)h->mc8, h->pre,
+                           h->vbound, h->cls, wcap, h->eval_med_cap, h->eval_grp_cap);
+    const long long nt = class_tiles(n);
+    hipLaunchKernelGGL(k_class_count, dim3((unsigned)nt), dim3(BS), 0, st, (const int *)h->cls, n, nt, h->clscnt);
+    LF_TRY(lf_exclusive_scan_i32_to_i64(h, h->clscnt, h->clsbase, LF_PATH_COUNT * nt + 1));
+    hipLaunchKernelGGL(k_class_place, dim3((unsigned)nt), dim3(BS), 0, st, (const int *)h->cls, n, nt,
+                       (const long long *)h->clsbase, h->plist_all, h->prec_all, (int)q, nq, dq,
+                       (const int *)h->order, (const long long *)h->rowptr, (const int *)h->deg);
+    if (first) {                             // in-count units of every node in node order: they never change
+        long long *ucnt = nullptr;
         LF_TRY(lf_tmp_alloc(h, (void **)&ucnt, sizeof(long long) * (n + 1)));
-        LF_TRY(lf_tmp_alloc(h, (void **)&ubase, sizeof(long long) * (n + 1)));
         hipLaunchKernelGGL(k_unit_counts, dim3(grid_for(n + 1, BS)), dim3(BS), 0, st, (const int *)h->order,
                            (const int *)h->deg, n, ucnt);
-        LF_TRY(lf_exclusive_scan_i64(h, ucnt, ubase, n + 1));
-        if (n > 0)
-            hipLaunchKernelGGL(k_unit_fill, dim3(grid_for(n, BS)), dim3(BS), 0, st, (const int *)h->order,
-                               (const long long *)h->rowptr, (const int *)h->deg, (const long long *)ubase, n, h->unit,
-                               h->unit_cap);
-        hipLaunchKernelGGL(k_queue_units, dim3(grid_for(nq + 1, BS)), dim3(BS), 0, st, (const long long *)ubase, n,
-                           (int)q, nq, dq + REP_UNITS(nq));
+        LF_TRY(lf_exclusive_scan_i64(h, ucnt, h->ubase, n + 1));
+        hipLaunchKernelGGL(k_unit_fill, dim3(grid_for(n, BS)), dim3(BS), 0, st, (const int *)h->order,
+                           (const long long *)h->rowptr, (const int *)h->deg, (const long long *)h->ubase, n, h->unit,
+                           h->unit_cap);
+        h->static_ready = true;
     }
+    // chunks and buckets of the table-path nodes, all on the device, and the queues' positions
+    hipLaunchKernelGGL(k_table_layout, dim3(1), dim3(1024), 0, st, (const int *)h->plist_all,
+                       (const long long *)(h->clsbase + LF_PATH_TABLE * nt), nt, (const int *)h->order,
+                       (const int *)h->deg, (const long long *)h->vbound, h->tpos, h->tcur);
+    unsigned fill_grid = grid_for(n * WAVE, BS);
+    if (fill_grid > 2048) fill_grid = 2048;
+    h->fill_grid = fill_grid;
+    table_fill(h, q, nq);
     // the host's one wait of the iteration start: list offsets per queue and path, the
     // queues' table-path and unit positions
     LF_HIP(h, hipMemcpyAsync(h->hqoff, dq, sizeof(long long) * nrep, hipMemcpyDeviceToHost, st));
@@ -1924,11 +1973,11 @@ static int size_queue_complete(lf_handle *h, long long q)
     const long long nq = (n + q - 1) / q;
     bool moved = h->pending_moved;
     h->second_half_work = false;
-    const long long *nt_dev = h->dq + LF_PATH_TABLE * (nq + 1) + nq;
     {   // the records of path c start after those of the paths before it
         long long base = 0;
         for (int c = 0; c < LF_PATH_COUNT; c++) {
             h->prec[c] = h->prec_all + base;
+            h->plist[c] = h->plist_all + base;
             base += h->hqoff[c * (nq + 1) + nq];
         }
     }
@@ -1958,7 +2007,7 @@ static int size_queue_complete(lf_handle *h, long long q)
             h->tbuck_cap = f * bucks + 1024;
         }
         moved = true;
-        table_fill(h, nt_dev);
+        table_fill(h, q, nq);
         LF_HIP(h, hipGetLastError());
         h->second_half_work = true;
     }
@@ -2015,17 +2064,7 @@ static int size_queue_complete(lf_handle *h, long long q)
 // (after a stream sync or a completed event recorded behind it).
 static int begin_enqueue_plain(lf_handle *h, long long qq)
 {
-    LF_TRY(size_queue_enqueue(h, qq));
-    if (h->n > 0) {
-        if (!h->lines) {
-            LF_TRY(lf_dev_alloc(h, (void **)&h->lines, sizeof(NodeLine) * h->n));
-            h->graph_version++;
-        }
-        hipLaunchKernelGGL(k_line_build, dim3(grid_for(h->n, 256)), dim3(256), 0, h->stream, lf_ctx(h));
-    }
-    LF_TRY(lf_zero(h, &h->ctr->joins, sizeof(unsigned long long) * 2));
-    hipLaunchKernelGGL(k_queue_reset, dim3(1), dim3(WAVE), 0, h->stream, lf_ctx(h));
-    return LF_OK;
+    return size_queue_enqueue(h, qq);
 }
 
 // ---- iteration starts and ends replayed from graphs --------------------------------
@@ -2051,13 +2090,16 @@ static unsigned long long phase_key(lf_handle *h, long long qq, int which)
     unsigned long long k = 14695981039346656037ull;
     Ctx cx = lf_ctx(h);
     cx.qtag = 0;
-    // the path lists' record pointers move with the path counts at every start and are
-    // read only by the queue kernels
-    for (int c = 0; c < LF_PATH_COUNT; c++) cx.prec[c] = nullptr;
+    // the path lists' pointers move with the path counts at every start and are read only by
+    // the queue kernels
+    for (int c = 0; c < LF_PATH_COUNT; c++) {
+        cx.prec[c] = nullptr;
+        cx.plist[c] = nullptr;
+    }
     k = fnv_add(k, &cx, sizeof cx);
     const long long v[] = {which, qq, h->cur, h->profiling, h->tmp_chunk, (long long)h->tmp_off,
                            h->eval_wave_cap, h->eval_med_cap, h->eval_grp_cap,
-                           (long long)h->allocs->size(), (long long)h->tmp_chunks->size()};
+                           h->refresh_blocks, h->static_ready, h->lines_ready, (long long)h->allocs->size(), (long long)h->tmp_chunks->size()};
     k = fnv_add(k, v, sizeof v);
     k = fnv_add(k, h->allocs->data(), sizeof(void *) * h->allocs->size());
     k = fnv_add(k, h->alloc_sizes->data(), sizeof(size_t) * h->alloc_sizes->size());
@@ -2313,6 +2355,7 @@ int lf_lines_back(lf_handle *h)
     if (h->n > 0 && h->lines) {
         refresh_alone(h);
         hipLaunchKernelGGL(k_line_back, dim3(grid_for(h->n, 256)), dim3(256), 0, h->stream, lf_ctx(h));
+        h->lines_ready = false;
     }
     return hipGetLastError() == hipSuccess ? LF_OK : LF_EDEVICE;
 }
@@ -2320,8 +2363,6 @@ int lf_lines_back(lf_handle *h)
 static int finish_enqueue_plain(lf_handle *h)
 {
     refresh_alone(h);
-    hipLaunchKernelGGL(k_queue_reset, dim3(1), dim3(WAVE), 0, h->stream, lf_ctx(h));
-    if (h->n > 0) hipLaunchKernelGGL(k_line_back, dim3(grid_for(h->n, 256)), dim3(256), 0, h->stream, lf_ctx(h));
     LF_HIP(h, hipGetLastError());
     LF_TRY(lf_prof_begin(h, LF_K_ITEREND));
     LF_TRY(lf_iteration_end_enqueue(h));

@@ -144,8 +144,7 @@ struct DevCounters {
     int undecided;                 // initial clustering rounds
     int error;                     // bit flags, see LF_DEVERR_*
     int live;                      // communities with >= 2 members (iteration end)
-    int max_mem;                   // largest membership count (iteration end)
-    int pad[3];
+    int pad[4];
     X256 score;
 };
 
@@ -304,12 +303,17 @@ struct lf_handle {
     long long q_cap;         // capacity of the per-queue arrays
     // table path and work lists (sized per iteration)
     int *cls;                // [n] evaluation path per order position (this iteration)
-    long long *cscan;        // [n + 1] scan scratch of the path lists
-    int *plist[LF_PATH_COUNT];
-    NodeRec *prec_all;       // [n] node records of all path lists, path after path
-    long long *pbase;        // [LF_PATH_COUNT + 1] device: first record of each path
-    NodeRec *prec[LF_PATH_COUNT];   // host-set views into prec_all
-    long long *cflag;        // [n + 1] scan scratch of the path lists
+    int *clscnt;             // [path][tile] nodes of each path per tile of the order
+    long long *clsbase;      // their exclusive sums
+    int *plist_all;          // [n] the path lists, path after path
+    NodeRec *prec_all;       // [n] their node records
+    int *plist[LF_PATH_COUNT];      // host-set views of each path
+    NodeRec *prec[LF_PATH_COUNT];
+    unsigned char *mc8;      // [n] membership counts (255: see the header)
+    int *pre;                // [n] neighbours earlier in the order
+    long long *ubase;        // [n + 1] first in-count unit of each order position
+    bool static_ready;       // pre, unit and ubase are those of this clustering
+    bool lines_ready;        // lines and mc8 hold the current memberships
     TabPos *tpos;            // [n + 1]
     int *tcur;               // [n]
     ChunkRec *tchunk;
