@@ -52,6 +52,8 @@ static int create_failed(lf_handle *h, int rc)
     if (h->own_stream && h->stream) (void)hipStreamDestroy(h->stream);
     delete h->allocs;
     delete h->alloc_sizes;
+    delete h->kept;
+    delete h->kept_sizes;
     delete h->tmp_chunks;
     delete h->evpool;
     delete h->evkind;
@@ -69,6 +71,8 @@ int lf_create(lf_handle **out, int device, void *hip_stream, uint32_t flags)
     if (!h) return LF_ENOMEM;
     h->allocs = new std::vector<void *>();
     h->alloc_sizes = new std::vector<size_t>();
+    h->kept = new std::vector<void *>();
+    h->kept_sizes = new std::vector<size_t>();
     h->tmp_chunks = new std::vector<TmpChunk>();
     h->evpool = new std::vector<hipEvent_t>();
     h->evkind = new std::vector<int>();
@@ -116,6 +120,9 @@ int lf_destroy(lf_handle *h)
     if (h->cap_stream) (void)hipStreamDestroy(h->cap_stream);
     // the handle's work has completed on its stream: its blocks can serve other handles
     for (size_t k = 0; k < h->allocs->size(); k++) lf_dev_release(h->device, (*h->allocs)[k], (*h->alloc_sizes)[k]);
+    for (size_t k = 0; k < h->kept->size(); k++) lf_dev_release(h->device, (*h->kept)[k], (*h->kept_sizes)[k]);
+    delete h->kept;
+    delete h->kept_sizes;
     delete h->allocs;
     delete h->alloc_sizes;
     delete h->tmp_chunks;
@@ -164,7 +171,8 @@ int lf_load_graph(lf_handle *h, int64_t n, int64_t n_pairs, const int64_t *src, 
     if (!(flags & LF_RELABEL) && n >= (1ll << 31) - 1)
         return lf_set_error(h, LF_EOVERFLOW, "n >= 2^31 - 1");
     reset_graph(h);
-    LF_HIP(h, hipStreamSynchronize(h->stream));
+    // device arrays may have been written on another stream of the caller's
+    LF_HIP(h, (flags & LF_DEVICE_PTR) ? hipDeviceSynchronize() : hipStreamSynchronize(h->stream));
     LF_TRY(lf_prof_begin(h, LF_K_BUILD));
     int rc = lf_build_graph(h, n, n_pairs, (const long long *)src, (const long long *)dst, flags);
     if (rc != LF_OK) {

@@ -1043,7 +1043,7 @@ int lf_server_destroy(lf_server *s)
 int lf_get_memory(lf_handle *h, uint64_t *bytes, uint64_t *peak)
 {
     if (!h) return LF_EINVAL;
-    if (bytes) *bytes = h->dev_bytes;
+    if (bytes) *bytes = h->dev_bytes + h->kept_bytes;
     if (peak) *peak = h->dev_bytes_peak;
     return LF_OK;
 }

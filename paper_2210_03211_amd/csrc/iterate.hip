@@ -2446,5 +2446,6 @@ int lf_iterate(lf_handle *h, int q, double theta, int max_iters, lf_run_info *ou
     }
     out->wtilde = h->Wt;
     out->wcc_hat = h->Wt / h->cc;
+    lf_trim_kept(h);
     return LF_OK;
 }

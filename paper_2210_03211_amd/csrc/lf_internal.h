@@ -371,10 +371,13 @@ struct lf_handle {
     // allocation registry
     std::vector<void *> *allocs;
     std::vector<size_t> *alloc_sizes;
+    std::vector<void *> *kept;              // blocks given up, oldest first (lf_dev_free)
+    std::vector<size_t> *kept_sizes;
+    size_t kept_bytes;
     std::vector<TmpChunk> *tmp_chunks;      // scratch arena (lf_tmp_alloc)
     int tmp_chunk;
     size_t tmp_off;
-    size_t dev_bytes, dev_bytes_peak;   // device memory the handle holds (now / at most)
+    size_t dev_bytes, dev_bytes_peak;   // device memory in use by the handle (now / at most)
     // iteration starts and ends replayed from graphs (members of a batch)
     int phase_graphs;
     PhaseGraph pg[2][2];                // [start, end][slot parity]
@@ -402,6 +405,7 @@ int lf_set_error(lf_handle *h, int code, const char *fmt, ...);
 
 int lf_dev_alloc(lf_handle *h, void **p, size_t bytes);
 void lf_dev_free(lf_handle *h, void *p);
+void lf_trim_kept(lf_handle *h);
 // size an lf_dev_alloc request occupies; a block whose device work has completed goes
 // back to the per-device cache (or to HIP)
 size_t lf_alloc_class(size_t bytes);
