@@ -42,8 +42,8 @@ static inline unsigned grid_for(long long n, int block) { return (unsigned)((n +
 // A3: initial clustering
 // ------------------------------------------------------------------------------------
 // state: 0 undecided, 1 opener, 2 joins an opener
-__global__ void k_lfmis_round(const long long *rowptr, const int *col, const int *rank, long long n,
-                              int *state, int *cursor, int *undecided)
+__global__ void k_lfmis_round(const long long *rowptr, const int *col, const int *col_rank, const int *rank,
+                              long long n, int *state, int *cursor, int *undecided)
 {
     int cnt = 0;
     for (long long x = blockIdx.x * (long long)blockDim.x + threadIdx.x; x < n;
@@ -55,9 +55,8 @@ __global__ void k_lfmis_round(const long long *rowptr, const int *col, const int
         int mine = 0;
         bool pending = false;
         for (; c < e; c++) {
-            int y = col[c];
-            if (rank[y] >= rx) continue;
-            int sy = __atomic_load_n(&state[y], __ATOMIC_RELAXED);
+            if (col_rank[c] >= rx) continue;
+            int sy = __atomic_load_n(&state[col[c]], __ATOMIC_RELAXED);
             if (sy == 1) { mine = 2; break; }
             if (sy == 0) { pending = true; break; }
         }
@@ -85,22 +84,20 @@ __global__ void k_opener_ids(const int *order, const int *flag, const long long 
 }
 
 // every non-opener joins its lowest-ranked opener neighbour; one wave per node
-__global__ void __launch_bounds__(256) k_join_openers(const long long *rowptr, const int *col, const int *rank,
-                                                      const int *state, long long n, int *comm_of)
+__global__ void __launch_bounds__(256) k_join_openers(const long long *rowptr, const int *col, const int *col_rank,
+                                                      const int *order, const int *state, long long n, int *comm_of)
 {
     long long x = (blockIdx.x * (long long)blockDim.x + threadIdx.x) / WAVE;
     int lane = threadIdx.x & (WAVE - 1);
     if (x >= n || state[x] != 2) return;
-    int best = 0x7fffffff, who = -1;
+    unsigned best = 0x7fffffff;
     for (long long e = rowptr[x] + lane; e < rowptr[x + 1]; e += WAVE) {
-        int y = col[e];
-        if (state[y] == 1 && rank[y] < best) { best = rank[y]; who = y; }
+        const unsigned r = (unsigned)col_rank[e];
+        if (r < best && state[col[e]] == 1) best = r;
     }
-    for (int m = 32; m >= 1; m >>= 1) {
-        int ob = __shfl_xor(best, m, WAVE), ow = __shfl_xor(who, m, WAVE);
-        if (ob < best) { best = ob; who = ow; }
-    }
-    if (lane == 0) comm_of[x] = comm_of[who];
+    WAVE_SYNC();
+    best = 0x7fffffffu - wave_max_u32(0x7fffffffu - best);
+    if (lane == 0) comm_of[x] = comm_of[order[best]];
 }
 
 // one membership per node plus one free slot; in-count within its community
@@ -799,8 +796,8 @@ int lf_initial_clustering(lf_handle *h)
     while (n > 0) {
         LF_HIP(h, hipMemsetAsync(und, 0, sizeof(int) * RB, st));
         for (int r = 0; r < RB; r++)
-            hipLaunchKernelGGL(k_lfmis_round, dim3(gr), dim3(BS), 0, st, h->rowptr, h->col, h->rank, n, state,
-                               cursor, und + r);
+            hipLaunchKernelGGL(k_lfmis_round, dim3(gr), dim3(BS), 0, st, h->rowptr, h->col, h->col_rank, h->rank, n,
+                               state, cursor, und + r);
         rounds += RB;
         int hu[RB];
         LF_HIP(h, hipMemcpyAsync(hu, und, sizeof(int) * RB, hipMemcpyDeviceToHost, st));
@@ -816,8 +813,8 @@ int lf_initial_clustering(lf_handle *h)
     int lastf = 0;
     if (n > 0) {
         hipLaunchKernelGGL(k_opener_ids, dim3(grid_for(n, BS)), dim3(BS), 0, st, h->order, flag, pos, n, comm_of);
-        hipLaunchKernelGGL(k_join_openers, dim3(grid_for(n * WAVE, BS)), dim3(BS), 0, st, h->rowptr, h->col, h->rank,
-                           state, n, comm_of);
+        hipLaunchKernelGGL(k_join_openers, dim3(grid_for(n * WAVE, BS)), dim3(BS), 0, st, h->rowptr, h->col, h->col_rank,
+                           h->order, state, n, comm_of);
         LF_HIP(h, hipMemcpyAsync(&lastp, pos + n - 1, sizeof(long long), hipMemcpyDeviceToHost, st));
         LF_HIP(h, hipMemcpyAsync(&lastf, flag + n - 1, sizeof(int), hipMemcpyDeviceToHost, st));
     }
