@@ -413,9 +413,10 @@ int lf_batch_member_info(lf_batch *b, int32_t member_id, lf_run_info *out);
 int lf_batch_remove(lf_batch *b, int32_t member_id);
 int lf_batch_destroy(lf_batch *b);
 const char *lf_batch_last_error(lf_batch *b);
-/* on != 0 (the default): each step replays a graph of the per-step launches,
-   captured once, with the step's grids and member count set on its kernel nodes;
-   on = 0: the launches are issued one by one.  Results are the same either way. */
+/* on != 0: each step replays a graph of the per-step launches, captured once, with the
+   step's grids set on its kernel nodes; on = 0: the launches are issued one by one.  Results
+   are the same either way; without a call the batch takes the way that is faster for the
+   number of launches in a step (four at most: one by one). */
 int lf_batch_set_graph(lf_batch *b, int32_t on);
 
 /*
@@ -463,7 +464,7 @@ const char *lf_server_last_error(lf_server *s);
    that ran plainly, were captured into graphs, and were replayed from them (counts).
    ms holds 14 values. */
 int lf_server_timing(lf_server *s, double *ms);
-/* Graph replay of the server's batch steps (lf_batch_set_graph); on by default. */
+/* Graph replay of the server's batch steps (lf_batch_set_graph). */
 int lf_server_set_graph(lf_server *s, int32_t on);
 
 #ifdef __cplusplus

@@ -59,14 +59,22 @@ struct lf_batch {
     hipStream_t side[BATCH_SIDES];
     std::deque<BatchMember *> waitq[BATCH_SIDES];   // members whose queued start or end is
                                              // not yet read, in each side stream's order
+    // a step's descriptors, one upload: LF_MULTI_GRIDS arrays of boff_n(cap) first blocks,
+    // then the members (an upload each took two copies of 2.4 us and their gaps per step)
+    void *hstep[2];
     Member *hmem[2];
     int *hboff[2];
     hipEvent_t hev[2];
+    void *dstep;
     Member *dmem;
     int *dboff;
     int cap;                                 // members the buffers hold
     int slot;
-    bool use_graph;                          // replay the step from a captured graph
+    // Replay the step from a captured graph, only where lf_batch_set_graph asked for it: a step
+    // is four launches at most, and updating and replaying a graph of them costs the host 28
+    // us where launching them costs 15 (32 graphs of 4,000 nodes, queue 64: 339 ms in all
+    // with replays, 313 with launches).
+    bool use_graph;
     hipGraph_t graph;
     hipGraphExec_t exec;
     hipGraphNode_t node[LF_MULTI_KERNELS];
@@ -85,6 +93,10 @@ static int batch_error(lf_batch *b, int code, const char *msg)
     return code;
 }
 
+// first-block entries per grid: the members', their end and at least one BOFF_END
+static int boff_n(int cap) { return (cap + 2 + 63) / 64 * 64; }
+static size_t boff_bytes(int cap) { return sizeof(int) * LF_MULTI_GRIDS * boff_n(cap); }
+
 // Capture the multi-graph launches of a step once (grids and member counts are set
 // per step on the executable graph; descriptors live at fixed device addresses).
 static int batch_capture(lf_batch *b)
@@ -98,12 +110,12 @@ static int batch_capture(lf_batch *b)
     const void *fn[LF_MULTI_KERNELS];
     int grid[LF_MULTI_KERNELS], block[LF_MULTI_KERNELS];
     lf_multi_kernels(fn, grid, block);
-    const int zero = 0;
+    const int n = boff_n(b->cap);
     if (hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal) != hipSuccess)
         return batch_error(b, LF_EDEVICE, "stream capture failed to start");
     for (int i = 0; i < LF_MULTI_KERNELS; i++) {
-        const int *o = b->dboff + grid[i] * (b->cap + 1);
-        void *args[3] = {(void *)&b->dmem, (void *)&o, (void *)&zero};
+        const int *o = b->dboff + grid[i] * n;
+        void *args[3] = {(void *)&b->dmem, (void *)&o, (void *)&n};
         (void)hipLaunchKernel(fn[i], dim3(1), dim3(block[i]), args, 0, b->stream);
     }
     hipGraph_t g = nullptr;
@@ -137,17 +149,18 @@ static int batch_capture(lf_batch *b)
     return LF_OK;
 }
 
-// one step from the executable graph: grids and member count of every node, then replay
-static int batch_replay(lf_batch *b, int nm, const int *total)
+// one step from the executable graph: the grid of every node, then replay
+static int batch_replay(lf_batch *b, const int *total)
 {
     if (!b->exec || b->graph_cap != b->cap) LF_TRY(batch_capture(b));
     const void *fn[LF_MULTI_KERNELS];
     int grid[LF_MULTI_KERNELS], block[LF_MULTI_KERNELS];
     lf_multi_kernels(fn, grid, block);
+    const int n = boff_n(b->cap);
     for (int i = 0; i < LF_MULTI_KERNELS; i++) {
         const int t = grid[i];
-        const int *o = b->dboff + t * (b->cap + 1);
-        void *args[3] = {(void *)&b->dmem, (void *)&o, (void *)&nm};
+        const int *o = b->dboff + t * n;
+        void *args[3] = {(void *)&b->dmem, (void *)&o, (void *)&n};
         hipKernelNodeParams p;
         memset(&p, 0, sizeof p);
         p.func = (void *)fn[i];
@@ -169,23 +182,24 @@ static int batch_reserve(lf_batch *b, int nm)
     if (nm <= b->cap) return LF_OK;
     int cap = b->cap ? b->cap : 64;
     while (cap < nm) cap *= 2;
+    const size_t off = boff_bytes(cap), bytes = off + sizeof(Member) * cap;
     for (int s = 0; s < 2; s++) {
-        if (b->hmem[s]) {
+        if (b->hstep[s]) {
             (void)hipEventSynchronize(b->hev[s]);
-            (void)hipHostFree(b->hmem[s]);
-            (void)hipHostFree(b->hboff[s]);
+            (void)hipHostFree(b->hstep[s]);
+            b->hstep[s] = nullptr;
         }
-        if (hipHostMalloc((void **)&b->hmem[s], sizeof(Member) * cap, hipHostMallocDefault) != hipSuccess ||
-            hipHostMalloc((void **)&b->hboff[s], sizeof(int) * LF_MULTI_GRIDS * (cap + 1), hipHostMallocDefault) !=
-                hipSuccess)
+        if (hipHostMalloc(&b->hstep[s], bytes, hipHostMallocDefault) != hipSuccess)
             return batch_error(b, LF_ENOMEM, "pinned host buffers of the batch");
+        b->hboff[s] = (int *)b->hstep[s];
+        b->hmem[s] = (Member *)((char *)b->hstep[s] + off);
     }
     (void)hipStreamSynchronize(b->stream);
-    if (b->dmem) (void)hipFree(b->dmem);
-    if (b->dboff) (void)hipFree(b->dboff);
-    if (hipMalloc((void **)&b->dmem, sizeof(Member) * cap) != hipSuccess ||
-        hipMalloc((void **)&b->dboff, sizeof(int) * LF_MULTI_GRIDS * (cap + 1)) != hipSuccess)
-        return batch_error(b, LF_ENOMEM, "device buffers of the batch");
+    if (b->dstep) (void)hipFree(b->dstep);
+    b->dstep = nullptr;
+    if (hipMalloc(&b->dstep, bytes) != hipSuccess) return batch_error(b, LF_ENOMEM, "device buffers of the batch");
+    b->dboff = (int *)b->dstep;
+    b->dmem = (Member *)((char *)b->dstep + off);
     b->cap = cap;
     return LF_OK;
 }
@@ -236,9 +250,10 @@ int lf_batch_create(lf_batch **out, int device, void *hip_stream)
     b->device = device;
     b->cap = 0;
     b->slot = 0;
+    b->dstep = nullptr;
     b->dmem = nullptr;
     b->dboff = nullptr;
-    b->use_graph = true;
+    b->use_graph = false;
     b->graph = nullptr;
     b->exec = nullptr;
     b->graph_cap = 0;
@@ -251,6 +266,7 @@ int lf_batch_create(lf_batch **out, int device, void *hip_stream)
     b->launch_ms = 0.0;
     b->err[0] = 0;
     for (int s = 0; s < 2; s++) {
+        b->hstep[s] = nullptr;
         b->hmem[s] = nullptr;
         b->hboff[s] = nullptr;
         b->hev[s] = nullptr;
@@ -447,6 +463,7 @@ int lf_batch_step(lf_batch *b, int32_t *running)
         auto t1 = std::chrono::steady_clock::now();
         Member *hm = b->hmem[s];
         int *hb = b->hboff[s];
+        const int bn = boff_n(b->cap);
         int total[LF_MULTI_GRIDS] = {0, 0, 0, 0};
         for (int i = 0; i < nm; i++) {
             BatchMember *m = act[i];
@@ -456,21 +473,23 @@ int lf_batch_step(lf_batch *b, int32_t *running)
             hm[i].cx = m->cx;
             const int blocks[LF_MULTI_GRIDS] = {g.refresh, g.big, g.tie, g.apply};
             for (int t = 0; t < LF_MULTI_GRIDS; t++) {
-                hb[t * (b->cap + 1) + i] = total[t];
+                hb[t * bn + i] = total[t];
                 total[t] += blocks[t];
             }
         }
-        for (int t = 0; t < LF_MULTI_GRIDS; t++) hb[t * (b->cap + 1) + nm] = total[t];
+        for (int t = 0; t < LF_MULTI_GRIDS; t++) {
+            hb[t * bn + nm] = total[t];
+            for (int i = nm + 1; i < bn; i++) hb[t * bn + i] = BOFF_END;
+        }
         auto t2 = std::chrono::steady_clock::now();
         b->params_ms += std::chrono::duration<double, std::milli>(t2 - t1).count();
-        if (hipMemcpyAsync(b->dmem, hm, sizeof(Member) * nm, hipMemcpyHostToDevice, b->stream) != hipSuccess ||
-            hipMemcpyAsync(b->dboff, hb, sizeof(int) * LF_MULTI_GRIDS * (b->cap + 1), hipMemcpyHostToDevice, b->stream) !=
-                hipSuccess ||
+        if (hipMemcpyAsync(b->dstep, b->hstep[s], boff_bytes(b->cap) + sizeof(Member) * nm, hipMemcpyHostToDevice,
+                           b->stream) != hipSuccess ||
             hipEventRecord(b->hev[s], b->stream) != hipSuccess)
             return batch_error(b, LF_EDEVICE, "descriptor upload failed");
         if (b->use_graph) {
-            LF_TRY(batch_replay(b, nm, total));
-        } else if (lf_launch_multi(b->stream, b->dmem, b->dboff, b->cap, nm, total) != LF_OK) {
+            LF_TRY(batch_replay(b, total));
+        } else if (lf_launch_multi(b->stream, b->dmem, b->dboff, bn, total) != LF_OK) {
             return batch_error(b, LF_EDEVICE, "multi-graph launch failed");
         }
         auto t3 = std::chrono::steady_clock::now();
@@ -586,14 +605,12 @@ int lf_batch_destroy(lf_batch *b)
     for (size_t i = 0; i < b->members.size(); i++)
         if (b->members[i]) lf_batch_remove(b, (int32_t)i);
     for (int s = 0; s < 2; s++) {
-        if (b->hmem[s]) (void)hipHostFree(b->hmem[s]);
-        if (b->hboff[s]) (void)hipHostFree(b->hboff[s]);
+        if (b->hstep[s]) (void)hipHostFree(b->hstep[s]);
         (void)hipEventDestroy(b->hev[s]);
     }
     if (b->exec) (void)hipGraphExecDestroy(b->exec);
     if (b->graph) (void)hipGraphDestroy(b->graph);
-    if (b->dmem) (void)hipFree(b->dmem);
-    if (b->dboff) (void)hipFree(b->dboff);
+    if (b->dstep) (void)hipFree(b->dstep);
     if (b->own_stream) (void)hipStreamDestroy(b->stream);
     for (int k = 0; k < BATCH_SIDES; k++) (void)hipStreamDestroy(b->side[k]);
     delete b;

@@ -90,18 +90,105 @@ struct NodeLds {
 // through lists, 520 without; co-purchase shape, queue 256 (some 70 blocks) 103 against 115.
 #define LIST_BLOCKS 4096
 
-// member owning block b of a multi-graph launch (boff: first block of each member, nm + 1
-// entries); -1 past the last member's blocks
-__device__ __forceinline__ int find_member(const int *boff, int nm, int b)
+__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ long long uni(long long v)
 {
-    if (b >= boff[nm]) return -1;
-    int lo = 0, hi = nm - 1;
-    while (lo < hi) {
-        int mid = (lo + hi + 1) >> 1;
-        if (boff[mid] <= b) lo = mid;
-        else hi = mid - 1;
+    return ((long long)uni((int)(v >> 32)) << 32) | (unsigned)uni((int)v);
+}
+
+// one word of every 64-byte line of the arguments, so that they are all under way together
+// and the scalar cache holds them afterwards
+__device__ __forceinline__ void touch_args(const Ctx &cx, const QStep &qs)
+{
+    static_assert(sizeof(Ctx) > 320 && sizeof(Ctx) <= 384 && sizeof(QStep) > 64 && sizeof(QStep) <= 128,
+                  "lines of the arguments");
+    const int *a = (const int *)&cx, *b = (const int *)&qs;
+    asm volatile("" ::"s"(a[0]), "s"(a[16]), "s"(a[32]), "s"(a[48]), "s"(a[64]), "s"(a[80]), "s"(b[0]), "s"(b[16]),
+                 "s"(b[sizeof(QStep) / 4 - 2]));
+}
+
+// Member owning block b of a multi-graph launch, its blocks [b0, b1); -1 past the last one's.
+// boff: n (a multiple of 64) entries, the first block of each member, ascending, then the
+// number of blocks and BOFF_END to the end.  The wave reads 64 entries at a time.
+__device__ __forceinline__ int find_member(const int *boff, int n, int b, int &b0, int &b1)
+{
+    const int lane = threadIdx.x & (WAVE - 1);
+    int m = -1;
+    b0 = b1 = 0;
+    for (int i = 0; i < n; i += WAVE) {
+        const int v = boff[i + lane];
+        const unsigned long long at = __ballot(v <= b);
+        m += __popcll(at);
+        if (at) b0 = __builtin_amdgcn_readlane(v, 63 - __clzll((long long)at));
+        if (~at) {                           // the first entry past b ends the search
+            b1 = __builtin_amdgcn_readlane(v, __ffsll((long long)~at) - 1);
+            break;
+        }
     }
-    return lo;
+    return b1 != BOFF_END ? m : -1;
+}
+
+// Descriptors are constant during a launch.  Read as such, a line at a time ahead, they stay
+// scalar; and every pointer is declared a global one, which those loaded from memory are not
+// by themselves (a flat access also waits for the LDS).
+template <class T>
+__device__ __forceinline__ void as_global(T *&p)
+{
+    unsigned long long v;
+    __builtin_memcpy(&v, &p, sizeof v);
+    p = (T *)(__attribute__((address_space(1))) T *)v;
+}
+
+__device__ __forceinline__ void read_member(const Member *mem, Ctx &cx, QStep &qs)
+{
+    static_assert(sizeof(Ctx) % 8 == 0 && sizeof(QStep) % 8 == 0 && sizeof(Member) == sizeof(Ctx) + sizeof(QStep),
+                  "read as 64-bit words");
+    const __attribute__((address_space(4))) long long *w = (const __attribute__((address_space(4))) long long *)mem;
+    long long a[sizeof(Ctx) / 8], b[sizeof(QStep) / 8];
+#pragma unroll
+    for (unsigned k = 0; k < sizeof(Ctx) / 8; k++) a[k] = w[k];
+#pragma unroll
+    for (unsigned k = 0; k < sizeof(QStep) / 8; k++) b[k] = w[sizeof(Ctx) / 8 + k];
+    __builtin_memcpy(&cx, a, sizeof(Ctx));
+    __builtin_memcpy(&qs, b, sizeof(QStep));
+    as_global(cx.rowptr);
+    as_global(cx.col);
+    as_global(cx.deg);
+    as_global(cx.order);
+    as_global(cx.nh);
+    as_global(cx.slot);
+    as_global(cx.ln);
+    as_global(cx.cr);
+    as_global(cx.cm_off);
+    as_global(cx.cm_len);
+    as_global(cx.cm_node);
+    as_global(cx.tflag);
+    as_global(cx.ovf_node);
+    as_global(cx.ovf_comm);
+    as_global(cx.ovf_flag);
+    as_global(cx.dec);
+    as_global(cx.ctr);
+#pragma unroll
+    for (int k = 0; k < LF_PATH_COUNT; k++) {
+        as_global(cx.plist[k]);
+        as_global(cx.prec[k]);
+    }
+    as_global(cx.col_rank);
+    as_global(cx.tpos);
+    as_global(cx.tchunk);
+    as_global(cx.tbuck);
+    as_global(cx.tcur);
+    as_global(cx.tvis);
+    as_global(cx.trow);
+    as_global(cx.tres);
+    as_global(cx.lhdr);
+    as_global(cx.lpair);
+    as_global(cx.ldeg);
+    as_global(cx.unit);
+    as_global(cx.part_rec);
+    as_global(cx.part_done);
+    as_global(cx.macc);
+    touch_args(cx, qs);
 }
 
 // single-graph kernel K(Ctx, QStep) and multi-graph kernel K_multi over Member descriptors,
@@ -112,12 +199,16 @@ __device__ __forceinline__ int find_member(const int *boff, int nm, int b)
         __shared__ LDS_T lds;                                                                 \
         BODY(cx, qs, (int)blockIdx.x, (int)gridDim.x, lds);                                   \
     }                                                                                         \
-    __global__ void __launch_bounds__(BOUNDS) K##_multi(const Member *mem, const int *boff, int nm) \
+    __global__ void __launch_bounds__(BOUNDS) K##_multi(const Member *mem, const int *boff, int n) \
     {                                                                                         \
         __shared__ LDS_T lds;                                                                 \
-        const int m = find_member(boff, nm, (int)blockIdx.x);                                 \
+        int b0, b1;                                                                           \
+        const int m = find_member(boff, n, (int)blockIdx.x, b0, b1);                          \
         if (m < 0) return;                                                                    \
-        BODY(mem[m].cx, mem[m].qs, (int)blockIdx.x - boff[m], boff[m + 1] - boff[m], lds);    \
+        Ctx cx;                                                                               \
+        QStep qs;                                                                             \
+        read_member(mem + m, cx, qs);                                                         \
+        BODY(cx, qs, (int)blockIdx.x - b0, b1 - b0, lds);                                     \
     }
 
 struct NoLds {
@@ -2308,19 +2399,18 @@ int lf_launch_queue(lf_handle *h, Ctx &cx, const QStep &qs, const QGrids &g)
     return LF_OK;
 }
 
-// One queue of each of nm graphs: four grids, each block finding its graph from dboff
-// (LF_MULTI_GRIDS arrays of first-block offsets, at stride cap + 1, each with nm + 1
-// entries); total[i] = blocks of grid i.
-int lf_launch_multi(hipStream_t st, const Member *dmem, const int *dboff, int cap, int nm, const int *total)
+// One queue of each of several graphs: four grids, each block finding its graph from dboff
+// (LF_MULTI_GRIDS arrays of n first-block offsets); total[i] = blocks of grid i.
+int lf_launch_multi(hipStream_t st, const Member *dmem, const int *dboff, int n, const int *total)
 {
     const int *o = dboff;
-    if (total[0] > 0) hipLaunchKernelGGL(k_refresh_multi, dim3(total[0]), dim3(GT), 0, st, dmem, o, nm);
-    o += cap + 1;
-    if (total[1] > 0) hipLaunchKernelGGL(k_eval_big_multi, dim3(total[1]), dim3(GT), 0, st, dmem, o, nm);
-    o += cap + 1;
-    if (total[2] > 0) hipLaunchKernelGGL(k_big_tie_multi, dim3(total[2]), dim3(GT), 0, st, dmem, o, nm);
-    o += cap + 1;
-    if (total[3] > 0) hipLaunchKernelGGL(k_apply_multi, dim3(total[3]), dim3(256), 0, st, dmem, o, nm);
+    if (total[0] > 0) hipLaunchKernelGGL(k_refresh_multi, dim3(total[0]), dim3(GT), 0, st, dmem, o, n);
+    o += n;
+    if (total[1] > 0) hipLaunchKernelGGL(k_eval_big_multi, dim3(total[1]), dim3(GT), 0, st, dmem, o, n);
+    o += n;
+    if (total[2] > 0) hipLaunchKernelGGL(k_big_tie_multi, dim3(total[2]), dim3(GT), 0, st, dmem, o, n);
+    o += n;
+    if (total[3] > 0) hipLaunchKernelGGL(k_apply_multi, dim3(total[3]), dim3(256), 0, st, dmem, o, n);
     return hipGetLastError() == hipSuccess ? LF_OK : LF_EDEVICE;
 }
 

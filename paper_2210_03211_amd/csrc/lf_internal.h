@@ -240,6 +240,8 @@ struct Member {
     QStep qs;
 };
 
+#define BOFF_END 0x7fffffff        // past a multi-graph launch's last first-block entry
+
 // launch grids of one queue's kernels (0 = not launched)
 struct QGrids {
     int refresh, eval, big, tie, apply;
@@ -483,7 +485,7 @@ int lf_iter_begin_complete(lf_handle *h, long long qq, long long *nq);
 void lf_queue_params(lf_handle *h, long long k, long long nq, long long qq, bool compact_grids, QStep *qs,
                      QGrids *g);
 int lf_launch_queue(lf_handle *h, Ctx &cx, const QStep &qs, const QGrids &g);
-int lf_launch_multi(hipStream_t st, const Member *dmem, const int *dboff, int cap, int nm, const int *total);
+int lf_launch_multi(hipStream_t st, const Member *dmem, const int *dboff, int n, const int *total);
 #define LF_MULTI_GRIDS 4         // per-step launches of a batch with grids of their own
 #define LF_MULTI_KERNELS 4       // kernels of a batch step
 void lf_multi_kernels(const void **fn, int *grid, int *block);
