@@ -34,6 +34,7 @@
 #define INB 64          // neighbours per in-count unit (one per lane)
 #define HOLE (-2)       // a membership left in the current iteration (removed at its end)
 #define PART 512        // members per re-sum part
+#define EDITS 64        // queued nodes of an edit block of k_apply
 #define MACC 19         // digit counters per multi-part community (3 x 6 digits, in-sum)
 
 static inline unsigned grid_for(long long n, int block) { return (unsigned)((n + block - 1) / block); }
@@ -89,6 +90,16 @@ struct NodeLds {
 // 10,000 blocks) 93 ms through lists, 85 without; 4M nodes, queue 4096 (about 1,500 blocks) 500
 // through lists, 520 without; co-purchase shape, queue 256 (some 70 blocks) 103 against 115.
 #define LIST_BLOCKS 4096
+
+// Every kernel of a queue is a chain of dependent reads, some 0.7 us each, so the kernels keep
+// to three rules.  What does not depend on each other is read in one go: a read under a lane
+// condition makes the compiler wait before the next one, so such reads take a clamped index
+// and their value is dropped afterwards, and `arrived` keeps them from being moved behind a
+// branch.  What is the same for a wave is made so for the compiler (uni).  And all of the
+// arguments are read at once instead of a line at a time where each is first used.  (k_apply's
+// in-count units had six round trips in a row where three depend on each other; 4M
+// social-shaped nodes, queue 4096: k_apply 7.5 -> 6.5 us, k_refresh 10.8 -> 10.1, whole run 462 ->
+// 437 ms.)
 
 __device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
 __device__ __forceinline__ long long uni(long long v)
@@ -197,6 +208,7 @@ __device__ __forceinline__ void read_member(const Member *mem, Ctx &cx, QStep &q
     __global__ void __launch_bounds__(BOUNDS) K(Ctx cx, QStep qs)                             \
     {                                                                                         \
         __shared__ LDS_T lds;                                                                 \
+        touch_args(cx, qs);                                                                   \
         BODY(cx, qs, (int)blockIdx.x, (int)gridDim.x, lds);                                   \
     }                                                                                         \
     __global__ void __launch_bounds__(BOUNDS) K##_multi(const Member *mem, const int *boff, int n) \
@@ -414,6 +426,16 @@ struct GathLds {
     int wtot[4];
 };
 
+// node at position p of a path list, and its queue position
+__device__ __forceinline__ NodeRec node_rec(const Ctx &cx, const QStep &qs, int path, int p, int &j)
+{
+    v4i r = *(const v4i *)&cx.prec[path][p];
+    int pos = cx.plist[path][p];
+    arrived(r, pos);
+    j = uni(pos) - qs.cstart;
+    return NodeRec{((long long)uni(r.y) << 32) | (unsigned)uni(r.x), uni(r.z), uni(r.w)};
+}
+
 // Flatten queued node j with NT threads (one wave, or a workgroup of GT threads) if its
 // neighbours (<= VCAP), visits and own memberships fit (2 * (visits + own) <= table,
 // <= VCAP of them, <= MXCAP own).  Returns false otherwise, the same for all NT threads.
@@ -430,45 +452,56 @@ __device__ __forceinline__ bool gather_node(const Ctx &cx, const NodeRec nr, int
     const int x = nr.x, d = nr.d;
     const long long rb = nr.rb;
     if (d > VCAP) return false;
-    // the adjacency gathers need only the node record; the header is fetched beside them
+    // the adjacency gathers need only the node record; the own line (count, placement and
+    // inline memberships) is fetched beside them
+    const NodeLine *lxp = cx.ln + x;
     int yv[NB];
 #pragma unroll
     for (int b = 0; b < NB; b++) {
-        int q = b * NT + tid;
-        yv[b] = q < d ? cx.col[rb + q] : -1;
+        const int q = b * NT + tid;
+        yv[b] = x;
+        if (d > 0) yv[b] = cx.col[rb + (q < d ? q : d - 1)];
     }
-    // own line: count, placement and (inline) memberships, read beside the adjacency
-    const NodeLine *lxp = cx.ln + x;
-    mcnt = lxp->cnt;
-    const long long xoff = lxp->off;
-    Slot own = {-1, 0};
-    if (tid < LINE_SLOTS) own = lxp->s[tid];
-    if (mcnt > MXCAP) return false;
-    if (xoff >= 0 && tid < mcnt) own = cx.slot[xoff + tid];
+    v4i hx = *(const v4i *)lxp;
+    long long ownw = *(const long long *)&lxp->s[tid < LINE_SLOTS ? tid : LINE_SLOTS - 1];
+    arrived(hx, ownw);
+#pragma unroll
+    for (int b = 0; b < NB; b++) arrived(yv[b]);
     // one line per neighbour: its count, degree and memberships in one gather
     constexpr int NL = NB == 1 ? 1 : 0;     // lines held
     NodeLine held;
     int yc[NB], yd[NB];
     long long yo[NB];
+    if constexpr (NL == 1) {
+        RawLine r = read_line(cx.ln + yv[0]);
+        arrived(r.q[0], r.q[1], r.q[2], r.q[3]);
+        held = as_line(r);
+        yc[0] = held.cnt;
+        yd[0] = held.deg;
+        yo[0] = held.off;
+    } else {
+        v4i hy[NB];
 #pragma unroll
-    for (int b = 0; b < NB; b++) {
-        yc[b] = 0;
-        yd[b] = 0;
-        yo[b] = -1;
-        if (yv[b] >= 0) {
-            const NodeLine *lp = cx.ln + yv[b];
-            if constexpr (NL == 1) {
-                held = *lp;
-                yc[b] = held.cnt;
-                yd[b] = held.deg;
-                yo[b] = held.off;
-            } else {
-                yc[b] = lp->cnt;
-                yd[b] = lp->deg;
-                yo[b] = lp->off;
-            }
+        for (int b = 0; b < NB; b++) hy[b] = *(const v4i *)(cx.ln + yv[b]);
+#pragma unroll
+        for (int b = 0; b < NB; b++) {
+            arrived(hy[b]);
+            yc[b] = hy[b].x;
+            yd[b] = hy[b].y;
+            yo[b] = ((long long)hy[b].w << 32) | (unsigned)hy[b].z;
         }
     }
+#pragma unroll
+    for (int b = 0; b < NB; b++)
+        if (b * NT + tid >= d) {
+            yc[b] = 0;
+            yo[b] = -1;
+        }
+    Slot own = {(int)ownw, (int)(ownw >> 32)};
+    mcnt = uni(hx.x);
+    const long long xoff = ((long long)uni(hx.w) << 32) | (unsigned)uni(hx.z);
+    if (mcnt > MXCAP) return false;
+    if (xoff >= 0 && tid < mcnt) own = cx.slot[xoff + tid];
     // neighbour memberships flattened into the list behind the own ones: an inline
     // membership is kept as its (community, in-count) pair, one in the slot array as the
     // complement of its slot index
@@ -582,8 +615,8 @@ __device__ __forceinline__ void gather_path(const Ctx &cx, const QStep &qs, int 
                                             GathLds<VCAP> &L, int wcap, const NodeList out)
 {
     constexpr int NB = VCAP / NT;
-    const int j = cx.plist[path][p] - qs.cstart;
-    const NodeRec nr = cx.prec[path][p];
+    int j;
+    const NodeRec nr = node_rec(cx, qs, path, p, j);
     long long e[NB];
     int dg[NB], N, mcnt;
     if (!gather_node<NT, VCAP>(cx, nr, tid, L, wcap, path, e, dg, N, mcnt)) {
@@ -616,8 +649,8 @@ __device__ __forceinline__ void whole_path(const Ctx &cx, const QStep &qs, int p
                                            WholeLds<VCAP> &L, int wcap)
 {
     constexpr int NB = VCAP / NT;
-    const int j = cx.plist[path][p] - qs.cstart;
-    const NodeRec nr = cx.prec[path][p];
+    int j;
+    const NodeRec nr = node_rec(cx, qs, path, p, j);
     long long e[NB];
     int dg[NB], N, mcnt;
     if (!gather_node<NT, VCAP>(cx, nr, tid, L.g, wcap, path, e, dg, N, mcnt)) {
@@ -641,7 +674,7 @@ union EvalLds {
 
 __device__ __forceinline__ void eval_small_med(const Ctx &cx, const QStep &qs, int blk, EvalLds &L)
 {
-    const int wv = threadIdx.x / WAVE, lane = threadIdx.x & (WAVE - 1);
+    const int wv = uni((int)threadIdx.x / WAVE), lane = threadIdx.x & (WAVE - 1);
     if (blk < qs.es) {
         const int i = blk * EW + wv;        // small blocks have no block barriers
         if (i < qs.ln) score_node<WAVE, VSMALL>(cx, small_list(cx, qs, i), lane, L.w[wv], LF_PATH_SMALL);
@@ -665,6 +698,7 @@ __device__ __forceinline__ void reset_apply_counters(const Ctx &cx, int blk)
 __global__ void __launch_bounds__(EW * WAVE) k_eval(Ctx cx, QStep qs)
 {
     __shared__ EvalLds lds;
+    touch_args(cx, qs);
     reset_apply_counters(cx, (int)blockIdx.x);
     eval_small_med(cx, qs, (int)blockIdx.x, lds);
 }
@@ -676,7 +710,8 @@ __global__ void __launch_bounds__(EW * WAVE) k_eval_whole(Ctx cx, QStep qs)
         WholeLds<VSMALL> w[EW];
         WholeLds<VMED> m;
     } lds;
-    const int blk = (int)blockIdx.x, wv = threadIdx.x / WAVE, lane = threadIdx.x & (WAVE - 1);
+    const int blk = (int)blockIdx.x, wv = uni((int)threadIdx.x / WAVE), lane = threadIdx.x & (WAVE - 1);
+    touch_args(cx, qs);
     reset_apply_counters(cx, blk);
     if (blk < qs.es) {
         const int i = blk * EW + wv;        // small blocks have no block barriers
@@ -728,13 +763,15 @@ __device__ __forceinline__ void table_chunk(const Ctx &cx, const QStep &qs, int 
     const int tid = threadIdx.x;
     const ChunkRec cr = cx.tchunk[k];
     const int P = cr.P;
-    const int y = tid < cr.cnt ? cx.col[cr.rb + tid] : -1;
+    const int y = cx.col[cr.rb + (tid < cr.cnt ? tid : cr.cnt - 1)];   // (a chunk is never empty)
+    RawLine rl = read_line(cx.ln + y);
     for (int t = tid; t < P; t += GT) S.hist[t] = 0;
-    NodeLine ly;
-    ly.cnt = 0;
-    ly.deg = 0;
-    ly.off = -1;
-    if (y >= 0) ly = cx.ln[y];
+    arrived(rl.q[0], rl.q[1], rl.q[2], rl.q[3]);
+    NodeLine ly = as_line(rl);
+    if (tid >= cr.cnt) {
+        ly.cnt = 0;
+        ly.off = -1;
+    }
     __syncthreads();
     int mine = 0;                            // memberships (holes left out)
     if (ly.off < 0) {
@@ -748,10 +785,11 @@ __device__ __forceinline__ void table_chunk(const Ctx &cx, const QStep &qs, int 
         for (int t0 = 0; t0 < ly.cnt; t0 += 4) {   // four slot loads per round trip
             int c[4];
 #pragma unroll
-            for (int q = 0; q < 4; q++) c[q] = t0 + q < ly.cnt ? cx.slot[ly.off + t0 + q].comm : -1;
+            for (int q = 0; q < 4; q++) c[q] = cx.slot[ly.off + (t0 + q < ly.cnt ? t0 + q : t0)].comm;
+            arrived(c[0], c[1], c[2], c[3]);
 #pragma unroll
             for (int q = 0; q < 4; q++)
-                if (c[q] >= 0) {
+                if (t0 + q < ly.cnt && c[q] >= 0) {
                     atomicAdd(&S.hist[bucket_of(c[q], P)], 1);
                     mine++;
                 }
@@ -803,14 +841,17 @@ __device__ __forceinline__ void table_chunk(const Ctx &cx, const QStep &qs, int 
                 out[atomicAdd(&S.hist[bucket_of(ly.s[t].comm, P)], 1)] = TabVisit{ly.s[t].comm, ly.s[t].in, ly.deg, 0};
     } else {
         for (int t0 = 0; t0 < ly.cnt; t0 += 4) {
-            Slot sl[4];
+            long long sl[4];
 #pragma unroll
             for (int q = 0; q < 4; q++)
-                sl[q] = t0 + q < ly.cnt ? cx.slot[ly.off + t0 + q] : Slot{-1, 0};
+                sl[q] = *(const long long *)&cx.slot[ly.off + (t0 + q < ly.cnt ? t0 + q : t0)];
+            arrived(sl[0], sl[1], sl[2], sl[3]);
 #pragma unroll
-            for (int q = 0; q < 4; q++)
-                if (sl[q].comm >= 0)
-                    out[atomicAdd(&S.hist[bucket_of(sl[q].comm, P)], 1)] = TabVisit{sl[q].comm, sl[q].in, ly.deg, 0};
+            for (int q = 0; q < 4; q++) {
+                const int c = (int)sl[q];
+                if (t0 + q < ly.cnt && c >= 0)
+                    out[atomicAdd(&S.hist[bucket_of(c, P)], 1)] = TabVisit{c, (int)(sl[q] >> 32), ly.deg, 0};
+            }
         }
     }
 }
@@ -1128,18 +1169,18 @@ QUEUE_KERNELS(k_big_tie, GT, NoLds, body_big_tie)
 // membership after the queue from the neighbour's own decision rather than from its
 // slots: the result is a from-scratch recount of every in-count on the new partition.
 
-// Re-sum parts of community C at its first touch in the queue, planned from its member
+// Re-sum parts of a community at its first touch in the queue, planned from its member
 // list's length then (joiners of the same queue that come later are the last part's).
-// Every lane of the wave calls this (want = false: it only takes part in the wave's
-// reservation).
-__device__ __forceinline__ void plan_parts(const Ctx &cx, bool want, int C, long long base, long long cap,
-                                           long long len)
+__device__ __forceinline__ int part_count(long long cap, long long len)
 {
-    int parts = (int)(((len < cap ? len : cap) + PART - 1) / PART);
-    if (parts < 1) parts = 1;
-    int p0 = wave_reserve(&cx.ctr->parts_total, want && parts == 1);
-    if (!want) return;
-    if (parts > 1) p0 = atomicAdd(&cx.ctr->parts_total, parts);
+    const int parts = (int)(((len < cap ? len : cap) + PART - 1) / PART);
+    return parts < 1 ? 1 : parts;
+}
+
+// records of community C's parts from p0 on; ms: its digit counters when there are several
+__device__ __forceinline__ void plan_parts(const Ctx &cx, int C, long long base, long long cap, int parts, int p0,
+                                           int ms)
+{
     PartRec pr;
     pr.base = base;
     pr.C = C;
@@ -1152,7 +1193,6 @@ __device__ __forceinline__ void plan_parts(const Ctx &cx, bool want, int C, long
         pr.C = -1;                                    // the records that exist stay empty
     } else if (parts > 1) {
         cx.part_done[C] = 0;
-        int ms = atomicAdd(&cx.ctr->mslots, 1);
         if (ms >= cx.mslot_cap) {
             atomicOr(&cx.ctr->error, LF_DEVERR_CAP);
             ms = 0;
@@ -1166,70 +1206,84 @@ __device__ __forceinline__ void plan_parts(const Ctx &cx, bool want, int C, long
     }
 }
 
-// membership edits of queue position j (threads past the queue only take part in the
-// wave-wide counting and reservations)
-__device__ __forceinline__ void apply_edit(const Ctx &cx, const QStep &qs, int j)
+struct EditLds {
+    int sum[4][256 / WAVE];  // per wave: parts, digit counters, joins, leaves
+    int base[2];             // the block's first part and digit counter
+};
+
+// Membership edits of queue position j; every thread of the block calls this (those past the
+// queue take part in the counting only).  The queue's counters are one line of memory,
+// whose atomics are served one after the other, so a block counts in LDS and adds once per
+// counter, and a block has few enough nodes that their counters' atomics (six per node, each its
+// own line) spread over the chip.  With three per wave the edits of a queue took 9.3 us where the
+// in-counts beside them took 4.0 (1M nodes, dense, queue 16,384).  Whole runs, 32 / 64 / 128 / 256
+// nodes to a block: 4M social-shaped nodes 437 / 434 / 433 / 436 ms, 32 graphs in a batch 312 /
+// 293 / 297 / 307.
+__device__ __forceinline__ void apply_edit(const Ctx &cx, const QStep &qs, int j, EditLds &S)
 {
     const int cstart = qs.cstart, clen = qs.clen;
     const int lane = threadIdx.x & (WAVE - 1);
     const bool inq = j < clen;
-    int J = -1, L = -1, x = -1;
-    if (inq) {
-        const Decision dc = cx.dec[j];
-        J = dc.J;
-        L = dc.L;
-        x = cx.order[cstart + j];
-    }
-    unsigned long long ml = __ballot(L >= 0);
-    if (lane == 0 && ml) atomicAdd(&cx.ctr->leaves, (unsigned long long)__popcll(ml));
-    const bool act = inq && (J >= 0 || L >= 0);
+    const int jc = inq ? j : clen - 1;      // (a queue is never empty)
+    v4i dc = *(const v4i *)&cx.dec[jc];
+    int x = cx.order[cstart + jc];
+    arrived(dc, x);
+    const int J = inq ? dc.x : -1, L = inq ? dc.y : -1;
+    const bool act = J >= 0 || L >= 0;
     bool firstL = false, firstJ = false, joined = false;
-    long long cmoL = 0, cmeL = 0, cmoJ = 0, cmeJ = 0;
+    long long cmoL = 0, capL = 0, cmoJ = 0, capJ = 0;
     int lenL = 0, lenJ = 0;
     int own_scanned = 0;
     if (act) {
-        // the node's line and slot capacity and both member-list ranges in one round trip
-        const NodeLine hx = cx.ln[x];
-        const long long nxt = cx.nh[x + 1].off;
+        // everything that depends on x, J and L alone in one round trip: the node's line and
+        // slot capacity, both member-list ranges, and the counters of both communities
+        const int Lc = L >= 0 ? L : J, Jc = J >= 0 ? J : L;
+        RawLine rx = read_line(cx.ln + x);
+        long long nxt = cx.nh[x + 1].off;
+        cmoL = cx.cm_off[Lc];
+        capL = cx.cm_off[Lc + 1];
+        cmoJ = cx.cm_off[Jc];
+        capJ = cx.cm_off[Jc + 1];
+        lenL = cx.cm_len[Lc];
+        int oldL = 1, oldJ = 1, p = 0;
         if (L >= 0) {
-            cmoL = cx.cm_off[L];
-            cmeL = cx.cm_off[L + 1];
-            lenL = cx.cm_len[L];
+            oldL = atomicExch(&cx.tflag[L], 1);
+            atomicSub(&cx.cr[L].s, 1);
         }
         if (J >= 0) {
-            cmoJ = cx.cm_off[J];
-            cmeJ = cx.cm_off[J + 1];
+            p = atomicAdd(&cx.cm_len[J], 1);
+            oldJ = atomicExch(&cx.tflag[J], 1);
+            atomicAdd(&cx.cr[J].s, 1);
         }
+        arrived(rx.q[0], rx.q[1], rx.q[2], rx.q[3], nxt);
+        arrived(cmoL, capL, cmoJ, capJ);
+        arrived(lenL, p, oldL, oldJ);
+        const NodeLine hx = as_line(rx);
+        capL -= cmoL;
+        capJ -= cmoJ;
+        lenJ = p + 1;
+        firstL = oldL == 0;                 // first touch of the community in this queue
+        firstJ = oldJ == 0;
         // a node's slots change only in its own queue, so they hold no hole yet and its
         // free slot is at cnt
         const int cnt = hx.cnt;
         const long long capx = hx.off < 0 ? LINE_SLOTS : nxt - hx.off;
         Slot *xs = hx.off < 0 ? cx.ln[x].s : cx.slot + hx.off;
-        const bool jfits = J >= 0 && cnt < capx;
-        if (J >= 0 && !jfits) atomicOr(&cx.ctr->error, LF_DEVERR_SLOTS);
         own_scanned = L >= 0 ? cnt : 0;
-        int oldL = 1, oldJ = 1, p = 0;
-        if (L >= 0) {
-            atomicSub(&cx.cr[L].s, 1);
-            oldL = atomicExch(&cx.tflag[L], 1);
-        }
-        if (jfits) {
-            atomicAdd(&cx.cr[J].s, 1);
-            p = atomicAdd(&cx.cm_len[J], 1);
-            lenJ = p + 1;
-            oldJ = atomicExch(&cx.tflag[J], 1);
-        }
         if (L >= 0) {
             int tin = 0;
             const int t = line_find(cx, hx, L, &tin);
             if (t >= 0) xs[t].comm = HOLE;  // only the community word: in-counts are updated beside
-            firstL = oldL == 0;             // first touch of L in this queue
         }
-        if (jfits) {
-            xs[cnt].comm = J;               // the free slot; its in-count is counted by the units
-            cx.ln[x].cnt = cnt + 1;
-            joined = true;
-            if (p < cmeJ - cmoJ) {
+        if (J >= 0) {
+            if (cnt < capx) {
+                xs[cnt].comm = J;           // the free slot; its in-count is counted by the units
+                cx.ln[x].cnt = cnt + 1;
+                joined = true;
+            } else {
+                atomicOr(&cx.ctr->error, LF_DEVERR_SLOTS);   // the run fails; the lists stay whole
+            }
+            if (p < capJ) {
                 cx.cm_node[cmoJ + p] = x;
             } else {
                 int e = atomicAdd(&cx.ctr->ovf_cnt, 1);
@@ -1237,11 +1291,8 @@ __device__ __forceinline__ void apply_edit(const Ctx &cx, const QStep &qs, int j
                 cx.ovf_comm[e] = J;
                 cx.ovf_flag[J] = 1;
             }
-            firstJ = oldJ == 0;
         }
     }
-    unsigned long long mj = __ballot(joined);
-    if (mj && lane == __ffsll((long long)mj) - 1) atomicAdd(&cx.ctr->joins, (unsigned long long)__popcll(mj));
     if (cx.stats) {
         const long long mv = wave_sum_i64(act ? 1 : 0), os = wave_sum_i64(own_scanned);
         if (lane == 0 && mv) {
@@ -1249,8 +1300,31 @@ __device__ __forceinline__ void apply_edit(const Ctx &cx, const QStep &qs, int j
             atomicAdd(&cx.ctr->apply[LF_APPLY_OWN_SLOTS], (unsigned long long)os);
         }
     }
-    plan_parts(cx, firstL, L, cmoL, cmeL - cmoL, lenL);
-    plan_parts(cx, firstJ, J, cmoJ, cmeJ - cmoJ, lenJ);
+    // one reservation per block for the parts of all its communities and their digit counters
+    const int nL = firstL ? part_count(capL, lenL) : 0, nJ = firstJ ? part_count(capJ, lenJ) : 0;
+    const int mL = nL > 1, mJ = nJ > 1;
+    int tot;
+    const int at = wave_incl_scan(nL + nJ, &tot) - (nL + nJ);
+    const unsigned long long bL = __ballot(mL), bJ = __ballot(mJ), below = (1ull << lane) - 1;
+    const int many = __popcll(bL) + __popcll(bJ);
+    const int wv = uni((int)threadIdx.x / WAVE);
+    const int nj = __popcll(__ballot(joined)), nl = __popcll(__ballot(L >= 0));
+    if (lane < 4) S.sum[lane][wv] = lane == 0 ? tot : lane == 1 ? many : lane == 2 ? nj : nl;
+    __syncthreads();
+    if (threadIdx.x < 4) {
+        int v = 0;
+        for (int w = 0; w < 256 / WAVE; w++) v += S.sum[lane][w];
+        if (lane < 2) S.base[lane] = v ? atomicAdd(lane ? &cx.ctr->mslots : &cx.ctr->parts_total, v) : 0;
+        else if (v) atomicAdd(lane == 2 ? &cx.ctr->joins : &cx.ctr->leaves, (unsigned long long)v);
+    }
+    __syncthreads();
+    int p0 = S.base[0] + at, ms = S.base[1] + __popcll(bL & below) + __popcll(bJ & below);
+    for (int w = 0; w < wv; w++) {
+        p0 += S.sum[0][w];
+        ms += S.sum[1][w];
+    }
+    if (nL) plan_parts(cx, L, cmoL, capL, nL, p0, ms);
+    if (nJ) plan_parts(cx, J, cmoJ, capJ, nJ, p0 + nL, ms + mL);
 }
 
 // in-count changes of the neighbours in unit u (one wave): a neighbour y that holds J
@@ -1260,27 +1334,25 @@ __device__ __forceinline__ void apply_unit(const Ctx &cx, const QStep &qs, long 
 {
     const int lane = threadIdx.x & (WAVE - 1);
     const UnitRec ur = cx.unit[u];
-    const int j = ur.r - qs.cstart;
+    const int cnt = uni(ur.cnt), x = uni(ur.x);
+    const long long e = uni(ur.rb) + (lane < cnt ? lane : cnt - 1);
     // the unit's neighbours, the node's decision, join position and line placement
-    const int y = lane < ur.cnt ? cx.col[ur.rb + lane] : -1;
-    const int ry = lane < ur.cnt ? cx.col_rank[ur.rb + lane] : -1;
-    const Decision dc = cx.dec[j];
-    const int J = dc.J, L = dc.L, pos = dc.pos;
-    const long long xoff = cx.ln[ur.x].off;
-    if (J < 0 && L < 0) return;             // uniform over the wave
-    NodeLine ly;
-    ly.cnt = 0;
-    ly.off = -1;
-    int Jy = -1, Ly = -1;
-    if (y >= 0) {
-        ly = cx.ln[y];
-        const int jy = ry - qs.cstart;
-        if (jy >= 0 && jy < qs.clen) {
-            const Decision dy = cx.dec[jy];
-            Jy = dy.J;
-            Ly = dy.L;
-        }
-    }
+    int y = cx.col[e];
+    int ry = cx.col_rank[e];
+    v4i dc = *(const v4i *)&cx.dec[uni(ur.r) - qs.cstart];
+    long long xo = cx.ln[x].off;
+    arrived(y, ry, dc, xo);
+    const int J = uni(dc.x), L = uni(dc.y), pos = uni(dc.z);
+    const long long xoff = uni(xo);
+    if (J < 0 && L < 0) return;
+    const int jy = ry - qs.cstart;
+    const bool queued = jy >= 0 && jy < qs.clen;
+    RawLine r = read_line(cx.ln + y);
+    v4i dy = *(const v4i *)&cx.dec[queued ? jy : 0];
+    arrived(r.q[0], r.q[1], r.q[2], r.q[3], dy);
+    const NodeLine ly = as_line(r);
+    const int Jy = queued ? dy.x : -1, Ly = queued ? dy.y : -1;
+    if (lane >= cnt) y = -1;
     bool inJ = false;
     if (y >= 0) {
         if (ly.off < 0) {
@@ -1299,10 +1371,11 @@ __device__ __forceinline__ void apply_unit(const Ctx &cx, const QStep &qs, long 
             for (int t0 = 0; t0 < ly.cnt; t0 += 4) {   // four slot loads per round trip
                 int cc[4];
 #pragma unroll
-                for (int q = 0; q < 4; q++) cc[q] = t0 + q < ly.cnt ? ys[t0 + q].comm : -1;
+                for (int q = 0; q < 4; q++) cc[q] = ys[t0 + q < ly.cnt ? t0 + q : t0].comm;
+                arrived(cc[0], cc[1], cc[2], cc[3]);
 #pragma unroll
                 for (int q = 0; q < 4; q++) {
-                    const int c = cc[q];
+                    const int c = t0 + q < ly.cnt ? cc[q] : -1;
                     if (J >= 0 && c == J) {
                         inJ = true;
                         if (Jy != J && Ly != J) atomicAdd(&ys[t0 + q].in, 1);
@@ -1313,35 +1386,36 @@ __device__ __forceinline__ void apply_unit(const Ctx &cx, const QStep &qs, long 
             }
         }
     }
-    int fresh = (J >= 0 && y >= 0 && (Jy == J || (inJ && Ly != J))) ? 1 : 0;
-    fresh = wave_sum_int(fresh);
-    if (lane == 0 && J >= 0 && fresh) {
-        Slot *xs = xoff < 0 ? cx.ln[ur.x].s : cx.slot + xoff;
+    const int fresh = __popcll(__ballot(J >= 0 && y >= 0 && (Jy == J || (inJ && Ly != J))));
+    if (lane == 0 && fresh) {
+        Slot *xs = xoff < 0 ? cx.ln[x].s : cx.slot + xoff;
         if (xoff >= 0 || pos < LINE_SLOTS) atomicAdd(&xs[pos].in, fresh);
     }
     if (cx.stats) {
         const long long sc = wave_sum_i64(y >= 0 ? ly.cnt : 0);
         if (lane == 0) {
             atomicAdd(&cx.ctr->apply[LF_APPLY_IN_ITEMS], 1ull);
-            atomicAdd(&cx.ctr->apply[LF_APPLY_IN_NEIGHBOURS], (unsigned long long)ur.cnt);
+            atomicAdd(&cx.ctr->apply[LF_APPLY_IN_NEIGHBOURS], (unsigned long long)cnt);
             atomicAdd(&cx.ctr->apply[LF_APPLY_IN_SLOTS], (unsigned long long)sc);
         }
     }
 }
 
 // blocks [0, eb) edit (a thread per queued node), the rest take one in-count unit per wave
-__device__ __forceinline__ void body_apply(const Ctx &cx, const QStep &qs, int blk, int nblk, NoLds &)
+__device__ __forceinline__ void body_apply(const Ctx &cx, const QStep &qs, int blk, int nblk, EditLds &S)
 {
     (void)nblk;
-    const int eb = (qs.clen + 255) / 256;
+    const int eb = (qs.clen + EDITS - 1) / EDITS;
     if (blk < eb) {
-        apply_edit(cx, qs, blk * 256 + threadIdx.x);
+        const int lane = threadIdx.x & (WAVE - 1), wv = uni((int)threadIdx.x / WAVE);
+        constexpr int PER = EDITS / (256 / WAVE);
+        apply_edit(cx, qs, lane < PER ? blk * EDITS + wv * PER + lane : qs.clen, S);
         return;
     }
-    const long long w = (long long)(blk - eb) * (blockDim.x / WAVE) + threadIdx.x / WAVE;
+    const long long w = (long long)(blk - eb) * (256 / WAVE) + uni((int)threadIdx.x / WAVE);
     if (w < qs.un) apply_unit(cx, qs, qs.ub + w);
 }
-QUEUE_KERNELS(k_apply, 256, NoLds, body_apply)
+QUEUE_KERNELS(k_apply, 256, EditLds, body_apply)
 
 // ------------------------------------------------------------------------------------
 // exact re-sum of the touched communities
@@ -1387,6 +1461,8 @@ __device__ __forceinline__ X192 x192_from_digits24(const unsigned long long *D)
     return r;
 }
 
+#define MPAR 1
+
 // Exact re-sum of one part (one wave): the members' terms at sizes s, s+1 and s-1, and the
 // sum of their in-counts.
 __device__ __forceinline__ void refresh_part(const Ctx &cx, const PartRec &pr, int lane, int &bad)
@@ -1394,13 +1470,21 @@ __device__ __forceinline__ void refresh_part(const Ctx &cx, const PartRec &pr, i
     const int C = pr.C;
     const int k = pr.k;
     const long long base = pr.base, cap = pr.cap;
-    // size, list length and overflow after the edits, read beside the part's entries
-    const int s = cx.cr[C].s;
-    long long len = cx.cm_len[C];
-    const int ovf = cx.ovf_flag[C];
     const long long lo = (long long)k * PART;
-    int mem = lo + lane < cap ? cx.cm_node[base + lo + lane] : -1;
-    if (len > cap) len = cap;
+    // size, list length and overflow after the edits, beside the part's first members (below
+    // the list's capacity; those past its length are dropped)
+    int s = cx.cr[C].s, ovf = cx.ovf_flag[C], fill = cx.cm_len[C];
+    int y[MPAR];
+#pragma unroll
+    for (int t = 0; t < MPAR; t++) {
+        const long long i = lo + t * WAVE + lane;
+        y[t] = 0;
+        if (cap > 0) y[t] = cx.cm_node[base + (i < cap ? i : cap - 1)];
+    }
+    arrived(s, ovf, fill);
+    s = uni(s);
+    ovf = uni(ovf);
+    const long long len = uni(fill) < cap ? uni(fill) : cap;
     // the plan is from the list's length at the community's first touch; the parts that hold
     // members after the edits (the same count for every part of C: the length is final here)
     // do the re-sum, the last one with whatever joined beyond the plan
@@ -1412,17 +1496,29 @@ __device__ __forceinline__ void refresh_part(const Ctx &cx, const PartRec &pr, i
     X192 S0 = x192_zero(), Sp = x192_zero(), Sm = x192_zero();
     long long ins = 0, mslots = 0;
     long long q = lo;
-    do {                                     // a lane's 128-bit sums are folded every 64 members
+    while (q < hi) {                         // a lane's 128-bit sums are folded every 64 members
         const long long end = hi - q < 64 * WAVE ? hi : q + 64 * WAVE;
         u128 a0 = 0, ap = 0, am = 0;
         long long sumi = 0;
 #pragma unroll 1
-        for (; q < end; q += WAVE) {
-            const int y = mem;
-            mem = q + WAVE + lane < hi ? cx.cm_node[base + q + WAVE + lane] : -1;
-            if (q + lane < hi) {
-                member_terms_line(cx, y, C, s, a0, ap, am, sumi, bad);
-                if (cx.stats) mslots += cx.ln[y].cnt;
+        for (; q < end; q += MPAR * WAVE) {  // MPAR members per lane in one round trip
+            RawLine r[MPAR];
+            int nx[MPAR];
+#pragma unroll
+            for (int t = 0; t < MPAR; t++) {
+                r[t] = read_line(cx.ln + (q + t * WAVE + lane < hi ? y[t] : 0));
+                const long long i = q + (MPAR + t) * WAVE + lane;
+                nx[t] = cx.cm_node[base + (i < hi ? i : hi - 1)];
+            }
+#pragma unroll
+            for (int t = 0; t < MPAR; t++) {
+                arrived(r[t].q[0], r[t].q[1], r[t].q[2], r[t].q[3], nx[t]);
+                y[t] = nx[t];
+                const NodeLine ly = as_line(r[t]);
+                if (q + t * WAVE + lane < hi) {
+                    member_terms_of(cx, ly, C, s, a0, ap, am, sumi, bad);
+                    if (cx.stats) mslots += ly.cnt;
+                }
             }
         }
         WAVE_SYNC();
@@ -1431,7 +1527,7 @@ __device__ __forceinline__ void refresh_part(const Ctx &cx, const PartRec &pr, i
         x192_add(Sm, wave_sum_u128(am));
         ins += (long long)wave_sum_u32((unsigned)sumi & 0xffffffu) +
                ((long long)wave_sum_u32((unsigned)(sumi >> 24)) << 24);
-    } while (q < hi);
+    }
     if (cx.stats) {
         mslots = wave_sum_i64(mslots);
         if (lane == 0) {
@@ -1494,22 +1590,39 @@ union StepLds {
 __device__ __forceinline__ void body_refresh(const Ctx &cx, const QStep &qs, int blk, int nblk, StepLds &L)
 {
     (void)nblk;
-    const int wv = threadIdx.x / WAVE, lane = threadIdx.x & (WAVE - 1);
+    const int wv = uni((int)threadIdx.x / WAVE), lane = threadIdx.x & (WAVE - 1);
     int b = blk;
     if (b < qs.rb) {
         const long long nw = (long long)qs.rb * (GT / WAVE);
         int bad = 0;
         long long p = (long long)b * (GT / WAVE) + wv;
         // the wave's first part is read beside the count (the buffer holds part_cap records)
-        PartRec pr;
-        if (p < cx.part_cap) pr = cx.part_rec[p];
-        int count = __atomic_load_n(&cx.ctr->parts_total, __ATOMIC_RELAXED);
+        int count = cx.ctr->parts_total;
+        v4i a0 = {0, 0, -1, 0}, a1 = {0, 0, 0, 0};
+        if (p < cx.part_cap) {
+            const v4i *q = (const v4i *)&cx.part_rec[p];
+            a0 = q[0];
+            a1 = q[1];
+        }
+        arrived(count, a0, a1);
+        count = uni(count);
         if (count > cx.part_cap) count = cx.part_cap;
         while (p < count) {
+            PartRec pr;
+            pr.base = ((long long)uni(a0.y) << 32) | (unsigned)uni(a0.x);
+            pr.C = uni(a0.z);
+            pr.k = uni(a0.w);
+            pr.parts = uni(a1.x);
+            pr.cap = uni(a1.y);
+            pr.ms = uni(a1.z);
             if (pr.C >= 0 && pr.C < cx.K) refresh_part(cx, pr, lane, bad);   // else: after a flagged overflow
             WAVE_SYNC();
             p += nw;
-            if (p < count) pr = cx.part_rec[p];
+            if (p < count) {
+                const v4i *q = (const v4i *)&cx.part_rec[p];
+                a0 = q[0];
+                a1 = q[1];
+            }
         }
         if (bad) atomicOr(&cx.ctr->error, LF_DEVERR_INEXACT);
         return;
@@ -2364,7 +2477,7 @@ void lf_queue_params(lf_handle *h, long long k, long long nq, long long qq, bool
     g->big = heavy + (fuse ? light : 0);
     if (g->big < 1 && g->eval == 0) g->big = 1;   // block 0 resets the queue's counters
     g->tie = (int)grid_for(br.nt, GT / WAVE);
-    g->apply = (int)grid_for(clen, 256) + (int)grid_for(qs->un, 256 / WAVE);
+    g->apply = (int)grid_for(clen, EDITS) + (int)grid_for(qs->un, 256 / WAVE);
 }
 
 // the kernels of one queue of one graph, in order, on the handle's stream

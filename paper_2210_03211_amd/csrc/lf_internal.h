@@ -51,7 +51,7 @@ struct UnitRec {
 // One re-sum part: up to PART entries of a touched community's member list, planned at
 // the community's first touch in a queue from the list's capacity (fixed within an
 // iteration); size, list length and overflow are read when the part is summed.
-struct PartRec {
+struct __align__(16) PartRec {     // read as two 16-byte words
     long long base;          // the community's member-list offset
     int C;                   // the community (-1: an empty record after a flagged overflow)
     int k, parts;            // this part and the community's number of parts

@@ -71,19 +71,54 @@ __device__ __forceinline__ void store_comm(const Ctx &cx, int C, int s, X192 a0,
     cx.tflag[C] = 0;
 }
 
+// Values read together: without this the compiler moves a read behind the branches that do not
+// need it, where it is a round trip of its own.  All the operands have arrived behind it.
+template <class A>
+__device__ __forceinline__ void arrived(A &a) { asm volatile("" : "+v"(a)); }
+template <class A, class B>
+__device__ __forceinline__ void arrived(A &a, B &b) { asm volatile("" : "+v"(a), "+v"(b)); }
+template <class A, class B, class C>
+__device__ __forceinline__ void arrived(A &a, B &b, C &c) { asm volatile("" : "+v"(a), "+v"(b), "+v"(c)); }
+template <class A, class B, class C, class D>
+__device__ __forceinline__ void arrived(A &a, B &b, C &c, D &d)
+{
+    asm volatile("" : "+v"(a), "+v"(b), "+v"(c), "+v"(d));
+}
+template <class A, class B, class C, class D, class E>
+__device__ __forceinline__ void arrived(A &a, B &b, C &c, D &d, E &e)
+{
+    asm volatile("" : "+v"(a), "+v"(b), "+v"(c), "+v"(d), "+v"(e));
+}
+
+typedef int v4i __attribute__((ext_vector_type(4)));
+
+// a node's line in four 16-byte reads; valid once all four have arrived
+struct RawLine {
+    v4i q[4];
+};
+
+__device__ __forceinline__ RawLine read_line(const NodeLine *p)
+{
+    const v4i *v = (const v4i *)p;
+    return RawLine{{v[0], v[1], v[2], v[3]}};
+}
+
+__device__ __forceinline__ NodeLine as_line(const RawLine &r) { return __builtin_bit_cast(NodeLine, r); }
+
 // position of community c among a node's cnt slots (-1 if absent); *in gets its in-count
 __device__ __forceinline__ int find_slot_in(const Slot *slot, long long off, int cnt, int c, int *in)
 {
     for (int t = 0; t < cnt; t += 4) {         // four independent loads per round trip
-        const Slot s0 = slot[off + t];
-        Slot s1 = {-2, 0}, s2 = {-2, 0}, s3 = {-2, 0};
-        if (t + 1 < cnt) s1 = slot[off + t + 1];
-        if (t + 2 < cnt) s2 = slot[off + t + 2];
-        if (t + 3 < cnt) s3 = slot[off + t + 3];
-        if (s0.comm == c) { *in = s0.in; return t; }
-        if (s1.comm == c) { *in = s1.in; return t + 1; }
-        if (s2.comm == c) { *in = s2.in; return t + 2; }
-        if (s3.comm == c) { *in = s3.in; return t + 3; }
+        long long w[4];
+#pragma unroll
+        for (int k = 0; k < 4; k++) w[k] = *(const long long *)&slot[off + (t + k < cnt ? t + k : t)];
+        arrived(w[0], w[1], w[2], w[3]);
+#pragma unroll
+        for (int k = 0; k < 4; k++)
+            if ((int)w[k] == c) {
+                *in = (int)(w[k] >> 32);
+                return t + k;
+            }
     }
     return -1;
 }
@@ -259,13 +294,20 @@ __device__ __forceinline__ int line_find(const Ctx &cx, const NodeLine &l, int c
 }
 
 // member_terms on the membership lines
-__device__ __forceinline__ void member_terms_line(const Ctx &cx, int y, int C, int s, u128 &a0, u128 &ap,
-                                                  u128 &am, long long &sumi, int &bad)
+__device__ __forceinline__ void member_terms_of(const Ctx &cx, const NodeLine &ly, int C, int s, u128 &a0, u128 &ap,
+                                                u128 &am, long long &sumi, int &bad)
 {
-    const NodeLine ly = cx.ln[y];
     int in = 0;
     if (line_find(cx, ly, C, &in) < 0) return;   // left C earlier in this iteration
     member_add(in, ly.deg, s, a0, ap, am, sumi, bad);
+}
+
+__device__ __forceinline__ void member_terms_line(const Ctx &cx, int y, int C, int s, u128 &a0, u128 &ap,
+                                                  u128 &am, long long &sumi, int &bad)
+{
+    RawLine r = read_line(cx.ln + y);
+    arrived(r.q[0], r.q[1], r.q[2], r.q[3]);
+    member_terms_of(cx, as_line(r), C, s, a0, ap, am, sumi, bad);
 }
 
 // The lanes executing this call with want = true receive consecutive indices from *ctr,

@@ -73,3 +73,75 @@ def test_batch_sizes(lf, orc, members, replay):
         h.close()
         o.close()
     b.close()
+
+
+def cover(lists):
+    off = np.zeros(len(lists) + 1, np.int64)
+    off[1:] = np.cumsum([len(p) for p in lists])
+    return off, np.concatenate([np.asarray(p, np.int32) for p in lists]).astype(np.int32)
+
+
+def warm_run(lf, orc, g, lists, K, q, iters, opts=None):
+    off, ids = cover(lists)
+    h = lf.Handle(0)
+    for k, v in (opts or {}).items():
+        h.lf_set_option(k, v)
+    import torch
+    h.load_graph(g.n, torch.from_numpy(g.src).cuda(), torch.from_numpy(g.dst).cuda())
+    h.init_from_memberships(off, ids, K)
+    o = orc.Oracle()
+    o.load_graph(g.n, g.src, g.dst)
+    o.init_from_memberships(off, ids, K)
+    same_hist(h.run_iterations(q, 0.0, iters), o.run_iterations(q, 0.0, iters))
+    same_state(h, o)
+    o.close()
+    h.close()
+
+
+@pytest.mark.parametrize("size,q", [(64, 16), (65, 16), (511, 7), (512, 64), (513, 64), (1100, 300), (1100, 1600)])
+def test_community_parts(lf, orc, size, q):
+    """Communities of one size, dense enough inside that members stay and others join."""
+    say("parts", size, q)
+    rng = np.random.default_rng(size)
+    n = 3 * size if size > 200 else 20 * size
+    home = np.arange(n) // size
+    a = rng.integers(0, n, 12 * n)
+    inside = home[a] * size + rng.integers(0, size, a.size)
+    b = np.where(rng.random(a.size) < 0.8, np.minimum(inside, n - 1), rng.integers(0, n, a.size))
+    g = G.Graph(n, a.astype(np.int64), b.astype(np.int64))
+    K = int(home.max()) + 2
+    lists = [[int(home[x])] if rng.random() < 0.9 else [K - 1] for x in range(n)]
+    warm_run(lf, orc, g, lists, K, q, 3)
+    warm_run(lf, orc, g, lists, K, q, 2, {"refresh_blocks": 1})
+
+
+@pytest.mark.parametrize("most", [5, 6, 7, 13, 254, 255, 300])
+def test_many_memberships(lf, orc, most):
+    """Nodes with up to `most` memberships, inline and beyond the line, some of which they
+    leave while their neighbours read them, over several iterations."""
+    say("memberships", most)
+    rng = np.random.default_rng(most)
+    g = G.random_gnp(300, 0.08, most)
+    K = 2 * most + 20
+    count = np.where(rng.random(g.n) < 0.1, most, rng.integers(1, 4, g.n))
+    count[rng.random(g.n) < 0.1] = max(1, most - 1)
+    lists = [rng.choice(K, c, replace=False) for c in count]
+    warm_run(lf, orc, g, lists, K, 32, 4)
+
+
+@pytest.mark.parametrize("n,d", [(17000, 5), (9000, 60)])
+def test_one_queue_without_lists(lf, orc, n, d):
+    """All nodes in one queue, enough blocks that it is gathered and scored in one launch."""
+    say("whole", n, d)
+    rng = np.random.default_rng(n)
+    a = np.repeat(np.arange(n), d // 2 + 1)
+    b = (a + rng.integers(1, 3 * d, a.size)) % n
+    g = G.Graph(n, a.astype(np.int64), b.astype(np.int64))
+    h = loaded(lf, g).init_communities()
+    o = orc.Oracle()
+    o.load_graph(g.n, g.src, g.dst)
+    o.init_communities()
+    same_hist(h.run_iterations(n, 0.0, 3), o.run_iterations(n, 0.0, 3))
+    same_state(h, o)
+    h.close()
+    o.close()
