@@ -3,7 +3,8 @@
     python -m paper_2210_03211_amd.build          # compile every source, link the library
 
 Every HIP source is compiled for gfx950 with FMA contraction off (the decision arithmetic
-must round exactly like its definition) and packed-FP32 instructions disabled.
+must round exactly like its definition), packed-FP32 instructions disabled and a kernel's
+leading scalar arguments put into registers by its dispatch.
 """
 from __future__ import annotations
 
@@ -23,6 +24,7 @@ ARCH = os.environ.get("LF_OFFLOAD_ARCH", "gfx950")
 FLAGS = [
     "--offload-arch=" + ARCH, "-O3", "-fPIC", "-std=c++17", "-ffp-contract=off",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    "-mllvm", "-amdgpu-kernarg-preload-count=14",
     "-Wno-unused-result", "-I", os.path.join(ROOT, "include"), "-I", CSRC,
 ]
 
