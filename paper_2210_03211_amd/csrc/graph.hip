@@ -391,20 +391,20 @@ __device__ __forceinline__ void wcc_hit(const WccTri &wt, int u, int v, int w, l
 // Nearly all probes miss.  A bit per hash of N+(u)'s members (one LDS read) turns most of them
 // away; the rest are queued per wave, and only a full wave of them does the binary search, so
 // that its log2(m) dependent LDS reads are paid by 64 likely hits at a time instead of by
-// every probe.  k_tri_group on 1M nodes, 39M edges: 13.2 -> 5.2 ms.  (A hash table instead,
-// probed until an empty entry, was slower than the plain binary search, 88 against 40 ms in
-// k_tri_wave: each step lasts as long as the longest run among 64 lanes.)
+// every probe.  (A hash table instead, probed until an empty entry, was slower than the plain
+// binary search, 88 against 40 ms: each step lasts as long as the longest run among 64 lanes.)
 __device__ __forceinline__ unsigned tri_hash(int v, int lg) { return (unsigned)v * 0x9E3779B1u >> (32 - lg); }
 
-template <bool WCC>
+template <bool WCC, class J>             // J holds an index in N+(u)
 struct TriQueue {
-    int w[2 * WAVE], j[2 * WAVE];
+    int w[2 * WAVE];
     long long e[WCC ? 2 * WAVE : 1];
+    J j[2 * WAVE];
 };
 
 // up to 64 queued probes of one wave: (list index j of v, third corner w, its edge e)
-template <bool WCC>
-__device__ __forceinline__ int tri_drain(TriQueue<WCC> &Q, int n, int lane, int u, long long b, const int *nbr, int m,
+template <bool WCC, class J>
+__device__ __forceinline__ int tri_drain(TriQueue<WCC, J> &Q, int n, int lane, int u, long long b, const int *nbr, int m,
                                          int *cnt, const WccTri &wt)
 {
     int hit = 0;
@@ -425,21 +425,21 @@ __device__ __forceinline__ int tri_drain(TriQueue<WCC> &Q, int n, int lane, int 
 }
 
 // queue the probes of a wave's lanes that pass the filter; a full wave of them is drained
-template <bool WCC>
-__device__ __forceinline__ int tri_push(TriQueue<WCC> &Q, int &qn, bool cand, int w, int j, long long e, int lane, int u,
+template <bool WCC, class J>
+__device__ __forceinline__ int tri_push(TriQueue<WCC, J> &Q, int &qn, bool cand, int w, int j, long long e, int lane, int u,
                                         long long b, const int *nbr, int m, int *cnt, const WccTri &wt)
 {
     const unsigned long long mask = __ballot(cand);
     if (cand) {
         const int at = qn + __popcll(mask & ((1ull << lane) - 1));
         Q.w[at] = w;
-        Q.j[at] = j;
+        Q.j[at] = (J)j;
         if constexpr (WCC) Q.e[at] = e;
     }
     qn += __popcll(mask);
     WAVE_SYNC();
     if (qn < WAVE) return 0;
-    const int hit = tri_drain<WCC>(Q, WAVE, lane, u, b, nbr, m, cnt, wt);
+    const int hit = tri_drain(Q, WAVE, lane, u, b, nbr, m, cnt, wt);
     qn -= WAVE;
     WAVE_SYNC();
     if (lane < qn) {
@@ -452,36 +452,99 @@ __device__ __forceinline__ int tri_push(TriQueue<WCC> &Q, int &qn, bool cand, in
 }
 
 #define TRI_WAVE_CAP 256
+#define TRI_GROUP 512           // threads per longer out-list
 #define TRI_GROUP_BITS 16       // filter bits per workgroup
-#define TRI_WAVES 4
+#define TRI_WAVE_BITS 12        // per wave of the short out-lists
+#define TRI_GW 16               // lanes per list of theirs
+#define TRI_PER 4               // entries per lane
+#define TRI_WAVES 1
 
-// the wave's bitwise or of x (every lane active)
-__device__ __forceinline__ unsigned op_or(unsigned a, unsigned b) { return a | b; }
-__device__ __forceinline__ unsigned wave_or_u32(unsigned x)
+// four entries of an out-list from p on (the array is padded by as many)
+__device__ __forceinline__ v4i read_entries(const int *p)
 {
-    DPP_INCLUSIVE(x, op_or);
-    return (unsigned)__builtin_amdgcn_readlane((int)x, WAVE - 1);
+    v4i r;
+    __builtin_memcpy(&r, p, sizeof r);
+    return r;
 }
 
-// one wave per node with |N+(u)| <= TRI_WAVE_CAP; longer out-lists are deferred.  The waves
-// of a block share nothing and never meet: with block barriers around the probe loop a
-// block lasted as long as the heaviest of its four nodes.  Probes are taken 64 at a time;
-// which out-neighbour's list a lane is in follows from one mask of the list starts within
-// the 64 (empty lists are left out) instead of a binary search per probe.  What bounds it is
-// the search of w in N+(u), log2(m) dependent LDS reads.  Measured: 4M nodes, 35M edges
-// 11.1 -> 8.7 ms; 1M nodes, 39M edges, dense 54.4 -> 39.7 ms.  With k_tri_group's filter and
-// queue here too: 9.4 and 37.1 ms, their LDS leaving fewer waves on a CU.
+// A wave probes the lists k = first, first + stride, .. < ns of one node u: TRI_GW lanes walk one
+// list at a time, TRI_PER entries each, and take the next one that is left when theirs ends; the
+// next entries are read before these are tested, and a test is one filter bit.  range(k, e0, e1)
+// gives a list's entries [e0, e1), index(k) its node's place in N+(u).
+template <bool WCC, class J, class Range, class Index>
+__device__ __forceinline__ int tri_walk(const int *orc, int first, int stride, int ns, Range range, Index index,
+                                        const unsigned *bits, int lg, TriQueue<WCC, J> &Q, int lane, int u, long long b,
+                                        const int *nbr, int m, int *cnt, const WccTri &wt)
+{
+    const int gl = TRI_PER * (lane & (TRI_GW - 1));
+    const unsigned long long before = (1ull << (lane & ~(TRI_GW - 1))) - 1;
+    int total = 0, qn = 0, taken = WAVE / TRI_GW, k = first + stride * (lane / TRI_GW);
+    int e = 0, e1 = 0;                      // (a group without a list has nothing to test)
+    if (k < ns) {
+        range(k, e, e1);
+        e += gl;
+    }
+    v4i w = read_entries(orc + (e < e1 ? e : 0));
+    while (__ballot(k < ns)) {
+        int en = e + TRI_PER * TRI_GW, e1n = e1, kn = k;
+        const bool need = k < ns && en - gl >= e1;
+        const unsigned long long nm = __ballot(need && gl == 0);
+        if (nm) {
+            if (need) {
+                kn = first + stride * (taken + __popcll(nm & before));
+                en = e1n = 0;
+                if (kn < ns) {
+                    range(kn, en, e1n);
+                    en += gl;
+                }
+            }
+            taken += __popcll(nm);
+        }
+        const v4i wn = read_entries(orc + (en < e1n ? en : 0));
+        unsigned word[TRI_PER], hw[TRI_PER];
+#pragma unroll
+        for (int t = 0; t < TRI_PER; t++) {
+            hw[t] = tri_hash(w[t], lg);
+            word[t] = bits[hw[t] >> 5];
+        }
+#pragma unroll
+        for (int t = 0; t < TRI_PER; t++) {
+            const bool cand = e + t < e1 && (word[t] >> (hw[t] & 31) & 1);
+            if (__ballot(cand)) {
+                const int j = cand ? index(k) : 0;
+                total += tri_push(Q, qn, cand, w[t], j, e + t, lane, u, b, nbr, m, cnt, wt);
+            }
+        }
+        k = kn;
+        e = en;
+        e1 = e1n;
+        w = wn;
+    }
+    return total + tri_drain(Q, qn, lane, u, b, nbr, m, cnt, wt);
+}
+
+// One wave, a block of its own, per node with |N+(u)| <= TRI_WAVE_CAP; longer out-lists are
+// deferred.  What bounds it is the work per probe (7G probes on the dense graph below), and for
+// graphs of short lists the chain oro -> orc -> oro -> orc of a node, so that as many waves as
+// fit should be resident: 5 KB of LDS each, and no wave waits for another of its block.  1M nodes,
+// 33M edges, dense: 39.7 ms with a search of N+(u) per probe; 20.2 with the walk at one entry
+// per lane, 11.5 at four, 10.1 with 20 KB instead of 25.6 per block of four waves, 7.5 with two
+// waves per block, 6.1 with one.  4M nodes, 35M edges: 8.7 -> 2.9 ms; the pass of the exact WCC, 1M
+// nodes, 8M edges: 2.6 -> 0.95 ms.
 // WCC = false: triangle counts per node into tri; true: wcc_hit per triangle instead.
 template <bool WCC>
-__global__ void __launch_bounds__(256) k_tri_wave(const long long *oro, const int *orc, long long n,
+__global__ void __launch_bounds__(TRI_WAVES * WAVE) k_tri_wave(const long long *oro, const int *orc, long long n,
                                                   unsigned long long *tri, int *defer, int *ndefer, WccTri wt)
 {
     __shared__ int s_nbr[TRI_WAVES][TRI_WAVE_CAP];
-    __shared__ int s_pre[TRI_WAVES][TRI_WAVE_CAP];
-    __shared__ int s_cnt[TRI_WAVES][TRI_WAVE_CAP];
-    __shared__ short s_seg[TRI_WAVES][TRI_WAVE_CAP];
-    int wv = threadIdx.x / WAVE, lane = threadIdx.x & (WAVE - 1);
-    long long u = blockIdx.x * (long long)TRI_WAVES + wv;
+    __shared__ int s_cnt[TRI_WAVES][WCC ? 1 : TRI_WAVE_CAP];
+    __shared__ int s_start[TRI_WAVES][TRI_WAVE_CAP];
+    __shared__ unsigned short s_len[TRI_WAVES][TRI_WAVE_CAP];
+    __shared__ unsigned char s_seg[TRI_WAVES][TRI_WAVE_CAP];
+    __shared__ unsigned s_bits[TRI_WAVES][(1 << TRI_WAVE_BITS) / 32];
+    __shared__ TriQueue<WCC, unsigned char> s_q[TRI_WAVES];
+    const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x / WAVE), lane = threadIdx.x & (WAVE - 1);
+    const long long u = blockIdx.x * (long long)TRI_WAVES + wv;
     long long b = 0;
     int m = 0;
     if (u < n) {
@@ -492,62 +555,47 @@ __global__ void __launch_bounds__(256) k_tri_wave(const long long *oro, const in
         if (lane == 0) defer[atomicAdd(ndefer, 1)] = (int)u;
         m = 0;
     }
-    if (m < 2) m = 0;                      // a triangle needs two out-neighbours of u
-    int *nbr = s_nbr[wv], *pre = s_pre[wv], *cnt = s_cnt[wv];
-    short *seg = s_seg[wv];
-    // stage N+(u); the non-empty N+(v): their index in N+(u) and first probe
-    int W = 0, ns = 0;                      // probes, non-empty lists
+    if (m < 2) return;                     // a triangle needs two out-neighbours of u
+    int *nbr = s_nbr[wv], *cnt = s_cnt[wv];
+    int *start = s_start[wv];
+    unsigned short *len = s_len[wv];
+    unsigned char *seg = s_seg[wv];
+    unsigned *bits = s_bits[wv];
+    TriQueue<WCC, unsigned char> &Q = s_q[wv];
+    for (int t = lane; t < (1 << TRI_WAVE_BITS) / 32; t += WAVE) bits[t] = 0;
+    WAVE_SYNC();
+    // stage N+(u) and its filter; the non-empty N+(v): first entry (below 2^30, as 2|E| < 2^31),
+    // length (below 2^16: its members have as many neighbours each) and index in N+(u)
+    int ns = 0;
     for (int base = 0; base < m; base += WAVE) {
         const int j = base + lane;
-        int len = 0;
+        int r0 = 0, r1 = 0;
         if (j < m) {
             const int v = orc[b + j];
             nbr[j] = v;
-            cnt[j] = 0;
-            len = (int)(oro[v + 1] - oro[v]);
+            if constexpr (!WCC) cnt[j] = 0;
+            const unsigned hv = tri_hash(v, TRI_WAVE_BITS);
+            atomicOr(&bits[hv >> 5], 1u << (hv & 31));
+            r0 = (int)oro[v];
+            r1 = (int)oro[v + 1];
         }
-        int tot;
-        const int incl = wave_incl_scan(len, &tot);
-        const unsigned long long has = __ballot(len > 0);
-        if (len > 0) {
+        const unsigned long long has = __ballot(r1 > r0);
+        if (r1 > r0) {
             const int k = ns + __popcll(has & ((1ull << lane) - 1));
-            pre[k] = W + incl - len;
-            seg[k] = (short)j;
+            start[k] = r0;
+            len[k] = (unsigned short)(r1 - r0);
+            seg[k] = (unsigned char)j;
         }
-        W += tot;
         ns += __popcll(has);
     }
     WAVE_SYNC();
-    int total = 0;
-    int s0 = 0;                             // list of the chunk's first probe
-    for (int f0 = 0; f0 < W; f0 += WAVE) {  // same trip count on every lane
-        // list starts after f0 within the chunk: at most 63 of them, in lists s0 + 1 ..
-        const int q = s0 + 1 + lane;
-        const int at = q < ns ? pre[q] - f0 : WAVE;
-        const unsigned lo = wave_or_u32(at < 32 ? 1u << at : 0u);
-        const unsigned hi = wave_or_u32(at >= 32 && at < WAVE ? 1u << (at - 32) : 0u);
-        const unsigned long long starts = ((unsigned long long)hi << 32) | lo;
-        const int f = f0 + lane;
-        if (f < W) {
-            const int s = s0 + __popcll(starts & ((2ull << lane) - 1));
-            const int j = seg[s], v = nbr[j];
-            const long long evw = oro[v] + (f - pre[s]);
-            const int w = orc[evw];
-            const int p = lds_find(nbr, m, w);
-            if (p >= 0) {
-                if constexpr (WCC) {
-                    wcc_hit(wt, (int)u, v, w, b + j, b + p, evw);
-                } else {
-                    atomicAdd(&cnt[p], 1);
-                    atomicAdd(&cnt[j], 1);
-                    total++;
-                }
-            }
-        }
-        s0 += __popcll(starts);
-        // the next chunk may open exactly at a list's start
-        if (s0 + 1 < ns && pre[s0 + 1] == f0 + WAVE) s0++;
-    }
+    if (ns == 0) return;
+    auto range = [&](int k, int &e0, int &e1) {
+        e0 = start[k];
+        e1 = e0 + len[k];
+    };
+    auto index = [&](int k) { return (int)seg[k]; };
+    int total = tri_walk(orc, 0, 1, ns, range, index, bits, TRI_WAVE_BITS, Q, lane, (int)u, b, nbr, m, cnt, wt);
     WAVE_SYNC();
     if constexpr (!WCC) {
         for (int j = lane; j < m; j += WAVE)
@@ -557,12 +605,13 @@ __global__ void __launch_bounds__(256) k_tri_wave(const long long *oro, const in
     }
 }
 
-// one workgroup per deferred node; out-list and counters in LDS when they fit (LDS sized for
-// the longest out-list, so that two workgroups share a CU), otherwise in this workgroup's slice
-// of global scratch.  A wave takes one N+(v) at a time (those of a hub's out-neighbours are
-// long).
+// One workgroup per deferred node; out-list and counters in LDS when they fit (LDS sized for
+// the longest out-list, so that several workgroups share a CU), otherwise in this workgroup's
+// slice of global scratch.  Its waves walk every eighth list each.  8,263 nodes of 257 to 682
+// out-neighbours (the dense graph above): a list per wave with a search per probe 13.2 ms, with
+// the filter 5.2, this walk 4.1 with 1,024 threads, 3.2 with 512, 3.4 with 256.
 template <bool WCC>
-__global__ void __launch_bounds__(1024) k_tri_group(const long long *oro, const int *orc,
+__global__ void __launch_bounds__(TRI_GROUP) k_tri_group(const long long *oro, const int *orc,
                                                     const int *list, int nlist,
                                                     unsigned long long *tri, int lds_cap,
                                                     int *gscratch, long long gslice, WccTri wt)
@@ -570,7 +619,7 @@ __global__ void __launch_bounds__(1024) k_tri_group(const long long *oro, const 
     extern __shared__ int s_dyn[];
     __shared__ int s_total;
     __shared__ unsigned bits[(1 << TRI_GROUP_BITS) / 32];
-    __shared__ TriQueue<WCC> s_q[1024 / WAVE];
+    __shared__ TriQueue<WCC, int> s_q[TRI_GROUP / WAVE];
     const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x / WAVE, nw = blockDim.x / WAVE;
     for (int it = blockIdx.x; it < nlist; it += gridDim.x) {
         int u = list[it];
@@ -579,7 +628,7 @@ __global__ void __launch_bounds__(1024) k_tri_group(const long long *oro, const 
         const bool lds = m <= lds_cap;
         int *nbr = lds ? s_dyn : gscratch + (long long)blockIdx.x * gslice;
         int *cnt = lds ? s_dyn + lds_cap : nbr + m;
-        TriQueue<WCC> &Q = s_q[wv];
+        TriQueue<WCC, int> &Q = s_q[wv];
         if (threadIdx.x == 0) s_total = 0;
         for (int t = threadIdx.x; t < (1 << TRI_GROUP_BITS) / 32; t += blockDim.x) bits[t] = 0;
         __syncthreads();
@@ -591,24 +640,13 @@ __global__ void __launch_bounds__(1024) k_tri_group(const long long *oro, const 
             atomicOr(&bits[hv >> 5], 1u << (hv & 31));
         }
         __syncthreads();
-        int total = 0, qn = 0;
-        for (int j = wv; j < m; j += nw) {
-            const int v = nbr[j];
-            const long long e1 = oro[v + 1];
-            for (long long e0 = oro[v]; e0 < e1; e0 += WAVE) {
-                const long long evw = e0 + lane;
-                bool cand = false;
-                int w = 0;
-                if (evw < e1) {
-                    w = orc[evw];
-                    const unsigned hw = tri_hash(w, TRI_GROUP_BITS);
-                    cand = (bits[hw >> 5] >> (hw & 31)) & 1;
-                }
-                WAVE_SYNC();
-                total += tri_push<WCC>(Q, qn, cand, w, j, evw, lane, u, b, nbr, m, cnt, wt);
-            }
-        }
-        total += tri_drain<WCC>(Q, qn, lane, u, b, nbr, m, cnt, wt);
+        auto range = [&](int k, int &e0, int &e1) {
+            const int v = nbr[k];
+            e0 = (int)oro[v];
+            e1 = (int)oro[v + 1];
+        };
+        auto index = [](int k) { return k; };
+        int total = tri_walk(orc, wv, nw, m, range, index, bits, TRI_GROUP_BITS, Q, lane, u, b, nbr, m, cnt, wt);
         WAVE_SYNC();
         if constexpr (!WCC) {
             total = wave_sum_int(total);
@@ -786,7 +824,7 @@ int lf_triangle_pass(lf_handle *h, const WccTri *wt, int *launches, long long **
     int *cnt = nullptr;
     LF_TRY(lf_tmp_alloc(h, (void **)&od, sizeof(int) * (n > 0 ? n : 1)));
     LF_TRY(lf_tmp_alloc(h, (void **)&oro, sizeof(long long) * (n + 1)));
-    LF_TRY(lf_tmp_alloc(h, (void **)&orc, sizeof(int) * (h->ne > 0 ? h->ne : 1)));
+    LF_TRY(lf_tmp_alloc(h, (void **)&orc, sizeof(int) * (h->ne + TRI_PER)));   // (read_entries)
     LF_TRY(lf_tmp_alloc(h, (void **)&defer, sizeof(int) * (n > 0 ? n : 1)));
     LF_TRY(lf_tmp_alloc(h, (void **)&cnt, sizeof(int) * 4));
     LF_HIP(h, hipMemsetAsync(cnt, 0, sizeof(int) * 4, st));
@@ -821,7 +859,8 @@ int lf_triangle_pass(lf_handle *h, const WccTri *wt, int *launches, long long **
         int lds_cap = (maxdev - 49152) / (2 * (int)sizeof(int));
         if (maxod < lds_cap) lds_cap = maxod;
         if (h->tri_lds_cap > 0 && h->tri_lds_cap < lds_cap) lds_cap = h->tri_lds_cap;
-        int blocks = ndefer < 1024 ? ndefer : 1024;
+        const int most = maxod > lds_cap ? 1024 : 8192;    // (a slice of scratch each past the cap)
+        const int blocks = ndefer < most ? ndefer : most;
         int *gs = nullptr;
         long long gslice = 2ll * maxod + 2;
         if (maxod > lds_cap) LF_TRY(lf_tmp_alloc(h, (void **)&gs, sizeof(int) * gslice * blocks));
@@ -829,10 +868,10 @@ int lf_triangle_pass(lf_handle *h, const WccTri *wt, int *launches, long long **
         const void *fn = wt ? (const void *)k_tri_group<true> : (const void *)k_tri_group<false>;
         LF_HIP(h, hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem));
         if (wt)
-            hipLaunchKernelGGL(k_tri_group<true>, dim3(blocks), dim3(1024), shmem, st, oro, orc, defer, ndefer,
+            hipLaunchKernelGGL(k_tri_group<true>, dim3(blocks), dim3(TRI_GROUP), shmem, st, oro, orc, defer, ndefer,
                                h->tri, lds_cap, gs, gslice, w);
         else
-            hipLaunchKernelGGL(k_tri_group<false>, dim3(blocks), dim3(1024), shmem, st, oro, orc, defer, ndefer,
+            hipLaunchKernelGGL(k_tri_group<false>, dim3(blocks), dim3(TRI_GROUP), shmem, st, oro, orc, defer, ndefer,
                                h->tri, lds_cap, gs, gslice, w);
         LF_HIP(h, hipGetLastError());
         LF_HIP(h, hipStreamSynchronize(st));
