@@ -41,32 +41,110 @@ static inline unsigned grid_for(long long n, int block) { return (unsigned)((n +
 // ------------------------------------------------------------------------------------
 // A3: initial clustering
 // ------------------------------------------------------------------------------------
-// state: 0 undecided, 1 opener, 2 joins an opener
-__global__ void k_lfmis_round(const long long *rowptr, const int *col, const int *col_rank, const int *rank,
-                              long long n, int *state, int *cursor, int *undecided)
+// state: 0 undecided, 1 opener, 2 joins an opener.  An undecided node looks at its neighbours
+// earlier in the order from where it stopped last: an opener among them decides it, the first
+// undecided one ends the round for it, and when none is left it opens.  A thread looks at
+// LFMIS_OWN neighbours, four per round trip; the wave takes over the nodes that have more, 256
+// neighbours per round trip.  A state read from the cache may be older than the round, which
+// only delays the node.  Whether any node is left is a plain store: counted with an atomic per
+// wave on one address, a round took as long as 15,600 of them in a row.  1M nodes, 8M edges:
+// 195 us for each of 15 rounds -> 81 us for the first and less for each after it, all of
+// them 2.8 -> 0.44 ms; 4M nodes, 35M edges 5.0 -> 1.4 ms.
+#define LFMIS_OWN 16
+__device__ __forceinline__ int lfmis_state(const int *state, int y)
 {
-    int cnt = 0;
-    for (long long x = blockIdx.x * (long long)blockDim.x + threadIdx.x; x < n;
-         x += (long long)gridDim.x * blockDim.x) {
-        if (__atomic_load_n(&state[x], __ATOMIC_RELAXED) != 0) continue;
-        int rx = rank[x];
-        long long b = rowptr[x], e = rowptr[x + 1];
-        long long c = b + cursor[x];
-        int mine = 0;
+    return __hip_atomic_load(&state[y], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+__global__ void __launch_bounds__(256) k_lfmis_round(const long long *rowptr, const int *col, const int *col_rank,
+                                                     const int *rank, long long n, int *state, int *cursor,
+                                                     int *undecided)
+{
+    const int lane = threadIdx.x & (WAVE - 1);
+    bool left = false;
+    for (long long x0 = blockIdx.x * (long long)blockDim.x + (threadIdx.x - lane); x0 < n;
+         x0 += (long long)gridDim.x * blockDim.x) {
+        const long long x = x0 + lane;
+        const bool open = x < n && lfmis_state(state, (int)x) == 0;
+        if (!__ballot(open)) continue;
+        int rx = 0, mine = 0;
+        long long b = 0, c = 0, e = 0;
         bool pending = false;
-        for (; c < e; c++) {
-            if (col_rank[c] >= rx) continue;
-            int sy = __atomic_load_n(&state[col[c]], __ATOMIC_RELAXED);
-            if (sy == 1) { mine = 2; break; }
-            if (sy == 0) { pending = true; break; }
+        if (open) {
+            rx = rank[x];
+            b = rowptr[x];
+            e = rowptr[x + 1];
+            c = b + cursor[x];
         }
-        cursor[x] = (int)(c - b);
-        if (mine == 0 && !pending) mine = 1;
-        if (mine) __atomic_store_n(&state[x], mine, __ATOMIC_RELAXED);
-        else cnt++;
+        const long long own = c + LFMIS_OWN < e ? c + LFMIS_OWN : e;
+        while (c < own && mine == 0 && !pending) {
+            int ry[4], sy[4];
+#pragma unroll
+            for (int k = 0; k < 4; k++) {
+                const long long q = c + k < own ? c + k : own - 1;
+                ry[k] = col_rank[q];
+                sy[k] = lfmis_state(state, col[q]);
+            }
+            long long next = c + 4 < own ? c + 4 : own;
+#pragma unroll
+            for (int k = 3; k >= 0; k--) {       // the first undecided one, unless an opener is among them
+                if (c + k >= own || ry[k] >= rx) continue;
+                if (sy[k] == 1) mine = 2;
+                if (sy[k] == 0) {
+                    pending = true;
+                    next = c + k;
+                }
+            }
+            if (mine) pending = false;
+            c = next;
+        }
+        WAVE_SYNC();
+        unsigned long long more = __ballot(open && mine == 0 && !pending && c < e);
+        while (more) {
+            const int src = __ffsll((long long)more) - 1;
+            more &= more - 1;
+            const int rs = __shfl(rx, src, WAVE);
+            const long long es = __shfl(e, src, WAVE);
+            long long q = __shfl(c, src, WAVE);
+            int got = 0;
+            bool wait = false;
+            for (; q < es && got == 0 && !wait; q += 4 * WAVE) {
+                int ry[4], sy[4];
+#pragma unroll
+                for (int k = 0; k < 4; k++) {
+                    const long long p = q + k * WAVE + lane < es ? q + k * WAVE + lane : es - 1;
+                    ry[k] = col_rank[p];
+                    sy[k] = lfmis_state(state, col[p]);
+                }
+                long long stop = -1;
+#pragma unroll
+                for (int k = 3; k >= 0; k--) {   // (the clamped last entry changes nothing)
+                    const unsigned long long o = __ballot(ry[k] < rs && sy[k] == 1);
+                    const unsigned long long u = __ballot(ry[k] < rs && sy[k] == 0);
+                    if (o) got = 2;
+                    if (u) stop = q + k * WAVE + __ffsll((long long)u) - 1;
+                }
+                if (got == 0 && stop >= 0) {
+                    wait = true;
+                    q = (stop < es ? stop : es - 1) - 4 * WAVE;
+                }
+            }
+            if (lane == src) {
+                c = q < es ? q : es;
+                mine = got;
+                pending = wait;
+            }
+            WAVE_SYNC();
+        }
+        if (open) {
+            cursor[x] = (int)(c - b);
+            if (mine == 0 && !pending) mine = 1;
+            if (mine) __hip_atomic_store(&state[x], mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            else left = true;
+        }
+        WAVE_SYNC();
     }
-    cnt = wave_sum_int(cnt);
-    if ((threadIdx.x & (WAVE - 1)) == 0 && cnt) atomicAdd(undecided, cnt);
+    if (__ballot(left) && lane == 0) *undecided = 1;
 }
 
 __global__ void k_opener_flags(const int *order, const int *state, long long n, int *flag)
