@@ -709,9 +709,8 @@ Ctx lf_ctx(lf_handle *h)
     c.unit = h->unit;
     c.part_rec = h->part_rec;
     c.part_done = h->part_done;
-    c.macc = h->macc;
+    c.psum = h->psum;
     c.part_cap = (int)h->part_cap;
-    c.mslot_cap = (int)h->mslot_cap;
     c.stats = (h->profiling >> LF_PROF_COUNTERS_BIT) & 1;
     return c;
 }

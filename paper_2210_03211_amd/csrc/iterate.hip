@@ -33,9 +33,10 @@
 #define MXCAP 32        // own memberships kept in LDS (wave path)
 #define INB 64          // neighbours per in-count unit (one per lane)
 #define HOLE (-2)       // a membership left in the current iteration (removed at its end)
+#define RB_MORE 3       // re-sum blocks of a queue per block of the option: 1,536 by default, six
+                        // per CU (warm start, 700,000 nodes, queue 4096: 2 per CU 25.0 ms, 6 23.9)
 #define PART 512        // members per re-sum part
 #define EDITS 64        // queued nodes of an edit block of k_apply
-#define MACC 19         // digit counters per multi-part community (3 x 6 digits, in-sum)
 
 static inline unsigned grid_for(long long n, int block) { return (unsigned)((n + block - 1) / block); }
 
@@ -198,7 +199,7 @@ __device__ __forceinline__ void read_member(const Member *mem, Ctx &cx, QStep &q
     as_global(cx.unit);
     as_global(cx.part_rec);
     as_global(cx.part_done);
-    as_global(cx.macc);
+    as_global(cx.psum);
     touch_args(cx, qs);
 }
 
@@ -696,7 +697,6 @@ __device__ __forceinline__ void reset_apply_counters(const Ctx &cx, int blk)
     if (blk == 0 && threadIdx.x == 0) {
         DevCounters *c = cx.ctr;
         c->parts_total = 0;
-        c->mslots = 0;
     }
 }
 
@@ -1190,28 +1190,20 @@ __device__ __forceinline__ int part_count(long long cap, long long len)
     return parts < 1 ? 1 : parts;
 }
 
-// records of community C's parts from p0 on; ms: its digit counters when there are several
-__device__ __forceinline__ void plan_parts(const Ctx &cx, int C, long long base, long long cap, int parts, int p0,
-                                           int ms)
+// records of community C's parts from p0 on
+__device__ __forceinline__ void plan_parts(const Ctx &cx, int C, long long base, long long cap, int parts, int p0)
 {
     PartRec pr;
     pr.base = base;
     pr.C = C;
     pr.parts = parts;
     pr.cap = (int)cap;
-    pr.ms = -1;
-    pr.pad = 0;
+    pr.pad[0] = pr.pad[1] = 0;
     if (p0 + parts > cx.part_cap) {
         atomicOr(&cx.ctr->error, LF_DEVERR_CAP);     // the run fails with this error
         pr.C = -1;                                    // the records that exist stay empty
     } else if (parts > 1) {
         cx.part_done[C] = 0;
-        if (ms >= cx.mslot_cap) {
-            atomicOr(&cx.ctr->error, LF_DEVERR_CAP);
-            ms = 0;
-        }
-        pr.ms = ms;
-        for (int k = 0; k < MACC; k++) cx.macc[(long long)ms * MACC + k] = 0;
     }
     for (int k = 0; k < parts && p0 + k < cx.part_cap; k++) {
         pr.k = k;
@@ -1220,8 +1212,8 @@ __device__ __forceinline__ void plan_parts(const Ctx &cx, int C, long long base,
 }
 
 struct EditLds {
-    int sum[4][256 / WAVE];  // per wave: parts, digit counters, joins, leaves
-    int base[2];             // the block's first part and digit counter
+    int sum[3][256 / WAVE];  // per wave: parts, joins, leaves
+    int base;                // the block's first part
 };
 
 // Membership edits of queue position j; every thread of the block calls this (those past the
@@ -1314,31 +1306,25 @@ __device__ __forceinline__ void apply_edit(const Ctx &cx, const QStep &qs, int j
             atomicAdd(&cx.ctr->apply[LF_APPLY_OWN_SLOTS], (unsigned long long)os);
         }
     }
-    // one reservation per block for the parts of all its communities and their digit counters
+    // one reservation per block for the parts of all its communities
     const int nL = firstL ? part_count(capL, lenL) : 0, nJ = firstJ ? part_count(capJ, lenJ) : 0;
-    const int mL = nL > 1, mJ = nJ > 1;
     int tot;
     const int at = wave_incl_scan(nL + nJ, &tot) - (nL + nJ);
-    const unsigned long long bL = __ballot(mL), bJ = __ballot(mJ), below = (1ull << lane) - 1;
-    const int many = __popcll(bL) + __popcll(bJ);
     const int wv = uni((int)threadIdx.x / WAVE);
     const int nj = __popcll(__ballot(joined)), nl = __popcll(__ballot(L >= 0));
-    if (lane < 4) S.sum[lane][wv] = lane == 0 ? tot : lane == 1 ? many : lane == 2 ? nj : nl;
+    if (lane < 3) S.sum[lane][wv] = lane == 0 ? tot : lane == 1 ? nj : nl;
     __syncthreads();
-    if (threadIdx.x < 4) {
+    if (threadIdx.x < 3) {
         int v = 0;
         for (int w = 0; w < 256 / WAVE; w++) v += S.sum[lane][w];
-        if (lane < 2) S.base[lane] = v ? atomicAdd(lane ? &cx.ctr->mslots : &cx.ctr->parts_total, v) : 0;
-        else if (v) atomicAdd(lane == 2 ? &cx.ctr->joins : &cx.ctr->leaves, (unsigned long long)v);
+        if (lane == 0) S.base = v ? atomicAdd(&cx.ctr->parts_total, v) : 0;
+        else if (v) atomicAdd(lane == 1 ? &cx.ctr->joins : &cx.ctr->leaves, (unsigned long long)v);
     }
     __syncthreads();
-    int p0 = S.base[0] + at, ms = S.base[1] + __popcll(bL & below) + __popcll(bJ & below);
-    for (int w = 0; w < wv; w++) {
-        p0 += S.sum[0][w];
-        ms += S.sum[1][w];
-    }
-    if (nL) plan_parts(cx, L, cmoL, capL, nL, p0, ms);
-    if (nJ) plan_parts(cx, J, cmoJ, capJ, nJ, p0 + nL, ms + mL);
+    int p0 = S.base + at;
+    for (int w = 0; w < wv; w++) p0 += S.sum[0][w];
+    if (nL) plan_parts(cx, L, cmoL, capL, nL, p0);
+    if (nJ) plan_parts(cx, J, cmoJ, capJ, nJ, p0 + nL);
 }
 
 // in-count changes of the neighbours in unit u (one wave): a neighbour y that holds J
@@ -1468,34 +1454,11 @@ __device__ __forceinline__ X192 wave_sum_u128(u128 v)
     return r;
 }
 
-// 24-bit digits of a non-negative sum below 2^160 (the last one takes the rest), and back
-// from digit counters
-__device__ __forceinline__ u64 x192_digit24(const X192 &v, int k)
-{
-    const int li = (24 * k) >> 6, bi = (24 * k) & 63;
-    const u64 a = li == 0 ? v.w0 : v.w1, b = li == 0 ? v.w1 : v.w2;
-    const u64 d = bi ? (a >> bi) | (b << (64 - bi)) : a;
-    return k < 5 ? d & 0xffffffull : d;
-}
-
-__device__ __forceinline__ X192 x192_from_digits24(const unsigned long long *D)
-{
-    X192 r = x192_zero();
-#pragma unroll 1
-    for (int k = 0; k < 6; k++) {            // (rolled up: registers matter more here)
-        const u64 d = __atomic_load_n(D + k, __ATOMIC_RELAXED);
-        const int li = (24 * k) >> 6, bi = (24 * k) & 63;
-        const u64 lo = d << bi, hi = bi ? d >> (64 - bi) : 0;
-        x192_add(r, X192{li == 0 ? lo : 0, li == 0 ? hi : li == 1 ? lo : 0, li == 1 ? hi : 0});
-    }
-    return r;
-}
-
 #define MPAR 1
 
 // Exact re-sum of one part (one wave): the members' terms at sizes s, s+1 and s-1, and the
 // sum of their in-counts.
-__device__ __forceinline__ void refresh_part(const Ctx &cx, const PartRec &pr, int lane, int &bad)
+__device__ __forceinline__ void refresh_part(const Ctx &cx, const PartRec &pr, long long p, int lane, int &bad)
 {
     const int C = pr.C;
     const int k = pr.k;
@@ -1581,29 +1544,48 @@ __device__ __forceinline__ void refresh_part(const Ctx &cx, const PartRec &pr, i
             ins += wave_sum_i64(sumi);
         }
     }
-    if (lane != 0) return;
     if (parts == 1) {
-        store_comm(cx, C, s, S0, Sp, Sm, ins, bad);
+        if (lane == 0) store_comm(cx, C, s, S0, Sp, Sm, ins, bad);
         return;
     }
-    // the parts of a community meet in its digit counters, and the last one stores the sums
-    unsigned long long *acc = (unsigned long long *)&cx.macc[(long long)pr.ms * MACC];
-#pragma unroll 1
-    for (int q = 0; q < 6; q++) {
-        atomicAdd(acc + q, x192_digit24(S0, q));
-        atomicAdd(acc + 6 + q, x192_digit24(Sp, q));
-        atomicAdd(acc + 12 + q, x192_digit24(Sm, q));
-    }
-    atomicAdd(acc + 18, (unsigned long long)ins);
-    // This wave's additions must have been performed before it counts its part.  They are
-    // device-scope atomics, which complete at the memory side, so waiting for them is
-    // enough; a device-scope fence would also write the whole L2 back (measured: 212 us per
-    // queue with fences, 82 with the wait, where planted communities of up to 3,000 members
-    // are re-summed on a 700,000-node graph at queue 4096).
+    // A community's parts leave their sums beside each other (their records are consecutive),
+    // and the last one to finish adds them up.  The sums are written and read past the caches
+    // (device scope), so that waiting for the writes before the part is counted is enough; a
+    // device-scope fence would also write the whole L2 back (212 us per queue with fences where
+    // planted communities of up to 3,000 members are re-summed on a 700,000-node graph at
+    // queue 4096, 82 with the wait).  One write by ten lanes instead of 19 atomics in a row on the
+    // community's digit counters: a whole warm start of those nodes 28.7 -> 25.0 ms.  With parts
+    // of 256 members instead of 512 it takes 23.6 (24.0 here), but small graphs with communities
+    // of some 300 lose 2 %.
+    u64 word = lane == 0 ? S0.w0 : lane == 1 ? S0.w1 : lane == 2 ? S0.w2 : lane == 3 ? Sp.w0 : lane == 4 ? Sp.w1
+             : lane == 5 ? Sp.w2 : lane == 6 ? Sm.w0 : lane == 7 ? Sm.w1 : lane == 8 ? Sm.w2 : (u64)ins;
+    if (lane < PSUM) __hip_atomic_store(&cx.psum[p * PSUM + lane], word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    if (atomicAdd(&cx.part_done[C], 1) == parts - 1)
-        store_comm(cx, C, s, x192_from_digits24(acc), x192_from_digits24(acc + 6), x192_from_digits24(acc + 12),
-                   (long long)__atomic_load_n(acc + 18, __ATOMIC_RELAXED), bad);
+    int done = 0;
+    if (lane == 0) done = atomicAdd(&cx.part_done[C], 1);
+    if (uni(done) != parts - 1) return;
+    S0 = Sp = Sm = x192_zero();
+    ins = 0;
+    for (int i0 = 0; i0 < parts; i0 += WAVE) {
+        X192 t[3] = {x192_zero(), x192_zero(), x192_zero()};
+        long long ti = 0;
+        if (i0 + lane < parts) {
+            unsigned long long *w = cx.psum + (p - k + i0 + lane) * PSUM;
+#pragma unroll
+            for (int v = 0; v < 3; v++) {
+                t[v].w0 = __hip_atomic_load(w + 3 * v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                t[v].w1 = __hip_atomic_load(w + 3 * v + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                t[v].w2 = __hip_atomic_load(w + 3 * v + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            ti = (long long)__hip_atomic_load(w + 9, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        WAVE_SYNC();
+        x192_add(S0, wave_sum_x192(t[0]));
+        x192_add(Sp, wave_sum_x192(t[1]));
+        x192_add(Sm, wave_sum_x192(t[2]));
+        ins += wave_sum_i64(ti);
+    }
+    if (lane == 0) store_comm(cx, C, s, S0, Sp, Sm, ins, bad);
 }
 
 // Between two queues: the re-sums of the communities that the queue before touched (rb blocks,
@@ -1644,8 +1626,7 @@ __device__ __forceinline__ void body_refresh(const Ctx &cx, const QStep &qs, int
             pr.k = uni(a0.w);
             pr.parts = uni(a1.x);
             pr.cap = uni(a1.y);
-            pr.ms = uni(a1.z);
-            if (pr.C >= 0 && pr.C < cx.K) refresh_part(cx, pr, lane, bad);   // else: after a flagged overflow
+            if (pr.C >= 0 && pr.C < cx.K) refresh_part(cx, pr, p, lane, bad);   // else: after a flagged overflow
             WAVE_SYNC();
             p += nw;
             if (p < count) {
@@ -1732,7 +1713,6 @@ __global__ void __launch_bounds__(256) k_node_bounds(Ctx cx, const unsigned char
         c->joins = 0;
         c->leaves = 0;
         c->parts_total = 0;
-        c->mslots = 0;
         c->ovf_cnt = 0;
         c->live = 0;
     }
@@ -2060,7 +2040,7 @@ __global__ void k_unit_fill(const int *order, const long long *rowptr, const int
 // ------------------------------------------------------------------------------------
 void lf_free_iteration_buffers(lf_handle *h)
 {
-    void **ptrs[] = {(void **)&h->dec, (void **)&h->unit, (void **)&h->part_rec, (void **)&h->macc,
+    void **ptrs[] = {(void **)&h->dec, (void **)&h->unit, (void **)&h->part_rec, (void **)&h->psum,
                      (void **)&h->ubase, (void **)&h->tpos, (void **)&h->tcur, (void **)&h->tchunk,
                      (void **)&h->tbuck, (void **)&h->tvis, (void **)&h->trow, (void **)&h->tres,
                      (void **)&h->lhdr, (void **)&h->lpair, (void **)&h->ldeg};
@@ -2073,7 +2053,6 @@ void lf_free_iteration_buffers(lf_handle *h)
     h->static_ready = false;
     h->lines_ready = false;
     h->part_cap = 0;
-    h->mslot_cap = 0;
     h->tchunk_cap = 0;
     h->tbuck_cap = 0;
     h->tvis_cap = 0;
@@ -2293,15 +2272,10 @@ static int size_queue_complete(lf_handle *h, long long q)
         lf_dev_free(h, h->part_rec);
         h->part_rec = nullptr;
         LF_TRY(lf_dev_alloc(h, (void **)&h->part_rec, sizeof(PartRec) * pcap));
+        lf_dev_free(h, h->psum);
+        h->psum = nullptr;
+        LF_TRY(lf_dev_alloc(h, (void **)&h->psum, sizeof(unsigned long long) * PSUM * pcap));
         h->part_cap = pcap;
-        moved = true;
-    }
-    long long mcap = 2 * q + 64;
-    if (mcap > h->mslot_cap) {
-        lf_dev_free(h, h->macc);
-        h->macc = nullptr;
-        LF_TRY(lf_dev_alloc(h, (void **)&h->macc, sizeof(long long) * MACC * mcap));
-        h->mslot_cap = mcap;
         moved = true;
     }
     if (moved) h->graph_version++;
@@ -2483,7 +2457,7 @@ void lf_queue_params(lf_handle *h, long long k, long long nq, long long qq, bool
         ln[c] = (int)(qo[c * (nq + 1) + k + 1] - ls[c]);
     }
     const int gb = h->hub_blocks;
-    int rbk = h->refresh_blocks;
+    int rbk = RB_MORE * h->refresh_blocks;
     if (compact_grids) {
         int want = (int)grid_for(clen, 8);
         if (want < rbk) rbk = want;
@@ -2599,7 +2573,7 @@ static void refresh_alone(lf_handle *h)
 {
     QStep qs;
     memset(&qs, 0, sizeof qs);
-    qs.rb = h->refresh_blocks;
+    qs.rb = RB_MORE * h->refresh_blocks;
     launch_refresh(qs.rb, h->stream, lf_ctx(h), qs);
 }
 

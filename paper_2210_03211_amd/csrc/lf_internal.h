@@ -56,9 +56,9 @@ struct __align__(16) PartRec {     // read as two 16-byte words
     int C;                   // the community (-1: an empty record after a flagged overflow)
     int k, parts;            // this part and the community's number of parts
     int cap;                 // member-list capacity
-    int ms;                  // carry-save counter slot of a multi-part community (-1: one part)
-    int pad;
+    int pad[2];
 };
+#define PSUM 10              // words of a part's sums: S, S+, S- (192 bits each), in-counts
 
 // A node of a path list with what its evaluation reads first (row offset, id, degree), so
 // that its adjacency gathers can start without first resolving the order position.
@@ -138,7 +138,7 @@ struct DevCounters {
     int unused3;
     int unused2;
     int parts_total;               // re-sum parts (queue)
-    int mslots;                    // multi-part re-sum accumulators in use (queue)
+    int unused4;
     int refresh_next;              // work counter of the full re-sum at initialisation
     int ovf_cnt;                   // joiners that did not fit their member list (iteration)
     int undecided;                 // initial clustering rounds
@@ -200,8 +200,8 @@ struct Ctx {
     // re-sum parts
     PartRec *part_rec;       // [part_cap] the re-sum parts of the queue
     int *part_done;          // [K] parts of a multi-part community finished
-    long long *macc;         // [mslot_cap * 19] carry-save accumulators
-    int part_cap, mslot_cap;
+    unsigned long long *psum; // [part_cap * PSUM] sums of the parts of multi-part communities
+    int part_cap, pad;
     int stats;               // collect the per-path work counters
 };
 
@@ -346,8 +346,8 @@ struct lf_handle {
     long long unit_cap;
     PartRec *part_rec;
     int *part_done;
-    long long *macc;
-    long long part_cap, mslot_cap;
+    unsigned long long *psum;
+    long long part_cap;
     long long *vbound;       // [n] per-node bounds used to size the per-queue buffers
     int graph_version;       // bumped whenever a buffer used by captured launches moves
     DevCounters *ctr;
