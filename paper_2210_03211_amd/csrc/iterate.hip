@@ -1129,7 +1129,33 @@ __device__ __forceinline__ void body_eval_big(const Ctx &cx, const QStep &qs, in
     if (qs.lists) eval_small_med(cx, qs, b - r.nb, L.e);
 }
 #define BIG_BOUNDS GT, 4
+#define MID_BOUNDS GT, 8
 SINGLE_KERNEL(k_eval_big, BIG_BOUNDS, BigLds, body_eval_big)
+
+// The same without the workgroup path, whose LDS (37 KB) and registers (112) leave four blocks
+// to a CU where buckets and light nodes alone have eight.  The vector units are 43 % busy with
+// four (dense graph), so for long launches the workgroup path gets a launch of its own: from
+// SPLIT_BLOCKS blocks of the rest on, below which the launch costs more.  1M nodes, dense, queue
+// 16,384: 101.8 ms in one launch, 97.3 split with six blocks to a CU, 95.5 with eight; 1M nodes,
+// queue 65,536: 60.4, 58.9, 58.3.  4M nodes, queue 4096, one launch or split from 4096 / 2048 / 1024
+// blocks on: 412.5, 411, 418.5, 420.5 ms.
+#define SPLIT_BLOCKS 4096
+union MidLds {
+    BuckLds b;
+    EvalLds e;
+};
+__global__ void __launch_bounds__(MID_BOUNDS) k_eval_mid(Ctx cx, QStep qs)
+{
+    __shared__ MidLds lds;
+    touch_args(cx, qs);
+    const int b = (int)blockIdx.x;
+    reset_apply_counters(cx, b);
+    if (b < qs.br.nb) {
+        eval_bucket(cx, qs, b, lds.b);
+        return;
+    }
+    if (qs.lists) eval_small_med(cx, qs, b - qs.br.nb, lds.e);
+}
 MULTI_KERNEL(k_eval_big, BIG_BOUNDS, BigLds, body_eval_big)
 
 // the decision of every table-path node of the queue: the best of its buckets (one wave per
@@ -2522,8 +2548,11 @@ int lf_launch_queue(lf_handle *h, Ctx &cx, const QStep &qs, const QGrids &g)
     }
     if (g.big > 0) {
         LF_TRY(lf_prof_begin(h, LF_K_EVAL_BIG));
-        hipLaunchKernelGGL(k_eval_big, dim3(g.big), dim3(GT), 0, st, cx, qs);
-        LF_TRY(lf_prof_end(h, LF_K_EVAL_BIG, 1));
+        const int bg = qs.br.bg, mid = g.big - bg;
+        const bool split = mid > SPLIT_BLOCKS;
+        if (!split || bg > 0) hipLaunchKernelGGL(k_eval_big, dim3(split ? bg : g.big), dim3(GT), 0, st, cx, qs);
+        if (split) hipLaunchKernelGGL(k_eval_mid, dim3(mid), dim3(GT), 0, st, cx, qs);
+        LF_TRY(lf_prof_end(h, LF_K_EVAL_BIG, split && bg > 0 ? 2 : 1));
     }
     if (g.tie > 0) {
         LF_TRY(lf_prof_begin(h, LF_K_TAB_TIE));

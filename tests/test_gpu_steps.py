@@ -145,3 +145,27 @@ def test_one_queue_without_lists(lf, orc, n, d):
     same_state(h, o)
     h.close()
     o.close()
+
+
+@pytest.mark.parametrize("n,opts", [(9000, {"wave_table": 16, "med_table": 16, "grp_table": 16}),
+                                    (7000, {"wave_table": 16, "med_table": 64, "grp_table": 256})])
+def test_split_launch_of_larger_nodes(lf, orc, n, opts):
+    """More buckets in a queue than one launch for all larger nodes takes, without and with
+    workgroup-path nodes beside them."""
+    import torch
+    say("split", n, opts)
+    rng = np.random.default_rng(n)
+    a = np.repeat(np.arange(n), rng.integers(30, 90, n))
+    b = (a + rng.integers(1, 200, a.size)) % n
+    g = G.Graph(n, a.astype(np.int64), b.astype(np.int64))
+    h = lf.Handle(0)
+    for k, v in opts.items():
+        h.lf_set_option(k, v)
+    h.load_graph(g.n, torch.from_numpy(g.src).cuda(), torch.from_numpy(g.dst).cuda()).init_communities()
+    o = orc.Oracle()
+    o.load_graph(g.n, g.src, g.dst)
+    o.init_communities()
+    same_hist(h.run_iterations(n, 0.0, 2), o.run_iterations(n, 0.0, 2))
+    same_state(h, o)
+    h.close()
+    o.close()
