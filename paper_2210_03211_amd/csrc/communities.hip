@@ -336,52 +336,60 @@ __global__ void k_member_fill(const NodeHdr *nh, const Slot *slot, long long n, 
     }
 }
 
-__global__ void k_iota(int *a, long long n)
-{
-    long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x;
-    if (i < n) a[i] = (int)i;
-}
-
 // ------------------------------------------------------------------------------------
-// exact re-sum of touched communities (persistent: each wave takes REFRESH_CHUNK
-// consecutive entries of the touched list at a time until it is exhausted; one returning
-// atomic per community on the shared counter would serialise the launch)
+// exact re-sum of every community
 // ------------------------------------------------------------------------------------
-#define REFRESH_CHUNK 16
-__global__ void __launch_bounds__(256) k_refresh_list(Ctx cx, int fixed_count)
+// Most communities have some ten members, so a row of 16 lanes sums one; those of more than
+// ROW_MEMBERS, or with joiners that did not fit their list, are left to the whole wave.  With a
+// wave for each, most lanes idle and three 192-bit reductions through LDS: 0.72 -> 0.09 ms
+// for the clusters of 1M nodes, 2.29 -> 0.37 ms for those of 4M.
+#define ROW_MEMBERS 64
+__global__ void __launch_bounds__(256) k_refresh_list(Ctx cx, int count)
 {
-    int lane = threadIdx.x & (WAVE - 1);
-    int count = fixed_count >= 0 ? fixed_count : __atomic_load_n(&cx.ctr->tcount, __ATOMIC_RELAXED);
+    const int lane = threadIdx.x & (WAVE - 1), sub = lane & 15;
+    const long long nw = (long long)gridDim.x * (blockDim.x / WAVE);
     int bad = 0;
-    // unsigned: the last grabs may pass 2^31 when the list nears the int range
-    unsigned idx = 0, end = 0;
-    while (true) {
-        if (idx == end) {
-            if (lane == 0) idx = atomicAdd((unsigned *)&cx.ctr->refresh_next, (unsigned)REFRESH_CHUNK);
-            idx = __shfl(idx, 0, WAVE);
-            end = idx + REFRESH_CHUNK;
-        }
-        if (idx >= (unsigned)count) break;
-        int C = cx.tlist[idx++];
+    for (long long i0 = (blockIdx.x * (long long)blockDim.x + threadIdx.x) / WAVE * 4; i0 < count; i0 += 4 * nw) {
+        const bool in = i0 + lane / 16 < count;
+        const int C = in ? (int)i0 + lane / 16 : (int)i0;
         const int s = cx.cr[C].s;
-        long long base = cx.cm_off[C];
-        long long cap = cx.cm_off[C + 1] - base;
-        long long len = cx.cm_len[C];
-        if (len > cap) len = cap;
-        X192 a0 = x192_zero(), ap = x192_zero(), am = x192_zero();
+        const long long base = cx.cm_off[C], cap = cx.cm_off[C + 1] - base;
+        const int fill = cx.cm_len[C], ovf = cx.ovf_flag[C];
+        const long long len = fill < cap ? fill : cap;
+        const bool row = in && len <= ROW_MEMBERS && !ovf;
+        u128 a0 = 0, ap = 0, am = 0;
         long long sumi = 0;
-        for (long long j = lane; j < len; j += WAVE)
+        for (long long j = sub; row && j < len; j += 16)
             member_terms(cx, cx.cm_node[base + j], C, s, a0, ap, am, sumi, bad);
-        if (cx.ovf_flag[C]) {
-            int no = __atomic_load_n(&cx.ctr->ovf_cnt, __ATOMIC_RELAXED);
-            for (int e = lane; e < no; e += WAVE)
-                if (cx.ovf_comm[e] == C) member_terms(cx, cx.ovf_node[e], C, s, a0, ap, am, sumi, bad);
+        WAVE_SYNC();
+        const X192 S0 = row_sum_u128(a0), Sp = row_sum_u128(ap), Sm = row_sum_u128(am);
+        const long long ins = (long long)row_sum_u32((unsigned)sumi & 0xffffffu) +
+                              ((long long)row_sum_u32((unsigned)(sumi >> 24)) << 24);
+        if (row && sub == 15) store_comm(cx, C, s, S0, Sp, Sm, ins, bad);
+        WAVE_SYNC();
+        unsigned long long rest = __ballot(in && !row && sub == 0);
+        while (rest) {
+            const int src = __ffsll((long long)rest) - 1;
+            rest &= rest - 1;
+            const int Cw = __shfl(C, src, WAVE), sw = __shfl(s, src, WAVE);
+            const long long bw = __shfl(base, src, WAVE), lw = __shfl(len, src, WAVE);
+            X192 b0 = x192_zero(), bp = x192_zero(), bm = x192_zero();
+            long long sumw = 0;
+            for (long long j = lane; j < lw; j += WAVE)
+                member_terms(cx, cx.cm_node[bw + j], Cw, sw, b0, bp, bm, sumw, bad);
+            if (cx.ovf_flag[Cw]) {
+                const int no = cx.ctr->ovf_cnt;
+                for (int e = lane; e < no; e += WAVE)
+                    if (cx.ovf_comm[e] == Cw) member_terms(cx, cx.ovf_node[e], Cw, sw, b0, bp, bm, sumw, bad);
+            }
+            WAVE_SYNC();
+            b0 = wave_sum_x192(b0);
+            bp = wave_sum_x192(bp);
+            bm = wave_sum_x192(bm);
+            sumw = wave_sum_i64(sumw);
+            if (lane == 0) store_comm(cx, Cw, sw, b0, bp, bm, sumw, bad);
+            WAVE_SYNC();
         }
-        a0 = wave_sum_x192(a0);
-        ap = wave_sum_x192(ap);
-        am = wave_sum_x192(am);
-        sumi = wave_sum_i64(sumi);
-        if (lane == 0) store_comm(cx, C, s, a0, ap, am, sumi, bad);
     }
     if (bad) atomicOr(&cx.ctr->error, LF_DEVERR_INEXACT);
 }
@@ -684,7 +692,6 @@ Ctx lf_ctx(lf_handle *h)
     c.cm_len = h->cm_len;
     c.cm_node = h->cm_node;
     c.tflag = h->tflag;
-    c.tlist = h->tlist;
     c.ovf_node = h->ovf_node;
     c.ovf_comm = h->ovf_comm;
     c.ovf_flag = h->ovf_flag;
@@ -719,7 +726,7 @@ void lf_free_partition(lf_handle *h)
 {
     void **ptrs[] = {(void **)&h->nh, (void **)&h->slot[0], (void **)&h->slot[1], (void **)&h->lines, (void **)&h->cr,
                      (void **)&h->cm_off, (void **)&h->cm_len, (void **)&h->cm_node, (void **)&h->tflag,
-                     (void **)&h->tlist, (void **)&h->ovf_node,
+                     (void **)&h->ovf_node,
                      (void **)&h->ovf_comm, (void **)&h->ovf_flag, (void **)&h->ctr,
                      (void **)&h->part_done, (void **)&h->vbound,
                      (void **)&h->cls, (void **)&h->clscnt, (void **)&h->clsbase, (void **)&h->plist_all,
@@ -929,7 +936,6 @@ static int alloc_partition_state(lf_handle *h, long long K, long long slots)
     LF_TRY(lf_dev_alloc(h, (void **)&h->cm_off, sizeof(long long) * (KK + 1)));
     LF_TRY(lf_dev_alloc(h, (void **)&h->cm_len, sizeof(int) * KK));
     LF_TRY(lf_dev_alloc(h, (void **)&h->tflag, sizeof(int) * KK));
-    LF_TRY(lf_dev_alloc(h, (void **)&h->tlist, sizeof(int) * KK));
     LF_TRY(lf_dev_alloc(h, (void **)&h->ovf_flag, sizeof(int) * KK));
     LF_TRY(lf_dev_alloc(h, (void **)&h->part_done, sizeof(int) * KK));
     LF_TRY(lf_dev_alloc(h, (void **)&h->vbound, sizeof(long long) * (nn + 1)));
@@ -962,10 +968,8 @@ static int finish_partition(lf_handle *h)
     const int BS = 256;
     const long long K = h->K;
     LF_TRY(rebuild_member_lists(h));
-    if (K > 0) hipLaunchKernelGGL(k_iota, dim3(grid_for(K, BS)), dim3(BS), 0, st, h->tlist, K);
-    LF_HIP(h, hipMemsetAsync(&h->ctr->refresh_next, 0, sizeof(int), st));
     Ctx cx = lf_ctx(h);
-    int rb = (int)((K + 3) / 4);
+    int rb = (int)((K + 15) / 16);           // a row of lanes per community
     if (rb > 4096) rb = 4096;
     if (rb < 1) rb = 1;
     hipLaunchKernelGGL(k_refresh_list, dim3(rb), dim3(256), 0, st, cx, (int)K);

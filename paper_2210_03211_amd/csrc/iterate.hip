@@ -1462,24 +1462,6 @@ MULTI_KERNEL(k_apply, 256, EditLds, multi_apply)
 // ------------------------------------------------------------------------------------
 // exact re-sum of the touched communities
 // ------------------------------------------------------------------------------------
-// The wave's exact sum of its lanes' 128-bit values: each is cut into six 24-bit limbs, whose
-// sums over 64 lanes fit 32-bit words, so a limb is one DPP reduction (no carries, no LDS).
-__device__ __forceinline__ X192 wave_sum_u128(u128 v)
-{
-    const unsigned w0 = (unsigned)v, w1 = (unsigned)(v >> 32), w2 = (unsigned)(v >> 64), w3 = (unsigned)(v >> 96);
-    const u64 t0 = wave_sum_u32(w0 & 0xffffffu);
-    const u64 t1 = wave_sum_u32((w0 >> 24) | ((w1 & 0xffffu) << 8));
-    const u64 t2 = wave_sum_u32((w1 >> 16) | ((w2 & 0xffu) << 16));
-    const u64 t3 = wave_sum_u32(w2 >> 8);
-    const u64 t4 = wave_sum_u32(w3 & 0xffffffu);
-    const u64 t5 = wave_sum_u32(w3 >> 24);
-    const u64 lo = t0 + (t1 << 24), mid = t2 + (t3 << 24), hi = t4 + (t5 << 24);   // at 2^0, 2^48, 2^96
-    X192 r = {lo, 0, 0};
-    x192_add(r, X192{mid << 48, mid >> 16, 0});
-    x192_add(r, X192{0, hi << 32, hi >> 32});
-    return r;
-}
-
 #define MPAR 1
 
 // Exact re-sum of one part (one wave): the members' terms at sizes s, s+1 and s-1, and the

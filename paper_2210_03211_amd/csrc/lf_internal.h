@@ -132,14 +132,7 @@ struct DevCounters {
     unsigned long long work[LF_PATH_COUNT][5]; // evaluation work per path (cumulative): nodes,
                                    // neighbours, visits, candidates, own memberships
     unsigned long long apply[LF_APPLY_COUNT];  // apply work (cumulative, LF_APPLY_*)
-    int tcount;                    // communities re-summed at initialisation
-    int unused0;
-    int unused1;
-    int unused3;
-    int unused2;
     int parts_total;               // re-sum parts (queue)
-    int unused4;
-    int refresh_next;              // work counter of the full re-sum at initialisation
     int ovf_cnt;                   // joiners that did not fit their member list (iteration)
     int undecided;                 // initial clustering rounds
     int error;                     // bit flags, see LF_DEVERR_*
@@ -170,7 +163,6 @@ struct Ctx {
     int *cm_len;             // member-list fill (may exceed capacity: overflow)
     int *cm_node;            // member lists
     int *tflag;              // touched flag per community (1: in this queue, 2: removed)
-    int *tlist;              // community list of the re-sum at initialisation
     unsigned qtag;           // tag of the current queue (unique within a run)
     int *ovf_node;           // overflow joiners (node, community)
     int *ovf_comm;
@@ -298,7 +290,7 @@ struct lf_handle {
     int *cm_len;
     int *cm_node;
     long long cm_cap;        // capacity of cm_node
-    int *tflag, *tlist;
+    int *tflag;
     unsigned qtag;           // next queue tag
     int *ovf_node, *ovf_comm, *ovf_flag;
     Decision *dec;

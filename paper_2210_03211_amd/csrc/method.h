@@ -219,11 +219,48 @@ __device__ __forceinline__ unsigned wave_sum_u32(unsigned x)
     return (unsigned)__builtin_amdgcn_readlane((int)x, WAVE - 1);
 }
 
+// the sum over the lane's row of 16 lanes, valid on the row's last lane
+__device__ __forceinline__ unsigned row_sum_u32(unsigned x)
+{
+    DPP_STEP(x, op_add, 0x111, 0xf);
+    DPP_STEP(x, op_add, 0x112, 0xf);
+    DPP_STEP(x, op_add, 0x114, 0xf);
+    DPP_STEP(x, op_add, 0x118, 0xf);
+    return x;
+}
+
 // the largest of the lanes' values (unsigned), the same on every lane
 __device__ __forceinline__ unsigned wave_max_u32(unsigned x)
 {
     DPP_INCLUSIVE(x, op_max);
     return (unsigned)__builtin_amdgcn_readlane((int)x, WAVE - 1);
+}
+
+// Exact sum of lanes' 128-bit values: each is cut into six 24-bit limbs, whose sums over 64
+// lanes fit 32-bit words, so a limb is one DPP reduction (no carries, no LDS).
+template <class Sum>
+__device__ __forceinline__ X192 sum_limbs(u128 v, Sum sum)
+{
+    const unsigned w0 = (unsigned)v, w1 = (unsigned)(v >> 32), w2 = (unsigned)(v >> 64), w3 = (unsigned)(v >> 96);
+    const u64 t0 = sum(w0 & 0xffffffu);
+    const u64 t1 = sum((w0 >> 24) | ((w1 & 0xffffu) << 8));
+    const u64 t2 = sum((w1 >> 16) | ((w2 & 0xffu) << 16));
+    const u64 t3 = sum(w2 >> 8);
+    const u64 t4 = sum(w3 & 0xffffffu);
+    const u64 t5 = sum(w3 >> 24);
+    const u64 lo = t0 + (t1 << 24), mid = t2 + (t3 << 24), hi = t4 + (t5 << 24);   // at 2^0, 2^48, 2^96
+    X192 r = {lo, 0, 0};
+    x192_add(r, X192{mid << 48, mid >> 16, 0});
+    x192_add(r, X192{0, hi << 32, hi >> 32});
+    return r;
+}
+__device__ __forceinline__ X192 wave_sum_u128(u128 v)     // the wave's, on every lane
+{
+    return sum_limbs(v, [](unsigned x) { return wave_sum_u32(x); });
+}
+__device__ __forceinline__ X192 row_sum_u128(u128 v)      // the row's, on its last lane
+{
+    return sum_limbs(v, [](unsigned x) { return row_sum_u32(x); });
 }
 
 // best (change, community) of the wave's lanes, on every lane: the largest positive change
@@ -258,8 +295,9 @@ __device__ __forceinline__ void member_add(int i, int d, int s, Acc &a0, Acc &ap
 }
 
 // exact g-sums of one member y of C (at sizes s, s+1, s-1) if y is still in C
-__device__ __forceinline__ void member_terms(const Ctx &cx, int y, int C, int s, X192 &a0, X192 &ap,
-                                             X192 &am, long long &sumi, int &bad)
+template <class Acc>
+__device__ __forceinline__ void member_terms(const Ctx &cx, int y, int C, int s, Acc &a0, Acc &ap,
+                                             Acc &am, long long &sumi, int &bad)
 {
     NodeHdr hy = cx.nh[y];
     int in = 0;

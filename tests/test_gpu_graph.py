@@ -92,3 +92,37 @@ def test_one_handle_many_graphs(lf, orc):
             assert np.array_equal(u, v)
         o.close()
     h.close()
+
+
+@pytest.mark.parametrize("shape", ["even", "clustered", "narrow", "signed"])
+def test_relabelled_ids(lf, orc, shape):
+    """Ids found through a table of their leading bits: spread evenly, nearly all in one entry,
+    closer together than the table is fine; negative ids are refused."""
+    import torch
+    rng = np.random.default_rng(5)
+    n = 70_000
+    if shape == "even":
+        ids = np.sort(rng.choice(1 << 40, n, replace=False))
+    elif shape == "clustered":
+        ids = np.concatenate([[0, 3], 5_000_000_000 + np.arange(n - 4), [1 << 61, (1 << 62) - 1]])
+    elif shape == "narrow":
+        ids = 77 + np.arange(n)
+    else:
+        ids = np.concatenate([np.arange(n // 2) * 9, -1 - np.arange(n - n // 2) * 1_000_000_007])
+    a = np.concatenate([np.arange(n), rng.integers(0, n, 3 * n)])
+    b = np.concatenate([(np.arange(n) + 1) % n, rng.integers(0, n, 3 * n)])
+    src, dst = ids[a].astype(np.int64), ids[b].astype(np.int64)
+    print("[case] ids", shape, flush=True)
+    h, o = lf.Handle(0), orc.Oracle()
+    if shape == "signed":
+        with pytest.raises(lf.LazyFoxError) as e:
+            h.load_graph(0, torch.from_numpy(src).cuda(), torch.from_numpy(dst).cuda(), relabel=True)
+        assert e.value.code == lf.LF_EINVAL
+        return
+    h.load_graph(0, torch.from_numpy(src).cuda(), torch.from_numpy(dst).cuda(), relabel=True)
+    o.load_graph(0, src, dst, relabel=True)
+    assert h.n == o.n == n
+    for u, v in zip(h.csr() + (h.orig_ids(),), o.csr() + (o.orig_ids(),)):
+        assert np.array_equal(u, v)
+    h.close()
+    o.close()
