@@ -161,21 +161,25 @@ __global__ void k_opener_ids(const int *order, const int *flag, const long long 
     if (flag[r]) comm_of[order[r]] = (int)pos[r];
 }
 
-// every non-opener joins its lowest-ranked opener neighbour; one wave per node
+// every non-opener joins its lowest-ranked opener neighbour
 __global__ void __launch_bounds__(256) k_join_openers(const long long *rowptr, const int *col, const int *col_rank,
                                                       const int *order, const int *state, long long n, int *comm_of)
 {
-    long long x = (blockIdx.x * (long long)blockDim.x + threadIdx.x) / WAVE;
-    int lane = threadIdx.x & (WAVE - 1);
-    if (x >= n || state[x] != 2) return;
-    unsigned best = 0x7fffffff;
-    for (long long e = rowptr[x] + lane; e < rowptr[x + 1]; e += WAVE) {
-        const unsigned r = (unsigned)col_rank[e];
-        if (r < best && state[col[e]] == 1) best = r;
-    }
-    WAVE_SYNC();
-    best = 0x7fffffffu - wave_max_u32(0x7fffffffu - best);
-    if (lane == 0) comm_of[x] = comm_of[order[best]];
+    for_rows(rowptr, n, [&](long long x, int sub, int width) {
+        const bool joins = x >= 0 && state[x] == 2;
+        unsigned best = 0x7fffffff;
+        if (joins) {
+            const long long r1 = rowptr[x + 1];
+            for (long long e = rowptr[x] + sub; e < r1; e += width) {
+                const unsigned r = (unsigned)col_rank[e];
+                if (r < best && state[col[e]] == 1) best = r;
+            }
+        }
+        WAVE_SYNC();
+        best = 0x7fffffffu - best;
+        best = 0x7fffffffu - (width == 16 ? row_max_u32(best) : wave_max_u32(best));
+        if (joins && sub == width - 1) comm_of[x] = comm_of[order[best]];
+    });
 }
 
 // one membership per node plus one free slot; in-count within its community
@@ -183,28 +187,32 @@ __global__ void __launch_bounds__(256) k_init_slots(const long long *rowptr, con
                                                     const int *comm_of, long long n, NodeHdr *nh, Slot *slot,
                                                     CommRec *cr)
 {
-    long long x = (blockIdx.x * (long long)blockDim.x + threadIdx.x) / WAVE;
-    int lane = threadIdx.x & (WAVE - 1);
-    if (x > n) return;
-    if (x == n) {
-        if (lane == 0) { nh[n].off = 2 * n; nh[n].cnt = 0; nh[n].deg = 0; }
-        return;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        nh[n].off = 2 * n;
+        nh[n].cnt = 0;
+        nh[n].deg = 0;
     }
-    int c = comm_of[x];
-    int in = 0;
-    for (long long e = rowptr[x] + lane; e < rowptr[x + 1]; e += WAVE) in += comm_of[col[e]] == c;
-    in = wave_sum_int(in);
-    if (lane == 0) {
-        NodeHdr hd;
-        hd.off = 2 * x;
-        hd.cnt = 1;
-        hd.deg = deg[x];
-        nh[x] = hd;
-        Slot s0 = {c, in}, s1 = {-1, 0};
-        slot[2 * x] = s0;
-        slot[2 * x + 1] = s1;
-        atomicAdd(&cr[c].s, 1);
-    }
+    for_rows(rowptr, n, [&](long long x, int sub, int width) {
+        int c = 0, in = 0;
+        if (x >= 0) {
+            c = comm_of[x];
+            const long long r1 = rowptr[x + 1];
+            for (long long e = rowptr[x] + sub; e < r1; e += width) in += comm_of[col[e]] == c;
+        }
+        WAVE_SYNC();
+        in = width == 16 ? (int)row_sum_u32((unsigned)in) : (int)wave_sum_u32((unsigned)in);
+        if (x >= 0 && sub == width - 1) {
+            NodeHdr hd;
+            hd.off = 2 * x;
+            hd.cnt = 1;
+            hd.deg = deg[x];
+            nh[x] = hd;
+            Slot s0 = {c, in}, s1 = {-1, 0};
+            slot[2 * x] = s0;
+            slot[2 * x + 1] = s1;
+            atomicAdd(&cr[c].s, 1);
+        }
+    });
 }
 
 // warm start: checks of a given cover (waves stride over the nodes): offsets non-decreasing
@@ -897,7 +905,7 @@ int lf_initial_clustering(lf_handle *h)
     int lastf = 0;
     if (n > 0) {
         hipLaunchKernelGGL(k_opener_ids, dim3(grid_for(n, BS)), dim3(BS), 0, st, h->order, flag, pos, n, comm_of);
-        hipLaunchKernelGGL(k_join_openers, dim3(grid_for(n * WAVE, BS)), dim3(BS), 0, st, h->rowptr, h->col, h->col_rank,
+        hipLaunchKernelGGL(k_join_openers, dim3(grid_for(n * 16, BS)), dim3(BS), 0, st, h->rowptr, h->col, h->col_rank,
                            h->order, state, n, comm_of);
         LF_HIP(h, hipMemcpyAsync(&lastp, pos + n - 1, sizeof(long long), hipMemcpyDeviceToHost, st));
         LF_HIP(h, hipMemcpyAsync(&lastf, flag + n - 1, sizeof(int), hipMemcpyDeviceToHost, st));
@@ -908,7 +916,7 @@ int lf_initial_clustering(lf_handle *h)
     if (K >= (1ll << 31) - 1) return lf_set_error(h, LF_EOVERFLOW, "too many communities");
     LF_TRY(alloc_partition_state(h, K, 2 * n));
     if (n >= 0)
-        hipLaunchKernelGGL(k_init_slots, dim3(grid_for((n + 1) * WAVE, BS)), dim3(BS), 0, st, h->rowptr, h->col,
+        hipLaunchKernelGGL(k_init_slots, dim3(grid_for(n > 0 ? n * 16 : 1, BS)), dim3(BS), 0, st, h->rowptr, h->col,
                            h->deg, comm_of, n, h->nh, h->slot[0], h->cr);
     LF_TRY(finish_partition(h));
     LF_TRY(lf_prof_end(h, LF_K_INITCLUST, rounds + 8));

@@ -229,6 +229,35 @@ __device__ __forceinline__ unsigned row_sum_u32(unsigned x)
     return x;
 }
 
+// the largest of the row's values (unsigned), valid on its last lane
+__device__ __forceinline__ unsigned row_max_u32(unsigned x)
+{
+    DPP_STEP(x, op_max, 0x111, 0xf);
+    DPP_STEP(x, op_max, 0x112, 0xf);
+    DPP_STEP(x, op_max, 0x114, 0xf);
+    DPP_STEP(x, op_max, 0x118, 0xf);
+    return x;
+}
+
+// Passes over all nodes' neighbours: most nodes have far fewer than 64, so a row of 16 lanes
+// takes a node (four per wave) and only those of more than ROW_DEG neighbours get the whole
+// wave, one after the other.  body(x, sub, width) runs with the node's 16 or 64 lanes (the other
+// rows' nodes beside it); all lanes of the wave call it, x < 0 where there is no node.
+#define ROW_DEG 256
+template <class Body>
+__device__ __forceinline__ void for_rows(const long long *rowptr, long long n, Body body)
+{
+    const int lane = threadIdx.x & (WAVE - 1), sub = lane & 15;
+    const long long x = (blockIdx.x * (long long)blockDim.x + threadIdx.x) / 16;
+    if (x - lane / 16 >= n) return;          // uniform over the wave
+    const bool in = x < n, longer = in && rowptr[x + 1] - rowptr[x] > ROW_DEG;
+    body(in && !longer ? x : -1, sub, 16);
+    for (unsigned long long rest = __ballot(longer && sub == 0); rest; rest &= rest - 1) {
+        WAVE_SYNC();
+        body(x - lane / 16 + (__ffsll((long long)rest) - 1) / 16, lane, WAVE);
+    }
+}
+
 // the largest of the lanes' values (unsigned), the same on every lane
 __device__ __forceinline__ unsigned wave_max_u32(unsigned x)
 {
