@@ -31,9 +31,10 @@
 //    lists rebuilt and the exact partition score reduced.
 //
 // Layout in HBM: CSR (rowptr int64, col int32); per node a 16-byte header {slot offset,
-// count, degree}; membership slots {community, in-count} (8 bytes); per community SoA
-// arrays (size, internal edges, score, S+ and S- as 192-bit fixed point); member lists with
-// per-community capacity for the iteration's joiners (overflow goes to a global list).
+// count, degree} and, within an iteration, a 64-byte line with up to six memberships;
+// membership slots {community, in-count} (8 bytes); per community one 64-byte record (size,
+// internal edges, score, S+ and S- as 160-bit fixed point); member lists with per-community
+// capacity for the iteration's joiners (overflow goes to a global list).
 #include "method.h"
 
 static inline unsigned grid_for(long long n, int block) { return (unsigned)((n + block - 1) / block); }
@@ -165,7 +166,7 @@ __global__ void k_opener_ids(const int *order, const int *flag, const long long 
 __global__ void __launch_bounds__(256) k_join_openers(const long long *rowptr, const int *col, const int *col_rank,
                                                       const int *order, const int *state, long long n, int *comm_of)
 {
-    for_rows(rowptr, n, [&](long long x, int sub, int width) {
+    for_rows(n, [&](long long x) { return rowptr[x + 1] - rowptr[x]; }, [&](long long x, int sub, int width) {
         const bool joins = x >= 0 && state[x] == 2;
         unsigned best = 0x7fffffff;
         if (joins) {
@@ -192,7 +193,7 @@ __global__ void __launch_bounds__(256) k_init_slots(const long long *rowptr, con
         nh[n].cnt = 0;
         nh[n].deg = 0;
     }
-    for_rows(rowptr, n, [&](long long x, int sub, int width) {
+    for_rows(n, [&](long long x) { return rowptr[x + 1] - rowptr[x]; }, [&](long long x, int sub, int width) {
         int c = 0, in = 0;
         if (x >= 0) {
             c = comm_of[x];
@@ -215,99 +216,115 @@ __global__ void __launch_bounds__(256) k_init_slots(const long long *rowptr, con
     });
 }
 
-// warm start: checks of a given cover (waves stride over the nodes): offsets non-decreasing
-// within [0, total] (bit 0), ids in [0, K) (bit 1; K < 0: any id >= 0), no id twice per
-// node (bit 2); chk[1] = largest id.  One atomic per wave at the end: a single hot
-// counter updated per node would serialise millions of atomics.
+// warm start: checks of a given cover: offsets non-decreasing within [0, total] (bit 0), ids in
+// [0, K) (bit 1; K < 0: any id >= 0), no id twice per node (bit 2); chk[1] = largest id.  A
+// thread per node, a wave for those with more than CHECK_OWN ids, one atomic per block at the
+// end (a wave per node, and one atomic each: 206 us for 1M nodes, now 23).
+#define CHECK_OWN 16
 __global__ void __launch_bounds__(256) k_cover_check(const long long *off, const int *ids, long long n,
                                                      long long total, int K, int *chk)
 {
+    __shared__ int s_err[256 / WAVE], s_mx[256 / WAVE];
     const int lane = threadIdx.x & (WAVE - 1);
-    const long long nw = (long long)gridDim.x * (blockDim.x / WAVE);
     int err = 0, mx = -1;
-    for (long long x = (blockIdx.x * (long long)blockDim.x + threadIdx.x) / WAVE; x < n; x += nw) {
-        const long long a0 = off[x], a1 = off[x + 1];
-        if (a0 < 0 || a1 < a0 || a1 > total) {
-            err |= 1;
-            continue;
-        }
-        for (long long a = a0 + lane; a < a1; a += WAVE) {
-            const int c = ids[a];
-            if (c < 0 || (K >= 0 && c >= K)) err |= 2;
-            if (c > mx) mx = c;
-            for (long long b = a0; b < a; b++) err |= ids[b] == c ? 4 : 0;
+    // one id against the range and those before it in the list
+    auto check = [&](long long a0, long long a) {
+        const int c = ids[a];
+        if (c < 0 || (K >= 0 && c >= K)) err |= 2;
+        if (c > mx) mx = c;
+        for (long long b = a0; b < a; b++) err |= ids[b] == c ? 4 : 0;
+    };
+    for (long long x0 = blockIdx.x * (long long)blockDim.x + (threadIdx.x - lane); x0 < n;
+         x0 += (long long)gridDim.x * blockDim.x) {
+        const long long x = x0 + lane;
+        const long long a0 = x < n ? off[x] : 0, a1 = x < n ? off[x + 1] : 0;
+        const bool bad = a0 < 0 || a1 < a0 || a1 > total;
+        if (bad) err |= 1;
+        const bool own = !bad && a1 - a0 <= CHECK_OWN;
+        for (long long a = a0; own && a < a1; a++) check(a0, a);
+        for (unsigned long long rest = __ballot(!bad && !own); rest; rest &= rest - 1) {
+            const int src = __ffsll((long long)rest) - 1;
+            const long long w0 = __shfl(a0, src, WAVE), w1 = __shfl(a1, src, WAVE);
+            for (long long a = w0 + lane; a < w1; a += WAVE) check(w0, a);
+            WAVE_SYNC();
         }
     }
-    for (int o = 32; o >= 1; o >>= 1) {
-        err |= __shfl_xor(err, o, WAVE);
-        const int om = __shfl_xor(mx, o, WAVE);
-        mx = om > mx ? om : mx;
-    }
+    for (int o = 32; o >= 1; o >>= 1) err |= __shfl_xor(err, o, WAVE);
+    mx = (int)wave_max_u32((unsigned)(mx + 1)) - 1;
     if (lane == 0) {
-        if (err) atomicOr(&chk[0], err);
-        if (mx >= 0) atomicMax(&chk[1], mx);
+        s_err[threadIdx.x / WAVE] = err;
+        s_mx[threadIdx.x / WAVE] = mx;
     }
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    for (int w = 1; w < 256 / WAVE; w++) {
+        err |= s_err[w];
+        mx = s_mx[w] > mx ? s_mx[w] : mx;
+    }
+    if (err) atomicOr(&chk[0], err);
+    if (mx >= 0) atomicMax(&chk[1], mx);
 }
 
 // warm start: node x's memberships in the given order plus one free slot (slot offset
 // off[x] + x); in-count of each = neighbours whose cover lists the community; sizes.
-// One wave per node; a pass over the neighbours' lists counts up to COVER_CHUNK of x's
-// communities at once (a node's ids are distinct, so each neighbour adds at most one to
+// A row of lanes per node (a wave for the longest; 0.61 -> 0.46 ms for 700,000 nodes); a pass over
+// the neighbours' lists counts up to COVER_CHUNK of x's communities at once (a node's ids are distinct, so each neighbour adds at most one to
 // each count), so a node with few memberships gathers its neighbourhood once.
 #define COVER_CHUNK 8
 __global__ void __launch_bounds__(256) k_cover_slots(const long long *rowptr, const int *col, const int *deg,
                                                      const long long *off, const int *ids, long long n, NodeHdr *nh,
                                                      Slot *slot, CommRec *cr)
 {
-    long long x = (blockIdx.x * (long long)blockDim.x + threadIdx.x) / WAVE;
-    int lane = threadIdx.x & (WAVE - 1);
-    if (x > n) return;
-    if (x == n) {
-        if (lane == 0) { nh[n].off = off[n] + n; nh[n].cnt = 0; nh[n].deg = 0; }
-        return;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        nh[n].off = off[n] + n;
+        nh[n].cnt = 0;
+        nh[n].deg = 0;
     }
-    const long long a0 = off[x];
-    const int cnt = (int)(off[x + 1] - a0);
-    const long long base = a0 + x;
-    const long long e0 = rowptr[x], e1 = rowptr[x + 1];
-    for (int a = 0; a < cnt; a += COVER_CHUNK) {
-        const int m = cnt - a < COVER_CHUNK ? cnt - a : COVER_CHUNK;   // uniform over the wave
-        int c[COVER_CHUNK], in[COVER_CHUNK];
+    for_rows(n, [&](long long x) { return rowptr[x + 1] - rowptr[x]; }, [&](long long x, int sub, int width) {
+        const long long a0 = x >= 0 ? off[x] : 0;
+        const int cnt = x >= 0 ? (int)(off[x + 1] - a0) : 0;
+        const long long base = a0 + x;
+        const long long e0 = x >= 0 ? rowptr[x] : 0, e1 = x >= 0 ? rowptr[x + 1] : 0;
+        for (int a = 0; __ballot(a < cnt); a += COVER_CHUNK) {
+            const int m = cnt - a < COVER_CHUNK ? cnt - a : COVER_CHUNK;   // (below 1: none left)
+            int c[COVER_CHUNK], in[COVER_CHUNK];
 #pragma unroll
-        for (int k = 0; k < COVER_CHUNK; k++) {
-            c[k] = k < m ? ids[a0 + a + k] : -1;   // ids are >= 0: -1 matches nothing
-            in[k] = 0;
-        }
-        for (long long e = e0 + lane; e < e1; e += WAVE) {
-            const int z = col[e];
-            const long long b1 = off[z + 1];
-            for (long long b = off[z]; b < b1; b++) {
-                const int d = ids[b];
-#pragma unroll
-                for (int k = 0; k < COVER_CHUNK; k++) in[k] += d == c[k];
+            for (int k = 0; k < COVER_CHUNK; k++) {
+                c[k] = k < m ? ids[a0 + a + k] : -1;   // ids are >= 0: -1 matches nothing
+                in[k] = 0;
             }
-        }
+            for (long long e = m > 0 ? e0 + sub : e1; e < e1; e += width) {
+                const int z = col[e];
+                const long long b1 = off[z + 1];
+                for (long long b = off[z]; b < b1; b++) {
+                    const int d = ids[b];
 #pragma unroll
-        for (int k = 0; k < COVER_CHUNK; k++) {
-            if (k < m) {
-                const int t = wave_sum_int(in[k]);
-                if (lane == 0) {
+                    for (int k = 0; k < COVER_CHUNK; k++) in[k] += d == c[k];
+                }
+            }
+            WAVE_SYNC();
+#pragma unroll
+            for (int k = 0; k < COVER_CHUNK; k++) {
+                if (!__ballot(k < m)) break;
+                const int t = width == 16 ? (int)row_sum_u32((unsigned)in[k]) : (int)wave_sum_u32((unsigned)in[k]);
+                if (k < m && sub == width - 1) {
                     Slot sl = {c[k], t};
                     slot[base + a + k] = sl;
                     atomicAdd(&cr[c[k]].s, 1);
                 }
             }
+            WAVE_SYNC();
         }
-    }
-    if (lane == 0) {
-        NodeHdr hd;
-        hd.off = base;
-        hd.cnt = cnt;
-        hd.deg = deg[x];
-        nh[x] = hd;
-        Slot free_slot = {-1, 0};
-        slot[base + cnt] = free_slot;
-    }
+        if (x >= 0 && sub == width - 1) {
+            NodeHdr hd;
+            hd.off = base;
+            hd.cnt = cnt;
+            hd.deg = deg[x];
+            nh[x] = hd;
+            Slot free_slot = {-1, 0};
+            slot[base + cnt] = free_slot;
+        }
+    });
 }
 
 // ------------------------------------------------------------------------------------
@@ -1007,8 +1024,8 @@ int lf_check_cover(lf_handle *h, const long long *off, const int *ids, long long
     LF_TRY(lf_tmp_alloc(h, (void **)&chk, 2 * sizeof(int)));
     const int init[2] = {0, -1};
     LF_HIP(h, hipMemcpyAsync(chk, init, sizeof init, hipMemcpyHostToDevice, st));
-    unsigned gc = grid_for(n * WAVE, BS);
-    if (gc > 2048) gc = 2048;
+    unsigned gc = grid_for(n, BS);
+    if (gc > 1024) gc = 1024;
     if (n > 0) hipLaunchKernelGGL(k_cover_check, dim3(gc), dim3(BS), 0, st, off, ids, n, total, n_comms, chk);
     int hc[2];
     LF_HIP(h, hipMemcpyAsync(hc, chk, sizeof hc, hipMemcpyDeviceToHost, st));
@@ -1037,7 +1054,7 @@ int lf_partition_from_cover(lf_handle *h, const long long *off, const int *ids, 
     LF_HIP(h, hipMemsetAsync(h->ctr, 0, sizeof(DevCounters), st));
     LF_TRY(lf_prof_begin(h, LF_K_INITCLUST));
     LF_TRY(alloc_partition_state(h, K, total + n));
-    hipLaunchKernelGGL(k_cover_slots, dim3(grid_for((n + 1) * WAVE, BS)), dim3(BS), 0, st, h->rowptr, h->col,
+    hipLaunchKernelGGL(k_cover_slots, dim3(grid_for(n > 0 ? n * 16 : 1, BS)), dim3(BS), 0, st, h->rowptr, h->col,
                        h->deg, off, ids, n, h->nh, h->slot[0], h->cr);
     LF_TRY(finish_partition(h));
     LF_TRY(lf_prof_end(h, LF_K_INITCLUST, 8));

@@ -317,7 +317,7 @@ int lf_build_graph(lf_handle *h, long long n, long long np, const long long *src
 
     LF_TRY(lf_dev_alloc(h, (void **)&h->deg, sizeof(int) * (n > 0 ? n : 1)));
     LF_TRY(lf_dev_alloc(h, (void **)&h->rowptr, sizeof(long long) * (n + 1)));
-    LF_TRY(lf_dev_alloc(h, (void **)&h->col, sizeof(int) * (2 * ne > 0 ? 2 * ne : 1)));
+    LF_TRY(lf_dev_alloc(h, (void **)&h->col, sizeof(int) * (2 * ne + READ_PAD)));
     LF_TRY(lf_dev_alloc(h, (void **)&h->orig_id, sizeof(long long) * (n > 0 ? n : 1)));
     // the sort's alternate buffer is the one compacted from: stream order makes that safe
     LF_TRY(lf_sort_u64(h, rev, rev_alt, ne, B, &sorted));
@@ -355,7 +355,7 @@ __device__ __forceinline__ bool before(int du, int u, int dv, int v)
 __global__ void __launch_bounds__(256) k_out_degree(const long long *rowptr, const int *col,
                                                     const int *deg, long long n, int *od)
 {
-    for_rows(rowptr, n, [&](long long u, int sub, int width) {
+    for_rows(n, [&](long long x) { return rowptr[x + 1] - rowptr[x]; }, [&](long long u, int sub, int width) {
         int c = 0;
         if (u >= 0) {
             const int du = deg[u];
@@ -377,7 +377,7 @@ __global__ void __launch_bounds__(256) k_out_fill(const long long *rowptr, const
                                                   int *orc)
 {
     const int row = threadIdx.x & (WAVE - 1) & 48;       // the row's first lane
-    for_rows(rowptr, n, [&](long long u, int sub, int width) {
+    for_rows(n, [&](long long x) { return rowptr[x + 1] - rowptr[x]; }, [&](long long u, int sub, int width) {
         const int du = u >= 0 ? deg[u] : 0;
         const long long r1 = u >= 0 ? rowptr[u + 1] : 0;
         long long base = u >= 0 ? rowptr[u] : 0, w = u >= 0 ? oro[u] : 0;
@@ -507,14 +507,6 @@ __device__ __forceinline__ int tri_push(TriQueue<WCC, J> &Q, int &qn, bool cand,
 #define TRI_GW 16               // lanes per list of theirs
 #define TRI_PER 4               // entries per lane
 #define TRI_WAVES 1
-
-// four entries of an out-list from p on (the array is padded by as many)
-__device__ __forceinline__ v4i read_entries(const int *p)
-{
-    v4i r;
-    __builtin_memcpy(&r, p, sizeof r);
-    return r;
-}
 
 // A wave probes the lists k = first, first + stride, .. < ns of one node u: TRI_GW lanes walk one
 // list at a time, TRI_PER entries each, and take the next one that is left when theirs ends; the
@@ -873,7 +865,7 @@ int lf_triangle_pass(lf_handle *h, const WccTri *wt, int *launches, long long **
     int *cnt = nullptr;
     LF_TRY(lf_tmp_alloc(h, (void **)&od, sizeof(int) * (n > 0 ? n : 1)));
     LF_TRY(lf_tmp_alloc(h, (void **)&oro, sizeof(long long) * (n + 1)));
-    LF_TRY(lf_tmp_alloc(h, (void **)&orc, sizeof(int) * (h->ne + TRI_PER)));   // (read_entries)
+    LF_TRY(lf_tmp_alloc(h, (void **)&orc, sizeof(int) * (h->ne + READ_PAD)));
     LF_TRY(lf_tmp_alloc(h, (void **)&defer, sizeof(int) * (n > 0 ? n : 1)));
     LF_TRY(lf_tmp_alloc(h, (void **)&cnt, sizeof(int) * 4));
     LF_HIP(h, hipMemsetAsync(cnt, 0, sizeof(int) * 4, st));
@@ -970,7 +962,7 @@ int lf_node_stats(lf_handle *h)
     LF_TRY(lf_dev_alloc(h, (void **)&h->order, sizeof(int) * (n > 0 ? n : 1)));
     LF_TRY(lf_dev_alloc(h, (void **)&h->rank, sizeof(int) * (n > 0 ? n : 1)));
     const long long m = 2 * h->ne;
-    LF_TRY(lf_dev_alloc(h, (void **)&h->col_rank, sizeof(int) * (m > 0 ? m : 1)));
+    LF_TRY(lf_dev_alloc(h, (void **)&h->col_rank, sizeof(int) * (m + READ_PAD)));
     unsigned *k1 = nullptr, *k1b = nullptr;
     int *v1 = nullptr, *v1b = nullptr;
     unsigned long long *k2 = nullptr, *k2b = nullptr;

@@ -123,22 +123,6 @@ __device__ __forceinline__ int find_slot_in(const Slot *slot, long long off, int
     return -1;
 }
 
-__device__ __forceinline__ int find_slot(const Slot *slot, long long off, int cnt, int c)
-{
-    // four independent loads per round trip (a node holds a handful of memberships)
-    for (int t = 0; t < cnt; t += 4) {
-        const int c0 = slot[off + t].comm;
-        const int c1 = t + 1 < cnt ? slot[off + t + 1].comm : -2;
-        const int c2 = t + 2 < cnt ? slot[off + t + 2].comm : -2;
-        const int c3 = t + 3 < cnt ? slot[off + t + 3].comm : -2;
-        if (c0 == c) return t;
-        if (c1 == c) return t + 1;
-        if (c2 == c) return t + 2;
-        if (c3 == c) return t + 3;
-    }
-    return -1;
-}
-
 // correction of one neighbour y (in C with in-count i, degree dy) when x joins C (its
 // in-count rises by one, the size to s+1) or leaves C (falls by one, size s-1)
 __device__ __forceinline__ u128 visit_term(bool leave, int i, int dy, int s, int &bad)
@@ -239,18 +223,37 @@ __device__ __forceinline__ unsigned row_max_u32(unsigned x)
     return x;
 }
 
+// four entries of an adjacency or out-list from p on, in one read (the arrays are padded by
+// READ_PAD entries)
+#define READ_PAD 4
+__device__ __forceinline__ v4i read_entries(const int *p)
+{
+    v4i r;
+    __builtin_memcpy(&r, p, sizeof r);
+    return r;
+}
+
+// the sum over the lane's 8 lanes of a row, valid on the last of them
+__device__ __forceinline__ unsigned oct_sum_u32(unsigned x)
+{
+    DPP_STEP(x, op_add, 0x111, 0xf);
+    DPP_STEP(x, op_add, 0x112, 0xf);
+    DPP_STEP(x, op_add, 0x114, 0xf);
+    return x;
+}
+
 // Passes over all nodes' neighbours: most nodes have far fewer than 64, so a row of 16 lanes
 // takes a node (four per wave) and only those of more than ROW_DEG neighbours get the whole
 // wave, one after the other.  body(x, sub, width) runs with the node's 16 or 64 lanes (the other
 // rows' nodes beside it); all lanes of the wave call it, x < 0 where there is no node.
 #define ROW_DEG 256
-template <class Body>
-__device__ __forceinline__ void for_rows(const long long *rowptr, long long n, Body body)
+template <class Degree, class Body>
+__device__ __forceinline__ void for_rows(long long n, Degree degree, Body body)
 {
     const int lane = threadIdx.x & (WAVE - 1), sub = lane & 15;
     const long long x = (blockIdx.x * (long long)blockDim.x + threadIdx.x) / 16;
     if (x - lane / 16 >= n) return;          // uniform over the wave
-    const bool in = x < n, longer = in && rowptr[x + 1] - rowptr[x] > ROW_DEG;
+    const bool in = x < n, longer = in && degree(x) > ROW_DEG;
     body(in && !longer ? x : -1, sub, 16);
     for (unsigned long long rest = __ballot(longer && sub == 0); rest; rest &= rest - 1) {
         WAVE_SYNC();
@@ -336,12 +339,6 @@ __device__ __forceinline__ void member_terms(const Ctx &cx, int y, int C, int s,
 }
 
 // ---- membership lines (the queue kernels' view of the memberships) --------------------
-// first membership slot of a node whose line is l
-__device__ __forceinline__ Slot *line_slots(const Ctx &cx, int x, const NodeLine &l)
-{
-    return l.off < 0 ? cx.ln[x].s : cx.slot + l.off;
-}
-
 // position of community c among the memberships of the node with line l (-1 if absent)
 // and its in-count: inline memberships come from the line itself
 __device__ __forceinline__ int line_find(const Ctx &cx, const NodeLine &l, int c, int *in)
@@ -377,29 +374,5 @@ __device__ __forceinline__ void member_terms_line(const Ctx &cx, int y, int C, i
     member_terms_of(cx, as_line(r), C, s, a0, ap, am, sumi, bad);
 }
 
-// The lanes executing this call with want = true receive consecutive indices from *ctr,
-// with a single atomic per wave (the leader is an active lane, so divergent callers are
-// fine); returns -1 for the others.
-__device__ __forceinline__ int wave_reserve(int *ctr, bool want)
-{
-    unsigned long long m = __ballot(want);
-    if (!m) return -1;
-    int lane = threadIdx.x & (WAVE - 1);
-    int leader = __ffsll((long long)m) - 1;
-    int base = 0;
-    if (lane == leader) base = atomicAdd(ctr, __popcll(m));
-    base = __shfl(base, leader, WAVE);
-    return want ? base + __popcll(m & ((1ull << lane) - 1)) : -1;
-}
-
 __device__ __forceinline__ unsigned hash_tab(int c) { return (unsigned)c * 0x9E3779B1u; }
 
-__device__ __forceinline__ unsigned long long hash64(unsigned long long k)
-{
-    k ^= k >> 33;
-    k *= 0xff51afd7ed558ccdull;
-    k ^= k >> 33;
-    k *= 0xc4ceb9fe1a85ec53ull;
-    k ^= k >> 33;
-    return k;
-}

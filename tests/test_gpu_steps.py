@@ -169,3 +169,31 @@ def test_split_launch_of_larger_nodes(lf, orc, n, opts):
     same_state(h, o)
     h.close()
     o.close()
+
+
+@pytest.mark.parametrize("refs", [1, 2, 7, 300])
+def test_f1_run_lengths(lf, orc, refs):
+    """Detected communities that share 1 to 4,000 nodes with a reference one (runs whose end is
+    found by doubling), one that meets hundreds of them (whole waves of runs), nodes with more
+    ids than one thread checks, and id counts at which the keys gain a bit."""
+    say("f1 runs", refs)
+    sizes = [1, 2, 3, 4, 63, 64, 65, 127, 128, 129, 1023, 4000]
+    n = sum(sizes)
+    g = G.Graph(n, np.arange(n, dtype=np.int64), np.roll(np.arange(n, dtype=np.int64), -1))
+    off, ids = cover([[c] for c, s in enumerate(sizes) for _ in range(s)])
+    rng = np.random.default_rng(refs)
+    few = [[int(rng.integers(0, refs))] for _ in range(n)]
+    for x in (5, 700, n - 1):
+        few[x] = rng.choice(refs, min(refs, 40), replace=False)
+    roff, rids = cover(few)
+    h = loaded(lf, g)
+    h.init_from_memberships(off, ids, len(sizes))
+    o = orc.Oracle()
+    o.load_graph(g.n, g.src, g.dst)
+    o.init_from_memberships(off, ids, len(sizes))
+    a, b = h.cover_f1(roff, rids), o.cover_f1(roff, rids)
+    assert a[0] == b[0]
+    assert np.array_equal(np.asarray(a[1]).view(np.int64), np.asarray(b[1]).view(np.int64))
+    assert np.array_equal(a[2], b[2])
+    h.close()
+    o.close()
