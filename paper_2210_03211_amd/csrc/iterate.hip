@@ -7,8 +7,8 @@
 // list of its nodes in order.  Per queue (all launches on the handle's stream, no host
 // synchronisation):
 //   k_refresh        the exact re-sums of the communities that the queue before touched, a
-//                    wave per part (multi-part communities meet in digit counters and the
-//                    last part stores them); beside them, by block role, the gather of this
+//                    wave per part (a community's parts leave their sums side by side and the
+//                    last one adds them up); beside them, by block role, the gather of this
 //                    queue's nodes: own and neighbours' memberships flattened into a list per
 //                    node, and the table path's visits (largest nodes) grouped by hash bucket
 //                    of their communities
@@ -17,7 +17,8 @@
 //                    with <= 256 (k_eval_whole gathers and scores, in very long queues)
 //   k_eval_big       in queues with larger nodes: the workgroup path (one workgroup per node
 //                    with <= 1024 entries), the table path's buckets (one block each), and the
-//                    small and medium paths; block 0 of the scoring resets the queue's counters
+//                    small and medium paths (k_eval_mid takes the latter two in long queues);
+//                    block 0 of the scoring resets the queue's counters
 //   k_big_tie        table path: the best of each node's buckets
 //   k_apply          the bulk apply: membership edits, sizes, member-list appends and
 //                    re-sum planning (a thread per queued node) beside the in-count
@@ -29,7 +30,6 @@
 #include "method.h"
 
 #define EW 4            // waves per block in the wave evaluation path
-#define ECAP 128        // table entries per wave (power of two)
 #define MXCAP 32        // own memberships kept in LDS (wave path)
 #define INB 64          // neighbours per in-count unit (one per lane)
 #define HOLE (-2)       // a membership left in the current iteration (removed at its end)
@@ -1699,23 +1699,18 @@ MULTI_KERNEL(k_refresh, GT, StepLds, body_refresh)
 // in the same queue are read at the queue's start).  So visits at evaluation <=
 // B = visits at the iteration start + neighbours earlier in the order, and the path
 // chosen from B always fits.  vbound[x] = B + own + 1 bounds x's distinct table keys.
-// NB_NODES consecutive nodes per wave: their neighbour ranges are walked as one flattened
-// range (most nodes have far fewer than 64 neighbours), each lane finding its node in the
-// wave's range starts, and the per-node sums collect in LDS.  A neighbour's membership count
-// comes from one byte per node (mc8, 255: look in the node's header), an array that the
-// caches hold where the headers do not (70M gathers on the 4M-node social-shaped graph: 643
-// us a pass against 1,360 from the headers), and the neighbours earlier in the order are
-// counted once per clustering (FIRST) and kept.
-#define NB_NODES 16
+// Eight lanes per node (a wave for the longest), four neighbours per lane at a time: one read of
+// columns, then four gathers under way.  A neighbour's membership count comes from one byte per
+// node (mc8, 255: look in the node's header), an array that the caches hold where the headers do
+// not, and the neighbours earlier in the order are counted once per clustering (FIRST) and
+// kept.  70M gathers on the 4M-node social-shaped graph: 1,360 us a pass from the headers, 643
+// from mc8 with a search for each neighbour's node, 551 now (8.7M gathers of 700,000 nodes 166 -> 90).
+#define NB_LANES 8
+#define NB_WAVE 512             // neighbours from which the whole wave takes the node
 template <bool FIRST>
 __global__ void __launch_bounds__(256) k_node_bounds(Ctx cx, const unsigned char *mc8, int *pre, long long *vbound,
                                                      int *cls, int wcap, int mcap, int gcap)
 {
-    __shared__ long long s_start[256 / WAVE][NB_NODES + 1];
-    __shared__ long long s_rb[256 / WAVE][NB_NODES];
-    __shared__ unsigned long long s_v[256 / WAVE][NB_NODES];
-    __shared__ unsigned s_pre[256 / WAVE][NB_NODES];
-    __shared__ int s_rx[256 / WAVE][NB_NODES];
     if (blockIdx.x == 0 && threadIdx.x == 0) {          // the iteration's counters
         DevCounters *c = cx.ctr;
         c->joins = 0;
@@ -1724,62 +1719,65 @@ __global__ void __launch_bounds__(256) k_node_bounds(Ctx cx, const unsigned char
         c->ovf_cnt = 0;
         c->live = 0;
     }
-    const int wv = threadIdx.x / WAVE, lane = threadIdx.x & (WAVE - 1);
-    const long long x0 = (blockIdx.x * (long long)(blockDim.x / WAVE) + wv) * NB_NODES;
-    if (x0 >= cx.n) return;                 // uniform over the wave; only wave-level syncs below
-    const int nn = cx.n - x0 < NB_NODES ? (int)(cx.n - x0) : NB_NODES;
-    long long rb = 0, d = 0;
-    int rx = 0;
-    if (lane < nn) {
-        rb = cx.rowptr[x0 + lane];
-        d = cx.rowptr[x0 + lane + 1] - rb;
-        rx = cx.rank[x0 + lane];
-    }
-    long long incl = d;                     // lanes >= nn add nothing
-    for (int o = 1; o < NB_NODES; o <<= 1) {
-        const long long t = __shfl_up(incl, o, WAVE);
-        if (lane >= o) incl += t;
-    }
-    const long long D = __shfl(incl, NB_NODES - 1, WAVE);
-    if (lane < NB_NODES) {
-        s_start[wv][lane + 1] = incl;
-        s_rb[wv][lane] = rb;
-        s_rx[wv][lane] = rx;
-        s_v[wv][lane] = 0;
-        s_pre[wv][lane] = 0;
-    }
-    if (lane == 0) s_start[wv][0] = 0;
-    WAVE_SYNC();
-    for (long long f = lane; f < D; f += WAVE) {
-        int lo = 0, hi = nn - 1;            // the last node whose range starts at or before f
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (s_start[wv][mid] <= f) lo = mid; else hi = mid - 1;
+    const int lane = threadIdx.x & (WAVE - 1), sub = lane & (NB_LANES - 1);
+    const long long x = (blockIdx.x * (long long)blockDim.x + threadIdx.x) / NB_LANES;
+    if (x - lane / NB_LANES >= cx.n) return;            // uniform over the wave
+    const bool in = x < cx.n;
+    const long long xc = in ? x : cx.n - 1;
+    const long long rb = cx.rowptr[xc], r1 = cx.rowptr[xc + 1];
+    const int rx = cx.rank[xc];
+    const NodeHdr hx = cx.nh[xc];
+    const bool longer = in && r1 - rb > NB_WAVE;
+    // visits and earlier neighbours among entries [e, e1) from e on in steps of `step`
+    auto count = [&](long long e, long long e1, int step, int rank, long long &v, unsigned &b) {
+        for (; e < e1; e += step) {
+            const v4i y = read_entries(cx.col + e);
+            v4i ry = {0, 0, 0, 0};
+            if (FIRST) ry = read_entries(cx.col_rank + e);
+            unsigned c[4];
+#pragma unroll
+            for (int t = 0; t < 4; t++) c[t] = mc8[e + t < e1 ? y[t] : y[0]];
+#pragma unroll
+            for (int t = 0; t < 4; t++)
+                if (e + t < e1) {
+                    v += c[t] == 255 ? cx.nh[y[t]].cnt : (int)c[t];
+                    if (FIRST) b += ry[t] < rank;
+                }
         }
-        const long long e = s_rb[wv][lo] + (f - s_start[wv][lo]);
-        const int y = cx.col[e];
-        unsigned c = mc8[y];
-        if (c == 255) c = (unsigned)cx.nh[y].cnt;
-        atomicAdd(&s_v[wv][lo], (unsigned long long)c);
-        if (FIRST && cx.col_rank[e] < s_rx[wv][lo]) atomicAdd(&s_pre[wv][lo], 1u);
-    }
+    };
+    long long v = 0;
+    unsigned b = 0;
+    count(rb + 4 * sub, in && !longer ? r1 : 0, 4 * NB_LANES, rx, v, b);
     WAVE_SYNC();
-    if (lane < nn) {
-        const long long x = x0 + lane;
-        NodeHdr hx = cx.nh[x];
-        int before;
-        if (FIRST) pre[x] = before = (int)s_pre[wv][lane];
-        else before = pre[x];
-        const long long B = (long long)s_v[wv][lane] + before, M = hx.cnt, dd = hx.deg;
-        vbound[x] = B + M + 1;
-        int c = LF_PATH_TABLE;
-        if (M <= MXCAP) {
-            if (dd <= VSMALL && B + M <= VSMALL && 2 * (B + M) <= wcap) c = LF_PATH_SMALL;
-            else if (dd <= VMED && B + M <= VMED && 2 * (B + M) <= mcap) c = LF_PATH_MED;
-            else if (dd <= VGRP && B + M <= VGRP && 2 * (B + M) <= gcap) c = LF_PATH_GROUP;
+    long long V = (long long)oct_sum_u32((unsigned)v & 0xffffffu) + ((long long)oct_sum_u32((unsigned)(v >> 24)) << 24);
+    unsigned P = FIRST ? oct_sum_u32(b) : 0;
+    for (unsigned long long rest = __ballot(longer && sub == 0); rest; rest &= rest - 1) {
+        const int src = __ffsll((long long)rest) - 1;
+        long long vw = 0;
+        unsigned bw = 0;
+        count(__shfl(rb, src, WAVE) + 4 * lane, __shfl(r1, src, WAVE), 4 * WAVE, __shfl(rx, src, WAVE), vw, bw);
+        WAVE_SYNC();
+        vw = (long long)wave_sum_u32((unsigned)vw & 0xffffffu) + ((long long)wave_sum_u32((unsigned)(vw >> 24)) << 24);
+        if (FIRST) bw = wave_sum_u32(bw);
+        if (lane / NB_LANES == src / NB_LANES) {
+            V = vw;
+            P = bw;
         }
-        cls[rx] = c;
+        WAVE_SYNC();
     }
+    if (!in || sub != NB_LANES - 1) return;
+    int before;
+    if (FIRST) pre[x] = before = (int)P;
+    else before = pre[x];
+    const long long B = V + before, M = hx.cnt, dd = hx.deg;
+    vbound[x] = B + M + 1;
+    int c = LF_PATH_TABLE;
+    if (M <= MXCAP) {
+        if (dd <= VSMALL && B + M <= VSMALL && 2 * (B + M) <= wcap) c = LF_PATH_SMALL;
+        else if (dd <= VMED && B + M <= VMED && 2 * (B + M) <= mcap) c = LF_PATH_MED;
+        else if (dd <= VGRP && B + M <= VGRP && 2 * (B + M) <= gcap) c = LF_PATH_GROUP;
+    }
+    cls[rx] = c;
 }
 
 // The path lists (ascending order positions, path after path): every tile of CLS_TILE positions
@@ -2158,7 +2156,7 @@ static int size_queue_enqueue(lf_handle *h, long long q)
     h->lines_ready = true;
     // paths of this iteration
     const bool first = !h->static_ready;
-    const dim3 bg(grid_for((n + NB_NODES - 1) / NB_NODES * WAVE, BS));
+    const dim3 bg(grid_for(n * NB_LANES, BS));
     const int wcap = h->eval_wave_cap < 2 * VSMALL ? h->eval_wave_cap : 2 * VSMALL;
     if (first)
         hipLaunchKernelGGL(k_node_bounds<true>, bg, dim3(BS), 0, st, lf_ctx(h), (const unsigned char *)h->mc8, h->pre,
