@@ -151,9 +151,9 @@ def eval_rates(timing, work):
 
 
 def kernel_rooflines(timing, work):
-    """Achieved algorithmic GB/s of each queue kernel with a byte model (HIP-event times of
-    a profiled pass, bytes of a counter pass), of the evaluation kernels together and of
-    the apply kernels together."""
+    """Achieved algorithmic GB/s by evaluation path, gather and scoring counted with the kernel
+    that scores (HIP-event times of a profiled pass, bytes of a counter pass), of the
+    evaluation kernels together and of the apply kernels together."""
     out = {}
     groups = {"evaluation": [0.0, 0.0], "apply": [0.0, 0.0]}
     for k in EVAL_KERNELS[:3] + APPLY_KERNELS:
@@ -172,6 +172,58 @@ def kernel_rooflines(timing, work):
         if ms > 0.0:
             gbs = b / (ms * 1e-3) / 1e9
             out[name] = {"GB_s": gbs, "frac": gbs / HBM_PEAK_GBS, "ms": ms}
+    return out
+
+
+# A queue's nodes are flattened (record, own memberships, neighbours, visits) by a launch
+# before the one that scores them (candidates, decision).  Up to this queue size that launch
+# is always k_refresh, whose blocks re-sum the queue before beside it; longer queues may have
+# their small and medium nodes gathered and scored in k_eval.
+LIST_QUEUE = 4096
+B_RECORD, B_DECISION = 16.0, 24.0
+
+
+def gather_bytes(w):
+    return B_RECORD * w["nodes"] + B_OWN * w.get("own", 0) + B_NEIGHBOUR * w["neighbours"] + B_VISIT * w["visits"]
+
+
+def score_bytes(w):
+    return B_DECISION * w["nodes"] + B_CAND * w["candidates"]
+
+
+def launch_bytes(kernel, work, queue):
+    """Algorithmic bytes one pass moves in the launches of `kernel` at this queue size (None
+    where a node's scoring may be in either of two kernels)."""
+    p = work["paths"]
+    if kernel == "k_refresh":
+        light = ("small", "medium") if queue <= LIST_QUEUE else ()
+        return apply_bytes(kernel, work) + sum(gather_bytes(p[c]) for c in ("group", "table") + light)
+    if kernel in ("k_eval", "k_eval_big"):
+        if queue <= LIST_QUEUE:
+            return None
+        return (path_bytes(p["small"]) + path_bytes(p["medium"]) if kernel == "k_eval"
+                else score_bytes(p["group"]) + score_bytes(p["table"]))
+    return apply_bytes(kernel, work)
+
+
+def launch_rooflines(timing, work, queue):
+    """Achieved algorithmic GB/s of a queue's launches: each kernel with a model at this queue
+    size, the scoring launches together, and all of a queue together."""
+    ms = timing["ms"]
+    p = work["paths"].values()
+    scoring = ("k_eval", "k_eval_big", "k_big_tie")
+    rows = {k: (launch_bytes(k, work, queue), ms.get(k, 0.0)) for k in scoring[:2] + APPLY_KERNELS}
+    if queue <= LIST_QUEUE:
+        rows["scoring"] = (sum(score_bytes(w) for w in p), sum(ms.get(k, 0.0) for k in scoring))
+    rows["queue"] = (sum(path_bytes(w) for w in p) + sum(apply_bytes(k, work) for k in APPLY_KERNELS),
+                     sum(ms.get(k, 0.0) for k in scoring + APPLY_KERNELS))
+    out = {}
+    for k, (b, t) in rows.items():
+        if b is not None and t > 0.0:
+            gbs = b / (t * 1e-3) / 1e9
+            out[k] = {"GB_s": gbs, "frac": gbs / HBM_PEAK_GBS, "ms": t, "bytes_per_pass": b}
+            if k in timing["launches"]:
+                out[k]["launches"] = timing["launches"][k]
     return out
 
 
@@ -439,7 +491,7 @@ def dense_bench(args, lf, h, torch, proc, outdir):
            "end_to_end_s": dt, "node_evals_per_s": nn * info["iterations"] / dt,
            "generator_wait_s": wait_s, "communities_created": K, "max_degree": int(np.max(np.diff(h.csr()[0]))),
            "kernel_ms_timing_pass": {k: round(v, 3) for k, v in timing["ms"].items()},
-           "kernel_rooflines": kernel_rooflines(timing, work),
+           "kernel_rooflines": launch_rooflines(timing, work, q),
            "work_per_step": {"node_evals": work["node_evals"], "paths": work["paths"], "apply": work["apply"]}}
     out.update(check_against_oracle(gd, info, off, ids, "dense run"))
     print("[bench] dense: %.3fs, %d iterations, %s" % (dt, info["iterations"], out.get("stored_oracle")),
@@ -582,7 +634,8 @@ def serving_bench(args, lf, gen):
 
     # continuous batching through the server
     srv = lf.Server(0, hbm_budget=int(args.serving_budget_gib * (1 << 30)), max_batch=args.serving_max_batch)
-    srv.set_graph(not args.serving_no_graph)
+    if args.serving_no_graph:           # else the way the server takes by itself
+        srv.set_graph(False)
     lat_b, hashes_b, evals_b = {}, {}, 0
     jid_of = {}
     nxt = 0
@@ -633,7 +686,7 @@ def serving_bench(args, lf, gen):
 
     def pct(d, p):
         return 1000.0 * float(np.percentile(np.array(list(d.values())), p))
-    out = {"jobs": len(jobs), "rate_per_s": args.serving_rate, "graph_replay": not args.serving_no_graph,
+    out = {"jobs": len(jobs), "rate_per_s": args.serving_rate, "graph_replay": False if args.serving_no_graph else "default",
            "workload": "serving mix: Poisson arrivals, planted power-law graphs, nodes lognormal(median 2,000, "
                        "sigma 1.2) in [50, 200,000], mean degree 8-40, mixing 0.2-0.4, per-job queue",
            "batched": {"p50_ms": pct(lat_b, 50), "p99_ms": pct(lat_b, 99), "jobs_per_s": len(jobs) / span_b,
@@ -757,7 +810,7 @@ def main():
     # pass / launches per pass) over its average launch time in the timed steps
     launches = prof["launches"][dom]
     avg_ms = prof["ms"][dom] / max(1, launches)
-    pass_bytes = kernel_bytes(dom, work)
+    pass_bytes = launch_bytes(dom, work, q)
     per_launch = pass_bytes / max(1, timing["launches"][dom]) if pass_bytes is not None else None
     achieved = per_launch / (avg_ms * 1e-3) / 1e9 if per_launch is not None else None
     traffic = stored_traffic(dom, args.workload, active_options(h))
@@ -795,7 +848,7 @@ def main():
     if tuned is not None:
         out["autotune"] = tuned
     out["options"] = active_options(h)
-    out["kernel_rooflines"] = kernel_rooflines(timing, work)
+    out["kernel_rooflines"] = launch_rooflines(timing, work, q)
     out["kernel_rooflines"]["triangles"] = triangle_roofline(h, timing["ms"].get("triangles", 0.0))
     out["exact_wcc"] = exact_wcc_bench(h, args.steps)
     out["postprocess"] = postprocess_bench(h, args.steps)
@@ -832,7 +885,7 @@ def main():
                 else:
                     wprof = h.lf_get_profile()
             h.lf_set_profiling(0)
-            sweep[str(qq)]["kernel_rooflines"] = kernel_rooflines(tprof, wprof)
+            sweep[str(qq)]["kernel_rooflines"] = launch_rooflines(tprof, wprof, qq)
             print("[bench] sweep q=%d: %.3fs %d iterations %s" % (qq, s, si["iterations"],
                                                                   sweep[str(qq)].get("stored_oracle")),
                   file=sys.stderr, flush=True)

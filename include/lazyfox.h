@@ -71,7 +71,7 @@ typedef struct {
 #define LF_K_EVAL 4         /* k_eval: scoring of the small (<= 64 list entries) and medium (<=
                                256) paths of queues without larger nodes, or with very many
                                of these (then k_eval_whole, which also gathers them) */
-#define LF_K_EVAL_BIG 5     /* k_eval_big: scoring of queues with larger nodes: workgroup path
+#define LF_K_EVAL_BIG 5     /* k_eval_big, k_eval_mid: scoring of queues with larger nodes: workgroup path
                                (<= 1024), the table path's buckets, and the small and medium
                                paths */
 #define LF_K_TAB_FINAL 6    /* no longer launched (its work is part of k_eval_big); kept so

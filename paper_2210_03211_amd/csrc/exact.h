@@ -234,21 +234,6 @@ __device__ __forceinline__ void x192_digits(const X192 &t, i64 &d0, i64 &d1, i64
     d3 = (i64)(int)(unsigned)(t.w1 >> 32);
 }
 
-// the same digits of a 128-bit term, and the 128-bit sum of digit counters
-__device__ __forceinline__ void x128_digits(u128 t, i64 &d0, i64 &d1, i64 &d2, i64 &d3)
-{
-    d0 = (i64)(unsigned)t;
-    d1 = (i64)(unsigned)(t >> 32);
-    d2 = (i64)(unsigned)(t >> 64);
-    d3 = (i64)(int)(unsigned)(t >> 96);
-}
-
-__device__ __forceinline__ u128 x128_from_digits(i64 D0, i64 D1, i64 D2, i64 D3)
-{
-    const u128 s0 = (u128)(__int128)D0, s1 = (u128)(__int128)D1, s2 = (u128)(u64)D2, s3 = (u128)(u64)D3;
-    return s0 + (s1 << 32) + (s2 << 64) + (s3 << 96);
-}
-
 __device__ __forceinline__ X192 x192_sext(i64 v)
 {
     X192 r;

@@ -88,8 +88,8 @@ struct NodeLds {
 // gather rides along in k_refresh and their scoring in k_eval_big (where there are larger
 // nodes).  Beyond, both launches are bound by throughput, the lists are only traffic, and one
 // light kernel does both.  Whole paths of social-shaped graphs: 1M nodes, queue 65,536 (over
-// 10,000 blocks) 93 ms through lists, 85 without; 4M nodes, queue 4096 (about 1,500 blocks) 500
-// through lists, 520 without; co-purchase shape, queue 256 (some 70 blocks) 103 against 115.
+// 10,000 blocks) 62 ms through lists, 56 without; 4M nodes, queue 4096 (about 1,500 blocks) 404
+// through lists, 433 without; co-purchase shape, queue 256 (some 70 blocks) 88 to 92 against 100.
 #define LIST_BLOCKS 4096
 
 // Every kernel of a queue is a chain of dependent reads, some 0.7 us each, so the kernels keep

@@ -134,11 +134,9 @@ struct DevCounters {
     unsigned long long apply[LF_APPLY_COUNT];  // apply work (cumulative, LF_APPLY_*)
     int parts_total;               // re-sum parts (queue)
     int ovf_cnt;                   // joiners that did not fit their member list (iteration)
-    int undecided;                 // initial clustering rounds
     int error;                     // bit flags, see LF_DEVERR_*
     int live;                      // communities with >= 2 members (iteration end)
     int pad[4];
-    X256 score;
 };
 
 #define LF_DEVERR_INEXACT 1        // a value did not fit the exact accumulator
