@@ -338,7 +338,7 @@ struct lf_handle {
     int *part_done;
     unsigned long long *psum;
     long long part_cap;
-    long long *vbound;       // [n] per-node bounds used to size the per-queue buffers
+    long long *vbound;       // [n] bounds of the table-path nodes, by order position
     int graph_version;       // bumped whenever a buffer used by captured launches moves
     DevCounters *ctr;
     double Wt;               // cc-free partition score
