@@ -1862,8 +1862,8 @@ __global__ void __launch_bounds__(256) k_class_place(const int *cls, long long n
 // visits placed so far cleared.  One block: what it reads per node lies in list order (the
 // bounds nearly so), LAYOUT_PER nodes per thread at a time, and the four sums share two barriers.
 // With gathers by node and a scan of its own for each sum an iteration of the dense graph's 3M
-// nodes spent 4.0 ms here and one of 4M social-shaped nodes 194 us, now 60; 1M dense nodes take
-// 97 us, and 266 with these sums but the gathers by node.
+// nodes spent 4.0 ms here, now 1.2, and one of 4M social-shaped nodes 194 us, now 60; 1M dense
+// nodes take 97 us, and 266 with these sums but the gathers by node.
 #define LAYOUT_PER 4
 __global__ void __launch_bounds__(1024) k_table_layout(const int *list, const NodeRec *prec, const long long *lbase,
                                                        long long ntiles, const long long *vbound, TabPos *tpos,
