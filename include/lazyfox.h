@@ -402,6 +402,9 @@ int lf_get_memory(lf_handle *h, uint64_t *bytes, uint64_t *peak);
  * lf_batch_member_info: LF_OK and `out` filled as by lf_run_iterations when the member is
  *   done; LF_EAGAIN while it iterates; its error status if it failed.
  * lf_batch_remove: the member leaves (done or not); its handle returns to its own stream.
+ *   One that leaves within an iteration keeps the memberships of the queues applied so far, as
+ *   if lf_init_from_memberships had been given them; on an error its communities have to be
+ *   initialised again.
  * lf_batch_destroy: removes every member (handles are not destroyed) and frees the batch.
  */
 typedef struct lf_batch lf_batch;

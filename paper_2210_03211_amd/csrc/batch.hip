@@ -557,19 +557,31 @@ int lf_batch_remove(lf_batch *b, int32_t member_id)
     if (!b || member_id < 0 || member_id >= (int32_t)b->members.size() || !b->members[member_id])
         return LF_EINVAL;
     BatchMember *m = b->members[member_id];
+    lf_handle *h = m->h;
     drop_member(b, m);
-    // mid-iteration the memberships live in the handle's lines: back to its slot layout
-    if (m->state == 0 && m->phase == PH_RUN) (void)lf_lines_back(m->h);
+    // Between two queues the memberships are in the handle's lines, and between an iteration
+    // end and its report the host does not know yet what the end left: both are finished here.
+    int rc = LF_OK;
+    const bool within = m->state == 0 && m->phase == PH_RUN;
+    if (within) rc = lf_iter_leave_enqueue(h);
     (void)hipStreamSynchronize(b->stream);
     for (int k = 0; k < BATCH_SIDES; k++) (void)hipStreamSynchronize(b->side[k]);
-    m->h->stream = m->saved_stream;
-    m->h->phase_graphs = 0;
-    lf_phase_graphs_drop(m->h);
+    h->stream = m->saved_stream;
+    h->phase_graphs = 0;
+    lf_phase_graphs_drop(h);
+    if (within || (m->state == 0 && m->phase == PH_END_WAIT)) {
+        long long joins, leaves, live;
+        if (rc == LF_OK) rc = lf_iter_finish_complete(h, &joins, &leaves, &live);
+        if (rc != LF_OK) {                       // no partition to go on from
+            h->state = 1;
+            batch_error(b, rc, "the member's partition could not be kept");
+        }
+    }
     (void)hipEventDestroy(m->ev);
     (void)hipEventDestroy(m->ran);
     delete m;
     b->members[member_id] = nullptr;
-    return LF_OK;
+    return rc;
 }
 
 // Take a finished member out of the batch without waiting: *left is recorded behind its
@@ -582,7 +594,6 @@ int lf_batch_detach(lf_batch *b, int32_t member_id, hipEvent_t *left)
         return LF_EINVAL;
     BatchMember *m = b->members[member_id];
     drop_member(b, m);
-    if (m->state == 0 && m->phase == PH_RUN) (void)lf_lines_back(m->h);
     hipStream_t sd = b->side[m->side];
     int rc = hipEventRecord(m->ran, b->stream) == hipSuccess && hipStreamWaitEvent(sd, m->ran, 0) == hipSuccess &&
                      hipEventRecord(m->ev, sd) == hipSuccess

@@ -455,10 +455,11 @@ __device__ __forceinline__ int block_excl_int(int v, int *s_w, int *total)
     return off + incl - v;
 }
 
-// communities with fewer than two members are removed: mark them (tflag = 2), zero their
-// statistics; the live ones are counted and their scores summed exactly per block; every
-// community's member list is emptied
-__global__ void __launch_bounds__(256) k_end_mark(Ctx cx, long long *capx, X256 *part)
+// communities with fewer than `least` members (two; 0 where a batch member leaves within an
+// iteration: none) are removed: mark them (tflag = 2), zero their statistics; the live ones
+// are counted and their scores summed exactly per block; every community's member list is
+// emptied
+__global__ void __launch_bounds__(256) k_end_mark(Ctx cx, int least, long long *capx, X256 *part)
 {
     __shared__ X256 s_x[256 / WAVE];
     __shared__ int s_live[256 / WAVE];
@@ -468,14 +469,14 @@ __global__ void __launch_bounds__(256) k_end_mark(Ctx cx, long long *capx, X256 
          c += (long long)gridDim.x * blockDim.x) {
         CommRec *r = &cx.cr[c];
         const int s = r->s;
-        if (s < 2) {
+        if (s < least) {
             if (s == 1) cx.tflag[c] = 2;
             r->s = 0;
             r->m = 0;
             r->W = 0.0;
             for (int k = 0; k < 5; k++) { r->Sp[k] = 0; r->Sm[k] = 0; }
         } else {
-            live++;
+            live += s >= 2;
             x256_add(acc, x256_from_double(r->W, bad));
         }
         cx.cm_len[c] = 0;
@@ -1064,9 +1065,10 @@ int lf_partition_from_cover(lf_handle *h, const long long *off, const int *ids, 
     return LF_OK;
 }
 
-// Iteration end, first half (queued): degenerate communities removed, slots compacted,
-// member lists rebuilt, score reduced, and one report copied to pinned host memory.
-int lf_iteration_end_enqueue(lf_handle *h)
+// Iteration end, first half (queued): communities with fewer than `least` members removed,
+// slots compacted, member lists rebuilt, score reduced, and one report copied to pinned host
+// memory.
+int lf_iteration_end_enqueue(lf_handle *h, int least)
 {
     TmpScope tmp_scope(h);
     hipStream_t st = h->stream;
@@ -1086,7 +1088,7 @@ int lf_iteration_end_enqueue(lf_handle *h)
     LF_TRY(lf_tmp_alloc(h, (void **)&ksum, sizeof(long long) * kt));
     LF_TRY(lf_tmp_alloc(h, (void **)&koff, sizeof(long long) * kt));
     LF_TRY(lf_tmp_alloc(h, (void **)&part, sizeof(X256) * np));
-    hipLaunchKernelGGL(k_end_mark, dim3(np), dim3(BS), 0, st, cx, capx, part);
+    hipLaunchKernelGGL(k_end_mark, dim3(np), dim3(BS), 0, st, cx, least, capx, part);
     hipLaunchKernelGGL(k_end_count, dim3((unsigned)nt), dim3(BS), 0, st, cx, nsum);
     LF_TRY(lf_exclusive_scan_i64(h, nsum, noff, nt));
     // the new layout holds at most the current one's entries plus one per node (a node's

@@ -2018,28 +2018,6 @@ __global__ void __launch_bounds__(256) k_line_build(Ctx cx, unsigned char *mc8)
     mc8[x] = hx.cnt < 255 ? (unsigned char)hx.cnt : 255;
 }
 
-// back to the slot layout where a batch member leaves within an iteration: the memberships in
-// order without the ones left (holes), and their count
-__global__ void __launch_bounds__(256) k_line_back(Ctx cx)
-{
-    const long long x = blockIdx.x * (long long)blockDim.x + threadIdx.x;
-    if (x >= cx.n) return;
-    const NodeLine l = cx.ln[x];
-    const long long o = cx.nh[x].off;
-    int w = 0;
-    if (l.off < 0) {
-#pragma unroll
-        for (int t = 0; t < LINE_SLOTS; t++)
-            if (t < l.cnt && l.s[t].comm >= 0) cx.slot[o + w++] = l.s[t];
-    } else {
-        for (int t = 0; t < l.cnt; t++) {
-            const Slot sl = cx.slot[o + t];
-            if (sl.comm >= 0) cx.slot[o + w++] = sl;
-        }
-    }
-    cx.nh[x].cnt = w;
-}
-
 // in-count units of every node in node order (one per INB neighbours; ubase = their
 // exclusive scan), and the first unit of every queue
 __global__ void k_unit_counts(const int *order, const int *deg, long long n, long long *cnt)
@@ -2615,15 +2593,16 @@ static void refresh_alone(lf_handle *h)
 
 // End of an iteration: counters reset, degenerate communities removed, exact score.
 // End of an iteration, in the same two halves as its start.
-// the membership lines back into the slot layout (a batch member leaving mid-iteration)
-int lf_lines_back(lf_handle *h)
+// A batch member leaves within an iteration, first half (queued): the queues applied so far
+// stand, and what an iteration end leaves is made from them, but for the removal of small
+// communities (a warm start may have them too): slots without holes and with one cleared free
+// slot per node, member lists without those who left and with those who did not fit, scores.
+// lf_iter_finish_complete is the second half.
+int lf_iter_leave_enqueue(lf_handle *h)
 {
-    if (h->n > 0 && h->lines) {
-        refresh_alone(h);
-        hipLaunchKernelGGL(k_line_back, dim3(grid_for(h->n, 256)), dim3(256), 0, h->stream, lf_ctx(h));
-        h->lines_ready = false;
-    }
-    return hipGetLastError() == hipSuccess ? LF_OK : LF_EDEVICE;
+    refresh_alone(h);
+    LF_HIP(h, hipGetLastError());
+    return lf_iteration_end_enqueue(h, 0);
 }
 
 static int finish_enqueue_plain(lf_handle *h)
@@ -2631,7 +2610,7 @@ static int finish_enqueue_plain(lf_handle *h)
     refresh_alone(h);
     LF_HIP(h, hipGetLastError());
     LF_TRY(lf_prof_begin(h, LF_K_ITEREND));
-    LF_TRY(lf_iteration_end_enqueue(h));
+    LF_TRY(lf_iteration_end_enqueue(h, 2));
     LF_TRY(lf_prof_end(h, LF_K_ITEREND, 8));
     return LF_OK;
 }

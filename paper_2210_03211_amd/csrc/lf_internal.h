@@ -480,10 +480,10 @@ int lf_launch_multi(hipStream_t st, const Member *dmem, const int *dboff, int n,
 #define LF_MULTI_KERNELS 4       // kernels of a batch step
 void lf_multi_kernels(const void **fn, int *grid, int *block);
 int lf_iter_finish(lf_handle *h, long long *joins, long long *leaves, long long *live);
-int lf_lines_back(lf_handle *h);          // lines -> slot layout (mid-iteration stop)
+int lf_iter_leave_enqueue(lf_handle *h);  // a stop between two queues
 int lf_iter_finish_enqueue(lf_handle *h);
 int lf_iter_finish_complete(lf_handle *h, long long *joins, long long *leaves, long long *live);
-int lf_iteration_end_enqueue(lf_handle *h);
+int lf_iteration_end_enqueue(lf_handle *h, int least);
 int lf_iteration_end_complete(lf_handle *h, long long *joins, long long *leaves, long long *live);
 int lf_check_dev_error(lf_handle *h);
 int lf_dev_error_status(lf_handle *h, int e);
