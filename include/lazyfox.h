@@ -256,7 +256,10 @@ int lf_postprocess(lf_handle *h, uint32_t flags, uint8_t *keep, int64_t *removed
  * when the relative WCC-hat improvement over the previous iteration is below `threshold`
  * (iteration 1 compares with the initial clustering), or after `max_iters` iterations.
  * A later call continues from the current partition.  `out` may be NULL.
- * Errors: LF_EINVAL (queue_size < 1, threshold NaN or < 0, max_iters < 0), LF_ESTATE.
+ * Errors: LF_EINVAL (queue_size < 1, threshold NaN or < 0, max_iters < 0), LF_ESTATE,
+ * LF_ENOMEM, LF_EDEVICE.  A failed allocation at an iteration's start leaves the partition of
+ * the last finished iteration, and the run can be taken up again (also with another queue
+ * size); after one at its end the communities have to be initialised again (LF_ESTATE).
  */
 int lf_run_iterations(lf_handle *h, int32_t queue_size, double threshold, int32_t max_iters,
                       lf_run_info *out);
@@ -353,6 +356,12 @@ int lf_autotune_forget(void);
  * Values must be finite with magnitude in [2^-113, 2^30] or zero; LF_EOVERFLOW otherwise.
  */
 int lf_debug_exact_sum(lf_handle *h, const double *values_dev, int64_t n, double *out);
+
+/*
+ * Diagnostic: the nth device allocation of the handle from now on (1: the next one) fails
+ * once with LF_ENOMEM, whether the device has room or not; 0: none does.
+ */
+int lf_debug_fail_alloc(lf_handle *h, int64_t nth);
 
 /*
  * lf_debug_exact_sum without any allocation, for callers that cannot allocate device

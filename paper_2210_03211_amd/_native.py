@@ -97,6 +97,7 @@ def load_library():
         "lf_reset_profile": [vp],
         "lf_debug_exact_sum": [vp, vp, i64, C.POINTER(dbl)],
         "lf_exact_sum_noalloc": [vp, vp, i64, C.POINTER(dbl)],
+        "lf_debug_fail_alloc": [vp, i64],
         "lf_debug_sort_pairs": [vp, vp, vp, i64, i32],
         "lf_debug_sort_pairs_u32": [vp, vp, vp, i64],
         "lf_debug_exclusive_scan": [vp, vp, i32, vp, i64],
@@ -466,6 +467,10 @@ class Handle:
         self._check(self.L.lf_exact_sum_noalloc(self.h, C.c_void_p(_ptr(values_dev)[0]), int(n), C.byref(out)),
                     "lf_exact_sum_noalloc")
         return out.value
+
+    def lf_debug_fail_alloc(self, nth):
+        """The nth device allocation from now on fails once (0: none)."""
+        self._check(self.L.lf_debug_fail_alloc(self.h, int(nth)), "lf_debug_fail_alloc")
 
     def lf_debug_sort_pairs(self, keys_dev, vals_dev=None, end_bit=64):
         """Stable radix sort in place of uint64 keys (as int64 tensor bits) and int32 values."""

@@ -441,6 +441,13 @@ int lf_exact_sum_noalloc(lf_handle *h, const double *values_dev, int64_t n, doub
     return lf_exact_sum_run(h, values_dev, n, out, part, err, dout);
 }
 
+int lf_debug_fail_alloc(lf_handle *h, int64_t nth)
+{
+    if (!h || nth < 0) return LF_EINVAL;
+    h->fail_alloc = nth;
+    return LF_OK;
+}
+
 int lf_debug_sort_pairs(lf_handle *h, uint64_t *keys_dev, int32_t *vals_dev, int64_t n, int32_t end_bit)
 {
     if (!h || n < 0 || (n > 0 && !keys_dev) || end_bit < 0 || end_bit > 64) return LF_EINVAL;

@@ -183,21 +183,27 @@ static int batch_reserve(lf_batch *b, int nm)
     int cap = b->cap ? b->cap : 64;
     while (cap < nm) cap *= 2;
     const size_t off = boff_bytes(cap), bytes = off + sizeof(Member) * cap;
+    b->cap = 0;                              // (until all of them are there)
     for (int s = 0; s < 2; s++) {
         if (b->hstep[s]) {
             (void)hipEventSynchronize(b->hev[s]);
             (void)hipHostFree(b->hstep[s]);
             b->hstep[s] = nullptr;
         }
-        if (hipHostMalloc(&b->hstep[s], bytes, hipHostMallocDefault) != hipSuccess)
+        if (hipHostMalloc(&b->hstep[s], bytes, hipHostMallocDefault) != hipSuccess) {
+            b->hstep[s] = nullptr;
             return batch_error(b, LF_ENOMEM, "pinned host buffers of the batch");
+        }
         b->hboff[s] = (int *)b->hstep[s];
         b->hmem[s] = (Member *)((char *)b->hstep[s] + off);
     }
     (void)hipStreamSynchronize(b->stream);
     if (b->dstep) (void)hipFree(b->dstep);
     b->dstep = nullptr;
-    if (hipMalloc(&b->dstep, bytes) != hipSuccess) return batch_error(b, LF_ENOMEM, "device buffers of the batch");
+    if (hipMalloc(&b->dstep, bytes) != hipSuccess) {
+        b->dstep = nullptr;
+        return batch_error(b, LF_ENOMEM, "device buffers of the batch");
+    }
     b->dboff = (int *)b->dstep;
     b->dmem = (Member *)((char *)b->dstep + off);
     b->cap = cap;

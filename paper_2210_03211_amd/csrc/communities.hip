@@ -772,9 +772,7 @@ static int alloc_member_lists(lf_handle *h)
 {
     if (h->cm_node) return LF_OK;
     const long long want = 2 * h->n + 1024;
-    LF_TRY(lf_dev_alloc(h, (void **)&h->cm_node, sizeof(int) * want));
-    h->cm_cap = want;
-    return LF_OK;
+    return lf_dev_regrow(h, (void **)&h->cm_node, &h->cm_cap, want, sizeof(int));
 }
 
 // member lists with capacity for joiners; requires sizes and slots to be current.  Queued
@@ -807,24 +805,23 @@ static int rebuild_member_lists_async(lf_handle *h)
 static int grow_member_lists(lf_handle *h, long long total)
 {
     if (!h->phase_graphs) LF_HIP(h, hipStreamSynchronize(h->stream));   // a batch member keeps the old list
-    lf_dev_free(h, h->cm_node);
-    h->cm_node = nullptr;
     // grown two-fold (four-fold for a batch member, whose captured iteration starts and
     // ends a moved buffer invalidates), so a growing cover reallocates only a few times
-    long long want = (h->phase_graphs ? 4 : 2) * total + 1024;
-    LF_TRY(lf_dev_alloc(h, (void **)&h->cm_node, sizeof(int) * want));
-    h->cm_cap = want;
+    const long long want = (h->phase_graphs ? 4 : 2) * total + 1024;
+    LF_TRY(lf_dev_regrow(h, (void **)&h->cm_node, &h->cm_cap, want, sizeof(int)));
     return rebuild_member_lists_async(h);
 }
 
-static int rebuild_member_lists(lf_handle *h)
+int lf_rebuild_member_lists(lf_handle *h)
 {
+    h->lists_ready = false;
     LF_TRY(rebuild_member_lists_async(h));
     long long total = 0;
     LF_HIP(h, hipMemcpyAsync(&total, h->cm_off + h->K, sizeof(long long), hipMemcpyDeviceToHost, h->stream));
     LF_HIP(h, hipStreamSynchronize(h->stream));
     if (total > h->cm_cap) LF_TRY(grow_member_lists(h, total));
     LF_HIP(h, hipStreamSynchronize(h->stream));
+    h->lists_ready = true;
     return LF_OK;
 }
 
@@ -993,7 +990,7 @@ static int finish_partition(lf_handle *h)
     hipStream_t st = h->stream;
     const int BS = 256;
     const long long K = h->K;
-    LF_TRY(rebuild_member_lists(h));
+    LF_TRY(lf_rebuild_member_lists(h));
     Ctx cx = lf_ctx(h);
     int rb = (int)((K + 15) / 16);           // a row of lanes per community
     if (rb > 4096) rb = 4096;
@@ -1096,11 +1093,8 @@ int lf_iteration_end_enqueue(lf_handle *h, int least)
     int other = 1 - h->cur;
     const long long bound = h->slot_used + n + 1;
     if (bound > h->slot_capb[other]) {
-        long long want = (h->phase_graphs ? 3 * bound : bound + bound / 2) + 1024;
-        lf_dev_free(h, h->slot[other]);
-        h->slot[other] = nullptr;
-        LF_TRY(lf_dev_alloc(h, (void **)&h->slot[other], sizeof(Slot) * want));
-        h->slot_capb[other] = want;
+        const long long want = (h->phase_graphs ? 3 * bound : bound + bound / 2) + 1024;
+        LF_TRY(lf_dev_regrow(h, (void **)&h->slot[other], &h->slot_capb[other], want, sizeof(Slot)));
     }
     hipLaunchKernelGGL(k_end_copy, dim3((unsigned)nt), dim3(BS), 0, st, cx, (const long long *)noff, h->slot[other],
                        capx, h->mc8);
@@ -1127,10 +1121,6 @@ int lf_iteration_end_complete(lf_handle *h, long long *joins, long long *leaves,
     hipStream_t st = h->stream;
     const long long *r = h->hrep;
     h->slot_used = r[REP_SLOTS];
-    if (r[REP_MEMBERS] > h->cm_cap) {        // rare: member lists outgrew their buffer
-        LF_TRY(grow_member_lists(h, r[REP_MEMBERS]));
-        if (!h->phase_graphs) LF_HIP(h, hipStreamSynchronize(st));
-    }
     double wt;
     memcpy(&wt, &r[REP_SCORE], sizeof wt);
     h->Wt = wt;
@@ -1140,6 +1130,12 @@ int lf_iteration_end_complete(lf_handle *h, long long *joins, long long *leaves,
     *joins = (long long)jl[0];
     *leaves = (long long)jl[1];
     *live = lv[0];
+    if (r[REP_MEMBERS] > h->cm_cap) {        // rare: member lists outgrew their buffer
+        h->lists_ready = false;              // (if this fails, the next run's first start fills them)
+        LF_TRY(grow_member_lists(h, r[REP_MEMBERS]));
+        if (!h->phase_graphs) LF_HIP(h, hipStreamSynchronize(st));
+        h->lists_ready = true;
+    }
     return LF_OK;
 }
 

@@ -2105,11 +2105,9 @@ static int size_queue_enqueue(lf_handle *h, long long q)
     const int BS = 256;
     long long n = h->n;
     bool moved = false;
+    if (!h->lists_ready) LF_TRY(lf_rebuild_member_lists(h));   // they did not fit at the last iteration end
     if (q > h->q_cap) {
-        lf_dev_free(h, h->dec);
-        h->dec = nullptr;
-        LF_TRY(lf_dev_alloc(h, (void **)&h->dec, sizeof(Decision) * q));
-        h->q_cap = q;
+        LF_TRY(lf_dev_regrow(h, (void **)&h->dec, &h->q_cap, q, sizeof(Decision)));
         moved = true;
     }
     const long long nq = (n + q - 1) / q;
@@ -2124,30 +2122,27 @@ static int size_queue_enqueue(lf_handle *h, long long q)
         h->hqoff_len = REP_LEN(nq);
     }
     const long long nrep = REP_LEN(nq);    // list offsets, table path, queue units
-    if (nrep > h->dq_cap) {                 // kept across the two halves (and iterations)
-        lf_dev_free(h, h->dq);
-        h->dq = nullptr;
-        LF_TRY(lf_dev_alloc(h, (void **)&h->dq, sizeof(long long) * (nrep + nrep / 4 + 64)));
-        h->dq_cap = nrep + nrep / 4 + 64;
-    }
+    if (nrep > h->dq_cap)                   // kept across the two halves (and iterations)
+        LF_TRY(lf_dev_regrow(h, (void **)&h->dq, &h->dq_cap, nrep + nrep / 4 + 64, sizeof(long long)));
     long long *dq = h->dq;
-    if (!h->tpos) {
-        h->tchunk_cap = 1024 + n / 16;
-        h->tbuck_cap = 1024 + n / 8;
-        LF_TRY(lf_dev_alloc(h, (void **)&h->ubase, sizeof(long long) * (n + 1)));
-        LF_TRY(lf_dev_alloc(h, (void **)&h->tpos, sizeof(TabPos) * (n + 1)));
-        LF_TRY(lf_dev_alloc(h, (void **)&h->tcur, sizeof(int) * (n + 1)));
-        LF_TRY(lf_dev_alloc(h, (void **)&h->tchunk, sizeof(ChunkRec) * h->tchunk_cap));
-        LF_TRY(lf_dev_alloc(h, (void **)&h->tbuck, sizeof(BuckRec) * h->tbuck_cap));
+    if (!h->ubase || !h->tpos || !h->tcur) {
+        if (!h->ubase) LF_TRY(lf_dev_alloc(h, (void **)&h->ubase, sizeof(long long) * (n + 1)));
+        if (!h->tpos) LF_TRY(lf_dev_alloc(h, (void **)&h->tpos, sizeof(TabPos) * (n + 1)));
+        if (!h->tcur) LF_TRY(lf_dev_alloc(h, (void **)&h->tcur, sizeof(int) * (n + 1)));
+        moved = true;
+    }
+    if (!h->tchunk) {
+        LF_TRY(lf_dev_regrow(h, (void **)&h->tchunk, &h->tchunk_cap, 1024 + n / 16, sizeof(ChunkRec)));
+        moved = true;
+    }
+    if (!h->tbuck) {
+        LF_TRY(lf_dev_regrow(h, (void **)&h->tbuck, &h->tbuck_cap, 1024 + n / 8, sizeof(BuckRec)));
         moved = true;
     }
     const long long ucap = n + 2 * h->ne / INB + 1;   // >= sum of ceil(degree / INB)
     if (ucap > h->unit_cap) {
-        lf_dev_free(h, h->unit);
-        h->unit = nullptr;
-        LF_TRY(lf_dev_alloc(h, (void **)&h->unit, sizeof(UnitRec) * ucap));
-        h->unit_cap = ucap;
         h->static_ready = false;
+        LF_TRY(lf_dev_regrow(h, (void **)&h->unit, &h->unit_cap, ucap, sizeof(UnitRec)));
         moved = true;
     }
     if (!h->lines) {
@@ -2233,18 +2228,10 @@ static int size_queue_complete(lf_handle *h, long long q)
     const long long chunks = tb[nq], bucks = tb[2 * nq + 1];
     if (chunks > h->tchunk_cap || bucks > h->tbuck_cap) {   // rare: grow and lay them out again
         const long long f = h->phase_graphs ? 4 : 2;        // a batch member's graphs survive more growth
-        if (chunks > h->tchunk_cap) {
-            lf_dev_free(h, h->tchunk);
-            h->tchunk = nullptr;
-            LF_TRY(lf_dev_alloc(h, (void **)&h->tchunk, sizeof(ChunkRec) * (f * chunks + 1024)));
-            h->tchunk_cap = f * chunks + 1024;
-        }
-        if (bucks > h->tbuck_cap) {
-            lf_dev_free(h, h->tbuck);
-            h->tbuck = nullptr;
-            LF_TRY(lf_dev_alloc(h, (void **)&h->tbuck, sizeof(BuckRec) * (f * bucks + 1024)));
-            h->tbuck_cap = f * bucks + 1024;
-        }
+        if (chunks > h->tchunk_cap)
+            LF_TRY(lf_dev_regrow(h, (void **)&h->tchunk, &h->tchunk_cap, f * chunks + 1024, sizeof(ChunkRec)));
+        if (bucks > h->tbuck_cap)
+            LF_TRY(lf_dev_regrow(h, (void **)&h->tbuck, &h->tbuck_cap, f * bucks + 1024, sizeof(BuckRec)));
         moved = true;
         table_fill(h, q, nq);
         LF_HIP(h, hipGetLastError());
@@ -2270,23 +2257,16 @@ static int size_queue_complete(lf_handle *h, long long q)
         {(void **)&h->trow, &h->trow_cap, most[3], sizeof(int)}};
     for (auto &bf : bufs) {
         if (bf.need <= *bf.cap) continue;
-        const long long want = bf.need + (1 + 4 * grown) * (bf.need / 4) + 256;
-        lf_dev_free(h, *bf.p);
-        *bf.p = nullptr;
-        LF_TRY(lf_dev_alloc(h, bf.p, bf.each * want));
-        *bf.cap = want;
+        LF_TRY(lf_dev_regrow(h, bf.p, bf.cap, bf.need + (1 + 4 * grown) * (bf.need / 4) + 256, bf.each));
         moved = true;
     }
     long long pcap = 2 * q + (h->cm_cap + n) / PART + 64;
     if (pcap > h->part_cap) {
         if (h->phase_graphs) pcap *= 2;
-        lf_dev_free(h, h->part_rec);
-        h->part_rec = nullptr;
-        LF_TRY(lf_dev_alloc(h, (void **)&h->part_rec, sizeof(PartRec) * pcap));
-        lf_dev_free(h, h->psum);
-        h->psum = nullptr;
-        LF_TRY(lf_dev_alloc(h, (void **)&h->psum, sizeof(unsigned long long) * PSUM * pcap));
-        h->part_cap = pcap;
+        long long sums = 0;
+        h->part_cap = 0;
+        LF_TRY(lf_dev_regrow(h, (void **)&h->psum, &sums, pcap, sizeof(unsigned long long) * PSUM));
+        LF_TRY(lf_dev_regrow(h, (void **)&h->part_rec, &h->part_cap, pcap, sizeof(PartRec)));
         moved = true;
     }
     if (moved) h->graph_version++;
@@ -2396,17 +2376,23 @@ static bool phase_allocates(lf_handle *h, int which, long long qq)
     const long long nq = (n + qq - 1) / qq;
     const long long nrep = REP_LEN(nq);
     const long long ucap = n + 2 * h->ne / INB + 1;
-    return qq > h->q_cap || h->hqoff_cap < nq + 1 || nrep > h->dq_cap || !h->tpos || ucap > h->unit_cap || (n > 0 && !h->lines);
+    return !h->lists_ready || qq > h->q_cap || h->hqoff_cap < nq + 1 || nrep > h->dq_cap || !h->ubase || !h->tpos ||
+           !h->tcur || !h->tchunk || !h->tbuck || ucap > h->unit_cap || (n > 0 && !h->lines);
+}
+
+static int run_plain(lf_handle *h, int which, long long qq)
+{
+    h->phase_runs[0]++;
+    h->phase_ran[which] = 0;                 // (all of its temporaries exist only if it ran through)
+    LF_TRY(which == 0 ? begin_enqueue_plain(h, qq) : finish_enqueue_plain(h));
+    h->phase_ran[which] = 1;
+    return LF_OK;
 }
 
 // one iteration start (0) or end (1), from a graph where the state allows
 static int run_phase(lf_handle *h, int which, long long qq)
 {
-    if (!h->phase_graphs || h->profiling) {
-        h->phase_runs[0]++;
-        h->phase_ran[which] = 1;
-        return which == 0 ? begin_enqueue_plain(h, qq) : finish_enqueue_plain(h);
-    }
+    if (!h->phase_graphs || h->profiling) return run_plain(h, which, qq);
     PhaseGraph &pg = h->pg[which][h->cur];
     const unsigned long long key = phase_key(h, qq, which);
     const bool allocates = phase_allocates(h, which, qq);
@@ -2429,14 +2415,18 @@ static int run_phase(lf_handle *h, int which, long long qq)
         h->phase_runs[1]++;
         return LF_OK;
     }
-    h->phase_runs[0]++;
-    h->phase_ran[which] = 1;
-    return which == 0 ? begin_enqueue_plain(h, qq) : finish_enqueue_plain(h);
+    return run_plain(h, which, qq);
 }
 
 int lf_iter_begin_enqueue(lf_handle *h, long long qq) { return run_phase(h, 0, qq); }
 
-int lf_iter_finish_enqueue(lf_handle *h) { return run_phase(h, 1, 0); }
+// a failure here leaves the queues' changes without an iteration end: no partition to go on from
+int lf_iter_finish_enqueue(lf_handle *h)
+{
+    const int rc = run_phase(h, 1, 0);
+    if (rc != LF_OK) h->state = 1;
+    return rc;
+}
 
 int lf_iter_begin_complete(lf_handle *h, long long qq, long long *nq)
 {
@@ -2601,8 +2591,9 @@ static void refresh_alone(lf_handle *h)
 int lf_iter_leave_enqueue(lf_handle *h)
 {
     refresh_alone(h);
-    LF_HIP(h, hipGetLastError());
-    return lf_iteration_end_enqueue(h, 0);
+    int rc = lf_iteration_end_enqueue(h, 0);
+    if (rc != LF_OK) h->state = 1;
+    return rc;
 }
 
 static int finish_enqueue_plain(lf_handle *h)
@@ -2654,7 +2645,11 @@ int lf_iterate(lf_handle *h, int q, double theta, int max_iters, lf_run_info *ou
             QStep qs;
             QGrids g;
             lf_queue_params(h, k, nq, qq, false, &qs, &g);
-            LF_TRY(lf_launch_queue(h, cx, qs, g));
+            const int rc = lf_launch_queue(h, cx, qs, g);
+            if (rc != LF_OK) {                   // queues applied in part: no partition to go on from
+                h->state = 1;
+                return rc;
+            }
         }
         long long joins = 0, leaves = 0, live = 0;
         LF_TRY(lf_iter_finish(h, &joins, &leaves, &live));

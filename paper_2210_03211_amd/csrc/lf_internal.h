@@ -306,6 +306,7 @@ struct lf_handle {
     long long *ubase;        // [n + 1] first in-count unit of each order position
     bool static_ready;       // pre, unit and ubase are those of this clustering
     bool lines_ready;        // lines and mc8 hold the current memberships
+    bool lists_ready;        // member lists hold the current memberships
     TabPos *tpos;            // [n + 1]
     int *tcur;               // [n]
     ChunkRec *tchunk;
@@ -370,6 +371,7 @@ struct lf_handle {
     int tmp_chunk;
     size_t tmp_off;
     size_t dev_bytes, dev_bytes_peak;   // device memory in use by the handle (now / at most)
+    long long fail_alloc;               // > 0: this many allocations from now, one fails (tests)
     // iteration starts and ends replayed from graphs (members of a batch)
     int phase_graphs;
     PhaseGraph pg[2][2];                // [start, end][slot parity]
@@ -397,6 +399,7 @@ int lf_set_error(lf_handle *h, int code, const char *fmt, ...);
 
 int lf_dev_alloc(lf_handle *h, void **p, size_t bytes);
 void lf_dev_free(lf_handle *h, void *p);
+int lf_dev_regrow(lf_handle *h, void **p, long long *cap, long long want, size_t each);
 void lf_trim_kept(lf_handle *h);
 // size an lf_dev_alloc request occupies; a block whose device work has completed goes
 // back to the per-device cache (or to HIP)
@@ -462,6 +465,7 @@ struct WccTri {
 int lf_triangle_pass(lf_handle *h, const WccTri *wt, int *launches, long long **oro_out, int **orc_out);
 
 int lf_initial_clustering(lf_handle *h);
+int lf_rebuild_member_lists(lf_handle *h);  // waits
 int lf_partition_from_cover(lf_handle *h, const long long *off, const int *ids, long long total, int n_comms);
 int lf_check_cover(lf_handle *h, const long long *off, const int *ids, long long total, int n_comms, int *maxid);
 int lf_iterate(lf_handle *h, int q, double theta, int max_iters, lf_run_info *out);

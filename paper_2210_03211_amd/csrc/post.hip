@@ -96,6 +96,7 @@ extern "C" int lf_postprocess(lf_handle *h, uint32_t flags, uint8_t *keep, int64
     if (flags & ~(LF_PP_DUPLICATES | LF_PP_CONTAINED | LF_PP_APPLY)) return lf_set_error(h, LF_EINVAL, "unknown flags");
     if (h->state < 2) return lf_set_error(h, LF_ESTATE, "no communities yet");
     LF_HIP(h, hipSetDevice(h->device));
+    if (!h->lists_ready) LF_TRY(lf_rebuild_member_lists(h));   // they did not fit at the last iteration end
     TmpScope tmp_scope(h);
     hipStream_t st = h->stream;
     const int BS = 256;

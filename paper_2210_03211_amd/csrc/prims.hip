@@ -172,6 +172,8 @@ static size_t take_kept(lf_handle *h, size_t bytes, void **p)
 int lf_dev_alloc(lf_handle *h, void **p, size_t bytes)
 {
     *p = nullptr;
+    if (h->fail_alloc > 0 && --h->fail_alloc == 0)
+        return lf_set_error(h, LF_ENOMEM, "allocation of %zu bytes failed as asked for", bytes);
     bytes = lf_alloc_class(bytes);
     const size_t got = take_kept(h, bytes, p);
     if (got) bytes = got;
@@ -229,6 +231,19 @@ void lf_dev_free(lf_handle *h, void *p)
         }
 }
 
+// A buffer of `want` elements in place of *p (its contents are not kept).  Pointer and capacity
+// change together: after a failed allocation the buffer has neither, so that no later call
+// takes the old capacity for the room behind a null pointer.
+int lf_dev_regrow(lf_handle *h, void **p, long long *cap, long long want, size_t each)
+{
+    lf_dev_free(h, *p);
+    *p = nullptr;
+    *cap = 0;
+    LF_TRY(lf_dev_alloc(h, p, each * (size_t)want));
+    *cap = want;
+    return LF_OK;
+}
+
 // Scratch arena of a handle: temporaries of one host routine are carved from chunks the
 // handle keeps, so iteration starts and ends allocate nothing once warm (hipFree would
 // synchronise the whole device).  Marks and releases nest like a stack; memory handed out
@@ -251,6 +266,7 @@ int lf_tmp_alloc(lf_handle *h, void **p, size_t bytes)
                 lf_dev_free(h, c.ptr);
                 c.ptr = nullptr;
                 size_t want = bytes > 2 * c.size ? bytes : 2 * c.size;
+                c.size = 0;                         // (until the larger one is there)
                 LF_TRY(lf_dev_alloc(h, &c.ptr, want));
                 c.size = want;
                 continue;
