@@ -30,6 +30,7 @@ struct BatchMember {
     lf_handle *h;
     hipStream_t saved_stream;
     long long qq, nq, k;     // queue size, queues of the current iteration, next queue
+    int slice, slices;       // next slice of that queue, its slices (lf_queue_params)
     int max_iters;
     double theta;
     int it;                  // iterations completed
@@ -337,6 +338,8 @@ int lf_batch_add(lf_batch *b, lf_handle *h, int32_t queue_size, double threshold
     m->qq = queue_size < n ? queue_size : (n > 0 ? n : 1);
     m->nq = 0;
     m->k = 0;
+    m->slice = 0;
+    m->slices = 1;
     m->max_iters = max_iters;
     m->theta = threshold;
     m->it = 0;
@@ -375,6 +378,7 @@ static int member_phase_done(lf_batch *b, BatchMember *m, bool *requeue)
         if (rc == LF_OK) {
             m->cx = lf_ctx(h);
             m->k = 0;
+            m->slice = 0;
             if (h->second_half_work) {
                 rc = hipEventRecord(m->ev, sd) == hipSuccess ? LF_OK : LF_EDEVICE;
                 m->begun = true;
@@ -474,7 +478,7 @@ int lf_batch_step(lf_batch *b, int32_t *running)
         for (int i = 0; i < nm; i++) {
             BatchMember *m = act[i];
             QGrids g;
-            lf_queue_params(m->h, m->k, m->nq, m->qq, true, &hm[i].qs, &g);
+            m->slices = lf_queue_params(m->h, m->k, m->nq, m->qq, true, m->slice, &hm[i].qs, &g);
             m->cx.qtag = m->h->qtag++;
             hm[i].cx = m->cx;
             const int blocks[LF_MULTI_GRIDS] = {g.refresh, g.big, g.tie, g.apply};
@@ -501,6 +505,8 @@ int lf_batch_step(lf_batch *b, int32_t *running)
         auto t3 = std::chrono::steady_clock::now();
         b->launch_ms += std::chrono::duration<double, std::milli>(t3 - t2).count();
         for (BatchMember *m : act) {
+            if (++m->slice < m->slices) continue;
+            m->slice = 0;
             m->k++;
             if (m->k == m->nq) {
                 // the end runs on the member's side stream once this step is done

@@ -91,6 +91,12 @@ struct NodeLds {
 // 10,000 blocks) 62 ms through lists, 56 without; 4M nodes, queue 4096 (about 1,500 blocks) 404
 // through lists, 433 without; co-purchase shape, queue 256 (some 70 blocks) 88 to 92 against 100.
 #define LIST_BLOCKS 4096
+// Workgroup-path nodes of a queue that go through lists at once, 12 KB of list each: what is
+// beyond is gathered and scored in further pairs of launches (slices of the queue), so that the
+// lists of a queue of millions of nodes take 0.8 GB.  Slices this long cost nothing: three
+// iterations of 262,144 such nodes in one queue spend 5.98 ms in the two kernels in one slice,
+// 6.04 ms in four.
+#define GROUP_SLICE 65536
 
 // Every kernel of a queue is a chain of dependent reads, some 0.7 us each, so the kernels keep
 // to three rules.  What does not depend on each other is read in one go: a read under a lane
@@ -421,8 +427,8 @@ __device__ __forceinline__ NodeList med_list(const Ctx &cx, const QStep &qs, int
 }
 __device__ __forceinline__ NodeList group_list(const Ctx &cx, const QStep &qs, int i)
 {
-    return list_at(cx, qs.ln + qs.em + i,
-                   (long long)qs.ln * VSMALL + (long long)qs.em * VMED + (long long)i * VGRP);
+    const int ln = qs.lists ? qs.ln : 0, em = qs.lists ? qs.em : 0;   // (the others have no lists)
+    return list_at(cx, ln + em + i, (long long)ln * VSMALL + (long long)em * VMED + (long long)i * VGRP);
 }
 
 template <int VCAP>
@@ -2197,6 +2203,12 @@ static int size_queue_enqueue(lf_handle *h, long long q)
     return LF_OK;
 }
 
+// whether a queue's small and medium nodes go through lists (the buffers are sized by this too)
+static bool light_lists(bool batch, long long small, long long med)
+{
+    return batch || (small + EW - 1) / EW + med <= LIST_BLOCKS;
+}
+
 // second half: the host reads what the first half copied (the caller has waited for it)
 // and grows whatever it found too small
 static int size_queue_complete(lf_handle *h, long long q)
@@ -2238,13 +2250,16 @@ static int size_queue_complete(lf_handle *h, long long q)
         h->second_half_work = true;
     }
     const long long grown = h->phase_graphs ? 3 : 0;        // spare room, in quarters beyond one
-    // flattened lists of the queue with the most entries
+    // flattened lists of the queue with the most entries (its first slice has the most)
     long long lnodes = 0, lentries = 0;
     for (long long k = 0; k < nq; k++) {
         long long m[LF_PATH_COUNT];
         for (int c = 0; c < LF_PATH_COUNT; c++) m[c] = h->hqoff[c * (nq + 1) + k + 1] - h->hqoff[c * (nq + 1) + k];
-        const long long nodes = m[LF_PATH_SMALL] + m[LF_PATH_MED] + m[LF_PATH_GROUP];
-        const long long entries = m[LF_PATH_SMALL] * VSMALL + m[LF_PATH_MED] * VMED + m[LF_PATH_GROUP] * VGRP;
+        const bool lists = light_lists(h->phase_graphs, m[LF_PATH_SMALL], m[LF_PATH_MED]);
+        const long long light = lists ? m[LF_PATH_SMALL] + m[LF_PATH_MED] : 0;
+        const long long group = m[LF_PATH_GROUP] < GROUP_SLICE ? m[LF_PATH_GROUP] : GROUP_SLICE;
+        const long long nodes = light + group;
+        const long long entries = (lists ? m[LF_PATH_SMALL] * VSMALL + m[LF_PATH_MED] * VMED : 0) + group * VGRP;
         if (nodes > lnodes) lnodes = nodes;
         if (entries > lentries) lentries = entries;
     }
@@ -2442,10 +2457,12 @@ int lf_iter_begin(lf_handle *h, long long qq, long long *nq)
     return lf_iter_begin_complete(h, qq, nq);
 }
 
-// Parameters and grids of queue k (of nq).  compact_grids sizes the grid-stride kernels by
+// Parameters and grids of slice `slice` of queue k (of nq); returns the queue's slices.  The
+// first one re-sums the queue before and takes all nodes but the workgroup path's beyond
+// GROUP_SLICE, the last one applies the queue.  compact_grids sizes the grid-stride kernels by
 // the queue instead of by the whole device (for many graphs sharing one launch).
-void lf_queue_params(lf_handle *h, long long k, long long nq, long long qq, bool compact_grids, QStep *qs,
-                     QGrids *g)
+int lf_queue_params(lf_handle *h, long long k, long long nq, long long qq, bool compact_grids, int slice, QStep *qs,
+                    QGrids *g)
 {
     const long long *qo = h->hqoff;                                // [path][nq + 1]
     const long long *tb = h->hqoff + REP_TABLE(nq);    // [4][nq + 1]
@@ -2457,12 +2474,21 @@ void lf_queue_params(lf_handle *h, long long k, long long nq, long long qq, bool
         ls[c] = (int)qo[c * (nq + 1) + k];
         ln[c] = (int)(qo[c * (nq + 1) + k + 1] - ls[c]);
     }
+    const bool lists = light_lists(compact_grids, ln[LF_PATH_SMALL], ln[LF_PATH_MED]);
+    const int slices = ln[LF_PATH_GROUP] > GROUP_SLICE ? (ln[LF_PATH_GROUP] - 1) / GROUP_SLICE + 1 : 1;
+    if (slices > 1) {
+        ls[LF_PATH_GROUP] += slice * GROUP_SLICE;
+        ln[LF_PATH_GROUP] -= slice * GROUP_SLICE;
+        if (ln[LF_PATH_GROUP] > GROUP_SLICE) ln[LF_PATH_GROUP] = GROUP_SLICE;
+    }
+    if (slice > 0) ln[LF_PATH_SMALL] = ln[LF_PATH_MED] = 0;
     const int gb = h->hub_blocks;
     int rbk = RB_MORE * h->refresh_blocks;
     if (compact_grids) {
         int want = (int)grid_for(clen, 8);
         if (want < rbk) rbk = want;
     }
+    if (slice > 0) rbk = 0;
     qs->cstart = (int)start;
     qs->clen = clen;
     qs->wcap = h->eval_wave_cap < 2 * VSMALL ? h->eval_wave_cap : 2 * VSMALL;
@@ -2472,9 +2498,9 @@ void lf_queue_params(lf_handle *h, long long k, long long nq, long long qq, bool
     qs->ln = ln[LF_PATH_SMALL];
     BigRoles &br = qs->br;
     br.c0 = (int)tb[k];
-    br.nc = (int)(tb[k + 1] - tb[k]);
+    br.nc = slice > 0 ? 0 : (int)(tb[k + 1] - tb[k]);
     br.b0 = (int)tb[nq + 1 + k];
-    br.nb = (int)(tb[nq + 2 + k] - tb[nq + 1 + k]);
+    br.nb = slice > 0 ? 0 : (int)(tb[nq + 2 + k] - tb[nq + 1 + k]);
     br.vis0 = tb[2 * (nq + 1) + k];
     br.row0 = tb[3 * (nq + 1) + k];
     br.bt = br.nc < 4 * gb ? br.nc : 4 * gb;
@@ -2490,17 +2516,19 @@ void lf_queue_params(lf_handle *h, long long k, long long nq, long long qq, bool
     qs->un = (int)(hu[k + 1] - hu[k]);
     qs->rb = rbk;
     const int light = qs->es + qs->em, heavy = br.bg + br.nb;
-    qs->lists = compact_grids || light <= LIST_BLOCKS;
+    qs->lists = lists;
     const bool fuse = compact_grids || (heavy > 0 && qs->lists);
     g->refresh = rbk + br.bt + br.bg + (qs->lists ? light : 0);
     g->eval = fuse ? 0 : light;
     g->big = heavy + (fuse ? light : 0);
     if (g->big < 1 && g->eval == 0) g->big = 1;   // block 0 resets the queue's counters
-    g->tie = (int)grid_for(br.nt, GT / WAVE);
-    g->apply = (int)grid_for(clen, EDITS) + (int)grid_for(qs->un, 256 / WAVE);
+    const bool last = slice == slices - 1;
+    g->tie = last ? (int)grid_for(br.nt, GT / WAVE) : 0;
+    g->apply = last ? (int)grid_for(clen, EDITS) + (int)grid_for(qs->un, 256 / WAVE) : 0;
+    return slices;
 }
 
-// the kernels of one queue of one graph, in order, on the handle's stream
+// the kernels of one slice of a queue of one graph, in order, on the handle's stream
 static void launch_refresh(int grid, hipStream_t st, const Ctx &cx, const QStep &qs)
 {
     hipLaunchKernelGGL(k_refresh, dim3(grid), dim3(GT), 0, st, qs.rb, qs.br.bt, qs.br.bg, qs.em, cx.part_rec, cx.ctr,
@@ -2534,6 +2562,7 @@ int lf_launch_queue(lf_handle *h, Ctx &cx, const QStep &qs, const QGrids &g)
         hipLaunchKernelGGL(k_big_tie, dim3(g.tie), dim3(GT), 0, st, cx, qs);
         LF_TRY(lf_prof_end(h, LF_K_TAB_TIE, 1));
     }
+    if (g.apply == 0) return LF_OK;
     LF_TRY(lf_prof_begin(h, LF_K_APPLY_EDIT));
     hipLaunchKernelGGL(k_apply, dim3(g.apply), dim3(256), 0, st, cx.unit + qs.ub, qs.un, qs.clen, cx.dec,
                        cx.order + qs.cstart, cx, qs);
@@ -2644,11 +2673,13 @@ int lf_iterate(lf_handle *h, int q, double theta, int max_iters, lf_run_info *ou
         for (long long k = 0; k < nq; k++) {
             QStep qs;
             QGrids g;
-            lf_queue_params(h, k, nq, qq, false, &qs, &g);
-            const int rc = lf_launch_queue(h, cx, qs, g);
-            if (rc != LF_OK) {                   // queues applied in part: no partition to go on from
-                h->state = 1;
-                return rc;
+            for (int slice = 0, slices = 1; slice < slices; slice++) {
+                slices = lf_queue_params(h, k, nq, qq, false, slice, &qs, &g);
+                const int rc = lf_launch_queue(h, cx, qs, g);
+                if (rc != LF_OK) {               // queues applied in part: no partition to go on from
+                    h->state = 1;
+                    return rc;
+                }
             }
         }
         long long joins = 0, leaves = 0, live = 0;

@@ -476,8 +476,8 @@ int lf_iter_begin(lf_handle *h, long long qq, long long *nq);
 // that work is done (a stream sync or a completed event behind it)
 int lf_iter_begin_enqueue(lf_handle *h, long long qq);
 int lf_iter_begin_complete(lf_handle *h, long long qq, long long *nq);
-void lf_queue_params(lf_handle *h, long long k, long long nq, long long qq, bool compact_grids, QStep *qs,
-                     QGrids *g);
+int lf_queue_params(lf_handle *h, long long k, long long nq, long long qq, bool compact_grids, int slice, QStep *qs,
+                    QGrids *g);
 int lf_launch_queue(lf_handle *h, Ctx &cx, const QStep &qs, const QGrids &g);
 int lf_launch_multi(hipStream_t st, const Member *dmem, const int *dboff, int n, const int *total);
 #define LF_MULTI_GRIDS 4         // per-step launches of a batch with grids of their own
