@@ -434,7 +434,7 @@ int lf_batch_set_graph(lf_batch *b, int32_t on);
 /*
  * Serving: community-detection jobs on graphs of uneven size.  lf_server_submit copies a
  * job's edge list (host memory, as for lf_load_graph without flags) and queues it;
- * LF_ENOMEM if its estimated device footprint exceeds the whole budget.  Each
+ * LF_ENOMEM if its least device footprint exceeds the whole budget.  Each
  * lf_server_tick admits queued jobs in arrival order while their estimated footprints fit
  * the budget and fewer than max_batch jobs run, runs one batch step, and hands finished
  * jobs over for retirement.  Four worker threads of the server, each with a stream of its

@@ -703,14 +703,34 @@ static double ms_since(std::chrono::steady_clock::time_point t0)
     return std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
 }
 
-// Device bytes a job may hold at most: graph build scratch, CSR, node arrays, membership
-// slots, community records and member lists (grown faster in a batch), and the per-queue
-// work lists; blocks are rounded up to their allocation class (at most one eighth more).
-static size_t job_footprint(long long n, long long npairs, int q)
+// Device bytes below which a job is never refused: one whose footprint (below) is more than the
+// whole budget then runs by itself.
+static size_t job_least(long long n, long long npairs, int q)
 {
     long long nn = n > 0 ? n : 1;
     long long qq = q < nn ? q : nn;
     size_t b = (size_t)(48ll << 20) + (size_t)nn * 768 + (size_t)npairs * 64 + (size_t)qq * 256;
+    return b + b / 8;
+}
+
+// Device bytes a job is expected to hold at most.  Per pair: 136 of build scratch and CSR, then
+// what grows with a node's memberships, weighted by degree (PAIR_MEMBERS of them; up to 15 seen in
+// dense graphs): member lists with room for joiners, and the table path's visits of the longest
+// queue (the largest nodes lie together in the order, so up to eight times its share of
+// all).  Per node 1,168 of arrays and community records, per queued node 512 of decisions and
+// re-sum parts, and the flattened lists.  Blocks are rounded up to their allocation class (at
+// most one eighth more).  Peaks measured / reserved, with queues of n / 32 and of all n nodes: served
+// mix, 45,620 nodes, 772K pairs 245 / 530 and 303 / 891 MB; dense, 30,000 nodes, 1.34M pairs 614 / 795
+// and 1,154 / 1,389.  It is an estimate all the same: 40,000 nodes that come to 28 memberships each, all
+// in one queue, took 4.6 GB of 3.9.
+#define PAIR_MEMBERS 12
+static size_t job_footprint(long long n, long long npairs, int q)
+{
+    const long long nn = n > 0 ? n : 1, qq = q < nn ? q : nn;
+    const double share = 8.0 * (double)qq / (double)nn;
+    const double visits = (2.0 * PAIR_MEMBERS + 1.0) * (double)npairs * (share < 1.0 ? share : 1.0);
+    const size_t b = (size_t)(48ll << 20) + (size_t)nn * 1168 + (size_t)npairs * (136 + 16 * PAIR_MEMBERS) +
+                     (size_t)(20.0 * visits) + (size_t)qq * 512 + (size_t)lf_batch_list_bytes(qq);
     return b + b / 8;
 }
 
@@ -836,8 +856,10 @@ int lf_server_submit(lf_server *s, int64_t n, int64_t n_pairs, const int64_t *sr
     if (!s || !job_id || n < 0 || n_pairs < 0 || (n_pairs > 0 && (!src || !dst)) || queue_size < 1 ||
         !(threshold >= 0.0) || max_iters < 0)
         return LF_EINVAL;
+    if (job_least(n, n_pairs, queue_size) > s->budget)
+        return server_error(s, LF_ENOMEM, "job footprint exceeds the whole device budget");
     size_t fp = job_footprint(n, n_pairs, queue_size);
-    if (fp > s->budget) return server_error(s, LF_ENOMEM, "job footprint exceeds the whole device budget");
+    if (fp > s->budget) fp = s->budget;      // nothing else is admitted beside it
     Job *j = new Job();
     j->id = s->next_id++;
     j->state = 0;

@@ -807,7 +807,9 @@ static int grow_member_lists(lf_handle *h, long long total)
     if (!h->phase_graphs) LF_HIP(h, hipStreamSynchronize(h->stream));   // a batch member keeps the old list
     // grown two-fold (four-fold for a batch member, whose captured iteration starts and
     // ends a moved buffer invalidates), so a growing cover reallocates only a few times
-    const long long want = (h->phase_graphs ? 4 : 2) * total + 1024;
+    // (the batch's spare room within 8 MB)
+    long long want = 2 * total + 1024;
+    if (h->phase_graphs) want += 2 * total < (2 << 20) ? 2 * total : (2 << 20);
     LF_TRY(lf_dev_regrow(h, (void **)&h->cm_node, &h->cm_cap, want, sizeof(int)));
     return rebuild_member_lists_async(h);
 }

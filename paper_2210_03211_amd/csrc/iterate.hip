@@ -95,8 +95,12 @@ struct NodeLds {
 // beyond is gathered and scored in further pairs of launches (slices of the queue), so that the
 // lists of a queue of millions of nodes take 0.8 GB.  Slices this long cost nothing: three
 // iterations of 262,144 such nodes in one queue spend 5.98 ms in the two kernels in one slice,
-// 6.04 ms in four.
+// 6.04 ms in four.  A batch holds the lists of all its members, so there a slice is shorter, and
+// the small and medium nodes, which always go through lists, are also taken LIST_BLOCKS blocks
+// at a time: a member's lists take 25 MB at most.
 #define GROUP_SLICE 65536
+#define BATCH_GROUP_SLICE 1024
+#define SPARE_BYTES (4 << 20)   // most a batch member's buffer takes beyond a quarter more than it needs
 
 // Every kernel of a queue is a chain of dependent reads, some 0.7 us each, so the kernels keep
 // to three rules.  What does not depend on each other is read in one go: a read under a lane
@@ -2209,6 +2213,16 @@ static bool light_lists(bool batch, long long small, long long med)
     return batch || (small + EW - 1) / EW + med <= LIST_BLOCKS;
 }
 
+static int group_slice(bool batch) { return batch ? BATCH_GROUP_SLICE : GROUP_SLICE; }
+
+// Entries of a batch member's lists at most, for queues of q nodes (the server reserves them).
+long long lf_batch_list_bytes(long long q)
+{
+    const long long light = q < LIST_BLOCKS ? q : LIST_BLOCKS, group = q < BATCH_GROUP_SLICE ? q : BATCH_GROUP_SLICE;
+    const long long entries = light * VMED + group * VGRP;
+    return entries * (long long)(sizeof(long long) + sizeof(int)) + q * (long long)sizeof(ListHdr);
+}
+
 // second half: the host reads what the first half copied (the caller has waited for it)
 // and grows whatever it found too small
 static int size_queue_complete(lf_handle *h, long long q)
@@ -2249,17 +2263,19 @@ static int size_queue_complete(lf_handle *h, long long q)
         LF_HIP(h, hipGetLastError());
         h->second_half_work = true;
     }
-    const long long grown = h->phase_graphs ? 3 : 0;        // spare room, in quarters beyond one
     // flattened lists of the queue with the most entries (its first slice has the most)
     long long lnodes = 0, lentries = 0;
     for (long long k = 0; k < nq; k++) {
         long long m[LF_PATH_COUNT];
         for (int c = 0; c < LF_PATH_COUNT; c++) m[c] = h->hqoff[c * (nq + 1) + k + 1] - h->hqoff[c * (nq + 1) + k];
         const bool lists = light_lists(h->phase_graphs, m[LF_PATH_SMALL], m[LF_PATH_MED]);
-        const long long light = lists ? m[LF_PATH_SMALL] + m[LF_PATH_MED] : 0;
-        const long long group = m[LF_PATH_GROUP] < GROUP_SLICE ? m[LF_PATH_GROUP] : GROUP_SLICE;
-        const long long nodes = light + group;
-        const long long entries = (lists ? m[LF_PATH_SMALL] * VSMALL + m[LF_PATH_MED] * VMED : 0) + group * VGRP;
+        long long light = lists ? m[LF_PATH_SMALL] + m[LF_PATH_MED] : 0;
+        long long elight = lists ? m[LF_PATH_SMALL] * VSMALL + m[LF_PATH_MED] * VMED : 0;
+        if (light > LIST_BLOCKS * EW) light = LIST_BLOCKS * EW;      // a slice's: a block has 256 entries,
+        if (elight > LIST_BLOCKS * VMED) elight = LIST_BLOCKS * VMED;   // of four nodes or one
+        const long long most = group_slice(h->phase_graphs);
+        const long long group = m[LF_PATH_GROUP] < most ? m[LF_PATH_GROUP] : most;
+        const long long nodes = light + group, entries = elight + group * VGRP;
         if (nodes > lnodes) lnodes = nodes;
         if (entries > lentries) lentries = entries;
     }
@@ -2272,7 +2288,10 @@ static int size_queue_complete(lf_handle *h, long long q)
         {(void **)&h->trow, &h->trow_cap, most[3], sizeof(int)}};
     for (auto &bf : bufs) {
         if (bf.need <= *bf.cap) continue;
-        LF_TRY(lf_dev_regrow(h, bf.p, bf.cap, bf.need + (1 + 4 * grown) * (bf.need / 4) + 256, bf.each));
+        // a batch member's graphs survive more growth, while that is cheap
+        long long spare = h->phase_graphs ? 3 * bf.need : 0;
+        if (spare > SPARE_BYTES / (long long)bf.each) spare = SPARE_BYTES / (long long)bf.each;
+        LF_TRY(lf_dev_regrow(h, bf.p, bf.cap, bf.need + bf.need / 4 + spare + 256, bf.each));
         moved = true;
     }
     long long pcap = 2 * q + (h->cm_cap + n) / PART + 64;
@@ -2459,7 +2478,8 @@ int lf_iter_begin(lf_handle *h, long long qq, long long *nq)
 
 // Parameters and grids of slice `slice` of queue k (of nq); returns the queue's slices.  The
 // first one re-sums the queue before and takes all nodes but the workgroup path's beyond
-// GROUP_SLICE, the last one applies the queue.  compact_grids sizes the grid-stride kernels by
+// one slice of it (in a batch also the small and medium blocks beyond LIST_BLOCKS), the last
+// one applies the queue.  compact_grids sizes the grid-stride kernels by
 // the queue instead of by the whole device (for many graphs sharing one launch).
 int lf_queue_params(lf_handle *h, long long k, long long nq, long long qq, bool compact_grids, int slice, QStep *qs,
                     QGrids *g)
@@ -2475,13 +2495,26 @@ int lf_queue_params(lf_handle *h, long long k, long long nq, long long qq, bool 
         ln[c] = (int)(qo[c * (nq + 1) + k + 1] - ls[c]);
     }
     const bool lists = light_lists(compact_grids, ln[LF_PATH_SMALL], ln[LF_PATH_MED]);
-    const int slices = ln[LF_PATH_GROUP] > GROUP_SLICE ? (ln[LF_PATH_GROUP] - 1) / GROUP_SLICE + 1 : 1;
+    const int gs = group_slice(compact_grids), es = (int)grid_for(ln[LF_PATH_SMALL], EW), em = ln[LF_PATH_MED];
+    int slices = ln[LF_PATH_GROUP] > gs ? (ln[LF_PATH_GROUP] - 1) / gs + 1 : 1;
+    if (compact_grids && es + em > slices * LIST_BLOCKS) slices = (es + em - 1) / LIST_BLOCKS + 1;
     if (slices > 1) {
-        ls[LF_PATH_GROUP] += slice * GROUP_SLICE;
-        ln[LF_PATH_GROUP] -= slice * GROUP_SLICE;
-        if (ln[LF_PATH_GROUP] > GROUP_SLICE) ln[LF_PATH_GROUP] = GROUP_SLICE;
+        // the slice's part [lo, hi) of `units` units of `per` nodes of a path
+        auto cut = [&](int c, int lo, int hi, int units, int per) {
+            lo = lo < 0 ? 0 : lo < units ? lo : units;
+            hi = hi < 0 ? 0 : hi < units ? hi : units;
+            const int end = hi * per < ln[c] ? hi * per : ln[c];
+            ls[c] += lo * per;
+            ln[c] = end > lo * per ? end - lo * per : 0;
+        };
+        cut(LF_PATH_GROUP, slice * gs, (slice + 1) * gs, ln[LF_PATH_GROUP], 1);
+        if (compact_grids) {
+            cut(LF_PATH_SMALL, slice * LIST_BLOCKS, (slice + 1) * LIST_BLOCKS, es, EW);
+            cut(LF_PATH_MED, slice * LIST_BLOCKS - es, (slice + 1) * LIST_BLOCKS - es, em, 1);
+        } else if (slice > 0) {
+            ln[LF_PATH_SMALL] = ln[LF_PATH_MED] = 0;
+        }
     }
-    if (slice > 0) ln[LF_PATH_SMALL] = ln[LF_PATH_MED] = 0;
     const int gb = h->hub_blocks;
     int rbk = RB_MORE * h->refresh_blocks;
     if (compact_grids) {

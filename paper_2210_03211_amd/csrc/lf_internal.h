@@ -399,6 +399,7 @@ int lf_set_error(lf_handle *h, int code, const char *fmt, ...);
 
 int lf_dev_alloc(lf_handle *h, void **p, size_t bytes);
 void lf_dev_free(lf_handle *h, void *p);
+void lf_dev_retire(lf_handle *h, void *p);
 int lf_dev_regrow(lf_handle *h, void **p, long long *cap, long long want, size_t each);
 void lf_trim_kept(lf_handle *h);
 // size an lf_dev_alloc request occupies; a block whose device work has completed goes
@@ -478,6 +479,7 @@ int lf_iter_begin_enqueue(lf_handle *h, long long qq);
 int lf_iter_begin_complete(lf_handle *h, long long qq, long long *nq);
 int lf_queue_params(lf_handle *h, long long k, long long nq, long long qq, bool compact_grids, int slice, QStep *qs,
                     QGrids *g);
+long long lf_batch_list_bytes(long long q);
 int lf_launch_queue(lf_handle *h, Ctx &cx, const QStep &qs, const QGrids &g);
 int lf_launch_multi(hipStream_t st, const Member *dmem, const int *dboff, int n, const int *total);
 #define LF_MULTI_GRIDS 4         // per-step launches of a batch with grids of their own

@@ -231,12 +231,34 @@ void lf_dev_free(lf_handle *h, void *p)
         }
 }
 
+// A block whose last use on the device has completed leaves the handle for the cache of all
+// handles.
+void lf_dev_retire(lf_handle *h, void *p)
+{
+    if (!p) return;
+    for (size_t k = 0; k < h->allocs->size(); k++)
+        if ((*h->allocs)[k] == p) {
+            const size_t bytes = (*h->alloc_sizes)[k];
+            h->dev_bytes -= bytes;
+            (*h->allocs)[k] = h->allocs->back();
+            (*h->alloc_sizes)[k] = h->alloc_sizes->back();
+            h->allocs->pop_back();
+            h->alloc_sizes->pop_back();
+            lf_dev_release(h->device, p, bytes);
+            return;
+        }
+}
+
 // A buffer of `want` elements in place of *p (its contents are not kept).  Pointer and capacity
 // change together: after a failed allocation the buffer has neither, so that no later call
-// takes the old capacity for the room behind a null pointer.
+// takes the old capacity for the room behind a null pointer.  A buffer grows at the start or
+// end of an iteration, behind all work that used it: the host has seen the iteration before
+// complete, and the buffers of this one are others.  So a batch member's old block goes to
+// the cache of all handles instead of staying with it until lf_destroy.
 int lf_dev_regrow(lf_handle *h, void **p, long long *cap, long long want, size_t each)
 {
-    lf_dev_free(h, *p);
+    if (h->phase_graphs) lf_dev_retire(h, *p);
+    else lf_dev_free(h, *p);
     *p = nullptr;
     *cap = 0;
     LF_TRY(lf_dev_alloc(h, p, each * (size_t)want));

@@ -97,3 +97,44 @@ def test_workgroup_path_in_slices(lf, orc, n):
     b.close()
     h.close()
     o.close()
+
+
+def jobs():
+    big = [j for j in G.serving_mix(n_jobs=400, seed=9) if j["n"] > 30000][0]
+    return [("near", near_graph(40_000, 40, 1)), ("served", G.serving_job_graph(big)),
+            ("dense", G.named_config("dense", scale=0.01)), ("small", G.named_config("tiny_sbm"))]
+
+
+@pytest.mark.parametrize("which", range(4))
+def test_server_reserves_for_long_queues(lf, which):
+    """What the server reserves covers the peak of the same job as a member of a batch, with a
+    queue of a share of the nodes and of all of them; one that only fits the budget by
+    itself is still admitted."""
+    name, g = jobs()[which]
+    for q in (g.n // 32, g.n):
+        h = loaded(lf, g, {})
+        b = lf.Batch(0)
+        m = b.add(h, q, 0.01, 50)
+        while b.step() > 0:
+            pass
+        assert b.member_info(m) is not None
+        b.remove(m)
+        peak = h.lf_get_memory()[1]
+        h.close()
+        b.close()
+        srv = lf.Server(0, hbm_budget=64 << 30, max_batch=4)
+        srv.submit(g.n, g.src, g.dst, q, 0.01, 1)
+        srv.tick()
+        reserved = srv.stats()["used"]
+        while srv.tick() > 0:
+            pass
+        srv.close()
+        say(name, "queue", q, "peak", peak, "reserved", reserved)
+        assert reserved >= peak
+        nn = 48 * 2**20 + g.n * 768 + g.src.size * 64 + q * 256
+        srv = lf.Server(0, hbm_budget=nn + nn // 8, max_batch=4)
+        jid = srv.submit(g.n, g.src, g.dst, q, 0.01, 1)
+        while srv.tick() > 0:
+            assert srv.stats()["used"] <= srv.stats()["budget"]
+        assert srv.fetch(jid) is not None
+        srv.close()
