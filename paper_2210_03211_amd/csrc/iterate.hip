@@ -764,6 +764,14 @@ __global__ void __launch_bounds__(EW * WAVE) k_eval_whole(Ctx cx, QStep qs)
 #define VBUCK 256           // entries of a bucket evaluated one per thread
 #define BUCK_AVG 192        // bound on visits per bucket aimed at
 
+// Neighbours of a chunk of a node of degree d: TAB_CHUNK (one per thread), or, of a node with
+// more than GT such chunks, as many rounds of them as leave it GT chunks, so that a bucket
+// finds its piece of every chunk with one thread each.
+__host__ __device__ __forceinline__ int chunk_span(int d)
+{
+    return d <= TAB_CHUNK * GT ? TAB_CHUNK : TAB_CHUNK * ((d - 1) / (TAB_CHUNK * GT) + 1);
+}
+
 // hash of a community: the top of h * P is its bucket of P, the rest orders it within
 __device__ __forceinline__ unsigned long long bucket_hash(int C, int P)
 {
@@ -778,43 +786,56 @@ struct PartLds {
     int base;
 };
 
-// the TAB_CHUNK-neighbour chunk k (thread per neighbour)
+// the line of neighbour i of a chunk (one without memberships past its last)
+__device__ __forceinline__ NodeLine chunk_line(const Ctx &cx, const ChunkRec &cr, int i)
+{
+    const int y = cx.col[cr.rb + (i < cr.cnt ? i : cr.cnt - 1)];   // (a chunk is never empty)
+    RawLine rl = read_line(cx.ln + y);
+    arrived(rl.q[0], rl.q[1], rl.q[2], rl.q[3]);
+    NodeLine ly = as_line(rl);
+    if (i >= cr.cnt) {
+        ly.cnt = 0;
+        ly.off = -1;
+    }
+    return ly;
+}
+
+// the chunk k (thread per neighbour, TAB_CHUNK of them a round)
 __device__ __forceinline__ void table_chunk(const Ctx &cx, const QStep &qs, int k, PartLds &S)
 {
     const int tid = threadIdx.x;
     const ChunkRec cr = cx.tchunk[k];
-    const int P = cr.P;
-    const int y = cx.col[cr.rb + (tid < cr.cnt ? tid : cr.cnt - 1)];   // (a chunk is never empty)
-    RawLine rl = read_line(cx.ln + y);
+    const int P = cr.P, cnt = uni(cr.cnt);
     for (int t = tid; t < P; t += GT) S.hist[t] = 0;
-    arrived(rl.q[0], rl.q[1], rl.q[2], rl.q[3]);
-    NodeLine ly = as_line(rl);
-    if (tid >= cr.cnt) {
-        ly.cnt = 0;
-        ly.off = -1;
-    }
+    NodeLine ly = chunk_line(cx, cr, tid);
     __syncthreads();
     int mine = 0;                            // memberships (holes left out)
-    if (ly.off < 0) {
+    int r0 = 0;                              // the round held in ly
+    while (true) {
+        if (ly.off < 0) {
 #pragma unroll
-        for (int t = 0; t < LINE_SLOTS; t++)
-            if (t < ly.cnt && ly.s[t].comm >= 0) {
-                atomicAdd(&S.hist[bucket_of(ly.s[t].comm, P)], 1);
-                mine++;
-            }
-    } else {
-        for (int t0 = 0; t0 < ly.cnt; t0 += 4) {   // four slot loads per round trip
-            int c[4];
-#pragma unroll
-            for (int q = 0; q < 4; q++) c[q] = cx.slot[ly.off + (t0 + q < ly.cnt ? t0 + q : t0)].comm;
-            arrived(c[0], c[1], c[2], c[3]);
-#pragma unroll
-            for (int q = 0; q < 4; q++)
-                if (t0 + q < ly.cnt && c[q] >= 0) {
-                    atomicAdd(&S.hist[bucket_of(c[q], P)], 1);
+            for (int t = 0; t < LINE_SLOTS; t++)
+                if (t < ly.cnt && ly.s[t].comm >= 0) {
+                    atomicAdd(&S.hist[bucket_of(ly.s[t].comm, P)], 1);
                     mine++;
                 }
+        } else {
+            for (int t0 = 0; t0 < ly.cnt; t0 += 4) {   // four slot loads per round trip
+                int c[4];
+#pragma unroll
+                for (int q = 0; q < 4; q++) c[q] = cx.slot[ly.off + (t0 + q < ly.cnt ? t0 + q : t0)].comm;
+                arrived(c[0], c[1], c[2], c[3]);
+#pragma unroll
+                for (int q = 0; q < 4; q++)
+                    if (t0 + q < ly.cnt && c[q] >= 0) {
+                        atomicAdd(&S.hist[bucket_of(c[q], P)], 1);
+                        mine++;
+                    }
+            }
         }
+        if (r0 + TAB_CHUNK >= cnt) break;
+        r0 += TAB_CHUNK;
+        ly = chunk_line(cx, cr, r0 + tid);
     }
     int total;
     (void)wave_incl_scan(mine, &total);
@@ -855,33 +876,41 @@ __device__ __forceinline__ void table_chunk(const Ctx &cx, const QStep &qs, int 
     if (tid == 0) row[P] = run;
     __syncthreads();
     TabVisit *out = cx.tvis + (cr.vis - qs.br.vis0);
-    if (ly.off < 0) {
+    while (true) {                           // (from the last round, which is held, to the first)
+        if (ly.off < 0) {
 #pragma unroll
-        for (int t = 0; t < LINE_SLOTS; t++)
-            if (t < ly.cnt && ly.s[t].comm >= 0)
-                out[atomicAdd(&S.hist[bucket_of(ly.s[t].comm, P)], 1)] = TabVisit{ly.s[t].comm, ly.s[t].in, ly.deg, 0};
-    } else {
-        for (int t0 = 0; t0 < ly.cnt; t0 += 4) {
-            long long sl[4];
+            for (int t = 0; t < LINE_SLOTS; t++)
+                if (t < ly.cnt && ly.s[t].comm >= 0)
+                    out[atomicAdd(&S.hist[bucket_of(ly.s[t].comm, P)], 1)] = TabVisit{ly.s[t].comm, ly.s[t].in, ly.deg, 0};
+        } else {
+            for (int t0 = 0; t0 < ly.cnt; t0 += 4) {
+                long long sl[4];
 #pragma unroll
-            for (int q = 0; q < 4; q++)
-                sl[q] = *(const long long *)&cx.slot[ly.off + (t0 + q < ly.cnt ? t0 + q : t0)];
-            arrived(sl[0], sl[1], sl[2], sl[3]);
+                for (int q = 0; q < 4; q++)
+                    sl[q] = *(const long long *)&cx.slot[ly.off + (t0 + q < ly.cnt ? t0 + q : t0)];
+                arrived(sl[0], sl[1], sl[2], sl[3]);
 #pragma unroll
-            for (int q = 0; q < 4; q++) {
-                const int c = (int)sl[q];
-                if (t0 + q < ly.cnt && c >= 0)
-                    out[atomicAdd(&S.hist[bucket_of(c, P)], 1)] = TabVisit{c, (int)(sl[q] >> 32), ly.deg, 0};
+                for (int q = 0; q < 4; q++) {
+                    const int c = (int)sl[q];
+                    if (t0 + q < ly.cnt && c >= 0)
+                        out[atomicAdd(&S.hist[bucket_of(c, P)], 1)] = TabVisit{c, (int)(sl[q] >> 32), ly.deg, 0};
+                }
             }
         }
+        if (r0 == 0) break;
+        r0 -= TAB_CHUNK;
+        ly = chunk_line(cx, cr, r0 + tid);
     }
 }
 
 // A bucket whose entries do not fit one per thread (a community that many of the node's
-// neighbours share, a node with very many chunks): the visits are streamed from memory,
-// twice, and the distinct communities kept in the table.  If they are more than VBUCK the
-// bucket is cut into R slices of its hash range, R doubling until every slice fits;
-// communities scored before a cut are scored again, which changes nothing.
+// neighbours share, a node with more visits than TAB_MAXP buckets hold): the visits are
+// streamed from memory, twice, and the distinct communities kept in the table.  The threads
+// take the visits in turn and find each by the first positions of the chunks' pieces: with a
+// walk over the chunks, all threads on one piece of a few visits, the buckets of a hub with a
+// million neighbours took 7.9 ms, 60,000 0.36, now 0.55 and 0.14.  If the communities are more
+// than VBUCK the bucket is cut into R slices of its hash range, R doubling until every slice
+// fits; communities scored before a cut are scored again, which changes nothing.
 struct GenLds {
     int key[2 * VBUCK];
     unsigned kk[2 * VBUCK];
@@ -889,8 +918,19 @@ struct GenLds {
     int cl[VBUCK];                  // table entry of each candidate
     int sz[VBUCK];
     unsigned long long acc[2][VBUCK];
+    int first[GT], lo[GT];          // per chunk: visits before its piece, where that starts
     int n, over;
 };
+
+// position of the bucket's visit i
+__device__ __forceinline__ int gen_visit(const GenLds &G, int i)
+{
+    int c = 0;                      // the last chunk whose piece starts at or before i
+#pragma unroll 1                    // (unrolled, the whole kernel spills more: dense graph 1.5 % slower)
+    for (int s = GT / 2; s > 0; s /= 2)
+        if (G.first[c + s] <= i) c += s;
+    return G.lo[c] + (i - G.first[c]);
+}
 
 __device__ __forceinline__ int gen_find(const GenLds &G, int C)
 {
@@ -931,7 +971,7 @@ __device__ __forceinline__ bool in_slice(int C, int P, int b, unsigned r, unsign
     return (int)(h >> 32) == b && (unsigned)(((h & 0xffffffffull) * R) >> 32) == r;
 }
 
-__device__ __forceinline__ Best bucket_general(const Ctx &cx, const BuckRec &br, const int *rows, const TabVisit *vis,
+__device__ __forceinline__ Best bucket_general(const Ctx &cx, const BuckRec &br, const TabVisit *vis, int nvis,
                                                const Slot *xs, int mcnt, GenLds &G)
 {
     const int tid = threadIdx.x;
@@ -953,12 +993,9 @@ __device__ __forceinline__ Best bucket_general(const Ctx &cx, const BuckRec &br,
                 const int C = xs[t].comm;
                 if (C >= 0 && in_slice(C, br.P, br.b, sl, R)) gen_insert(G, C, 0x80000000u);
             }
-            for (int c = 0; c < br.nch; c++) {
-                const int lo = rows[(long long)c * (br.P + 1) + br.b], hi = rows[(long long)c * (br.P + 1) + br.b + 1];
-                for (int i = lo + tid; i < hi; i += GT) {
-                    const int C = vis[i].comm;
-                    if (in_slice(C, br.P, br.b, sl, R)) gen_insert(G, C, 1u);
-                }
+            for (int i = tid; i < nvis; i += GT) {
+                const int C = vis[gen_visit(G, i)].comm;
+                if (in_slice(C, br.P, br.b, sl, R)) gen_insert(G, C, 1u);
             }
             __syncthreads();
             if (G.over) {                    // uniform
@@ -979,18 +1016,15 @@ __device__ __forceinline__ Best bucket_general(const Ctx &cx, const BuckRec &br,
                     (unsigned)o.in != (G.kk[gen_find(G, o.comm)] & 0x7fffffffu))
                     atomicOr(&cx.ctr->error, LF_DEVERR_INCOUNT);
             }
-            for (int c = 0; c < br.nch; c++) {
-                const int lo = rows[(long long)c * (br.P + 1) + br.b], hi = rows[(long long)c * (br.P + 1) + br.b + 1];
-                for (int i = lo + tid; i < hi; i += GT) {
-                    const TabVisit v = vis[i];
-                    if (!in_slice(v.comm, br.P, br.b, sl, R)) continue;
-                    const int h = gen_find(G, v.comm);
-                    const int o = G.ow[h];
-                    const u128 term = visit_term(G.kk[h] >> 31, v.in, v.deg, G.sz[o], bad);
-                    const unsigned long long lw = (unsigned long long)term;
-                    const unsigned long long was = atomicAdd(&G.acc[0][o], lw);
-                    atomicAdd(&G.acc[1][o], (unsigned long long)(term >> 64) + (was + lw < lw ? 1ull : 0ull));
-                }
+            for (int i = tid; i < nvis; i += GT) {
+                const TabVisit v = vis[gen_visit(G, i)];
+                if (!in_slice(v.comm, br.P, br.b, sl, R)) continue;
+                const int h = gen_find(G, v.comm);
+                const int o = G.ow[h];
+                const u128 term = visit_term(G.kk[h] >> 31, v.in, v.deg, G.sz[o], bad);
+                const unsigned long long lw = (unsigned long long)term;
+                const unsigned long long was = atomicAdd(&G.acc[0][o], lw);
+                atomicAdd(&G.acc[1][o], (unsigned long long)(term >> 64) + (was + lw < lw ? 1ull : 0ull));
             }
             __syncthreads();
             if (tid < nc) {
@@ -1029,7 +1063,7 @@ __device__ __forceinline__ void eval_bucket(const Ctx &cx, const QStep &qs, int 
     const int *rows = cx.trow + (br.row - qs.br.row0);
     const TabVisit *vis = cx.tvis + (br.vis - qs.br.vis0);
     int lo = 0, len = 0;
-    if (tid < br.nch) {
+    if (tid < br.nch) {                      // (a node has GT chunks at most)
         const int *rp = rows + (long long)tid * (br.P + 1) + br.b;
         lo = rp[0];
         len = rp[1] - lo;
@@ -1046,9 +1080,10 @@ __device__ __forceinline__ void eval_bucket(const Ctx &cx, const QStep &qs, int 
     int m, N;
     const int pm = node_incl_scan<GT>(ownb ? 1 : 0, tid, L.wtot, &m);
     const int pl = node_incl_scan<GT>(len, tid, L.wtot, &N);
+    const int nvis = N;
     N += m;
     Best r;
-    if (N <= VBUCK && br.nch <= GT && mcnt <= GT) {      // uniform
+    if (N <= VBUCK && mcnt <= GT) {          // uniform
         if (ownb) {
             L.vslot[pm - 1] = ((long long)own.in << 32) | (unsigned)own.comm;
             L.vdeg[pm - 1] = -1;
@@ -1082,7 +1117,9 @@ __device__ __forceinline__ void eval_bucket(const Ctx &cx, const QStep &qs, int 
         r = score_list<GT, 1, VBUCK>(cx, br.d, sv, dg, tid, L, T, lg);
     } else {
         __syncthreads();                     // the scans' LDS is read
-        r = bucket_general(cx, br, rows, vis, xs, mcnt, S.g);
+        S.g.first[tid] = pl - len;
+        S.g.lo[tid] = lo;
+        r = bucket_general(cx, br, vis, nvis, xs, mcnt, S.g);   // (its first barrier is before their use)
         wave_best(r.jd, r.j);
         wave_best(r.ld, r.l);
         const int wv = tid / WAVE;
@@ -1903,7 +1940,7 @@ __global__ void __launch_bounds__(1024) k_table_layout(const int *list, const No
             const long long P = (vb[i] + BUCK_AVG - 1) / BUCK_AVG;
             q[0] = in ? vb[i] : 0;
             q[3] = !in ? 0 : P < TAB_MAXP ? P : TAB_MAXP;
-            q[2] = in ? (d[i] + TAB_CHUNK - 1) / TAB_CHUNK : 0;
+            q[2] = in ? (d[i] - 1) / chunk_span(d[i]) + (d[i] > 0) : 0;
             q[1] = q[2] * (q[3] + 1);
         };
         long long sum[4] = {0, 0, 0, 0}, pos[4];
@@ -1980,12 +2017,13 @@ __global__ void __launch_bounds__(256) k_table_fill(const int *list, const long 
         const int r = plist[p], x = order[r], d = deg[x];
         const int nch = t1.chunk - t0.chunk, P = t1.bucket - t0.bucket;
         const long long rb = rowptr[x];
+        const int span = chunk_span(d);
         for (int c = lane; c < nch; c += WAVE) {
             ChunkRec cr;
-            cr.rb = rb + (long long)c * TAB_CHUNK;
+            cr.rb = rb + (long long)c * span;
             cr.vis = t0.vis;
             cr.row = t0.row + (long long)c * (P + 1);
-            cr.cnt = d - c * TAB_CHUNK < TAB_CHUNK ? d - c * TAB_CHUNK : TAB_CHUNK;
+            cr.cnt = d - c * span < span ? d - c * span : span;
             cr.p = (int)p;
             cr.P = P;
             cr.pad = 0;

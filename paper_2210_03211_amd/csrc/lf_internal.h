@@ -81,9 +81,9 @@ struct __align__(64) CommRec {
 };
 
 // Table path (the largest nodes), laid out at the start of an iteration: a node's
-// neighbours in chunks of TAB_CHUNK, its communities in hash buckets.  A chunk's visits are
-// grouped by bucket in the node's region of the visit buffer, with one row of bucket
-// positions per chunk; a bucket is then evaluated by one block.
+// neighbours in chunks of TAB_CHUNK or a multiple of it, its communities in hash buckets.  A
+// chunk's visits are grouped by bucket in the node's region of the visit buffer, with one row
+// of bucket positions per chunk; a bucket is then evaluated by one block.
 struct TabPos {                // per table-path node, exclusive sums over the nodes before it
     long long vis;             // visit region
     long long row;             // row entries
@@ -93,7 +93,7 @@ struct TabPos {                // per table-path node, exclusive sums over the n
 struct ChunkRec {
     long long rb;              // adjacency position of the chunk's first neighbour
     long long vis, row;        // the node's visit region, this chunk's row (iteration-wide)
-    int cnt;                   // neighbours (1 .. TAB_CHUNK)
+    int cnt;                   // neighbours (at least 1)
     int p, P;                  // table-path list position, buckets of the node
     int pad;
 };
