@@ -359,7 +359,8 @@ int lf_debug_exact_sum(lf_handle *h, const double *values_dev, int64_t n, double
 
 /*
  * Diagnostic: the nth device allocation of the handle from now on (1: the next one) fails
- * once with LF_ENOMEM, whether the device has room or not; 0: none does.
+ * once with LF_ENOMEM, whether the device has room or not; 0: none does.  nth < 0: the -nth
+ * allocation finds no room before the blocks that handles keep for later have gone back.
  */
 int lf_debug_fail_alloc(lf_handle *h, int64_t nth);
 

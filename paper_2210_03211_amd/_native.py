@@ -469,7 +469,8 @@ class Handle:
         return out.value
 
     def lf_debug_fail_alloc(self, nth):
-        """The nth device allocation from now on fails once (0: none)."""
+        """The nth device allocation from now on fails once (0: none; < 0: the -nth finds room only
+        once kept blocks have gone back)."""
         self._check(self.L.lf_debug_fail_alloc(self.h, int(nth)), "lf_debug_fail_alloc")
 
     def lf_debug_sort_pairs(self, keys_dev, vals_dev=None, end_bit=64):

@@ -107,6 +107,7 @@ int lf_create(lf_handle **out, int device, void *hip_stream, uint32_t flags)
     h->hub_blocks = 2 * cus;
     h->refresh_blocks = 2 * cus;
     h->K = -1;
+    lf_handle_register(h);
     *out = h;
     return LF_OK;
 }
@@ -119,6 +120,7 @@ int lf_destroy(lf_handle *h)
     lf_phase_graphs_drop(h);
     if (h->cap_stream) (void)hipStreamDestroy(h->cap_stream);
     // the handle's work has completed on its stream: its blocks can serve other handles
+    lf_handle_unregister(h);
     for (size_t k = 0; k < h->allocs->size(); k++) lf_dev_release(h->device, (*h->allocs)[k], (*h->alloc_sizes)[k]);
     for (size_t k = 0; k < h->kept->size(); k++) lf_dev_release(h->device, (*h->kept)[k], (*h->kept_sizes)[k]);
     delete h->kept;
@@ -184,6 +186,7 @@ int lf_load_graph(lf_handle *h, int64_t n, int64_t n_pairs, const int64_t *src, 
     }
     LF_TRY(lf_prof_end(h, LF_K_BUILD, 8));
     LF_TRY(lf_prof_flush(h));
+    lf_trim_kept_to_graph(h);
     h->state = 1;
     return LF_OK;
 }
@@ -204,6 +207,7 @@ int lf_init_communities(lf_handle *h)
     }
     h->state = 1;
     LF_TRY(lf_initial_clustering(h));
+    lf_trim_kept_to_graph(h);
     h->state = 2;
     return LF_OK;
 }
@@ -242,6 +246,7 @@ int lf_init_from_memberships(lf_handle *h, const int64_t *offsets, const int32_t
         dids = c;
     }
     LF_TRY(lf_partition_from_cover(h, doff, dids, total, n_comms));
+    lf_trim_kept_to_graph(h);
     h->state = 2;
     return LF_OK;
 }
@@ -443,7 +448,7 @@ int lf_exact_sum_noalloc(lf_handle *h, const double *values_dev, int64_t n, doub
 
 int lf_debug_fail_alloc(lf_handle *h, int64_t nth)
 {
-    if (!h || nth < 0) return LF_EINVAL;
+    if (!h) return LF_EINVAL;
     h->fail_alloc = nth;
     return LF_OK;
 }

@@ -1105,8 +1105,8 @@ int lf_server_destroy(lf_server *s)
 int lf_get_memory(lf_handle *h, uint64_t *bytes, uint64_t *peak)
 {
     if (!h) return LF_EINVAL;
-    if (bytes) *bytes = h->dev_bytes + h->kept_bytes;
-    if (peak) *peak = h->dev_bytes_peak;
+    if (bytes) *bytes = h->dev_bytes + lf_kept_bytes(h);
+    if (peak) *peak = h->held_peak;
     return LF_OK;
 }
 

@@ -364,14 +364,16 @@ struct lf_handle {
     // allocation registry
     std::vector<void *> *allocs;
     std::vector<size_t> *alloc_sizes;
-    std::vector<void *> *kept;              // blocks given up, oldest first (lf_dev_free)
+    std::vector<void *> *kept;              // blocks given up, oldest first (prims.hip; guarded there)
     std::vector<size_t> *kept_sizes;
     size_t kept_bytes;
     std::vector<TmpChunk> *tmp_chunks;      // scratch arena (lf_tmp_alloc)
     int tmp_chunk;
     size_t tmp_off;
     size_t dev_bytes, dev_bytes_peak;   // device memory in use by the handle (now / at most)
-    long long fail_alloc;               // > 0: this many allocations from now, one fails (tests)
+    size_t held_peak;                   // in use and kept, at most
+    long long fail_alloc;               // > 0: this many allocations from now, one fails; < 0: one
+                                        // finds room only once kept blocks have gone back (tests)
     // iteration starts and ends replayed from graphs (members of a batch)
     int phase_graphs;
     PhaseGraph pg[2][2];                // [start, end][slot parity]
@@ -402,6 +404,10 @@ void lf_dev_free(lf_handle *h, void *p);
 void lf_dev_retire(lf_handle *h, void *p);
 int lf_dev_regrow(lf_handle *h, void **p, long long *cap, long long want, size_t each);
 void lf_trim_kept(lf_handle *h);
+size_t lf_kept_bytes(lf_handle *h);
+void lf_trim_kept_to_graph(lf_handle *h);
+void lf_handle_register(lf_handle *h);
+void lf_handle_unregister(lf_handle *h);
 // size an lf_dev_alloc request occupies; a block whose device work has completed goes
 // back to the per-device cache (or to HIP)
 size_t lf_alloc_class(size_t bytes);

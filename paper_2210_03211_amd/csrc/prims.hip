@@ -131,21 +131,96 @@ int lf_zero(lf_handle *h, void *p, size_t bytes)
 // next.  A handle that loads one graph after another, or restarts from a cover, otherwise
 // spent some 8 ms per load of a 1M-node graph in hipMalloc and hipFree (which waits for the
 // device): 28 ms for load and initial clustering, 21.7 with kept blocks.  They go back to HIP,
-// oldest first, as soon as the handle would hold more than it ever had in use; what a run
-// of iterations has not taken up again goes back at its end, but for a quarter of what is in
-// use (lf_trim_kept); and lf_destroy gives them to the cache of all handles.
-static void drop_kept(lf_handle *h, size_t keep)
+// oldest first, where a new block would have the handle hold more than it ever had in use; at
+// the end of a load or a set-up beyond what a graph of that size goes on to take; at the end
+// of a run beyond a quarter of what is in use; and all of them, of every handle on the device,
+// where an allocation finds no room.  lf_destroy gives them to the cache of all handles.  One
+// mutex guards the lists of all handles: another thread's allocation may take a handle's
+// blocks back.
+namespace {
+std::mutex &kept_mu()
+{
+    static std::mutex *m = new std::mutex();
+    return *m;
+}
+std::vector<lf_handle *> &all_handles()      // under kept_mu
+{
+    static std::vector<lf_handle *> *v = new std::vector<lf_handle *>();
+    return *v;
+}
+// blocks of the oldest kept ones beyond `keep` bytes, taken off the list (under kept_mu)
+void kept_beyond(lf_handle *h, size_t keep, std::vector<void *> &out)
 {
     size_t n = 0;
     while (h->kept_bytes > keep) {
-        (void)hipFree((*h->kept)[n]);
+        out.push_back((*h->kept)[n]);
         h->kept_bytes -= (*h->kept_sizes)[n];
         n++;
     }
     h->kept->erase(h->kept->begin(), h->kept->begin() + n);
     h->kept_sizes->erase(h->kept_sizes->begin(), h->kept_sizes->begin() + n);
 }
+}  // namespace
 
+void lf_handle_register(lf_handle *h)
+{
+    std::lock_guard<std::mutex> g(kept_mu());
+    all_handles().push_back(h);
+}
+
+// from here on no other thread takes the handle's kept blocks
+void lf_handle_unregister(lf_handle *h)
+{
+    std::lock_guard<std::mutex> g(kept_mu());
+    std::vector<lf_handle *> &v = all_handles();
+    for (size_t k = 0; k < v.size(); k++)
+        if (v[k] == h) {
+            v[k] = v.back();
+            v.pop_back();
+            return;
+        }
+}
+
+size_t lf_kept_bytes(lf_handle *h)
+{
+    std::lock_guard<std::mutex> g(kept_mu());
+    return h->kept_bytes;
+}
+
+static void drop_kept(lf_handle *h, size_t keep)
+{
+    std::vector<void *> out;
+    {
+        std::lock_guard<std::mutex> g(kept_mu());
+        kept_beyond(h, keep, out);
+    }
+    for (void *p : out) (void)hipFree(p);
+}
+
+// every block that no handle of the device has in use goes back to HIP (hipFree waits for what
+// is queued on the owner's stream)
+static void reclaim(int device)
+{
+    std::vector<void *> out;
+    {
+        std::lock_guard<std::mutex> g(kept_mu());
+        for (lf_handle *h : all_handles())
+            if (h->device == device) kept_beyond(h, 0, out);
+    }
+    {
+        BlockCache &c = block_cache();
+        std::lock_guard<std::mutex> g(c.mu);
+        for (auto &f : c.free)
+            if (f.first.first == device) {
+                c.bytes -= f.first.second * f.second.size();
+                out.insert(out.end(), f.second.begin(), f.second.end());
+                f.second.clear();
+            }
+    }
+    for (void *p : out) (void)hipFree(p);
+}
+
+// the end of a run
 void lf_trim_kept(lf_handle *h)
 {
     if (h->phase_graphs) return;             // a batch member: hipFree would wait for the device
@@ -153,8 +228,17 @@ void lf_trim_kept(lf_handle *h)
     drop_kept(h, most);
 }
 
+// the end of a load or a set-up: what the handle's graph has yet to take (about 1 KB per node and
+// 16 bytes per edge until its iterations run) may stay
+void lf_trim_kept_to_graph(lf_handle *h)
+{
+    if (h->phase_graphs) return;
+    drop_kept(h, ((size_t)64 << 20) + 1024 * (size_t)h->n + 16 * (size_t)h->ne);
+}
+
 static size_t take_kept(lf_handle *h, size_t bytes, void **p)
 {
+    std::lock_guard<std::mutex> g(kept_mu());
     size_t best = h->kept->size();
     for (size_t k = 0; k < h->kept->size(); k++) {
         const size_t s = (*h->kept_sizes)[k];
@@ -174,10 +258,11 @@ int lf_dev_alloc(lf_handle *h, void **p, size_t bytes)
     *p = nullptr;
     if (h->fail_alloc > 0 && --h->fail_alloc == 0)
         return lf_set_error(h, LF_ENOMEM, "allocation of %zu bytes failed as asked for", bytes);
+    const bool no_room = h->fail_alloc < 0 && ++h->fail_alloc == 0;    // (as asked for)
     bytes = lf_alloc_class(bytes);
-    const size_t got = take_kept(h, bytes, p);
+    const size_t got = no_room ? 0 : take_kept(h, bytes, p);
     if (got) bytes = got;
-    if (!*p && bytes <= CACHE_BLOCK_MAX) {
+    if (!*p && bytes <= CACHE_BLOCK_MAX && !no_room) {
         BlockCache &c = block_cache();
         std::lock_guard<std::mutex> g(c.mu);
         auto it = c.free.find({h->device, bytes});
@@ -191,10 +276,10 @@ int lf_dev_alloc(lf_handle *h, void **p, size_t bytes)
         // a new block: the handle holds no more than it has had in use at most
         const size_t most = h->dev_bytes_peak > h->dev_bytes + bytes ? h->dev_bytes_peak : h->dev_bytes + bytes;
         drop_kept(h, most - h->dev_bytes - bytes);
-        hipError_t e = hipMalloc(p, bytes);
-        if (e != hipSuccess && h->kept_bytes > 0) {
+        hipError_t e = no_room ? hipErrorOutOfMemory : hipMalloc(p, bytes);
+        if (e != hipSuccess) {
             (void)hipGetLastError();
-            drop_kept(h, 0);
+            reclaim(h->device);
             e = hipMalloc(p, bytes);
         }
         if (e != hipSuccess) {
@@ -207,6 +292,8 @@ int lf_dev_alloc(lf_handle *h, void **p, size_t bytes)
     h->alloc_sizes->push_back(bytes);
     h->dev_bytes += bytes;
     if (h->dev_bytes > h->dev_bytes_peak) h->dev_bytes_peak = h->dev_bytes;
+    const size_t held = h->dev_bytes + lf_kept_bytes(h);
+    if (held > h->held_peak) h->held_peak = held;
     return LF_OK;
 }
 
@@ -220,9 +307,12 @@ void lf_dev_free(lf_handle *h, void *p)
     for (size_t k = 0; k < h->allocs->size(); k++)
         if ((*h->allocs)[k] == p) {
             h->dev_bytes -= (*h->alloc_sizes)[k];
-            h->kept->push_back(p);
-            h->kept_sizes->push_back((*h->alloc_sizes)[k]);
-            h->kept_bytes += (*h->alloc_sizes)[k];
+            {
+                std::lock_guard<std::mutex> g(kept_mu());
+                h->kept->push_back(p);
+                h->kept_sizes->push_back((*h->alloc_sizes)[k]);
+                h->kept_bytes += (*h->alloc_sizes)[k];
+            }
             (*h->allocs)[k] = h->allocs->back();
             (*h->alloc_sizes)[k] = h->alloc_sizes->back();
             h->allocs->pop_back();
