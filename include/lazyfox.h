@@ -13,6 +13,8 @@
  *  - "host" pointers are ordinary CPU memory owned by the caller; "device" pointers are
  *    HIP device memory on the handle's device, also owned by the caller;
  *  - inputs are copied: the caller may free or reuse them after the call returns;
+ *  - device inputs (LF_DEVICE_PTR) are complete, or written by work that is already queued on
+ *    the handle's stream or on the device's default stream, which the call waits for;
  *  - every call is synchronous with respect to the host and stream-ordered on the handle's
  *    HIP stream; a handle must be used by one host thread at a time, separate handles are
  *    independent;

@@ -40,6 +40,14 @@ static void *scratch_of(int device)
     return g_scratch_ptr[device];
 }
 
+// Device arrays that the caller's work on the default stream still writes: the handle's own
+// stream does not wait for that one.
+int lf_wait_inputs(lf_handle *h, uint32_t flags)
+{
+    if (flags & LF_DEVICE_PTR) LF_HIP(h, hipStreamSynchronize(nullptr));
+    return LF_OK;
+}
+
 extern "C" {
 
 // Releases what a handle under construction already holds (lf_create's failure paths;
@@ -172,9 +180,12 @@ int lf_load_graph(lf_handle *h, int64_t n, int64_t n_pairs, const int64_t *src, 
     if (n_pairs >= (1ll << 31) - 1) return lf_set_error(h, LF_EOVERFLOW, "n_pairs >= 2^31 - 1");
     if (!(flags & LF_RELABEL) && n >= (1ll << 31) - 1)
         return lf_set_error(h, LF_EOVERFLOW, "n >= 2^31 - 1");
+    // a handle that already holds a graph has always waited for the whole device here (its blocks
+    // went back to HIP), so device arrays from any stream were complete
+    if ((flags & LF_DEVICE_PTR) && h->state > 0) LF_HIP(h, hipDeviceSynchronize());
     reset_graph(h);
-    // device arrays may have been written on another stream of the caller's
-    LF_HIP(h, (flags & LF_DEVICE_PTR) ? hipDeviceSynchronize() : hipStreamSynchronize(h->stream));
+    LF_TRY(lf_wait_inputs(h, flags));
+    LF_HIP(h, hipStreamSynchronize(h->stream));
     LF_TRY(lf_prof_begin(h, LF_K_BUILD));
     int rc = lf_build_graph(h, n, n_pairs, (const long long *)src, (const long long *)dst, flags);
     if (rc != LF_OK) {
@@ -221,6 +232,7 @@ int lf_init_from_memberships(lf_handle *h, const int64_t *offsets, const int32_t
         return lf_set_error(h, LF_EINVAL, "null cover arrays or negative total");
     if (total + h->n >= (1ll << 31) - 1) return lf_set_error(h, LF_EOVERFLOW, "cover too large");
     LF_HIP(h, hipSetDevice(h->device));
+    LF_TRY(lf_wait_inputs(h, flags));
     if (h->state == 1 || !h->order) {
         void **ptrs[] = {(void **)&h->tri, (void **)&h->ccl, (void **)&h->order, (void **)&h->rank,
                      (void **)&h->col_rank};

@@ -128,6 +128,7 @@ extern "C" int lf_cover_f1(lf_handle *h, const int64_t *offsets, const int32_t *
     if (h->state < 2) return lf_set_error(h, LF_ESTATE, "no communities yet");
     if (!offsets || total < 0 || (total > 0 && !ids)) return lf_set_error(h, LF_EINVAL, "null cover arrays");
     LF_HIP(h, hipSetDevice(h->device));
+    LF_TRY(lf_wait_inputs(h, flags));
     TmpScope tmp_scope(h);
     hipStream_t st = h->stream;
     const int BS = 256;

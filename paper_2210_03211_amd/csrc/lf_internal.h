@@ -399,6 +399,7 @@ int lf_set_error(lf_handle *h, int code, const char *fmt, ...);
         if (rc_ != LF_OK) return rc_;                                                      \
     } while (0)
 
+int lf_wait_inputs(lf_handle *h, uint32_t flags);
 int lf_dev_alloc(lf_handle *h, void **p, size_t bytes);
 void lf_dev_free(lf_handle *h, void *p);
 void lf_dev_retire(lf_handle *h, void *p);
