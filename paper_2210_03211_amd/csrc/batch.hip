@@ -479,7 +479,6 @@ int lf_batch_step(lf_batch *b, int32_t *running)
             BatchMember *m = act[i];
             QGrids g;
             m->slices = lf_queue_params(m->h, m->k, m->nq, m->qq, true, m->slice, &hm[i].qs, &g);
-            m->cx.qtag = m->h->qtag++;
             hm[i].cx = m->cx;
             const int blocks[LF_MULTI_GRIDS] = {g.refresh, g.big, g.tie, g.apply};
             for (int t = 0; t < LF_MULTI_GRIDS; t++) {

@@ -981,7 +981,6 @@ static int alloc_partition_state(lf_handle *h, long long K, long long slots)
     LF_HIP(h, hipMemsetAsync(h->cr, 0, sizeof(CommRec) * KK, st));
     LF_HIP(h, hipMemsetAsync(h->tflag, 0, sizeof(int) * KK, st));
     LF_HIP(h, hipMemsetAsync(h->ovf_flag, 0, sizeof(int) * KK, st));
-    h->qtag = 0;
     return LF_OK;
 }
 

@@ -6,7 +6,7 @@
 // result therefore does not depend on summation order, thread count or reduction shape.
 //
 //  X192  two's-complement 192-bit integer, weight of the lowest bit 2^-120.  Holds the node
-//        terms g in (2^-62, 1] (lowest set bit >= 2^-114), local CCs, and any sum of up to
+//        terms g in (2^-62, 2] (lowest set bit >= 2^-114), local CCs, and any sum of up to
 //        2^31 of them.
 //  X256  two's-complement 256-bit integer, lowest bit 2^-192.  Holds community scores
 //        p * R(sum g) in (2^-124, 2^31) (lowest set bit >= 2^-176) and their sum.
@@ -198,8 +198,8 @@ __device__ __forceinline__ double x256_round(X256 a)   // a >= 0
 }
 
 // ---- 128-bit terms ---------------------------------------------------------------------
-// A node term g in {0} or (2^-62, 1] as a 128-bit integer (lowest bit 2^-120); anything
-// outside [2^-67, 2^7) sets the flag.  A candidate's corrections sum to well within the
+// A node term g in {0} or (2^-62, 2] as a 128-bit integer (lowest bit 2^-120); anything
+// outside [2^-68, 2^6) sets the flag.  A candidate's corrections sum to well within the
 // two's-complement range of +-2^7: a neighbour y of x in C changes by at most
 // 3 / (|C| - 2) (|C| >= 3; at most 1 below), and C has fewer than |C| of them.
 __device__ __forceinline__ u128 fx128(double v, int &bad)

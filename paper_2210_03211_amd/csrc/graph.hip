@@ -9,10 +9,11 @@
 // Triangles: every edge is oriented from the endpoint that is smaller in (degree, id)
 // order to the larger one, so each triangle {a < b < c} is found exactly once, at a with
 // the oriented edges a->b, a->c and b->c.  For a node u, a wave (or a workgroup for long
-// out-lists) stages N+(u) in LDS, walks the concatenation of N+(v) over v in N+(u) with
-// all its lanes, and binary-searches each w in the staged N+(u).  A hit credits u, v and
-// w; the credits of v and w (both in N+(u)) are accumulated in LDS counters and flushed
-// to HBM once per (u, position).
+// out-lists) stages N+(u) and a bit filter of its members in LDS; groups of 16 lanes walk the
+// lists N+(v), v in N+(u), four entries a lane, and what the filter lets pass is queued and
+// searched for in the staged N+(u) a full wave at a time.  A hit credits u, v and w; the
+// credits of v and w (both in N+(u)) are accumulated in LDS counters and flushed to HBM once
+// per (u, position).
 #include "method.h"
 
 static int bits_for(long long n)
@@ -506,7 +507,6 @@ __device__ __forceinline__ int tri_push(TriQueue<WCC, J> &Q, int &qn, bool cand,
 #define TRI_WAVE_BITS 12        // per wave of the short out-lists
 #define TRI_GW 16               // lanes per list of theirs
 #define TRI_PER 4               // entries per lane
-#define TRI_WAVES 1
 
 // A wave probes the lists k = first, first + stride, .. < ns of one node u: TRI_GW lanes walk one
 // list at a time, TRI_PER entries each, and take the next one that is left when theirs ends; the
@@ -574,35 +574,26 @@ __device__ __forceinline__ int tri_walk(const int *orc, int first, int stride, i
 // nodes, 8M edges: 2.6 -> 0.95 ms.
 // WCC = false: triangle counts per node into tri; true: wcc_hit per triangle instead.
 template <bool WCC>
-__global__ void __launch_bounds__(TRI_WAVES * WAVE) k_tri_wave(const long long *oro, const int *orc, long long n,
-                                                  unsigned long long *tri, int *defer, int *ndefer, WccTri wt)
+__global__ void __launch_bounds__(WAVE) k_tri_wave(const long long *oro, const int *orc, long long n,
+                                                   unsigned long long *tri, int *defer, int *ndefer, WccTri wt)
 {
-    __shared__ int s_nbr[TRI_WAVES][TRI_WAVE_CAP];
-    __shared__ int s_cnt[TRI_WAVES][WCC ? 1 : TRI_WAVE_CAP];
-    __shared__ int s_start[TRI_WAVES][TRI_WAVE_CAP];
-    __shared__ unsigned short s_len[TRI_WAVES][TRI_WAVE_CAP];
-    __shared__ unsigned char s_seg[TRI_WAVES][TRI_WAVE_CAP];
-    __shared__ unsigned s_bits[TRI_WAVES][(1 << TRI_WAVE_BITS) / 32];
-    __shared__ TriQueue<WCC, unsigned char> s_q[TRI_WAVES];
-    const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x / WAVE), lane = threadIdx.x & (WAVE - 1);
-    const long long u = blockIdx.x * (long long)TRI_WAVES + wv;
-    long long b = 0;
-    int m = 0;
-    if (u < n) {
-        b = oro[u];
-        m = (int)(oro[u + 1] - b);
-    }
+    __shared__ int nbr[TRI_WAVE_CAP];
+    __shared__ int cnt[WCC ? 1 : TRI_WAVE_CAP];
+    __shared__ int start[TRI_WAVE_CAP];
+    __shared__ unsigned short len[TRI_WAVE_CAP];
+    __shared__ unsigned char seg[TRI_WAVE_CAP];
+    __shared__ unsigned bits[(1 << TRI_WAVE_BITS) / 32];
+    __shared__ TriQueue<WCC, unsigned char> Q;
+    const int lane = threadIdx.x;
+    const long long u = blockIdx.x;
+    if (u >= n) return;
+    const long long b = oro[u];
+    int m = (int)(oro[u + 1] - b);
     if (m > TRI_WAVE_CAP) {
         if (lane == 0) defer[atomicAdd(ndefer, 1)] = (int)u;
         m = 0;
     }
     if (m < 2) return;                     // a triangle needs two out-neighbours of u
-    int *nbr = s_nbr[wv], *cnt = s_cnt[wv];
-    int *start = s_start[wv];
-    unsigned short *len = s_len[wv];
-    unsigned char *seg = s_seg[wv];
-    unsigned *bits = s_bits[wv];
-    TriQueue<WCC, unsigned char> &Q = s_q[wv];
     for (int t = lane; t < (1 << TRI_WAVE_BITS) / 32; t += WAVE) bits[t] = 0;
     WAVE_SYNC();
     // stage N+(u) and its filter; the non-empty N+(v): first entry (below 2^30, as 2|E| < 2^31),
@@ -884,10 +875,10 @@ int lf_triangle_pass(lf_handle *h, const WccTri *wt, int *launches, long long **
     if (n > 0) {
         hipLaunchKernelGGL(k_out_fill, dim3(gw), dim3(BS), 0, st, h->rowptr, h->col, h->deg, n, oro, orc);
         if (wt)
-            hipLaunchKernelGGL(k_tri_wave<true>, dim3(grid_for(n, TRI_WAVES)), dim3(TRI_WAVES * WAVE), 0, st,
+            hipLaunchKernelGGL(k_tri_wave<true>, dim3((unsigned)n), dim3(WAVE), 0, st,
                                oro, orc, n, h->tri, defer, cnt, w);
         else
-            hipLaunchKernelGGL(k_tri_wave<false>, dim3(grid_for(n, TRI_WAVES)), dim3(TRI_WAVES * WAVE), 0, st,
+            hipLaunchKernelGGL(k_tri_wave<false>, dim3((unsigned)n), dim3(WAVE), 0, st,
                                oro, orc, n, h->tri, defer, cnt, w);
     }
     int hc[4] = {0, 0, 0, 0};

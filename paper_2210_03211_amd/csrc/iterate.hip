@@ -1509,7 +1509,8 @@ MULTI_KERNEL(k_apply, 256, EditLds, multi_apply)
 // ------------------------------------------------------------------------------------
 // exact re-sum of the touched communities
 // ------------------------------------------------------------------------------------
-#define MPAR 1
+#define FOLD 64         // members per lane between two folds of its 128-bit sums
+static_assert(FOLD < TERMS_U128, "a lane's sums hold that many terms");
 
 // Exact re-sum of one part (one wave): the members' terms at sizes s, s+1 and s-1, and the
 // sum of their in-counts.
@@ -1522,13 +1523,8 @@ __device__ __forceinline__ void refresh_part(const Ctx &cx, const PartRec &pr, l
     // size, list length and overflow after the edits, beside the part's first members (below
     // the list's capacity; those past its length are dropped)
     int s = cx.cr[C].s, ovf = cx.ovf_flag[C], fill = cx.cm_len[C];
-    int y[MPAR];
-#pragma unroll
-    for (int t = 0; t < MPAR; t++) {
-        const long long i = lo + t * WAVE + lane;
-        y[t] = 0;
-        if (cap > 0) y[t] = cx.cm_node[base + (i < cap ? i : cap - 1)];
-    }
+    int y = 0;
+    if (cap > 0) y = cx.cm_node[base + (lo + lane < cap ? lo + lane : cap - 1)];
     arrived(s, ovf, fill);
     s = uni(s);
     ovf = uni(ovf);
@@ -1544,29 +1540,22 @@ __device__ __forceinline__ void refresh_part(const Ctx &cx, const PartRec &pr, l
     X192 S0 = x192_zero(), Sp = x192_zero(), Sm = x192_zero();
     long long ins = 0, mslots = 0;
     long long q = lo;
-    while (q < hi) {                         // a lane's 128-bit sums are folded every 64 members
-        const long long end = hi - q < 64 * WAVE ? hi : q + 64 * WAVE;
+    while (q < hi) {
+        const long long end = hi - q < FOLD * WAVE ? hi : q + FOLD * WAVE;
         u128 a0 = 0, ap = 0, am = 0;
         long long sumi = 0;
 #pragma unroll 1
-        for (; q < end; q += MPAR * WAVE) {  // MPAR members per lane in one round trip
-            RawLine r[MPAR];
-            int nx[MPAR];
-#pragma unroll
-            for (int t = 0; t < MPAR; t++) {
-                r[t] = read_line(cx.ln + (q + t * WAVE + lane < hi ? y[t] : 0));
-                const long long i = q + (MPAR + t) * WAVE + lane;
-                nx[t] = cx.cm_node[base + (i < hi ? i : hi - 1)];
-            }
-#pragma unroll
-            for (int t = 0; t < MPAR; t++) {
-                arrived(r[t].q[0], r[t].q[1], r[t].q[2], r[t].q[3], nx[t]);
-                y[t] = nx[t];
-                const NodeLine ly = as_line(r[t]);
-                if (q + t * WAVE + lane < hi) {
-                    member_terms_of(cx, ly, C, s, a0, ap, am, sumi, bad);
-                    if (cx.stats) mslots += ly.cnt;
-                }
+        for (; q < end; q += WAVE) {         // one member per lane in a round trip (two or four: slower)
+            const bool in = q + lane < hi;
+            const long long i = q + WAVE + lane;
+            RawLine r = read_line(cx.ln + (in ? y : 0));
+            int next = cx.cm_node[base + (i < hi ? i : hi - 1)];
+            arrived(r.q[0], r.q[1], r.q[2], r.q[3], next);
+            y = next;
+            const NodeLine ly = as_line(r);
+            if (in) {
+                member_terms_of(cx, ly, C, s, a0, ap, am, sumi, bad);
+                if (cx.stats) mslots += ly.cnt;
             }
         }
         WAVE_SYNC();
@@ -2375,7 +2364,6 @@ static unsigned long long phase_key(lf_handle *h, long long qq, int which)
 {
     unsigned long long k = 14695981039346656037ull;
     Ctx cx = lf_ctx(h);
-    cx.qtag = 0;
     // the path lists' pointers move with the path counts at every start and are read only by
     // the queue kernels
     for (int c = 0; c < LF_PATH_COUNT; c++) {
@@ -2609,7 +2597,6 @@ static void launch_refresh(int grid, hipStream_t st, const Ctx &cx, const QStep 
 int lf_launch_queue(lf_handle *h, Ctx &cx, const QStep &qs, const QGrids &g)
 {
     hipStream_t st = h->stream;
-    cx.qtag = h->qtag++;
     LF_TRY(lf_prof_begin(h, LF_K_REFRESH));
     launch_refresh(g.refresh, st, cx, qs);
     LF_TRY(lf_prof_end(h, LF_K_REFRESH, 1));

@@ -124,8 +124,8 @@ struct __align__(16) Decision {
     int J, L, pos, pad;
 };
 
-// Device-side counters and flags (one struct in device memory).  The per-queue counters
-// are reset by the first kernel of every queue.
+// Device-side counters and flags (one struct in device memory).  The per-queue counters are
+// reset by block 0 of every queue's scoring.
 struct DevCounters {
     unsigned long long joins;      // per iteration
     unsigned long long leaves;     // per iteration
@@ -161,7 +161,6 @@ struct Ctx {
     int *cm_len;             // member-list fill (may exceed capacity: overflow)
     int *cm_node;            // member lists
     int *tflag;              // touched flag per community (1: in this queue, 2: removed)
-    unsigned qtag;           // tag of the current queue (unique within a run)
     int *ovf_node;           // overflow joiners (node, community)
     int *ovf_comm;
     int *ovf_flag;
@@ -289,7 +288,6 @@ struct lf_handle {
     int *cm_node;
     long long cm_cap;        // capacity of cm_node
     int *tflag;
-    unsigned qtag;           // next queue tag
     int *ovf_node, *ovf_comm, *ovf_flag;
     Decision *dec;
     long long q_cap;         // capacity of the per-queue arrays

@@ -310,8 +310,10 @@ __device__ __forceinline__ void wave_best(double &bd, int &bc)
     bd = __longlong_as_double((long long)top);
 }
 
-// the g-terms of one member of C with in-count i and degree d at sizes s, s+1, s-1
-// (a 128-bit accumulator holds 255 of them, each at most 1)
+// the g-terms of one member of C with in-count i and degree d at sizes s, s+1, s-1.  A term is
+// at most 2: i <= s - 1 and i <= d, so at size s - 1 at most i / (i - 1), which is 2 where i = d = 2 and
+// s = 3.  An unsigned 128-bit accumulator (below 2^8) holds fewer than TERMS_U128 of them.
+#define TERMS_U128 128
 __device__ __forceinline__ void acc_add(X192 &a, u128 t) { x192_add(a, x192_sext128(t)); }
 __device__ __forceinline__ void acc_add(u128 &a, u128 t) { a += t; }
 

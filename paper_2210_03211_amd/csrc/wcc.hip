@@ -16,10 +16,9 @@
 //      its lowest endpoint in (degree, id) order) marks each oriented edge that closes a
 //      triangle and adds one to t(x,C) at all three corners for every community the three
 //      nodes share;
-//   3. one wave per node: per adjacency position whether the edge closes a triangle, and
-//      vt(x,V);
-//   4. one wave per membership: vt(x, V \ C), the node term, its digits into the
-//      community's carry-save counters;
+//   3. a wave per node: per adjacency position whether the edge closes a triangle, and vt(x,V);
+//   4. a row of 16 lanes per membership (a wave where the node has many neighbours):
+//      vt(x, V \ C), the node term, its digits into the community's carry-save counters;
 //   5. community totals folded and rounded; the partition total summed exactly.
 #include "method.h"
 
