@@ -2,9 +2,11 @@
 
     python3 -m paper_2210_03211_amd.profsum trace <dir> [min_total_ms]
         per kernel: dispatches, total / mean / min / max duration (kernel trace)
-    python3 -m paper_2210_03211_amd.profsum pmc <dir> [kernel_regex]
+    python3 -m paper_2210_03211_amd.profsum pmc <dir> [kernel_regex [passes]]
         per kernel: dispatches and the mean of every collected counter per dispatch; for
-        rocclr copy kernels also the largest value (the calibration copy's own dispatch)
+        rocclr copy kernels also the largest value (the calibration copy's own dispatch).  With
+        passes > 1, a kernel dispatched a multiple of that often counts in its last pass only
+        (bench.py's passes before the timed steps bracket launches and count work)
 
 <dir> is the rocprofv3 output directory (-d); every *kernel_trace.csv or
 *counter_collection.csv below it is read.
@@ -37,8 +39,11 @@ def counters(d):
     per = defaultdict(lambda: defaultdict(list))
     for f in glob.glob(os.path.join(d, "**", "*counter_collection.csv"), recursive=True):
         with open(f) as fh:
-            for r in csv.DictReader(fh):
-                per[short(r["Kernel_Name"])][r["Counter_Name"]].append(float(r["Counter_Value"]))
+            rows = list(csv.DictReader(fh))
+        if rows and "Dispatch_Id" in rows[0]:
+            rows.sort(key=lambda r: int(r["Dispatch_Id"]))
+        for r in rows:
+            per[short(r["Kernel_Name"])][r["Counter_Name"]].append(float(r["Counter_Value"]))
     return per
 
 
@@ -54,13 +59,13 @@ def trace_summary(d, min_total_ms=5.0):
     return out
 
 
-def pmc_summary(d, pattern=None):
+def pmc_summary(d, pattern=None, passes=1):
     out = []
     per = counters(d)
     for k in sorted(per):
         if pattern and not re.search(pattern, k):
             continue
-        cs = per[k]
+        cs = {c: v[-(len(v) // passes):] if len(v) % passes == 0 else v for c, v in per[k].items()}
         line = ["%-40s" % k, "n=%d" % len(next(iter(cs.values())))]
         for c, v in sorted(cs.items()):
             line.append("%s=%.6g" % (c, sum(v) / len(v)))
@@ -77,7 +82,7 @@ def main(argv):
     if argv[1] == "trace":
         lines = trace_summary(argv[2], float(argv[3]) if len(argv) > 3 else 5.0)
     else:
-        lines = pmc_summary(argv[2], argv[3] if len(argv) > 3 else None)
+        lines = pmc_summary(argv[2], argv[3] if len(argv) > 3 else None, int(argv[4]) if len(argv) > 4 else 1)
     print("\n".join(lines))
     return 0
 

@@ -28,3 +28,15 @@ def test_trace_and_counter_summaries(tmp_path):
     assert out[0].split() == ["__amd_rocclr_copyBuffer", "n=2", "FETCH_SIZE=6", "FETCH_SIZE_max=8"]
     assert out[1].split() == ["k_a", "n=2", "FETCH_SIZE=20"]
     assert profsum.pmc_summary(str(tmp_path), "^k_") == out[1:]
+
+
+def test_counters_of_the_last_pass(tmp_path):
+    """Three passes of two dispatches each, out of order in the file: the last two by dispatch
+    count; a kernel that is not dispatched a multiple of three times counts whole."""
+    (tmp_path / "a_counter_collection.csv").write_text(
+        "Dispatch_Id,Kernel_Name,Counter_Name,Counter_Value\n"
+        + "".join("%d,k_a(Ctx),FETCH_SIZE,%d\n" % (i, 10 * i) for i in (6, 1, 2, 5, 3, 4))
+        + "7,k_b(Ctx),FETCH_SIZE,4\n8,k_b(Ctx),FETCH_SIZE,8\n")
+    out = profsum.pmc_summary(str(tmp_path), None, 3)
+    assert out[0].split() == ["k_a", "n=2", "FETCH_SIZE=55"]
+    assert out[1].split() == ["k_b", "n=2", "FETCH_SIZE=6"]
