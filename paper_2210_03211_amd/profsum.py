@@ -1,12 +1,13 @@
 """Summaries of rocprofv3 CSV output, as kept under profiles/.
 
-    python3 -m paper_2210_03211_amd.profsum trace <dir> [min_total_ms]
+    python3 -m paper_2210_03211_amd.profsum trace <dir> [min_total_ms [passes]]
         per kernel: dispatches, total / mean / min / max duration (kernel trace)
     python3 -m paper_2210_03211_amd.profsum pmc <dir> [kernel_regex [passes]]
         per kernel: dispatches and the mean of every collected counter per dispatch; for
-        rocclr copy kernels also the largest value (the calibration copy's own dispatch).  With
-        passes > 1, a kernel dispatched a multiple of that often counts in its last pass only
-        (bench.py's passes before the timed steps bracket launches and count work)
+        rocclr copy kernels also the largest value (the calibration copy's own dispatch)
+
+With passes > 1, a kernel dispatched a multiple of that often counts in its last pass only
+(bench.py's passes before the timed steps bracket launches and count work).
 
 <dir> is the rocprofv3 output directory (-d); every *kernel_trace.csv or
 *counter_collection.csv below it is read.
@@ -47,11 +48,16 @@ def counters(d):
     return per
 
 
-def trace_summary(d, min_total_ms=5.0):
+def last_pass(v, passes):
+    return v[-(len(v) // passes):] if len(v) % passes == 0 else v
+
+
+def trace_summary(d, min_total_ms=5.0, passes=1):
     agg = defaultdict(list)
     for _, k, us in kernel_trace(d):
         agg[k].append(us)
     out = ["%-48s %9s %11s %9s %9s %10s" % ("kernel", "calls", "total_ms", "avg_us", "min_us", "max_us")]
+    agg = {k: last_pass(v, passes) for k, v in agg.items()}
     for k, v in sorted(agg.items(), key=lambda kv: -sum(kv[1])):
         if sum(v) < 1000.0 * min_total_ms:
             continue
@@ -65,7 +71,7 @@ def pmc_summary(d, pattern=None, passes=1):
     for k in sorted(per):
         if pattern and not re.search(pattern, k):
             continue
-        cs = {c: v[-(len(v) // passes):] if len(v) % passes == 0 else v for c, v in per[k].items()}
+        cs = {c: last_pass(v, passes) for c, v in per[k].items()}
         line = ["%-40s" % k, "n=%d" % len(next(iter(cs.values())))]
         for c, v in sorted(cs.items()):
             line.append("%s=%.6g" % (c, sum(v) / len(v)))
@@ -80,7 +86,8 @@ def main(argv):
         print(__doc__, file=sys.stderr)
         return 2
     if argv[1] == "trace":
-        lines = trace_summary(argv[2], float(argv[3]) if len(argv) > 3 else 5.0)
+        lines = trace_summary(argv[2], float(argv[3]) if len(argv) > 3 else 5.0,
+                              int(argv[4]) if len(argv) > 4 else 1)
     else:
         lines = pmc_summary(argv[2], argv[3] if len(argv) > 3 else None, int(argv[4]) if len(argv) > 4 else 1)
     print("\n".join(lines))

@@ -40,3 +40,7 @@ def test_counters_of_the_last_pass(tmp_path):
     out = profsum.pmc_summary(str(tmp_path), None, 3)
     assert out[0].split() == ["k_a", "n=2", "FETCH_SIZE=55"]
     assert out[1].split() == ["k_b", "n=2", "FETCH_SIZE=6"]
+    (tmp_path / "a_kernel_trace.csv").write_text(
+        "Kernel_Name,Start_Timestamp,End_Timestamp\n"
+        + "".join("k_a(Ctx),%d,%d\n" % (1000 * i, 1000 * i + 100 * i) for i in (3, 1, 2)))
+    assert profsum.trace_summary(str(tmp_path), 0.0, 3)[1].split() == ["k_a", "1", "0.0", "0.30", "0.30", "0.30"]
