@@ -138,3 +138,33 @@ def test_server_reserves_for_long_queues(lf, which):
             assert srv.stats()["used"] <= srv.stats()["budget"]
         assert srv.fetch(jid) is not None
         srv.close()
+
+
+@pytest.mark.parametrize("n,opts", [(16384, {}), (16385, {}), (40_001, {}), (4096, {"wave_table": 16}),
+                                    (9001, {"wave_table": 16}), (21_000, {"wave_table": 32}),
+                                    (9001, {"wave_table": 16, "med_table": 32})])
+def test_lists_of_a_batch_in_slices(lf, orc, n, opts):
+    """All nodes of a batch member in one queue, up to 4,096 blocks of small and medium nodes and
+    past it, of one path or both, with workgroup nodes beside them; another member beside it."""
+    say("batch slices", n, opts)
+    g, g2 = near_graph(n, 8, n), near_graph(500, 8, 3)
+    o = orc.Oracle().load_graph(g.n, g.src, g.dst).init_communities()
+    o2 = orc.Oracle().load_graph(g2.n, g2.src, g2.dst).init_communities()
+    for replay in (False, True):
+        h, h2 = loaded(lf, g, opts), loaded(lf, g2, opts)
+        b = lf.Batch(0)
+        b.set_graph(replay)
+        m, m2 = b.add(h, n, 0.0, 3), b.add(h2, 50, 0.0, 3)
+        while b.step() > 0:
+            pass
+        if not replay:
+            ref, ref2 = o.run_iterations(n, 0.0, 3), o2.run_iterations(50, 0.0, 3)
+        assert np.array_equal(bits(b.member_info(m)["wtilde_hist"]), bits(ref["wtilde_hist"]))
+        assert np.array_equal(bits(b.member_info(m2)["wtilde_hist"]), bits(ref2["wtilde_hist"]))
+        b.close()
+        same(h, o)
+        same(h2, o2)
+        h.close()
+        h2.close()
+    o.close()
+    o2.close()
